@@ -181,6 +181,9 @@ typedef struct {
     int32_t variant;      /* 0: automatic; 1: the row-streaming variant of the block compressors (every wave   */
                           /*    takes one row of a tile, no LDS exchange; what serves more workers than the     */
                           /*    fused kernel's LDS holds is chosen automatically anyway)                        */
+                          /* 2: no resident kernel: compressors that take a small problem's step in one launch use   */
+                          /*    the launches they use for large ones.  3: that kernel, but its workgroups do not     */
+                          /*    wait for each other at all, so that the last one does the step alone (tests)         */
     int32_t tile_plan;    /* -1: automatic; i >= 0 pins the i-th candidate launch shape of the fused kernel      */
                           /*    (an index past the last candidate leaves the choice automatic)                   */
     int64_t pitch_skew;   /* -1: automatic; else floats added to the padded row length of x and delta:          */
@@ -287,7 +290,8 @@ ds_status ds_diagnostics(ds_handle* h, double* out4);
  * guess of the previous step was too high or a candidate slot overflowed).  Norm-rescaled codes: the codes written
  * while forming v under a guessed band for max|v| stood (the band held the real maximum and no slot of undecided
  * elements overflowed), instead of the exact second pass.  GSpar: everything that was kept was among the elements
- * collected while forming v under an upper bound of lambda taken from the step before.  Results are identical
+ * collected while forming v under an upper bound of lambda taken from the step before.  Small problems, whose step is
+ * one launch that keeps v in registers, report whether the band would have held.  Results are identical
  * either way.  Synchronises; 0
  * for other compressors; DS_ESTATE before the first step. */
 ds_status ds_topk_candidate_rows(ds_handle* h, uint32_t* count);

@@ -442,7 +442,7 @@ ds_status ds_init_ex(const ds_config* cfg, const ds_plan_request* plan, char* er
     want.tile_plan = -1; want.pitch_skew = -1; want.autotune = 1;
     if (plan) {
         want = *plan;
-        if (want.variant < 0 || want.variant > 1) return bail(DS_EINVAL, "plan: variant must be 0 (automatic) or 1 (row-streaming)");
+        if (want.variant < 0 || want.variant > 3) return bail(DS_EINVAL, "plan: variant must be 0 (automatic), 1 (row-streaming), 2 (no resident kernel) or 3 (resident kernel without patience)");
         if (want.pitch_skew < -1 || want.pitch_skew > (int64_t)kMaxPitchSkew || (want.pitch_skew > 0 && (want.pitch_skew & 3)))
             return bail(DS_EINVAL, "plan: pitch_skew must be -1 (automatic) or a multiple of 4 up to 12288");
     }
@@ -458,13 +458,15 @@ ds_status ds_init_ex(const ds_config* cfg, const ds_plan_request* plan, char* er
 
     const bool sparse_pairs = cfg->comp.kind == DS_COMP_TOPK || cfg->comp.kind == DS_COMP_GSPAR;   // (column, value) messages
     const bool tiled = !sparse_pairs && cfg->comp.kind != DS_COMP_QUANT_L2NORM;
+    bool resident = false;                                 // a whole step in one launch (small problems)
     if (cfg->comp.kind == DS_COMP_GSPAR) {
         h->plan_name = "gspar/sift-scan-write";
     } else if (cfg->comp.kind == DS_COMP_TOPK) {
         h->plan_name = "topk/radix-select";
     } else if (cfg->comp.kind == DS_COMP_QUANT_L2NORM) {
-        h->plan_name = "l2norm/speculative-codes";
-        h->msg_half = (uint64_t)cfg->n * h->msg_row_bytes;     // the first pass writes codes while the old ones are still read
+        resident = want.variant != 2 && dsq::l2q_fits_resident(*cfg);
+        h->plan_name = resident ? "l2norm/resident" : "l2norm/speculative-codes";
+        if (!resident) h->msg_half = (uint64_t)cfg->n * h->msg_row_bytes;     // the first pass writes codes while the old ones are still read
     } else {
         // the row-streaming variant of the block compressors on request; it is also what serves a number of
         // workers whose codes do not fit in LDS
@@ -536,7 +538,7 @@ ds_status ds_init_ex(const ds_config* cfg, const ds_plan_request* plan, char* er
         if (st != DS_OK) return bail(st, err);
     }
     if (cfg->comp.kind == DS_COMP_QUANT_L2NORM) {
-        const ds_status st = dsq::l2q_create(h->cfg, h->ld, &h->l2q, err);
+        const ds_status st = dsq::l2q_create(h->cfg, h->ld, resident, want.variant == 3, &h->l2q, err);
         if (st != DS_OK) return bail(st, err);
     }
     h->err = warn;

@@ -144,6 +144,7 @@ struct L2Args {
     const float* coef;
     uint64_t ld, g_ld, N, msg_row_bytes;
     uint64_t msg_half;         // msg holds two buffers of this many bytes; a step writes the one the last step did not
+                               // (resident kernel: 0, one buffer)
     int n;
     float gamma, eta;
     unsigned long long* t_ptr;  // step cells in device memory: [0] the step counter (advanced once per step), [4] the
@@ -152,10 +153,13 @@ struct L2Args {
 };
 
 struct L2State;                // device scratch: per-row scales, per-chunk partial reductions
-ds_status l2q_create(const ds_config& cfg, uint64_t ld, L2State** out, std::string& err);
+// True if the problem is small enough for the kernel that takes a whole step in one launch (dsq_resident.h).
+bool l2q_fits_resident(const ds_config& cfg);
+// resident: steps take that kernel; impatient: its first meeting calls itself off at once (tests of what follows then).
+ds_status l2q_create(const ds_config& cfg, uint64_t ld, bool resident, bool impatient, L2State** out, std::string& err);
 void l2q_destroy(L2State* s);
 ds_status l2q_step(L2State* s, const L2Args& a, hipStream_t stream);
-// l2q_step leaves delta = v - C[v] and the gossip update of x to the next step's first pass;
+// Unless the handle is resident, l2q_step leaves delta = v - C[v] and the gossip update of x to the next step's first pass;
 // l2q_flush applies them now (no-op if nothing is pending).  Call before the state is read or replaced, with
 // the buffers, mixing matrix and eta the last step ran with (a.g is not used).
 ds_status l2q_flush(L2State* s, const L2Args& a, hipStream_t stream);

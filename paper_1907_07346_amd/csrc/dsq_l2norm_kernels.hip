@@ -39,6 +39,7 @@
 // cell 4 of the step cells names the one the last completed step wrote.
 
 #include "dsq_internal.h"
+#include "dsq_resident.h"
 
 namespace dsq {
 
@@ -76,6 +77,11 @@ struct L2Scratch {
     uint2* uslot;                 // n x nchunks x LQ_UCAP: (column offset in the chunk | placeholder code << 16, bits of v)
     uint32_t* row_flags;          // n: bit 0 = a slot of the row overflowed in this step's form pass
     uint32_t nchunks;
+    // resident kernel only (which needs none of pending, ucount, uslot, row_flags):
+    uint32_t* meetings;           // two meetings of all workgroups (dsq_resident.h) ...
+    unsigned long long* epoch;    // ... and the number of launches so far
+    uint64_t* codes;              // n x nchunks x 256 x words: the sixteen codes of each thread's columns, for the neighbours
+    float* norms;                 // n: the norms that are sent, for the neighbours
 };
 
 // Code of one element for a given inv = (L/2)/s: nearest level, ties to even; NaN goes to level 0.
@@ -374,6 +380,29 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_quantize(L2Args a, L2Scratch s
         s.csy2[(size_t)row * s.nchunks + blockIdx.x] = wave_sy2[0] + wave_sy2[1] + wave_sy2[2] + wave_sy2[3];
 }
 
+// The band the next step may assume for s: centred on this step's s, as wide as s has been moving lately.  A band too
+// wide to be worth it (many undecided elements), an all-zero row, or slots that keep overflowing (many levels: the
+// boundaries are dense) leave the next step without one.
+__device__ __forceinline__ void next_band(L2Row& r, float half_levels) {
+    const bool tried = r.s_hi > 0.f;
+    if (tried && r.overflowed) { r.streak = r.streak < 6u ? r.streak + 1u : 6u; r.wait = 1u << r.streak; }
+    else if (r.mode) r.streak = 0u;
+    const float rel = (r.s_prev > 0.f) ? fabsf(r.s - r.s_prev) / r.s_prev : 0.2f;      // first step: wait for a second look
+    r.drift = fmaxf(rel, 0.7f * r.drift);
+    r.s_prev = r.s;
+    const float h = 1.5f * r.drift + 0.02f;
+    r.s_lo = r.s_hi = r.inv_lo_s = r.inv_hi_s = 0.f;
+    if (r.wait > 0u) {
+        r.wait -= 1u;
+    } else if (r.s > 0.f && h <= 0.3f) {
+        r.s_lo = r.s * (1.f - h);
+        r.s_hi = r.s * (1.f + h);
+        r.inv_lo_s = half_levels / r.s_lo;
+        r.inv_hi_s = half_levels / r.s_hi;
+        if (!(r.s_lo > 0.f) || !(r.inv_lo_s < 3.0e38f)) r.s_lo = r.s_hi = r.inv_lo_s = r.inv_hi_s = 0.f;   // denormal ranges: no guess
+    }
+}
+
 // Per row: sum y^2 (an integer, any order), the decode scale, the message header, and the band the next form
 // pass may assume for s.  The last row to finish closes the step: its tail is now pending, the message buffers
 // change roles, the step counter moves.
@@ -395,26 +424,7 @@ __global__ void __launch_bounds__(LQ_ROW_THREADS) l2q_row_unit(L2Args a, L2Scrat
         for (int k = 0; k < LQ_ROW_THREADS / 64; ++k) total += wsum[k];
         L2Row r = s.rows[row];
         r.unit = (float)((double)r.nrm / sqrt((double)total));           // total >= N >= 1
-        // The band for the next step: centred on this step's s, as wide as s has been moving lately.  A band
-        // too wide to be worth it (many undecided elements), an all-zero row, or slots that keep overflowing
-        // (many levels: the boundaries are dense) leave the next step to the exact second pass.
-        const bool tried = r.s_hi > 0.f;
-        if (tried && r.overflowed) { r.streak = r.streak < 6u ? r.streak + 1u : 6u; r.wait = 1u << r.streak; }
-        else if (r.mode) r.streak = 0u;
-        const float rel = (r.s_prev > 0.f) ? fabsf(r.s - r.s_prev) / r.s_prev : 0.2f;      // first step: wait for a second look
-        r.drift = fmaxf(rel, 0.7f * r.drift);
-        r.s_prev = r.s;
-        const float h = 1.5f * r.drift + 0.02f;
-        r.s_lo = r.s_hi = r.inv_lo_s = r.inv_hi_s = 0.f;
-        if (r.wait > 0u) {
-            r.wait -= 1u;
-        } else if (r.s > 0.f && h <= 0.3f) {
-            r.s_lo = r.s * (1.f - h);
-            r.s_hi = r.s * (1.f + h);
-            r.inv_lo_s = half_levels / r.s_lo;
-            r.inv_hi_s = half_levels / r.s_hi;
-            if (!(r.s_lo > 0.f) || !(r.inv_lo_s < 3.0e38f)) r.s_lo = r.s_hi = r.inv_lo_s = r.inv_hi_s = 0.f;   // denormal ranges: no guess
-        }
+        next_band(r, half_levels);
         s.rows[row] = r;
         *reinterpret_cast<float*>(a.msg + (uint64_t)written * a.msg_half + (uint64_t)row * a.msg_row_bytes) = r.nrm;
         // every workgroup has read cell 4 by the time it counts itself; the last one flips it
@@ -450,46 +460,382 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_tail(L2Args a, L2Scratch s) {
 
 __global__ void l2q_clear_pending(L2Scratch s) { *s.pending = 0u; }
 
+// ---- the resident kernel: a whole step of a small problem in one launch ---------------------------------------
+// One workgroup per (row, chunk); xh and v stay in registers from the only read of x, g and delta to the only write
+// of x and delta (20 B + codes per parameter, nothing deferred, no speculation):
+//   measure   xh, v; max |v| and the tree sum of v^2 of the chunk                                     -> scratch
+//   meeting   (may part: see dsq_resident.h)
+//   encode    every workgroup of a row puts the row's range and norm together for itself; codes -> message and, as one
+//             64-bit word (2 and 4 bits) or two (8 bits) per thread, -> scratch; sum of y^2 of the chunk -> scratch
+//   meeting
+//   finish    the decode units of the neighbours, delta = v - C[v], x = xh + eta sum_j a_ij C[v_j]
+// What bounds it is the chain of two meetings and four round trips to memory.  8 workers x 272,474 parameters at 4 bits
+// with the state complete after every step: 20.3 us, of which loads and measure 4.4, the meetings 1.5-2 each, encode 2.5,
+// finish 4, launch 2.7; the six launches it takes otherwise: 40 us.
+template <int BITS>
+struct L2Resident {
+    static constexpr int L = (1 << BITS) - 1;
+    static constexpr int WORDS = BITS == 8 ? 2 : 1;           // 64-bit words that hold a thread's sixteen codes
+    static constexpr int WAVES = LQ_THREADS / 64;
+    static constexpr int UNITS = 32;                          // neighbours whose units are put together at once
+    struct Shared {
+        double sweep_sq[LQ_ITERS * WAVES];
+        double wave_sq[WAVES];
+        float wave_max[WAVES];
+        uint32_t wave_sy2[WAVES];
+        float unit[UNITS];
+    };
+
+    const L2Args& a;
+    const L2Scratch& s;
+    Shared& sh;
+    int row = 0;
+    uint32_t chunk = 0;
+    int e0 = 0, e1 = 0;
+    int near[4];                                              // the first neighbours, fetched before they are needed
+    float near_coef[4];
+    float4 xh[LQ_ITERS], v[LQ_ITERS];
+    float range = 0.f, nrm = 0.f;                             // nrm: in the workgroups of chunk 0 only
+
+    __device__ __forceinline__ L2Resident(const L2Args& a_, const L2Scratch& s_, Shared& sh_) : a(a_), s(s_), sh(sh_) {}
+
+    __device__ __forceinline__ uint64_t column(int it) const { return (uint64_t)chunk * LQ_CHUNK + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x; }
+
+    // line 5 for the sixteen columns of every thread
+    __device__ __forceinline__ void load(uint32_t which) {
+        __syncthreads();                                      // the shared memory of the chunk before is free
+        row = (int)(which / s.nchunks);
+        chunk = which % s.nchunks;
+        e0 = a.rowptr[row];
+        e1 = a.rowptr[row + 1];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            near[u] = a.col[e0 + u < e1 ? e0 + u : e0];
+            near_coef[u] = a.coef[e0 + u < e1 ? e0 + u : e0];
+        }
+        const float* xr = a.x + (uint64_t)row * a.ld;
+        const float* dr = a.delta + (uint64_t)row * a.ld;
+        const float* gr = a.g + (uint64_t)row * a.g_ld;
+        float4 g[LQ_ITERS];
+#pragma unroll
+        for (int it = 0; it < LQ_ITERS; ++it) {
+            const uint64_t col = column(it);
+            xh[it] = *reinterpret_cast<const float4*>(xr + col);
+            v[it] = *reinterpret_cast<const float4*>(dr + col);
+            g[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (col < a.N) g[it] = *reinterpret_cast<const float4*>(gr + col);
+        }
+#pragma unroll
+        for (int it = 0; it < LQ_ITERS; ++it) {
+            const uint64_t col = column(it);
+            if (col + 3 >= a.N) {                             // whatever lies behind column N-1 is not a gradient
+                if (col + 1 >= a.N) g[it].y = 0.f;
+                if (col + 2 >= a.N) g[it].z = 0.f;
+                g[it].w = 0.f;
+            }
+            xh[it].x = fmaf(-a.gamma, g[it].x, xh[it].x); v[it].x = xh[it].x + v[it].x;
+            xh[it].y = fmaf(-a.gamma, g[it].y, xh[it].y); v[it].y = xh[it].y + v[it].y;
+            xh[it].z = fmaf(-a.gamma, g[it].z, xh[it].z); v[it].z = xh[it].z + v[it].z;
+            xh[it].w = fmaf(-a.gamma, g[it].w, xh[it].w); v[it].w = xh[it].w + v[it].w;
+        }
+    }
+
+    __device__ __forceinline__ void measure() {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        float m = 0.f;
+#pragma unroll
+        for (int it = 0; it < LQ_ITERS; ++it) {
+            const float4 q = v[it];
+            m = fmaxf(m, fmaxf(fmaxf(fabsf(q.x), fabsf(q.y)), fmaxf(fabsf(q.z), fabsf(q.w))));
+            const double sw = wave_tree_f64(((double)q.x * (double)q.x + (double)q.y * (double)q.y) + ((double)q.z * (double)q.z + (double)q.w * (double)q.w));
+            if (lane == 0) sh.sweep_sq[it * WAVES + wave] = sw;                       // sweep index = column order
+        }
+        m = wave_max_f32(m);
+        if (lane == 0) sh.wave_max[wave] = m;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double t[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) t[k] = sh.sweep_sq[k];
+#pragma unroll
+            for (int len = 16; len > 1; len >>= 1)
+#pragma unroll
+                for (int p = 0; p < len / 2; ++p) t[p] = t[2 * p] + t[2 * p + 1];
+            const size_t ci = (size_t)row * s.nchunks + chunk;
+            agent_store(s.csq + ci, t[0]);
+            agent_store(s.cmax + ci, fmaxf(fmaxf(sh.wave_max[0], sh.wave_max[1]), fmaxf(sh.wave_max[2], sh.wave_max[3])));
+        }
+    }
+
+    // The row's range and, for the workgroup of chunk 0, which alone needs it now, the norm: the maximum of, and the tree
+    // continued over, the chunks (at most 1024 of them: four leaves per thread, the missing ones zero; with up to 256
+    // of them one leaf per thread is the same tree).
+    __device__ __forceinline__ void row_scale() {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        const double* sq = s.csq + (size_t)row * s.nchunks;
+        const float* mx = s.cmax + (size_t)row * s.nchunks;
+        const uint32_t per = s.nchunks <= (uint32_t)LQ_THREADS ? 1u : 4u;             // uniform
+        float m = 0.f;
+        double leaf[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+            const uint32_t c = per * threadIdx.x + q;
+            if (q < per && c < s.nchunks) {
+                m = fmaxf(m, agent_load(mx + c));
+                if (chunk == 0) leaf[q] = agent_load(sq + c);
+            }
+        }
+        m = wave_max_f32(m);
+        __syncthreads();                                      // wave_max may still be read from measure()
+        if (lane == 0) sh.wave_max[wave] = m;
+        if (chunk == 0) {                                     // uniform
+            const double sum = wave_tree_f64((leaf[0] + leaf[1]) + (leaf[2] + leaf[3]));
+            if (lane == 0) sh.wave_sq[wave] = sum;
+        }
+        __syncthreads();
+        range = fmaxf(fmaxf(sh.wave_max[0], sh.wave_max[1]), fmaxf(sh.wave_max[2], sh.wave_max[3]));
+        if (chunk == 0) nrm = (float)sqrt((sh.wave_sq[0] + sh.wave_sq[1]) + (sh.wave_sq[2] + sh.wave_sq[3]));
+    }
+
+    __device__ __forceinline__ void encode() {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        row_scale();
+        const float inv = (range > 0.f) ? (0.5f * (float)L) / range : 0.f;
+        const bool zero_row = !(range > 0.f);
+        uint8_t* mrow = a.msg + (uint64_t)row * a.msg_row_bytes;
+        const uint64_t code_bytes = a.msg_row_bytes - 4;      // whole 32-bit words
+        uint32_t sy2 = 0;
+        uint64_t all[WORDS] = {};
+#pragma unroll
+        for (int it = 0; it < LQ_ITERS; ++it) {
+            const uint64_t col = column(it);
+            const float vp[4] = {v[it].x, v[it].y, v[it].z, v[it].w};
+            uint32_t packed = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if (col + c < a.N) {                          // padding codes are 0 and do not count
+                    const int q = zero_row ? 0 : code_of<BITS>(vp[c], inv);
+                    const int y = 2 * q - L;
+                    sy2 += (uint32_t)(y * y);
+                    packed |= (uint32_t)q << (BITS * c);
+                }
+            }
+            all[it * 4 * BITS / 64] |= (uint64_t)packed << (it * 4 * BITS % 64);
+            const uint64_t byte = col * BITS / 8;
+            if (byte < code_bytes) {
+                if constexpr (BITS == 2) mrow[4 + byte] = (uint8_t)packed;
+                else if constexpr (BITS == 4) *reinterpret_cast<uint16_t*>(mrow + 4 + byte) = (uint16_t)packed;
+                else *reinterpret_cast<uint32_t*>(mrow + 4 + byte) = packed;
+            }
+        }
+        const size_t ci = (size_t)row * s.nchunks + chunk;
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) agent_store(s.codes + (ci * LQ_THREADS + threadIdx.x) * WORDS + w, all[w]);
+        sy2 = wave_sum_u32(sy2);
+        if (lane == 0) sh.wave_sy2[wave] = sy2;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            agent_store(s.csy2 + ci, sh.wave_sy2[0] + sh.wave_sy2[1] + sh.wave_sy2[2] + sh.wave_sy2[3]);
+            if (chunk == 0) {
+                agent_store(s.norms + row, nrm);
+                *reinterpret_cast<float*>(mrow) = nrm;
+            }
+        }
+    }
+
+    // The units of up to UNITS neighbours from edge eb on, one wave per neighbour.
+    __device__ __forceinline__ void put_units(int eb, int here) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        for (int u = wave; u < here; u += WAVES) {
+            const int nb = (eb == e0 && u < 4) ? (u == 0 ? near[0] : u == 1 ? near[1] : u == 2 ? near[2] : near[3]) : a.col[eb + u];
+            const float norm = agent_load(s.norms + nb);
+            const uint32_t* sy = s.csy2 + (size_t)nb * s.nchunks;
+            // a chunk's sum is below 2^28 (4096 * 255^2), a row's (at most 1024 chunks) below 2^38: in two halves
+            uint32_t lo = 0, hi = 0;
+            for (uint32_t c = lane; c < s.nchunks; c += 64) {
+                const uint32_t one = agent_load(sy + c);
+                lo += one & 0xFFFFu;
+                hi += one >> 16;
+            }
+            const unsigned long long sum = ((unsigned long long)wave_sum_u32(hi) << 16) + wave_sum_u32(lo);
+            if (lane == 0) sh.unit[u] = (float)((double)norm / sqrt((double)sum));      // sum >= N >= 1
+        }
+    }
+
+    // Lines 6 and 9.
+    __device__ __forceinline__ void finish() {
+        float acc[LQ_ITERS][4] = {};
+        for (int eb = e0; eb < e1; eb += UNITS) {
+            const int here = e1 - eb < UNITS ? e1 - eb : UNITS;
+            __syncthreads();                                  // the units of the neighbours before these are used up
+            constexpr int EB = BITS == 8 ? 2 : 4;             // the codes of so many neighbours are asked for together
+            for (int ub = 0; ub < here; ub += EB) {
+                uint64_t codes[EB][WORDS];
+                int nbs[EB];
+#pragma unroll
+                for (int u = 0; u < EB; ++u) {
+                    nbs[u] = (eb == e0 && ub == 0) ? near[u] : ub + u < here ? a.col[eb + ub + u] : row;
+#pragma unroll
+                    for (int w = 0; w < WORDS; ++w)
+                        codes[u][w] = agent_load(s.codes + (((size_t)nbs[u] * s.nchunks + chunk) * LQ_THREADS + threadIdx.x) * WORDS + w);
+                }
+                if (ub == 0) {                                // uniform; behind the loads of the codes
+                    put_units(eb, here);
+                    __syncthreads();
+                }
+#pragma unroll
+                for (int u = 0; u < EB; ++u) {
+                    if (ub + u < here) {                      // uniform; ascending neighbour index, own index included
+                        const float coef = (eb == e0 && ub == 0) ? near_coef[u] : a.coef[eb + ub + u];
+                        const float unit = sh.unit[ub + u];
+                        const bool own = nbs[u] == row;
+#pragma unroll
+                        for (int it = 0; it < LQ_ITERS; ++it) {
+                            const uint64_t col = column(it);
+                            const uint32_t four = (uint32_t)(codes[u][it * 4 * BITS / 64] >> (it * 4 * BITS % 64));
+                            float* vp = reinterpret_cast<float*>(&v[it]);
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                const float cv = (float)(2 * (int)((four >> (BITS * c)) & (uint32_t)L) - L) * unit;
+                                acc[it][c] = fmaf(coef, cv, acc[it][c]);
+                                if (own && col + c < a.N) vp[c] = vp[c] - cv;
+                            }
+                        }
+                    }
+                }
+            }
+        }
+        float* xr = a.x + (uint64_t)row * a.ld;
+        float* dr = a.delta + (uint64_t)row * a.ld;
+#pragma unroll
+        for (int it = 0; it < LQ_ITERS; ++it) {
+            const uint64_t col = column(it);
+            float* xp = reinterpret_cast<float*>(&xh[it]);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (col + c < a.N) xp[c] = fmaf(a.eta, acc[it][c], xp[c]);             // padding columns stay zero
+            *reinterpret_cast<float4*>(xr + col) = xh[it];
+            *reinterpret_cast<float4*>(dr + col) = v[it];
+        }
+    }
+
+    // One workgroup does everything: what it has written in this phase is there for the next.
+    __device__ __forceinline__ void phase_end() {
+        drain();
+        __syncthreads();
+    }
+
+    // What ds_topk_candidate_rows reports: would the range have stayed in the band the steps before suggest?  (Here v is
+    // in registers, nothing is guessed.)
+    __device__ __forceinline__ void keep_book() {
+        if (chunk != 0 || threadIdx.x != 0) return;
+        L2Row r = s.rows[row];
+        r.s = range;
+        r.nrm = nrm;
+        r.overflowed = 0u;
+        r.mode = (r.s_hi > 0.f && range >= r.s_lo && range <= r.s_hi) ? 1u : 0u;
+        next_band(r, 0.5f * (float)L);
+        s.rows[row] = r;
+    }
+};
+
+template <int BITS>
+__global__ void __launch_bounds__(LQ_THREADS, 5) l2q_resident(L2Args a, L2Scratch s, uint64_t patience) {
+    __shared__ typename L2Resident<BITS>::Shared sh;
+    const uint32_t blocks = gridDim.x;
+    const unsigned long long epoch = *s.epoch;
+    L2Resident<BITS> op(a, s, sh);
+    // The same code serves the one chunk of a workgroup and, after parting, all chunks of the last one: then a chunk's
+    // xh and v are formed anew in every phase (x and delta change only in the last one, each chunk for itself).
+    uint32_t first = blockIdx.x, last = blockIdx.x + 1u;
+    bool alone = false;
+    op.load(first);
+    for (;;) {
+        for (uint32_t i = first; i < last; ++i) {
+            if (alone) op.load(i);
+            op.measure();
+        }
+        if (alone || meet<true, false>(s.meetings, blocks, epoch, patience)) break;
+        if (!leave(a.t_ptr, blocks)) return;
+        alone = true;
+        first = 0u;
+        last = blocks;
+    }
+    if (alone) op.phase_end();
+    for (uint32_t i = first; i < last; ++i) {
+        if (alone) op.load(i);
+        op.encode();
+        op.keep_book();
+    }
+    if (alone) op.phase_end();
+    else (void)meet<false, true>(s.meetings + kMeetWords, blocks, epoch, 0, s.epoch, a.t_ptr);
+    for (uint32_t i = first; i < last; ++i) {
+        if (alone) op.load(i);
+        op.finish();
+    }
+    if (alone) close_alone(s.meetings, 2, blocks, epoch, s.epoch, a.t_ptr);
+}
+
 }  // namespace
 
 struct L2State {
     L2Scratch s{};
     int n = 0, bits = 0;
     bool stepped = false;          // a step has been enqueued (or may have been, by a replayed graph)
+    bool resident = false;         // steps run in one launch each and leave nothing pending
+    uint64_t patience = 0;         // of the resident kernel's first meeting
 };
 
 void l2q_destroy(L2State* st) {
     if (!st) return;
     L2Scratch& s = st->s;
-    void* ptrs[] = {s.rows, s.cmax, s.csq, s.csy2, s.pending, s.ucount, s.uslot, s.row_flags};
+    void* ptrs[] = {s.rows, s.cmax, s.csq, s.csy2, s.pending, s.ucount, s.uslot, s.row_flags, s.meetings, s.epoch, s.codes, s.norms};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     delete st;
 }
 
-ds_status l2q_create(const ds_config& cfg, uint64_t ld, L2State** out, std::string& err) {
+bool l2q_fits_resident(const ds_config& cfg) {
+    const uint64_t nchunks = (cfg.N + LQ_CHUNK - 1) / LQ_CHUNK;
+    if (nchunks > 4ull * LQ_THREADS) return false;            // row_scale() takes four chunks per thread
+    const uint32_t limit = cfg.comp.bits == 2 ? resident_limit(l2q_resident<2>, LQ_THREADS)
+                         : cfg.comp.bits == 4 ? resident_limit(l2q_resident<4>, LQ_THREADS) : resident_limit(l2q_resident<8>, LQ_THREADS);
+    return (uint64_t)cfg.n * nchunks <= limit;
+}
+
+ds_status l2q_create(const ds_config& cfg, uint64_t ld, bool resident, bool impatient, L2State** out, std::string& err) {
     L2State* st = new (std::nothrow) L2State();
     if (!st) { err = "out of host memory"; return DS_ENOMEM; }
     st->n = cfg.n;
     st->bits = cfg.comp.bits;
+    st->resident = resident;
+    st->patience = impatient ? 0 : kMeetPatience;
     L2Scratch& s = st->s;
     s.nchunks = (uint32_t)((cfg.N + LQ_CHUNK - 1) / LQ_CHUNK);
     if ((uint64_t)s.nchunks * LQ_CHUNK > ld) { err = "internal: row pitch smaller than the chunked row"; l2q_destroy(st); return DS_EINVAL; }
     const size_t n = (size_t)cfg.n, nc = s.nchunks;
-    bool ok = hipMalloc(&s.rows, n * sizeof(L2Row)) == hipSuccess &&
-              hipMalloc(&s.cmax, n * nc * sizeof(float)) == hipSuccess &&
-              hipMalloc(&s.csq, n * nc * sizeof(double)) == hipSuccess &&
-              hipMalloc(&s.csy2, n * nc * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.pending, sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.ucount, n * nc * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.uslot, n * nc * LQ_UCAP * sizeof(uint2)) == hipSuccess &&
-              hipMalloc(&s.row_flags, n * sizeof(uint32_t)) == hipSuccess;
     // rows start with no guess (s_hi = 0): the first two steps are exact (the first has no s_prev and counts as a
     // movement of 20 %, too wide a band), speculation starts with the third if s moved little between them
-    ok = ok && hipMemset(s.rows, 0, n * sizeof(L2Row)) == hipSuccess &&
-         hipMemset(s.ucount, 0, n * nc * sizeof(uint32_t)) == hipSuccess &&
-         hipMemset(s.row_flags, 0, n * sizeof(uint32_t)) == hipSuccess &&
-         hipMemset(s.pending, 0, sizeof(uint32_t)) == hipSuccess && hipDeviceSynchronize() == hipSuccess;
+    bool ok = hipMalloc(&s.rows, n * sizeof(L2Row)) == hipSuccess && hipMemset(s.rows, 0, n * sizeof(L2Row)) == hipSuccess &&
+              hipMalloc(&s.cmax, n * nc * sizeof(float)) == hipSuccess &&
+              hipMalloc(&s.csq, n * nc * sizeof(double)) == hipSuccess &&
+              hipMalloc(&s.csy2, n * nc * sizeof(uint32_t)) == hipSuccess;
+    if (resident) {
+        const size_t code_bytes = n * nc * LQ_THREADS * (st->bits == 8 ? 2 : 1) * sizeof(uint64_t);
+        ok = ok && hipMalloc(&s.meetings, 2 * kMeetWords * sizeof(uint32_t)) == hipSuccess &&
+             hipMemset(s.meetings, 0, 2 * kMeetWords * sizeof(uint32_t)) == hipSuccess &&
+             hipMalloc(&s.epoch, sizeof(unsigned long long)) == hipSuccess && hipMemset(s.epoch, 0, sizeof(unsigned long long)) == hipSuccess &&
+             hipMalloc(&s.codes, code_bytes) == hipSuccess && hipMalloc(&s.norms, n * sizeof(float)) == hipSuccess;
+    } else {
+        ok = ok && hipMalloc(&s.pending, sizeof(uint32_t)) == hipSuccess &&
+             hipMalloc(&s.ucount, n * nc * sizeof(uint32_t)) == hipSuccess &&
+             hipMalloc(&s.uslot, n * nc * LQ_UCAP * sizeof(uint2)) == hipSuccess &&
+             hipMalloc(&s.row_flags, n * sizeof(uint32_t)) == hipSuccess &&
+             hipMemset(s.ucount, 0, n * nc * sizeof(uint32_t)) == hipSuccess &&
+             hipMemset(s.row_flags, 0, n * sizeof(uint32_t)) == hipSuccess &&
+             hipMemset(s.pending, 0, sizeof(uint32_t)) == hipSuccess;
+    }
+    ok = ok && hipDeviceSynchronize() == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         err = "scratch allocation for the norm-rescaled compressor failed";
@@ -502,6 +848,13 @@ ds_status l2q_create(const ds_config& cfg, uint64_t ld, L2State** out, std::stri
 
 ds_status l2q_step(L2State* st, const L2Args& a, hipStream_t stream) {
     const L2Scratch& s = st->s;
+    if (st->resident) {
+        const dim3 grid(s.nchunks * (uint32_t)a.n), block(LQ_THREADS);
+        if (st->bits == 2)      hipLaunchKernelGGL(l2q_resident<2>, grid, block, 0, stream, a, s, st->patience);
+        else if (st->bits == 4) hipLaunchKernelGGL(l2q_resident<4>, grid, block, 0, stream, a, s, st->patience);
+        else                    hipLaunchKernelGGL(l2q_resident<8>, grid, block, 0, stream, a, s, st->patience);
+        return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
+    }
     const dim3 grid(s.nchunks, a.n), block(LQ_THREADS), rows(a.n), rblock(LQ_ROW_THREADS);
     const float hl = 0.5f * (float)((1 << st->bits) - 1);
     // All rows go through `form` before any row's codes are replaced: the tail that `form` applies reads the
@@ -520,7 +873,7 @@ ds_status l2q_step(L2State* st, const L2Args& a, hipStream_t stream) {
 }
 
 ds_status l2q_flush(L2State* st, const L2Args& a, hipStream_t stream) {
-    if (!st || !st->stepped) return DS_OK;
+    if (!st || !st->stepped) return DS_OK;                    // (never set by the resident kernel)
     const L2Scratch& s = st->s;
     const dim3 grid(s.nchunks, a.n), block(LQ_THREADS);
     // the kernels look at the device's pending flag themselves: a replayed graph of ds_step sets it

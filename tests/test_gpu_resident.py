@@ -1,0 +1,87 @@
+"""The kernels that take a whole step of a small problem in one launch (csrc/dsq_resident.h), against the CPU oracle.
+
+Three ways through every case (ds_plan_request.variant): 0, the resident kernel; 3, the same kernel calling its first
+meeting off at once, so that the workgroup that leaves last does the whole step alone; 2, the launches that large
+problems use.  Messages byte for byte, state bit for bit, with and without the state being read between steps.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1907_07346_amd import binding as b
+from paper_1907_07346_amd import workloads as wl
+from test_gpu_parity import assert_close, lock_step, oracle_state, say, small, upload
+
+pytestmark = pytest.mark.gpu
+
+# one parameter, one ragged chunk, whole chunks, ragged ones, over 256 chunks in a row (several tree leaves per thread),
+# and graphs whose rows have more than four neighbours
+CASES = [
+    small(wl.KIND_QUANT_L2NORM, 3, 1, bits=4),
+    small(wl.KIND_QUANT_L2NORM, 5, 4095, bits=2),
+    small(wl.KIND_QUANT_L2NORM, 4, 4096 * 2, bits=8),
+    small(wl.KIND_QUANT_L2NORM, 9, 4096 * 3 + 17, bits=4, topo=wl.TOPO_TORUS2D, torus=(3, 3)),
+    small(wl.KIND_QUANT_L2NORM, 3, 4096 * 180 + 1, bits=2),
+    small(wl.KIND_QUANT_L2NORM, 35, 4096 * 2 + 2, bits=8),
+]
+
+
+def _plan(variant):
+    return {"variant": variant}
+
+
+@pytest.mark.parametrize("w", CASES, ids=lambda w: w.name)
+@pytest.mark.parametrize("variant", [0, 3, 2])
+def test_resident_lock_step(w, variant):
+    say("case", w.name, "variant", variant)
+    ds = b.DeepSqueeze.from_workload(w, _plan(variant))
+    assert ("resident" in ds.ds_plan_name()) == (variant != 2), ds.ds_plan_name()
+    ds.ds_destroy()
+    lock_step(w, steps=2, plan=_plan(variant))
+
+
+@pytest.mark.parametrize("w", [CASES[3], CASES[4]], ids=lambda w: w.name)
+@pytest.mark.parametrize("variant", [0, 3])
+def test_resident_free_run(w, variant):
+    """Nothing read or written between the steps but the messages."""
+    ds = b.DeepSqueeze.from_workload(w, _plan(variant))
+    st = oracle_state(w)
+    for t in range(6):
+        g = wl.gradient(w, t)
+        ds.ds_step(upload(g))
+        _, msg = oracle.step(st, g, want_cv=False)
+        assert np.array_equal(ds.ds_read_messages(), msg), f"step {t}: messages differ"
+    x, d = ds.ds_read_state()
+    assert ds.ds_step_count() == 6
+    ds.ds_destroy()
+    assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
+
+
+@pytest.mark.parametrize("w", [small(wl.KIND_QUANT_L2NORM, 40, 300, bits=4)], ids=lambda w: w.name)
+def test_resident_dense_graph(w):
+    """Every worker averages with all 40: more neighbours than are put together at once."""
+    n = w.n
+    W = np.full((n, n), 1.0 / n, np.float32)
+    csr = (np.arange(n + 1, dtype=np.int32) * n, np.tile(np.arange(n, dtype=np.int32), n), W.reshape(-1))
+    lock_step(w, steps=2, W=W, csr=csr)
+
+
+def test_two_resident_handles_on_two_streams():
+    """Two handles step side by side on streams of their own: their workgroups fit next to each other."""
+    import torch
+    ws = [CASES[4], small(wl.KIND_QUANT_L2NORM, 8, 4096 * 40 + 1001, bits=4, seed=9)]
+    dss = [b.DeepSqueeze.from_workload(w) for w in ws]
+    sts = [oracle_state(w) for w in ws]
+    streams = [torch.cuda.Stream() for _ in ws]
+    gs = [[wl.gradient(w, t) for t in range(8)] for w in ws]
+    ups = [[upload(g) for g in one] for one in gs]
+    torch.cuda.synchronize()
+    for t in range(8):
+        for ds, up, s in zip(dss, ups, streams):
+            ds.ds_step(up[t], s)
+    for w, ds, st, one in zip(ws, dss, sts, gs):
+        for g in one:
+            oracle.step(st, g, want_cv=False, want_msg=False)
+        x, d = ds.ds_read_state()
+        ds.ds_destroy()
+        assert assert_close(f"{w.name} x", x, st.x) + assert_close(f"{w.name} delta", d, st.delta) == 0
