@@ -459,10 +459,9 @@ ds_status ds_init_ex(const ds_config* cfg, const ds_plan_request* plan, char* er
     const bool sparse_pairs = cfg->comp.kind == DS_COMP_TOPK || cfg->comp.kind == DS_COMP_GSPAR;   // (column, value) messages
     const bool tiled = !sparse_pairs && cfg->comp.kind != DS_COMP_QUANT_L2NORM;
     bool resident = false;                                 // a whole step in one launch (small problems)
-    if (cfg->comp.kind == DS_COMP_GSPAR) {
-        h->plan_name = "gspar/sift-scan-write";
-    } else if (cfg->comp.kind == DS_COMP_TOPK) {
-        h->plan_name = "topk/radix-select";
+    if (sparse_pairs) {
+        resident = want.variant != 2 && dsq::topk_fits_resident(*cfg);
+        h->plan_name = cfg->comp.kind == DS_COMP_GSPAR ? "gspar/sift-scan-write" : resident ? "topk/resident" : "topk/radix-select";
     } else if (cfg->comp.kind == DS_COMP_QUANT_L2NORM) {
         resident = want.variant != 2 && dsq::l2q_fits_resident(*cfg);
         h->plan_name = resident ? "l2norm/resident" : "l2norm/speculative-codes";
@@ -534,7 +533,7 @@ ds_status ds_init_ex(const ds_config* cfg, const ds_plan_request* plan, char* er
     h->plan_name += "/pitch+" + std::to_string(skew);
 
     if (sparse_pairs) {
-        const ds_status st = dsq::topk_create(h->cfg, h->ld, &h->topk, err);
+        const ds_status st = dsq::topk_create(h->cfg, h->ld, resident, want.variant == 3, &h->topk, err);
         if (st != DS_OK) return bail(st, err);
     }
     if (cfg->comp.kind == DS_COMP_QUANT_L2NORM) {
@@ -559,7 +558,7 @@ ds_status ds_step(ds_handle* h, const float* g_dev, uint64_t g_ld, void* hip_str
 
     if (h->topk) {
         const ds_status st = dsq::topk_step(h->topk, topk_args(h, g_dev, g_ld), stream);
-        if (st != DS_OK) return st;
+        if (st != DS_OK) return fail(h, st, "launching the sparsifying step failed");
     } else if (h->cfg.comp.kind == DS_COMP_QUANT_L2NORM) {
         const ds_status st = dsq::l2q_step(h->l2q, l2_args(h, g_dev, g_ld), stream);
         if (st != DS_OK) return fail(h, st, "launching the norm-rescaled step failed");

@@ -121,10 +121,13 @@ struct TopkArgs {
 };
 
 struct TopkState;              // device scratch of the radix select (histograms, per-chunk counts)
-ds_status topk_create(const ds_config& cfg, uint64_t ld, TopkState** out, std::string& err);
+// True if the problem is small enough for the kernel that takes a whole step in one launch (dsq_topk_resident.hip).
+bool topk_fits_resident(const ds_config& cfg);
+// resident: steps take that kernel; impatient: its first meeting calls itself off at once (tests of what follows then).
+ds_status topk_create(const ds_config& cfg, uint64_t ld, bool resident, bool impatient, TopkState** out, std::string& err);
 void topk_destroy(TopkState* s);
 ds_status topk_step(TopkState* s, const TopkArgs& a, hipStream_t stream);
-// topk_step leaves the sparse part of the gossip update of x to the next step's first pass;
+// Unless the handle is resident, topk_step leaves the sparse part of the gossip update of x to the next step's first pass;
 // topk_flush applies it now (no-op if nothing is pending).  Call before x is read or replaced, with the
 // buffers, mixing matrix and eta the last step ran with (a.g is not used).
 ds_status topk_flush(TopkState* s, const TopkArgs& a, hipStream_t stream);

@@ -323,6 +323,7 @@ static_assert(LQ_ROW_THREADS / 64 == 16, "the wave tree above is written for 16 
 // word, a correction of the chunk's sum of y^2).  Other rows: the codes of v (which `form` left in delta) and the
 // sum of y^2 per chunk, from scratch.
 static_assert(LQ_UCAP <= LQ_THREADS, "one slot entry per thread");
+static_assert(LQ_THREADS == kResThreads && LQ_ITERS == kResIters, "the resident kernel works on the same chunks");
 template <int BITS>
 __global__ void __launch_bounds__(LQ_THREADS) l2q_quantize(L2Args a, L2Scratch s) {
     constexpr int L = (1 << BITS) - 1;
@@ -473,7 +474,7 @@ __global__ void l2q_clear_pending(L2Scratch s) { *s.pending = 0u; }
 // with the state complete after every step: 20.3 us, of which loads and measure 4.4, the meetings 1.5-2 each, encode 2.5,
 // finish 4, launch 2.7; the six launches it takes otherwise: 40 us.
 template <int BITS>
-struct L2Resident {
+struct L2Resident : ResidentChunk<L2Args> {
     static constexpr int L = (1 << BITS) - 1;
     static constexpr int WORDS = BITS == 8 ? 2 : 1;           // 64-bit words that hold a thread's sixteen codes
     static constexpr int WAVES = LQ_THREADS / 64;
@@ -486,59 +487,14 @@ struct L2Resident {
         float unit[UNITS];
     };
 
-    const L2Args& a;
+    using Chunk = ResidentChunk<L2Args>;
+    using Chunk::a; using Chunk::row; using Chunk::chunk; using Chunk::e0; using Chunk::e1; using Chunk::near; using Chunk::near_coef;
+    using Chunk::xh; using Chunk::v; using Chunk::column;
     const L2Scratch& s;
     Shared& sh;
-    int row = 0;
-    uint32_t chunk = 0;
-    int e0 = 0, e1 = 0;
-    int near[4];                                              // the first neighbours, fetched before they are needed
-    float near_coef[4];
-    float4 xh[LQ_ITERS], v[LQ_ITERS];
     float range = 0.f, nrm = 0.f;                             // nrm: in the workgroups of chunk 0 only
 
-    __device__ __forceinline__ L2Resident(const L2Args& a_, const L2Scratch& s_, Shared& sh_) : a(a_), s(s_), sh(sh_) {}
-
-    __device__ __forceinline__ uint64_t column(int it) const { return (uint64_t)chunk * LQ_CHUNK + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x; }
-
-    // line 5 for the sixteen columns of every thread
-    __device__ __forceinline__ void load(uint32_t which) {
-        __syncthreads();                                      // the shared memory of the chunk before is free
-        row = (int)(which / s.nchunks);
-        chunk = which % s.nchunks;
-        e0 = a.rowptr[row];
-        e1 = a.rowptr[row + 1];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            near[u] = a.col[e0 + u < e1 ? e0 + u : e0];
-            near_coef[u] = a.coef[e0 + u < e1 ? e0 + u : e0];
-        }
-        const float* xr = a.x + (uint64_t)row * a.ld;
-        const float* dr = a.delta + (uint64_t)row * a.ld;
-        const float* gr = a.g + (uint64_t)row * a.g_ld;
-        float4 g[LQ_ITERS];
-#pragma unroll
-        for (int it = 0; it < LQ_ITERS; ++it) {
-            const uint64_t col = column(it);
-            xh[it] = *reinterpret_cast<const float4*>(xr + col);
-            v[it] = *reinterpret_cast<const float4*>(dr + col);
-            g[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (col < a.N) g[it] = *reinterpret_cast<const float4*>(gr + col);
-        }
-#pragma unroll
-        for (int it = 0; it < LQ_ITERS; ++it) {
-            const uint64_t col = column(it);
-            if (col + 3 >= a.N) {                             // whatever lies behind column N-1 is not a gradient
-                if (col + 1 >= a.N) g[it].y = 0.f;
-                if (col + 2 >= a.N) g[it].z = 0.f;
-                g[it].w = 0.f;
-            }
-            xh[it].x = fmaf(-a.gamma, g[it].x, xh[it].x); v[it].x = xh[it].x + v[it].x;
-            xh[it].y = fmaf(-a.gamma, g[it].y, xh[it].y); v[it].y = xh[it].y + v[it].y;
-            xh[it].z = fmaf(-a.gamma, g[it].z, xh[it].z); v[it].z = xh[it].z + v[it].z;
-            xh[it].w = fmaf(-a.gamma, g[it].w, xh[it].w); v[it].w = xh[it].w + v[it].w;
-        }
-    }
+    __device__ __forceinline__ L2Resident(const L2Args& a_, const L2Scratch& s_, Shared& sh_) : Chunk(a_, s_.nchunks), s(s_), sh(sh_) {}
 
     __device__ __forceinline__ void measure() {
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -705,8 +661,6 @@ struct L2Resident {
                 }
             }
         }
-        float* xr = a.x + (uint64_t)row * a.ld;
-        float* dr = a.delta + (uint64_t)row * a.ld;
 #pragma unroll
         for (int it = 0; it < LQ_ITERS; ++it) {
             const uint64_t col = column(it);
@@ -714,15 +668,8 @@ struct L2Resident {
 #pragma unroll
             for (int c = 0; c < 4; ++c)
                 if (col + c < a.N) xp[c] = fmaf(a.eta, acc[it][c], xp[c]);             // padding columns stay zero
-            *reinterpret_cast<float4*>(xr + col) = xh[it];
-            *reinterpret_cast<float4*>(dr + col) = v[it];
+            Chunk::store(it, threadIdx.x);
         }
-    }
-
-    // One workgroup does everything: what it has written in this phase is there for the next.
-    __device__ __forceinline__ void phase_end() {
-        drain();
-        __syncthreads();
     }
 
     // What ds_topk_candidate_rows reports: would the range have stayed in the band the steps before suggest?  (Here v is

@@ -185,6 +185,93 @@ __device__ __forceinline__ uint32_t wave_inclusive_u32(uint32_t v) {            
 }
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_u32(v), 63); }
 
+// The part of the state that one workgroup of a resident kernel keeps in registers: 4096 columns of a worker row, sixteen
+// columns of a thread in four quads of adjacent ones.
+constexpr int kResThreads = 256;
+constexpr int kResIters = 4;
+constexpr int kResChunk = 4 * kResThreads * kResIters;
+constexpr int kResNear = 4;                                 // neighbours whose index and coefficient are fetched ahead
+
+template <typename Args>                                    // L2Args or TopkArgs
+struct ResidentChunk {
+    const Args& a;
+    const uint32_t nchunks;
+    int row = 0;
+    uint32_t chunk = 0;
+    int e0 = 0, e1 = 0;
+    int near[kResNear];
+    float near_coef[kResNear];
+    float4 xh[kResIters], v[kResIters];
+
+    __device__ __forceinline__ ResidentChunk(const Args& a_, uint32_t nchunks_) : a(a_), nchunks(nchunks_) {}
+
+    __device__ __forceinline__ uint64_t column(int it) const { return (uint64_t)chunk * kResChunk + (uint64_t)it * (4 * kResThreads) + 4u * threadIdx.x; }
+    __device__ __forceinline__ size_t place() const { return (size_t)row * nchunks + chunk; }
+
+    __device__ __forceinline__ void locate(uint32_t which) {   // rows one after the other
+        __syncthreads();                                    // the shared memory of the chunk before is free
+        row = (int)(which / nchunks);
+        chunk = which % nchunks;
+        e0 = a.rowptr[row];
+        e1 = a.rowptr[row + 1];
+#pragma unroll
+        for (int u = 0; u < kResNear; ++u) {
+            near[u] = a.col[e0 + u < e1 ? e0 + u : e0];
+            near_coef[u] = a.coef[e0 + u < e1 ? e0 + u : e0];
+        }
+    }
+
+    // Algorithm 1, line 5, for the sixteen columns of every thread of chunk `which`
+    __device__ __forceinline__ void load(uint32_t which) {
+        locate(which);
+        const float* xr = a.x + (uint64_t)row * a.ld;
+        const float* dr = a.delta + (uint64_t)row * a.ld;
+        const float* gr = a.g + (uint64_t)row * a.g_ld;
+        float4 g[kResIters];
+#pragma unroll
+        for (int it = 0; it < kResIters; ++it) {
+            const uint64_t col = column(it);
+            xh[it] = *reinterpret_cast<const float4*>(xr + col);
+            v[it] = *reinterpret_cast<const float4*>(dr + col);
+            g[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (col < a.N) g[it] = *reinterpret_cast<const float4*>(gr + col);
+        }
+#pragma unroll
+        for (int it = 0; it < kResIters; ++it) {
+            const uint64_t col = column(it);
+            if (col + 3 >= a.N) {                           // whatever lies behind column N-1 is not a gradient
+                if (col + 1 >= a.N) g[it].y = 0.f;
+                if (col + 2 >= a.N) g[it].z = 0.f;
+                g[it].w = 0.f;
+            }
+            xh[it].x = fmaf(-a.gamma, g[it].x, xh[it].x); v[it].x = xh[it].x + v[it].x;
+            xh[it].y = fmaf(-a.gamma, g[it].y, xh[it].y); v[it].y = xh[it].y + v[it].y;
+            xh[it].z = fmaf(-a.gamma, g[it].z, xh[it].z); v[it].z = xh[it].z + v[it].z;
+            xh[it].w = fmaf(-a.gamma, g[it].w, xh[it].w); v[it].w = xh[it].w + v[it].w;
+        }
+    }
+
+    // The thread's index as a value the compiler knows nothing about: what is derived from it is worked out where it is
+    // needed, and addresses are not kept in registers from one end of the kernel to the other.
+    static __device__ __forceinline__ uint32_t thread_here() {
+        uint32_t t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
+    }
+
+    __device__ __forceinline__ void store(int it, uint32_t thread) const {
+        const uint64_t at = (uint64_t)row * a.ld + (uint64_t)chunk * kResChunk + (uint32_t)it * (4 * kResThreads) + 4u * thread;
+        *reinterpret_cast<float4*>(a.x + at) = xh[it];
+        *reinterpret_cast<float4*>(a.delta + at) = v[it];
+    }
+
+    // One workgroup does everything: what it has written in this phase is there for the next.
+    __device__ __forceinline__ void phase_end() const {
+        drain();
+        __syncthreads();
+    }
+};
+
 // How many workgroups a resident kernel may have: half of what the current device holds at once.
 template <typename K>
 uint32_t resident_limit(K kernel, int threads) {

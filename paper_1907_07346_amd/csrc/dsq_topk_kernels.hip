@@ -38,7 +38,7 @@
 // applied by topk_flush before anyone else looks at the state.
 
 #include "dsq_internal.h"
-#include "dsq_philox.h"
+#include "dsq_topk_common.h"
 
 namespace dsq {
 
@@ -55,37 +55,12 @@ constexpr int TK_HTHREADS = 1024;            // threads of those workgroups
 constexpr int TK_FWG = 64;                   // full-mode workgroups per row (grid-stride over the row's chunks)
 constexpr int TK_WPW = 8;                    // chunks per wave (= workgroup) in topk_write_cand
 constexpr int TK_RTHREADS = 1024;            // threads of the per-row kernels
-constexpr int BINS1 = 2048, SHIFT1 = 20;     // level 1: key bits 30..20
 constexpr int BINS2 = 2048, SHIFT2 = 9;      // level 2: key bits 19..9
 constexpr int BINS3 = 512;                   // level 3: key bits 8..0
 constexpr int HIST_BINS = 2048;
 constexpr uint32_t FINE_SPAN = 1u << SHIFT2; // keys in a level-2 bin
 constexpr int TK_HPARTS = 16;                // partial level-1 histograms per row the first pass spreads its atomics over
 constexpr uint32_t TK_LIST_CAP = 8192;       // candidates inside the threshold's level-2 bin a row can list
-constexpr float TK_TARGET = 1.6f;            // candidates aimed at, in units of k
-
-struct TopkRow {
-    uint32_t prefix1, need1;   // full mode: level-1 bin holding the threshold; how many to take inside it
-    uint32_t prefix2, need2;   // full mode: 22-bit prefix of the threshold key; how many to take among its matches
-    uint32_t tau, r_tie;       // threshold key; number of elements with key == tau to take (lowest indices)
-    uint32_t total;            // number of selected elements found by the scan (must equal k)
-    uint32_t tlo;              // candidate threshold key for the next first pass (0xffffffff: collect nothing)
-    uint32_t cand_mode;        // 1: this step's select runs on the candidate slots
-    uint32_t overflow;         // a slot overflowed in this step's first pass
-    uint32_t cand_total;       // candidates collected in this step
-    uint32_t tlo_used;         // the threshold this step's first pass collected with
-    uint32_t tau_prev;         // threshold key of the previous step (0xffffffff: none yet)
-    uint32_t bin_lo;           // candidate mode: first key of the histogram bin that holds the threshold
-    uint32_t bin_need;         //                 how many elements to take inside that bin
-    uint32_t list_count;       //                 elements of that bin listed so far by topk_bin_collect
-    float drift_prev;          // last step's movement of |tau| as a float (for the forecast of the next threshold)
-    float lambda;              // GSpar: this step's k / sum |v|
-    float lambda_hi;           // GSpar: the upper bound the NEXT first pass collects with (0: none)
-    uint32_t gs_mode;          // GSpar: 1 = this step's kept elements are among those its first pass collected
-    uint32_t gs_need_count;    // GSpar: chunks of the row that must decide from v itself (0: gs_count_dense has nothing to do)
-    uint32_t gs_need_write;    // GSpar: chunks that kept more than a slot holds (0: gs_write_dense has nothing to do)
-    uint32_t gs_total;         // GSpar: pairs in the row's last message (what a shorter message must clear behind it)
-};
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float4 ld4_stream(const float* p) {
@@ -96,8 +71,6 @@ __device__ __forceinline__ void st4_stream(float* p, const float4& v) {
     const f32x4 w = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(w, reinterpret_cast<f32x4*>(p));
 }
-
-__device__ __forceinline__ uint32_t key_of(float v) { return __float_as_uint(v) & 0x7FFFFFFFu; }
 
 // Exclusive prefix sum over the 256 threads of a workgroup; *total receives the sum.
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* wave_sums /*[4]*/, uint32_t* total) {
@@ -170,23 +143,6 @@ __device__ __forceinline__ uint32_t row_exclusive_scan(uint32_t v, uint32_t* wav
     }
     *total = tot;
     return base + inc - v;
-}
-
-constexpr uint32_t kGsparStreamTag = 0x47535052u;            // GSpar: 4th counter word of the mask's random stream
-
-// The keep decisions of four adjacent columns of worker `row`.
-__device__ __forceinline__ uint32_t gs_keep4(const TopkArgs& a, int row, uint64_t j, uint32_t t_lo, float lambda, const float4& v) {
-    uint32_t rnd[4];
-    philox4x32_10((uint32_t)(j >> 2), (uint32_t)row, t_lo, kGsparStreamTag, a.seed_lo, a.seed_hi, rnd);
-    const float vv[4] = {v.x, v.y, v.z, v.w};
-    uint32_t keep = 0;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const float p = lambda * fabsf(vv[c]);
-        const float u = (float)(rnd[c] >> 8) * (1.0f / 16777216.0f);
-        if (j + c < a.N && u < p) keep |= 1u << c;
-    }
-    return keep;
 }
 
 // Exclusive prefix sums of four small counts at once (16 bits each, packed; sums stay below 2^16) over the 256
@@ -707,36 +663,6 @@ __global__ void __launch_bounds__(TK_HTHREADS) topk_bin_collect(Scratch s) {
         if (sub == 0) { s.cnt_gt[cidx] = gt; s.cnt_eq[cidx] = 0; }
         cnt = cnt_next;
     }
-}
-
-// ---- where to collect candidates in the next step ------------------------------------------------
-// Near the threshold the number of keys above a level falls roughly exponentially with the level.  With
-// d = tau - tlo the distance that caught ratio * k candidates this step, d* = d ln(target) / ln(ratio) would
-// have caught target * k; the next level is (forecast of the next tau) - d*.  The forecast is made on |tau|
-// as a float (keys are only piecewise linear in the magnitude: the slope halves at every power of two): the
-// last movement repeated, or three quarters of it while the movement still changes by more than a quarter
-// from step to step (early in a run delta grows fast and then settles).  Without usable candidates (full
-// mode) a fixed distance of two million keys (a quarter of a binade) is taken.  Only speed depends on this
-// guess; a bad one sends the row through the exact full path.
-__device__ __forceinline__ uint32_t next_candidate_threshold(TopkRow& r, uint32_t tau, uint32_t k) {
-    const float d0 = 2.f * (float)(1u << SHIFT1);
-    float dist = d0;
-    if (r.cand_mode && r.cand_total > k && tau > r.tlo_used) {
-        const float ratio = (float)r.cand_total / (float)k;
-        dist = (float)(tau - r.tlo_used) * (logf(TK_TARGET) / logf(ratio));
-        dist = fminf(fmaxf(dist, 65536.f), 4.f * d0);
-    }
-    const float mag = __uint_as_float(tau);
-    float move = 0.f, next = mag;
-    if (r.tau_prev != 0xFFFFFFFFu) {
-        move = mag - __uint_as_float(r.tau_prev);
-        const bool steady = fabsf(move - r.drift_prev) <= 0.25f * fabsf(move);
-        next = mag + (steady ? move : 0.75f * move);
-        if (!(next > 0.f) || !(next < 3.0e38f)) next = mag;
-    }
-    r.drift_prev = move;
-    const float t = (float)__float_as_uint(next) - dist;
-    return t > 0.f ? (uint32_t)t : 0u;
 }
 
 // ---- per row: exact threshold (candidate mode), per-chunk counts, scan over chunks -----------------
@@ -1327,10 +1253,12 @@ struct TopkState {
     bool gspar = false;            // the GSpar operator runs on this state (its own select-free chain of kernels)
     bool pending = false;          // a step has been enqueued since the last flush (or may have been, by a
                                    // replayed graph): its sparse tail may not have been applied yet
+    SparseResidentState* resident = nullptr;   // a small problem's step is one launch and leaves nothing pending
 };
 
 void topk_destroy(TopkState* st) {
     if (!st) return;
+    sparse_resident_destroy(st->resident);
     void* ptrs[] = {st->s.hist, st->s.hist_part, st->s.hist2, st->s.hist3, st->s.rows, st->s.cnt_gt, st->s.cnt_eq, st->s.eq_before, st->s.out_off, st->s.cand_cnt, st->s.slot_val, st->s.slot_idx,
                     st->s.list, st->s.csum, st->s.gs_overflow};
     for (void* p : ptrs)
@@ -1338,7 +1266,9 @@ void topk_destroy(TopkState* st) {
     delete st;
 }
 
-ds_status topk_create(const ds_config& cfg, uint64_t ld, TopkState** out, std::string& err) {
+bool topk_fits_resident(const ds_config& cfg) { return sparse_fits_resident(cfg); }
+
+ds_status topk_create(const ds_config& cfg, uint64_t ld, bool resident, bool impatient, TopkState** out, std::string& err) {
     TopkState* st = new TopkState();
     st->n = cfg.n;
     st->gspar = cfg.comp.kind == DS_COMP_GSPAR;
@@ -1347,11 +1277,13 @@ ds_status topk_create(const ds_config& cfg, uint64_t ld, TopkState** out, std::s
     // the first pass reads and writes whole chunks of x and delta
     if ((uint64_t)s.nchunks * TK_CHUNK > ld) { err = "internal: row pitch smaller than the chunked row"; delete st; return DS_EINVAL; }
     const size_t n = (size_t)cfg.n, nc = s.nchunks;
-    bool ok = hipMalloc(&s.hist, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
+    bool ok = hipMalloc(&s.rows, n * sizeof(TopkRow)) == hipSuccess && hipMalloc(&s.gs_overflow, sizeof(uint32_t)) == hipSuccess &&
+              hipMemset(s.gs_overflow, 0, sizeof(uint32_t)) == hipSuccess;
+    if (resident) ok = ok && sparse_resident_create(cfg, impatient, s.rows, &st->resident) == DS_OK;
+    else ok = ok && hipMalloc(&s.hist, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc(&s.hist_part, n * TK_HPARTS * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc(&s.hist2, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc(&s.hist3, n * BINS3 * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.rows, n * sizeof(TopkRow)) == hipSuccess &&
               hipMalloc(&s.cnt_gt, n * nc * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc(&s.cnt_eq, n * nc * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc(&s.eq_before, n * nc * sizeof(uint32_t)) == hipSuccess &&
@@ -1361,14 +1293,12 @@ ds_status topk_create(const ds_config& cfg, uint64_t ld, TopkState** out, std::s
               hipMalloc(&s.slot_idx, n * nc * TK_CAP * sizeof(uint16_t)) == hipSuccess &&
               hipMalloc(&s.list, n * TK_LIST_CAP * sizeof(uint2)) == hipSuccess &&
               hipMalloc(&s.csum, (st->gspar ? n * nc : 1) * sizeof(double)) == hipSuccess &&
-              hipMalloc(&s.gs_overflow, sizeof(uint32_t)) == hipSuccess;
-    ok = ok && hipMemset(s.hist, 0, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
+         hipMemset(s.hist, 0, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
          hipMemset(s.hist_part, 0, n * TK_HPARTS * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
          hipMemset(s.hist2, 0, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
          hipMemset(s.hist3, 0, n * BINS3 * sizeof(uint32_t)) == hipSuccess &&
          hipMemset(s.out_off, 0, n * (nc + 1) * sizeof(uint32_t)) == hipSuccess &&
-         hipMemset(s.cand_cnt, 0, n * nc * sizeof(uint32_t)) == hipSuccess &&
-         hipMemset(s.gs_overflow, 0, sizeof(uint32_t)) == hipSuccess;
+         hipMemset(s.cand_cnt, 0, n * nc * sizeof(uint32_t)) == hipSuccess;
     if (ok) {
         hipLaunchKernelGGL(topk_init_rows, dim3((cfg.n + 63) / 64), dim3(64), 0, 0, s.rows, cfg.n);
         ok = hipDeviceSynchronize() == hipSuccess;
@@ -1414,6 +1344,7 @@ ds_status gspar_overflowed(TopkState* st, hipStream_t stream, bool* overflowed) 
 }
 
 ds_status topk_step(TopkState* st, const TopkArgs& a, hipStream_t stream) {
+    if (st->resident) return sparse_resident_step(st->resident, a, stream);
     const Scratch& s = st->s;
     const dim3 grid(s.nchunks, a.n), block(TK_THREADS), rblock(TK_RTHREADS);
     if (st->gspar) {

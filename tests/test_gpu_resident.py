@@ -24,6 +24,18 @@ CASES = [
     small(wl.KIND_QUANT_L2NORM, 3, 4096 * 180 + 1, bits=2),
     small(wl.KIND_QUANT_L2NORM, 35, 4096 * 2 + 2, bits=8),
 ]
+# top-k: the same sizes; everything sent; k whose keys are gathered and k that takes the radix select; one, a few and more
+# sent columns per thread than a record holds
+TOPK = [
+    small(wl.KIND_TOPK, 3, 1, k=1),
+    small(wl.KIND_TOPK, 5, 4095, k=41),
+    small(wl.KIND_TOPK, 4, 4096 * 2, k=4096 * 2),
+    small(wl.KIND_TOPK, 9, 4096 * 3 + 17, k=150, topo=wl.TOPO_TORUS2D, torus=(3, 3)),
+    small(wl.KIND_TOPK, 3, 4096 * 180 + 1, k=2500),
+    small(wl.KIND_TOPK, 3, 4096 * 90 + 1, k=30_000, grad="student_t3"),
+    small(wl.KIND_TOPK, 35, 4096 * 2 + 2, k=900),
+]
+CASES += TOPK
 
 
 def _plan(variant):
@@ -40,10 +52,10 @@ def test_resident_lock_step(w, variant):
     lock_step(w, steps=2, plan=_plan(variant))
 
 
-@pytest.mark.parametrize("w", [CASES[3], CASES[4]], ids=lambda w: w.name)
+@pytest.mark.parametrize("w", [CASES[3], CASES[4]] + TOPK, ids=lambda w: w.name)
 @pytest.mark.parametrize("variant", [0, 3])
 def test_resident_free_run(w, variant):
-    """Nothing read or written between the steps but the messages."""
+    """Nothing read or written between the steps but the messages (the guesses of one step serve the next)."""
     ds = b.DeepSqueeze.from_workload(w, _plan(variant))
     st = oracle_state(w)
     for t in range(6):
@@ -57,7 +69,7 @@ def test_resident_free_run(w, variant):
     assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
 
 
-@pytest.mark.parametrize("w", [small(wl.KIND_QUANT_L2NORM, 40, 300, bits=4)], ids=lambda w: w.name)
+@pytest.mark.parametrize("w", [small(wl.KIND_QUANT_L2NORM, 40, 300, bits=4), small(wl.KIND_TOPK, 40, 300, k=60)], ids=lambda w: w.name)
 def test_resident_dense_graph(w):
     """Every worker averages with all 40: more neighbours than are put together at once."""
     n = w.n
@@ -66,10 +78,33 @@ def test_resident_dense_graph(w):
     lock_step(w, steps=2, W=W, csr=csr)
 
 
-def test_two_resident_handles_on_two_streams():
+@pytest.mark.parametrize("k", [1, 700, 2600, 9000])
+@pytest.mark.parametrize("variant", [0, 3, 2])
+def test_resident_topk_many_equal_magnitudes(k, variant):
+    """Values of seven levels, most of them zero and half of the columns without a gradient: hundreds of equal magnitudes at
+    the threshold, which stays where it is for some steps and moves by a level, or to zero, in others."""
+    w = small(wl.KIND_TOPK, 5, 4096 * 2 + 1001, k=k, gamma=1.0)
+    rng = np.random.default_rng(k)
+    level = lambda p: rng.choice(np.arange(-3, 4).astype(np.float32), size=(w.n, w.N), p=p)
+    ds = b.DeepSqueeze.from_workload(w, _plan(variant))
+    st = oracle_state(w)
+    st.delta = level([0.05, 0.05, 0.1, 0.6, 0.1, 0.05, 0.05])
+    ds.ds_write_state(st.x, st.delta, st.t)
+    for t in range(8):
+        g = level([0.01, 0.01, 0.08, 0.8, 0.08, 0.01, 0.01]) if t in (2, 5) else np.zeros((w.n, w.N), np.float32)
+        ds.ds_step(upload(g))
+        _, msg = oracle.step(st, g, want_cv=False)
+        assert np.array_equal(ds.ds_read_messages(), msg), f"step {t}: messages differ"
+    x, d = ds.ds_read_state()
+    ds.ds_destroy()
+    assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
+
+
+@pytest.mark.parametrize("other", [small(wl.KIND_QUANT_L2NORM, 8, 4096 * 40 + 1001, bits=4, seed=9), TOPK[4]], ids=lambda w: w.name)
+def test_two_resident_handles_on_two_streams(other):
     """Two handles step side by side on streams of their own: their workgroups fit next to each other."""
     import torch
-    ws = [CASES[4], small(wl.KIND_QUANT_L2NORM, 8, 4096 * 40 + 1001, bits=4, seed=9)]
+    ws = [CASES[4], other]
     dss = [b.DeepSqueeze.from_workload(w) for w in ws]
     sts = [oracle_state(w) for w in ws]
     streams = [torch.cuda.Stream() for _ in ws]
