@@ -461,7 +461,7 @@ ds_status ds_init_ex(const ds_config* cfg, const ds_plan_request* plan, char* er
     bool resident = false;                                 // a whole step in one launch (small problems)
     if (sparse_pairs) {
         resident = want.variant != 2 && dsq::topk_fits_resident(*cfg);
-        h->plan_name = cfg->comp.kind == DS_COMP_GSPAR ? "gspar/sift-scan-write" : resident ? "topk/resident" : "topk/radix-select";
+        h->plan_name = cfg->comp.kind == DS_COMP_GSPAR ? (resident ? "gspar/resident" : "gspar/sift-scan-write") : resident ? "topk/resident" : "topk/radix-select";
     } else if (cfg->comp.kind == DS_COMP_QUANT_L2NORM) {
         resident = want.variant != 2 && dsq::l2q_fits_resident(*cfg);
         h->plan_name = resident ? "l2norm/resident" : "l2norm/speculative-codes";

@@ -34,11 +34,11 @@ struct TopkRow {
     uint32_t gs_total;         // GSpar: pairs in the row's last message (what a shorter message must clear behind it)
 };
 
-// The one-launch form of a step (top-k), on the rows of the state that owns it.
+// The one-launch form of a step, on the rows of the state that owns it.
 struct SparseResidentState;
 bool sparse_fits_resident(const ds_config& cfg);
 // impatient: the kernel's first meeting calls itself off at once (tests of what follows then).
-ds_status sparse_resident_create(const ds_config& cfg, bool impatient, TopkRow* rows, SparseResidentState** out);
+ds_status sparse_resident_create(const ds_config& cfg, bool impatient, TopkRow* rows, uint32_t* overflow, SparseResidentState** out);
 void sparse_resident_destroy(SparseResidentState* st);
 ds_status sparse_resident_step(SparseResidentState* st, const TopkArgs& a, hipStream_t stream);
 

@@ -1279,7 +1279,7 @@ ds_status topk_create(const ds_config& cfg, uint64_t ld, bool resident, bool imp
     const size_t n = (size_t)cfg.n, nc = s.nchunks;
     bool ok = hipMalloc(&s.rows, n * sizeof(TopkRow)) == hipSuccess && hipMalloc(&s.gs_overflow, sizeof(uint32_t)) == hipSuccess &&
               hipMemset(s.gs_overflow, 0, sizeof(uint32_t)) == hipSuccess;
-    if (resident) ok = ok && sparse_resident_create(cfg, impatient, s.rows, &st->resident) == DS_OK;
+    if (resident) ok = ok && sparse_resident_create(cfg, impatient, s.rows, s.gs_overflow, &st->resident) == DS_OK;
     else ok = ok && hipMalloc(&s.hist, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc(&s.hist_part, n * TK_HPARTS * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc(&s.hist2, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&

@@ -53,8 +53,11 @@ struct SparseScratch {
     uint32_t* row_hist;           // n x RS_LEVELS x RS_LEVEL_BINS, zero between launches
     uint32_t* sent;               // n x nchunks: pairs of the chunk ...
     uint64_t* pairs;              // n x nchunks x kResChunk: ... (column in the chunk | value << 32), in column order
+    double* csum;                 // GSpar: n x nchunks tree sums of |v| over the chunks
+    uint32_t* overflow;           // GSpar: set once a row kept more than its message holds
     uint32_t nchunks;
     uint32_t gather;              // 1: keys are exchanged; 0: the radix select is always taken
+    uint32_t deep;                // 1: two pairs of a neighbour per thread are asked for together, not one
 };
 
 struct SparseLaunch {             // the kernel's one argument
@@ -75,6 +78,7 @@ struct SparseShared {
     uint2 mine[RS_SLOT];                                      // the chunk's collected elements: column in the chunk, value
     uint32_t own[kResChunk / 32];                             // columns this worker sends
     uint32_t wave_a[RS_WAVES], wave_b[RS_WAVES];
+    double sweep[kResIters * RS_WAVES];                       // GSpar
     uint32_t res[4];
     uint32_t listed;
 };
@@ -198,37 +202,67 @@ struct SparseResident : ResidentChunk<TopkArgs> {
     }
 
     // What the neighbours send of the chunk, weighted and added up in LDS, the columns this worker sends, and the message.
-    __device__ __forceinline__ void sum_neighbours() {
+    // CAPPED (GSpar): a row's message holds `cap` pairs behind its header, what a row keeps beyond them is not sent; returns
+    // the pairs this row keeps.
+    template <bool CAPPED>
+    __device__ __forceinline__ uint32_t sum_neighbours(uint32_t cap) {
+        static_assert(RS_WAVES == kResNear, "a wave per neighbour");
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const size_t row0 = (size_t)row * nchunks;
-        uint32_t ahead = 0;                                   // pairs of the row in the chunks before this one
-        for (uint32_t c = threadIdx.x; c < chunk; c += kResThreads) ahead += agent_load(s.sent + row0 + c);
-        uint64_t* out = reinterpret_cast<uint64_t*>(a.msg + (uint64_t)row * a.k * 8);
+        uint32_t ahead = 0, kept = 0;                         // pairs of the row in the chunks before this one, and in all
+        if constexpr (!CAPPED)
+            for (uint32_t c = threadIdx.x; c < chunk; c += kResThreads) ahead += agent_load(s.sent + row0 + c);
+        uint64_t* out = reinterpret_cast<uint64_t*>(a.msg + (uint64_t)row * a.k * 8) + (CAPPED ? 1 : 0);
         const uint32_t col0 = chunk * (uint32_t)kResChunk;
         bool cleared = false;
         for (int eb = e0; eb < e1; eb += kResNear) {          // ascending neighbour index, own index included
-            uint64_t pair[kResNear];
+            uint64_t pair[kResNear], next[kResNear] = {};
             uint32_t count[kResNear];
             int nbs[kResNear];
 #pragma unroll
-            for (int u = 0; u < kResNear; ++u) {              // a pair per thread of each, whether there are that many or not
+            for (int u = 0; u < kResNear; ++u) {              // a pair per thread of each, or two, whether there are that many or not
                 nbs[u] = eb == e0 ? near[u] : eb + u < e1 ? a.col[eb + u] : row;
                 const size_t at = (size_t)nbs[u] * nchunks + chunk;
                 count[u] = agent_load(s.sent + at);
                 pair[u] = agent_load(s.pairs + at * kResChunk + threadIdx.x);
+                if (s.deep) next[u] = agent_load(s.pairs + at * kResChunk + kResThreads + threadIdx.x);
+            }
+            if constexpr (CAPPED) {
+                const int nb = wave == 0 ? nbs[0] : wave == 1 ? nbs[1] : wave == 2 ? nbs[2] : nbs[3];
+                uint32_t before = 0, all = 0;
+                for (uint32_t c = lane; c < nchunks; c += 64) {
+                    const uint32_t one = agent_load(s.sent + (size_t)nb * nchunks + c);
+                    before += c < chunk ? one : 0u;
+                    all += one;
+                }
+                before = wave_sum_u32(before);
+                all = wave_sum_u32(all);
+                __syncthreads();                              // the words may still be read
+                if (lane == 0) { sh.wave_a[wave] = before; sh.wave_b[wave] = all; }
             }
             if (!cleared) {                                   // uniform
-                cleared = true;
-                __syncthreads();                              // the words may still be read
+                if constexpr (!CAPPED) __syncthreads();       // the words may still be read
 #pragma unroll
                 for (int it = 0; it < kResIters; ++it) reinterpret_cast<float4*>(sh.acc)[it * kResThreads + threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);
                 if (threadIdx.x < kResChunk / 32) sh.own[threadIdx.x] = 0u;
-                ahead = group_sum_u32(ahead, sh.wave_a);      // (its barrier)
+                if constexpr (!CAPPED) ahead = group_sum_u32(ahead, sh.wave_a);   // (its barrier)
             }
+            if constexpr (CAPPED) __syncthreads();
+            cleared = true;
 #pragma unroll
             for (int u = 0; u < kResNear; ++u) {
                 if (eb + u < e1) {                            // uniform
                     const float w = eb == e0 ? near_coef[u] : a.coef[eb + u];
                     const bool own = nbs[u] == row;
+                    uint32_t n = count[u];
+                    if constexpr (CAPPED) {
+                        const uint32_t before = sh.wave_a[u], all = sh.wave_b[u];
+                        if (own) { ahead = before; kept = all; }
+                        if (all > cap) {
+                            const uint32_t room = before < cap ? cap - before : 0u;
+                            n = n < room ? n : room;
+                        }
+                    }
                     auto add = [&](uint32_t p, uint64_t one) {
                         const uint32_t q = (uint32_t)one & (uint32_t)(kResChunk - 1);
                         sh.acc[q] = fmaf(w, __uint_as_float((uint32_t)(one >> 32)), sh.acc[q]);
@@ -237,20 +271,22 @@ struct SparseResident : ResidentChunk<TopkArgs> {
                             out[ahead + p] = one + col0;      // the column's word does not overflow: N < 2^22
                         }
                     };
-                    if (threadIdx.x < count[u]) add(threadIdx.x, pair[u]);
-                    if (__builtin_amdgcn_readfirstlane(count[u]) > (uint32_t)kResThreads) {
+                    if (threadIdx.x < n) add(threadIdx.x, pair[u]);
+                    const uint32_t held = s.deep ? 2u * kResThreads : (uint32_t)kResThreads;
+                    if (s.deep && threadIdx.x + kResThreads < n) add(threadIdx.x + kResThreads, next[u]);
+                    if (__builtin_amdgcn_readfirstlane(n) > held) {
                         const uint64_t* from = s.pairs + ((size_t)nbs[u] * nchunks + chunk) * kResChunk;
-                        for (uint32_t p = threadIdx.x + kResThreads; p < count[u]; p += kResThreads) add(p, agent_load(from + p));
+                        for (uint32_t p = threadIdx.x + held; p < n; p += kResThreads) add(p, agent_load(from + p));
                     }
                     __syncthreads();
                 }
             }
         }
+        return kept;
     }
 
-    // Lines 6 and 9.
+    // Lines 6 and 9, after sum_neighbours().
     __device__ __forceinline__ void finish() {
-        sum_neighbours();
         const uint32_t thread = Chunk::thread_here();
 #pragma unroll
         for (int it = 0; it < kResIters; ++it) {
@@ -306,7 +342,6 @@ struct SparseResident : ResidentChunk<TopkArgs> {
     }
 
     __device__ __forceinline__ void finish_alone() {
-        sum_neighbours();
         for (uint32_t off = threadIdx.x; off < (uint32_t)kResChunk; off += kResThreads) {
             const uint64_t j = (uint64_t)chunk * kResChunk + off;
             if (j >= a.N) break;                              // padding columns stay zero
@@ -649,6 +684,7 @@ struct TopkResident : SparseResident {
         phase_end();
         for (uint32_t i = 0; i < blocks; ++i) {
             locate(i);
+            (void)sum_neighbours<false>(0);
             finish_alone();
         }
     }
@@ -716,8 +752,143 @@ __global__ void __launch_bounds__(kResThreads, 5) topk_resident(SparseLaunch lau
     }
     op.keep_book();
     (void)meet<false, true>(s.meetings + kMeetWords, blocks, epoch, 0, s.epoch, a.t_ptr);
+    (void)op.sum_neighbours<false>(0);
     op.finish();
     op.clear_counts();
+}
+
+// GSpar:
+//   measure   xh, v; the chunk's sum of |v|                                                        -> scratch
+//   meeting   (may part)
+//   mark      every workgroup of a row puts lambda = k / sum |v| together for itself; the chunk's kept elements, in column
+//             order                                                                                -> scratch
+//   meeting
+//   finish    as for top-k; the message's header and the zeros behind it by the workgroups of chunk 0
+// 8 workers x 272,474 parameters, 10 % kept, the state complete after every step: 26.4 us; the ten launches it takes
+// otherwise: 52 us.
+struct GsparResident : SparseResident {
+    using SparseResident::SparseResident;
+    uint32_t t_lo = 0;                                        // the step's counter, read before it is advanced
+    float lambda = 0.f;
+
+    __device__ __forceinline__ uint32_t room() const { return (uint32_t)a.k - 1u; }   // pairs a message holds
+
+    __device__ __forceinline__ void measure() {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+        for (int it = 0; it < kResIters; ++it) {              // padding columns hold v = 0
+            const double sw = wave_tree_f64(((double)fabsf(v[it].x) + (double)fabsf(v[it].y)) + ((double)fabsf(v[it].z) + (double)fabsf(v[it].w)));
+            if (lane == 0) sh.sweep[it * RS_WAVES + wave] = sw;   // sweep index = column order
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double t[kResIters * RS_WAVES];
+#pragma unroll
+            for (int q = 0; q < kResIters * RS_WAVES; ++q) t[q] = sh.sweep[q];
+#pragma unroll
+            for (int len = kResIters * RS_WAVES; len > 1; len >>= 1)
+#pragma unroll
+                for (int q = 0; q < len / 2; ++q) t[q] = t[2 * q] + t[2 * q + 1];
+            agent_store(s.csum + place(), t[0]);
+        }
+    }
+
+    // The tree continued over the row's chunks (at most 1024 of them: four leaves per thread, the missing ones zero; with
+    // up to 256 of them one leaf per thread is the same tree).
+    __device__ __forceinline__ void row_lambda() {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        const uint32_t per = nchunks <= (uint32_t)kResThreads ? 1u : 4u;          // uniform
+        double leaf[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+            const uint32_t c = per * threadIdx.x + q;
+            if (q < per && c < nchunks) leaf[q] = agent_load(s.csum + (size_t)row * nchunks + c);
+        }
+        const double part = wave_tree_f64((leaf[0] + leaf[1]) + (leaf[2] + leaf[3]));
+        __syncthreads();                                      // the words may still be read
+        if (lane == 0) sh.sweep[wave] = part;
+        __syncthreads();
+        const double sum = (sh.sweep[0] + sh.sweep[1]) + (sh.sweep[2] + sh.sweep[3]);
+        lambda = (sum > 0.0) ? (float)((double)a.k_expected / sum) : 0.f;
+    }
+
+    __device__ __forceinline__ void mark() {
+        uint32_t mask = 0;
+#pragma unroll
+        for (int it = 0; it < kResIters; ++it) mask |= gs_keep4(a, row, column(it), t_lo, lambda, v[it]) << (4 * it);
+        emit_mask(mask);
+    }
+
+    // What ds_topk_candidate_rows reports: would the bound that the step before suggests have held?
+    __device__ __forceinline__ void keep_book() {
+        if (chunk != 0 || threadIdx.x != 0) return;
+        const float used = s.rows[row].lambda_hi;
+        s.rows[row].lambda = lambda;
+        s.rows[row].gs_mode = (used > 0.f && lambda <= used) ? 1u : 0u;
+        s.rows[row].lambda_hi = (lambda > 0.f && lambda < 1.0e30f) ? lambda * 1.05f : 0.f;
+    }
+
+    // The header, and zeros behind a message shorter than the last one.
+    __device__ __forceinline__ void close_message(uint32_t kept) {
+        if (chunk != 0) return;                               // uniform
+        const uint32_t count = kept < room() ? kept : room(), last = s.rows[row].gs_total;
+        uint2* mrow = reinterpret_cast<uint2*>(a.msg + (uint64_t)row * a.k * 8);
+        for (uint32_t p = count + threadIdx.x; p < last; p += kResThreads) mrow[1 + p] = make_uint2(0u, 0u);
+        __syncthreads();                                      // every thread has read gs_total
+        if (threadIdx.x == 0) {
+            mrow[0] = make_uint2(count, 0u);
+            s.rows[row].gs_total = count;
+            if (kept > room()) atomicOr(s.overflow, 1u);
+        }
+    }
+
+    __device__ __forceinline__ void step_alone(uint32_t blocks) {
+        for (uint32_t i = 0; i < blocks; ++i) {               // every workgroup has measured before it left
+            locate(i);
+            if (chunk == 0) {
+                row_lambda();
+                keep_book();
+            }
+            emit_alone([&](uint64_t j, float val) {
+                uint32_t rnd[4];
+                philox4x32_10((uint32_t)(j >> 2), (uint32_t)row, t_lo, kGsparStreamTag, a.seed_lo, a.seed_hi, rnd);
+                const uint32_t word = (j & 3) == 0 ? rnd[0] : (j & 3) == 1 ? rnd[1] : (j & 3) == 2 ? rnd[2] : rnd[3];
+                return j < a.N && (float)(word >> 8) * (1.0f / 16777216.0f) < lambda * fabsf(val);
+            });
+        }
+        phase_end();
+        for (uint32_t i = 0; i < blocks; ++i) {
+            locate(i);
+            const uint32_t kept = sum_neighbours<true>(room());
+            finish_alone();
+            close_message(kept);
+        }
+    }
+};
+
+__global__ void __launch_bounds__(kResThreads, 5) gspar_resident(SparseLaunch launch) {
+    __shared__ SparseShared sh;
+    const TopkArgs& a = launch.a;
+    const SparseScratch& s = launch.s;
+    const uint32_t blocks = gridDim.x;
+    const unsigned long long epoch = *s.epoch;
+    GsparResident op(a, s, sh);
+    op.t_lo = (uint32_t)*a.t_ptr;
+    op.load(blockIdx.x);
+    op.measure();
+    if (!uniform(meet<true, false>(s.meetings, blocks, epoch, launch.patience))) {
+        if (!uniform(leave(a.t_ptr, blocks))) return;
+        op.step_alone(blocks);
+        close_alone(s.meetings, 2, blocks, epoch, s.epoch, a.t_ptr);
+        return;
+    }
+    op.row_lambda();
+    op.mark();
+    op.keep_book();
+    (void)meet<false, true>(s.meetings + kMeetWords, blocks, epoch, 0, s.epoch, a.t_ptr);
+    const uint32_t kept = op.sum_neighbours<true>(op.room());
+    op.finish();
+    op.close_message(kept);
 }
 static_assert(sizeof(SparseShared) <= 31 * 1024, "five workgroups share the 160 KB of a compute unit");
 
@@ -726,6 +897,7 @@ static_assert(sizeof(SparseShared) <= 31 * 1024, "five workgroups share the 160 
 struct SparseResidentState {
     SparseScratch s{};
     uint8_t* slab = nullptr;      // one allocation holds all of the scratch
+    bool gspar = false;
     uint64_t patience = 0;
 };
 
@@ -737,20 +909,23 @@ void sparse_resident_destroy(SparseResidentState* st) {
 
 bool sparse_fits_resident(const ds_config& cfg) {
     const uint64_t nchunks = (cfg.N + kResChunk - 1) / kResChunk;
-    if (cfg.comp.kind != DS_COMP_TOPK || nchunks > RS_MAX_CHUNKS) return false;
-    return (uint64_t)cfg.n * nchunks <= resident_limit(topk_resident, kResThreads);
+    if (nchunks > RS_MAX_CHUNKS) return false;
+    return (uint64_t)cfg.n * nchunks <= (cfg.comp.kind == DS_COMP_GSPAR ? resident_limit(gspar_resident, kResThreads) : resident_limit(topk_resident, kResThreads));
 }
 
-ds_status sparse_resident_create(const ds_config& cfg, bool impatient, TopkRow* rows, SparseResidentState** out) {
+ds_status sparse_resident_create(const ds_config& cfg, bool impatient, TopkRow* rows, uint32_t* overflow, SparseResidentState** out) {
     SparseResidentState* st = new (std::nothrow) SparseResidentState();
     if (!st) return DS_ENOMEM;
     st->patience = impatient ? 0 : kMeetPatience;
     SparseScratch& s = st->s;
+    st->gspar = cfg.comp.kind == DS_COMP_GSPAR;
     s.rows = rows;
+    s.overflow = overflow;
     s.nchunks = (uint32_t)((cfg.N + kResChunk - 1) / kResChunk);
     const size_t n = (size_t)cfg.n, all = n * s.nchunks;
     // about 1.6 k keys are collected; a chunk's have to fit in its slot with room for an uneven row
     s.gather = cfg.comp.k * kResChunk <= cfg.N * (RS_SLOT / 2) ? 1u : 0u;
+    s.deep = cfg.comp.k * kResChunk > cfg.N * (uint64_t)(kResThreads * 3 / 4) ? 1u : 0u;   // most chunks send more pairs than there are threads
     size_t bytes = 0;
     auto place = [&](auto*& p, size_t count) {                // two passes: sizes, then addresses
         if (st->slab) p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(st->slab + bytes);
@@ -761,14 +936,15 @@ ds_status sparse_resident_create(const ds_config& cfg, bool impatient, TopkRow* 
         bytes = 0;
         place(s.meetings, 2 * kMeetWords);
         place(s.epoch, 1);
-        place(s.window, n * RS_WINDOW);
-        place(s.row_arrivals, n * kMeetLine);
-        place(s.row_hist, n * RS_LEVELS * RS_LEVEL_BINS);
+        place(s.window, st->gspar ? 0 : n * RS_WINDOW);
+        place(s.row_arrivals, st->gspar ? 0 : n * kMeetLine);
+        place(s.row_hist, st->gspar ? 0 : n * RS_LEVELS * RS_LEVEL_BINS);
         zero = bytes;                                         // what lies before this has to be zero at the first launch
         place(s.reach, all);
         place(s.split, all);
         place(s.sent, all);
-        place(s.keys, all * RS_SLOT);
+        place(s.csum, st->gspar ? all : 0);
+        place(s.keys, st->gspar ? 0 : all * RS_SLOT);
         place(s.pairs, all * kResChunk);
         if (pass == 0 && hipMalloc(&st->slab, bytes) != hipSuccess) break;
     }
@@ -782,7 +958,10 @@ ds_status sparse_resident_create(const ds_config& cfg, bool impatient, TopkRow* 
 }
 
 ds_status sparse_resident_step(SparseResidentState* st, const TopkArgs& a, hipStream_t stream) {
-    hipLaunchKernelGGL(topk_resident, dim3(st->s.nchunks * (uint32_t)a.n), dim3(kResThreads), 0, stream, SparseLaunch{a, st->s, st->patience});
+    const dim3 grid(st->s.nchunks * (uint32_t)a.n), block(kResThreads);
+    const SparseLaunch launch{a, st->s, st->patience};
+    if (st->gspar) hipLaunchKernelGGL(gspar_resident, grid, block, 0, stream, launch);
+    else           hipLaunchKernelGGL(topk_resident, grid, block, 0, stream, launch);
     return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
 }
 

@@ -35,7 +35,17 @@ TOPK = [
     small(wl.KIND_TOPK, 3, 4096 * 90 + 1, k=30_000, grad="student_t3"),
     small(wl.KIND_TOPK, 35, 4096 * 2 + 2, k=900),
 ]
-CASES += TOPK
+# GSpar: the same sizes; few and many kept per chunk
+GSPAR = [
+    small(wl.KIND_GSPAR, 3, 1, k=1),
+    small(wl.KIND_GSPAR, 5, 4095, k=41),
+    small(wl.KIND_GSPAR, 4, 4096 * 2, k=4096 * 2),
+    small(wl.KIND_GSPAR, 9, 4096 * 3 + 17, k=150, topo=wl.TOPO_TORUS2D, torus=(3, 3), grad="student_t3"),
+    small(wl.KIND_GSPAR, 3, 4096 * 180 + 1, k=2500),
+    small(wl.KIND_GSPAR, 3, 4096 * 90 + 1, k=36_000),
+    small(wl.KIND_GSPAR, 35, 4096 * 2 + 2, k=900),
+]
+CASES += TOPK + GSPAR
 
 
 def _plan(variant):
@@ -52,7 +62,7 @@ def test_resident_lock_step(w, variant):
     lock_step(w, steps=2, plan=_plan(variant))
 
 
-@pytest.mark.parametrize("w", [CASES[3], CASES[4]] + TOPK, ids=lambda w: w.name)
+@pytest.mark.parametrize("w", [CASES[3], CASES[4]] + TOPK + GSPAR, ids=lambda w: w.name)
 @pytest.mark.parametrize("variant", [0, 3])
 def test_resident_free_run(w, variant):
     """Nothing read or written between the steps but the messages (the guesses of one step serve the next)."""
@@ -69,7 +79,7 @@ def test_resident_free_run(w, variant):
     assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
 
 
-@pytest.mark.parametrize("w", [small(wl.KIND_QUANT_L2NORM, 40, 300, bits=4), small(wl.KIND_TOPK, 40, 300, k=60)], ids=lambda w: w.name)
+@pytest.mark.parametrize("w", [small(wl.KIND_QUANT_L2NORM, 40, 300, bits=4), small(wl.KIND_TOPK, 40, 300, k=60), small(wl.KIND_GSPAR, 40, 300, k=60)], ids=lambda w: w.name)
 def test_resident_dense_graph(w):
     """Every worker averages with all 40: more neighbours than are put together at once."""
     n = w.n
@@ -100,7 +110,7 @@ def test_resident_topk_many_equal_magnitudes(k, variant):
     assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
 
 
-@pytest.mark.parametrize("other", [small(wl.KIND_QUANT_L2NORM, 8, 4096 * 40 + 1001, bits=4, seed=9), TOPK[4]], ids=lambda w: w.name)
+@pytest.mark.parametrize("other", [small(wl.KIND_QUANT_L2NORM, 8, 4096 * 40 + 1001, bits=4, seed=9), TOPK[4], GSPAR[4]], ids=lambda w: w.name)
 def test_two_resident_handles_on_two_streams(other):
     """Two handles step side by side on streams of their own: their workgroups fit next to each other."""
     import torch
