@@ -197,33 +197,8 @@ uint64_t autotune(ds_handle* h, uint64_t base_ld, size_t state_bytes, size_t msg
     return ok ? best_skew : dsq::kPitchSkew;
 }
 
-// Diagnostics (off the hot path): a thread walks all rows of its columns (grid-stride); fp64 accumulation.
-__global__ void __launch_bounds__(256) diagnostics_kernel(const float* __restrict__ x, const float* __restrict__ delta, uint64_t ld,
-                                                          uint64_t N, int n, const int32_t* __restrict__ rowptr,
-                                                          const int32_t* __restrict__ col, const float* __restrict__ coef,
-                                                          float eta, double* __restrict__ out) {
-    __shared__ double part[3][4];
-    double cons = 0.0, dsq_ = 0.0, mixed = 0.0;
-    for (uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x; j < N; j += (uint64_t)gridDim.x * 256) {
-        double sum = 0.0, sumsq = 0.0;
-        for (int i = 0; i < n; ++i) {
-            const double xv = x[(uint64_t)i * ld + j];
-            const double dv = delta[(uint64_t)i * ld + j];
-            sum += xv;
-            sumsq += xv * xv;
-            dsq_ += dv * dv;
-        }
-        const double mean = sum / n;
-        for (int i = 0; i < n; ++i) {                           // second pass: no cancellation
-            const double dev = (double)x[(uint64_t)i * ld + j] - mean;
-            cons += dev * dev;
-            double m = 0.0;
-            for (int e = rowptr[i]; e < rowptr[i + 1]; ++e) m += (double)coef[e] * (double)delta[(uint64_t)col[e] * ld + j];
-            m *= (double)eta;
-            mixed += m * m;
-        }
-        (void)sumsq;
-    }
+// Diagnostics (off the hot path); fp64 accumulation, the three sums of a workgroup added to `out`.
+__device__ __forceinline__ void add_diagnostics(double cons, double dsq_, double mixed, double (*part)[4], double* out) {
     double v[3] = {cons, dsq_, mixed};
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
@@ -237,6 +212,114 @@ __global__ void __launch_bounds__(256) diagnostics_kernel(const float* __restric
         const double tot = part[threadIdx.x][0] + part[threadIdx.x][1] + part[threadIdx.x][2] + part[threadIdx.x][3];
         atomicAdd(&out[threadIdx.x], tot);
     }
+}
+
+// n rows of C columns at a time in LDS, so that x and delta are read once: the deviations from the mean and the mixed
+// errors, which need all rows of a column, come from there.  A quad of columns per lane; the C/4 lanes of a row side by
+// side, 1024/C rows in flight per load of the workgroup.  Bound by HBM: 64 workers x 4 Mi columns on a torus 1595 -> 540 us
+// (2.1 GB; the kernel below, which reads x twice and delta once more for every neighbour, mostly past the caches).
+// LDS: [x: n x C][delta: n x C][column sums: 1024/C x C, then the means: C][rowptr n+1][col nnz][coef nnz]
+constexpr int kDiagGraphWords = 4096;
+constexpr size_t diagnostics_lds(int n, int C, size_t nnz) {
+    return (size_t)n * C * 8 + (size_t)1024 * 8 + (size_t)C * 8 + ((size_t)n + 1 + 2 * nnz) * 4;
+}
+template <int C>
+__global__ void __launch_bounds__(256) diagnostics_tile_kernel(const float* __restrict__ x, const float* __restrict__ delta, uint64_t ld,
+                                                               uint64_t tiles, int n, int nnz, const int32_t* __restrict__ graph, float eta,
+                                                               double* __restrict__ out) {
+    constexpr int LANES = C / 4, SIDE = 256 / LANES;             // lanes per row, rows side by side
+    extern __shared__ __align__(16) uint8_t lds[];
+    __shared__ double part[3][4];
+    float4* lx = reinterpret_cast<float4*>(lds);
+    float4* ldel = lx + (size_t)n * LANES;
+    double* sums = reinterpret_cast<double*>(ldel + (size_t)n * LANES);       // SIDE x C
+    double* means = sums + SIDE * C;
+    int32_t* rowptr = reinterpret_cast<int32_t*>(means + C);
+    const int32_t* col = rowptr + n + 1;
+    const float* coef = reinterpret_cast<const float*>(col + nnz);
+    for (int q = threadIdx.x; q < n + 1 + 2 * nnz; q += 256) rowptr[q] = graph[q];
+    const int quad = threadIdx.x % LANES, side = threadIdx.x / LANES;
+    double cons = 0.0, dsq_ = 0.0, mixed = 0.0;
+    for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {        // padding columns are zero: they add nothing
+        const uint64_t j = tile * C + 4u * quad;
+        double sum[4] = {0.0, 0.0, 0.0, 0.0};
+        constexpr int AHEAD = 4;                                 // rows of a thread asked for together
+        for (int i0 = side; i0 < n; i0 += AHEAD * SIDE) {
+            float4 xs[AHEAD], ds[AHEAD];
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                const int i = i0 + u * SIDE;
+                if (i < n) {
+                    xs[u] = *reinterpret_cast<const float4*>(x + (uint64_t)i * ld + j);
+                    ds[u] = *reinterpret_cast<const float4*>(delta + (uint64_t)i * ld + j);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                const int i = i0 + u * SIDE;
+                if (i < n) {
+                    lx[i * LANES + quad] = xs[u];
+                    ldel[i * LANES + quad] = ds[u];
+                    sum[0] += (double)xs[u].x; sum[1] += (double)xs[u].y; sum[2] += (double)xs[u].z; sum[3] += (double)xs[u].w;
+                    dsq_ += (double)ds[u].x * (double)ds[u].x + (double)ds[u].y * (double)ds[u].y + (double)ds[u].z * (double)ds[u].z + (double)ds[u].w * (double)ds[u].w;
+                }
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sums[side * C + 4 * quad + c] = sum[c];
+        __syncthreads();
+        if (threadIdx.x < C) {
+            double s = 0.0;
+#pragma unroll
+            for (int q = 0; q < SIDE; ++q) s += sums[q * C + threadIdx.x];
+            means[threadIdx.x] = s / n;
+        }
+        __syncthreads();
+        const double m[4] = {means[4 * quad], means[4 * quad + 1], means[4 * quad + 2], means[4 * quad + 3]};
+        for (int i = side; i < n; i += SIDE) {
+            const float4 xv = lx[i * LANES + quad];
+            const double d0 = (double)xv.x - m[0], d1 = (double)xv.y - m[1], d2 = (double)xv.z - m[2], d3 = (double)xv.w - m[3];
+            cons += d0 * d0 + d1 * d1 + d2 * d2 + d3 * d3;
+            double w0 = 0.0, w1 = 0.0, w2 = 0.0, w3 = 0.0;
+            for (int e = rowptr[i]; e < rowptr[i + 1]; ++e) {
+                const float4 dv = ldel[col[e] * LANES + quad];
+                const double w = (double)coef[e];
+                w0 += w * (double)dv.x; w1 += w * (double)dv.y; w2 += w * (double)dv.z; w3 += w * (double)dv.w;
+            }
+            w0 *= (double)eta; w1 *= (double)eta; w2 *= (double)eta; w3 *= (double)eta;
+            mixed += w0 * w0 + w1 * w1 + w2 * w2 + w3 * w3;
+        }
+        __syncthreads();                                         // the tile is used up
+    }
+    add_diagnostics(cons, dsq_, mixed, part, out);
+}
+
+// Any n: a thread walks all rows of its columns (grid-stride).
+__global__ void __launch_bounds__(256) diagnostics_kernel(const float* __restrict__ x, const float* __restrict__ delta, uint64_t ld,
+                                                          uint64_t N, int n, const int32_t* __restrict__ rowptr,
+                                                          const int32_t* __restrict__ col, const float* __restrict__ coef,
+                                                          float eta, double* __restrict__ out) {
+    __shared__ double part[3][4];
+    double cons = 0.0, dsq_ = 0.0, mixed = 0.0;
+    for (uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x; j < N; j += (uint64_t)gridDim.x * 256) {
+        double sum = 0.0;
+        for (int i = 0; i < n; ++i) {
+            const double xv = x[(uint64_t)i * ld + j];
+            const double dv = delta[(uint64_t)i * ld + j];
+            sum += xv;
+            dsq_ += dv * dv;
+        }
+        const double mean = sum / n;
+        for (int i = 0; i < n; ++i) {                           // second pass: no cancellation
+            const double dev = (double)x[(uint64_t)i * ld + j] - mean;
+            cons += dev * dev;
+            double m = 0.0;
+            for (int e = rowptr[i]; e < rowptr[i + 1]; ++e) m += (double)coef[e] * (double)delta[(uint64_t)col[e] * ld + j];
+            m *= (double)eta;
+            mixed += m * m;
+        }
+    }
+    add_diagnostics(cons, dsq_, mixed, part, out);
 }
 
 // Plain streaming copy, one 16-byte non-temporal load and store per lane, one-shot grid: the
@@ -729,10 +812,23 @@ ds_status ds_diagnostics(ds_handle* h, double* out4) {
     DSQ_HIP(h, hipMalloc(&d_out, 3 * sizeof(double)));
     hipError_t e = hipMemset(d_out, 0, 3 * sizeof(double));
     if (e == hipSuccess) {
+        const size_t nnz = h->graph.col.size();
+        const bool graph_fits = (size_t)h->cfg.n + 1 + 2 * nnz <= (size_t)kDiagGraphWords;
+        // 64 columns a tile up to 64 rows, 16 up to 256: 32 KB for the rows either way, so that three workgroups or more
+        // share a compute unit and one's loads run beside another's sums
+        auto tiles = [&](int C) { return (h->cfg.N + C - 1) / C; };
+        auto grid = [](uint64_t t) { return dim3((unsigned)(t < 4096 ? t : 4096)); };
         const uint64_t want = (h->cfg.N + 255) / 256;
         const unsigned blocks = (unsigned)(want < (1u << 20) ? want : (1u << 20));
-        hipLaunchKernelGGL(diagnostics_kernel, dim3(blocks), dim3(256), 0, nullptr, h->x, h->delta, h->ld, h->cfg.N, h->cfg.n,
-                           h->d_rowptr, h->d_col, h->d_coef, h->cfg.eta, d_out);
+        if (graph_fits && h->cfg.n <= 64)
+            hipLaunchKernelGGL(diagnostics_tile_kernel<64>, grid(tiles(64)), dim3(256), diagnostics_lds(h->cfg.n, 64, nnz), nullptr, h->x, h->delta,
+                               h->ld, tiles(64), h->cfg.n, (int)nnz, h->d_rowptr, h->cfg.eta, d_out);
+        else if (graph_fits && h->cfg.n <= 256)
+            hipLaunchKernelGGL(diagnostics_tile_kernel<16>, grid(tiles(16)), dim3(256), diagnostics_lds(h->cfg.n, 16, nnz), nullptr, h->x, h->delta,
+                               h->ld, tiles(16), h->cfg.n, (int)nnz, h->d_rowptr, h->cfg.eta, d_out);
+        else
+            hipLaunchKernelGGL(diagnostics_kernel, dim3(blocks), dim3(256), 0, nullptr, h->x, h->delta, h->ld, h->cfg.N, h->cfg.n,
+                               h->d_rowptr, h->d_col, h->d_coef, h->cfg.eta, d_out);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpy(out4, d_out, 3 * sizeof(double), hipMemcpyDeviceToHost);

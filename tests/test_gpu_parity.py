@@ -403,6 +403,30 @@ def test_diagnostics_match_their_definitions():
         ds.ds_destroy()
 
 
+@pytest.mark.parametrize("n,N,dense", [(3, 1, False), (64, 64 * 3, False), (64, 64 * 70 + 1, False), (65, 16 * 9 + 5, False), (256, 777, False),
+                                       (257, 130, False), (33, 5000, True), (60, 333, True)])
+def test_diagnostics_at_the_edges_of_their_tiles(n, N, dense):
+    """One column, whole and ragged tiles, the largest number of workers of either tile width and one more, and a graph of
+    3600 edges, which does not fit next to the tile (33 workers' does).  Bound: sums of at most 3e5 terms in double."""
+    w = small(wl.KIND_SIGN_MEANABS, n, N, block=64)
+    W = csr = None
+    if dense:
+        W = np.full((n, n), 1.0 / n, np.float32)
+        csr = (np.arange(n + 1, dtype=np.int32) * n, np.tile(np.arange(n, dtype=np.int32), n), W.reshape(-1))
+        cfg, keep = b.make_config(n, N, wl.TOPO_CSR, w.kind, w.gamma, w.eta, block=64, seed=w.seed, W_csr=csr)
+        ds = b.DeepSqueeze(cfg, keep)
+    else:
+        ds = b.DeepSqueeze.from_workload(w)
+    st = oracle_state(w, W)
+    st.x, st.delta = wl.random_state(w, seed=21)
+    st.x += np.float32(100.0)                                  # a mean far from zero: no cancellation in the consensus distance
+    ds.ds_write_state(st.x, st.delta, 0)
+    got, want = ds.ds_diagnostics(), oracle.diagnostics(st)
+    ds.ds_destroy()
+    for key in ("consensus_sq", "delta_sq", "delta_mixed_sq"):
+        assert abs(got[key] - want[key]) <= 1e-9 * abs(want[key]) + 1e-30, (key, got[key], want[key])
+
+
 # ------------------------------------------------------------------------------------ worked examples
 
 def test_hand_expanded_example_on_gpu(golden_dir):
