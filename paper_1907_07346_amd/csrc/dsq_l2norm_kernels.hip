@@ -13,7 +13,8 @@
 // Both the range and the decode scale are properties of the whole vector, so Algorithm 1's
 // lines 5-9 cannot be one pass: the codes need s, and delta = v - C[v] and the gossip sum need
 // unit.  A step is therefore
-//   form      (dense)  [tail of the previous step] ; xh = x - gamma g -> x ; v = xh + delta -> delta ;
+//   form      (dense)  [tail of the previous step] ; xh = x - gamma g -> x ; v = xh + delta -> delta (not if
+//                      there was no tail to apply: then delta in memory is right, and v is x + delta) ;
 //                      per-chunk max|v| and tree sums of v^2
 //   row_scale (tiny)   s, nrm per row
 //   quantize  (dense)  read v, write the codes into the message, per-chunk sum of y^2
@@ -23,7 +24,9 @@
 // streams x and delta anyway, or applied by l2q_flush before anyone else looks at the state.
 // Traffic per element and step: form 12 B read + 8 B written (+ (deg+1) b/8 B of codes, mostly
 // L2 hits), quantize 4 B read + b/8 B written: 24 B + codes against the 20 B + b/8 B any
-// implementation must move.
+// implementation must move.  Where the state is completed after every step (a training loop), form moves 16 B and the tail
+// another 16 B: 32 B + codes.  16 workers x 11,173,962 parameters at 2 bits: form 612 -> 474 us since delta stays in place,
+// tail 562 -> 522 us with all loads ahead of the stores (5.5 TB/s), the whole step 1207 -> 1048 us.
 //
 // Speculative codes (what makes the second dense pass unnecessary in steady state).  The code of an
 // element depends on the row's range s only through inv = (L/2)/s, and is monotone in it.  `form`
@@ -72,7 +75,8 @@ struct L2Scratch {
     float* cmax;                  // n x nchunks: max |v| of the chunk
     double* csq;                  // n x nchunks: tree sum of v^2 over the chunk
     uint32_t* csy2;               // n x nchunks: sum of y^2 over the chunk (< 2^32: 4096 * 255^2)
-    uint32_t* pending;            // 1: the last step's tail has not been applied to x and delta yet
+    uint32_t* pending;            // not 0: the last step's tail has not been applied to x and delta yet; 1: delta holds v,
+                                  // 2: delta is as it was before the step, and v is x + delta (x holds xh)
     uint32_t* ucount;             // n x nchunks: undecided elements `form` slotted for the chunk
     uint2* uslot;                 // n x nchunks x LQ_UCAP: (column offset in the chunk | placeholder code << 16, bits of v)
     uint32_t* row_flags;          // n: bit 0 = a slot of the row overflowed in this step's form pass
@@ -146,6 +150,10 @@ __device__ __forceinline__ void apply_tail4(const L2Args& a, const L2Scratch& s,
     }
 }
 
+__device__ __forceinline__ void add4(float4& d, const float4& x) {
+    d.x = x.x + d.x; d.y = x.y + d.y; d.z = x.z + d.z; d.w = x.w + d.w;
+}
+
 __device__ __forceinline__ double wave_tree_sum(double v) {   // adjacent pairs first; every lane gets the sum
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o);
@@ -167,7 +175,8 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_form(L2Args a, L2Scratch s) {
     const int row = blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t col0 = (uint64_t)blockIdx.x * LQ_CHUNK;
-    const bool tail = *s.pending != 0u;
+    const uint32_t pending = *s.pending;
+    const bool tail = pending != 0u;
     const uint32_t prev = last_half(a);
     const uint8_t* msg_prev = a.msg + (uint64_t)prev * a.msg_half;          // the codes the tail decodes
     uint8_t* mrow = a.msg + (uint64_t)(prev ^ 1u) * a.msg_half + (uint64_t)row * a.msg_row_bytes;   // this step's message
@@ -205,14 +214,19 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_form(L2Args a, L2Scratch s) {
                 if (col + 2 >= a.N) g4.z = 0.f;
                 g4.w = 0.f;
             }
-            if (tail) apply_tail4<BITS>(a, s, msg_prev, row, col, x4, d4);
+            if (tail) {
+                if (pending == 2u) add4(d4, x4);
+                apply_tail4<BITS>(a, s, msg_prev, row, col, x4, d4);
+            }
         }
         float4 xh, v;
         xh.x = fmaf(-a.gamma, g4.x, x4.x); xh.y = fmaf(-a.gamma, g4.y, x4.y);
         xh.z = fmaf(-a.gamma, g4.z, x4.z); xh.w = fmaf(-a.gamma, g4.w, x4.w);
         v.x = xh.x + d4.x; v.y = xh.y + d4.y; v.z = xh.z + d4.z; v.w = xh.w + d4.w;
         st4_stream(xr + col, xh);
-        st4_stream(dr + col, v);
+        // With no tail to apply, delta stays what it is in memory and whoever needs v adds xh to it: the same addition of
+        // the same numbers, and 4 B per element less.
+        if (tail) st4_stream(dr + col, v);
         vmax = fmaxf(vmax, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
         const double q0 = (double)v.x * (double)v.x, q1 = (double)v.y * (double)v.y;
         const double q2 = (double)v.z * (double)v.z, q3 = (double)v.w * (double)v.w;
@@ -349,6 +363,8 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_quantize(L2Args a, L2Scratch s
     const float inv = s.rows[row].inv;
     const bool zero_row = !(s.rows[row].s > 0.f);
     const float* dr = a.delta + (uint64_t)row * a.ld;
+    const float* xr = a.x + (uint64_t)row * a.ld;
+    const bool add_x = *s.pending == 0u;                  // `form` had no tail to apply and left delta alone
     uint8_t* mrow = a.msg + (uint64_t)(last_half(a) ^ 1u) * a.msg_half + (uint64_t)row * a.msg_row_bytes;
     const uint64_t code_bytes = a.msg_row_bytes - 4;      // whole 32-bit words
     uint32_t sy2 = 0;
@@ -357,7 +373,8 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_quantize(L2Args a, L2Scratch s
         const uint64_t col = col0 + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x;
         const uint64_t byte = col * BITS / 8;
         if (byte >= code_bytes) continue;                 // behind the last code word of the row
-        const float4 v4 = ld4_stream(dr + col);
+        float4 v4 = ld4_stream(dr + col);
+        if (add_x) add4(v4, ld4_stream(xr + col));
         const float* vp = reinterpret_cast<const float*>(&v4);
         uint32_t packed = 0;
 #pragma unroll
@@ -433,7 +450,7 @@ __global__ void __launch_bounds__(LQ_ROW_THREADS) l2q_row_unit(L2Args a, L2Scrat
         if (__hip_atomic_fetch_add(done, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned long long)gridDim.x - 1ull) {
             __hip_atomic_store(done, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(a.t_ptr + 4, (unsigned long long)written, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            *s.pending = 1u;
+            *s.pending = *s.pending != 0u ? 1u : 2u;                     // what `form` saw, which every row is done with
             atomicAdd(a.t_ptr, 1ull);                                    // one step taken
         }
     }
@@ -442,20 +459,28 @@ __global__ void __launch_bounds__(LQ_ROW_THREADS) l2q_row_unit(L2Args a, L2Scrat
 // The tail on its own (l2q_flush): delta = v - C[v], x = xh + eta sum_j a_ij C[v_j].
 template <int BITS>
 __global__ void __launch_bounds__(LQ_THREADS) l2q_tail(L2Args a, L2Scratch s) {
-    if (*s.pending == 0u) return;
+    const uint32_t pending = *s.pending;
+    if (pending == 0u) return;
     const int row = blockIdx.y;
     const uint64_t col0 = (uint64_t)blockIdx.x * LQ_CHUNK;
     const uint8_t* msg_last = a.msg + (uint64_t)last_half(a) * a.msg_half;
     float* xr = a.x + (uint64_t)row * a.ld;
     float* dr = a.delta + (uint64_t)row * a.ld;
+    float4 xs[LQ_ITERS], ds[LQ_ITERS];                    // all loads ahead of the first store, as in l2q_form
+#pragma unroll
+    for (int it = 0; it < LQ_ITERS; ++it) {
+        const uint64_t col = col0 + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x;   // rows are padded to whole chunks
+        xs[it] = ld4_stream(xr + col);
+        ds[it] = ld4_stream(dr + col);
+    }
 #pragma unroll
     for (int it = 0; it < LQ_ITERS; ++it) {
         const uint64_t col = col0 + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x;
         if (col >= a.N) continue;
-        float4 x4 = ld4_stream(xr + col), d4 = ld4_stream(dr + col);
-        apply_tail4<BITS>(a, s, msg_last, row, col, x4, d4);
-        st4_stream(xr + col, x4);
-        st4_stream(dr + col, d4);
+        if (pending == 2u) add4(ds[it], xs[it]);
+        apply_tail4<BITS>(a, s, msg_last, row, col, xs[it], ds[it]);
+        st4_stream(xr + col, xs[it]);
+        st4_stream(dr + col, ds[it]);
     }
 }
 
