@@ -550,12 +550,19 @@ ds_status ds_init_ex(const ds_config* cfg, const ds_plan_request* plan, char* er
         h->plan_name = resident ? "l2norm/resident" : "l2norm/speculative-codes";
         if (!resident) h->msg_half = (uint64_t)cfg->n * h->msg_row_bytes;     // the first pass writes codes while the old ones are still read
     } else {
-        // the row-streaming variant of the block compressors on request; it is also what serves a number of
-        // workers whose codes do not fit in LDS
+        // The row-streaming variant of the block compressors on request; it is also what serves a number of workers whose
+        // codes do not fit in LDS, and the faster one where the fused kernel's waves would own more rows than they can
+        // hold in registers (every shape ends at 64 rows) and a tile of 512 columns or more makes those rows a serial
+        // chain of 2 KB loads, formed twice: 256 workers x 272,474 parameters at 4 bits and blocks of 512, state complete
+        // after every step, 416 us fused and 349 streaming (28.5 B per element either way, but no last wave of 21
+        // tiles), 250 back to back; 100 workers x 12,000, 30 and 15 us.  With blocks of up to 256 columns the fused kernel
+        // stays ahead while the state fits in the memory-side cache (100 x 100,000 at 4 bits: 52 us against 65).
         dsq::TilePlan sp;
         const bool can_stream = dsq::stream_plan(h->cfg, sp);
         const bool fits = dsq::choose_tile_plans(h->cfg, (int)h->graph.col.size(), h->tile_candidates, err);
-        if (can_stream && (!fits || want.variant == 1)) {
+        const bool block_coded = cfg->comp.kind == DS_COMP_QUANT_MAXABS || cfg->comp.kind == DS_COMP_SIGN_MEANABS;
+        const bool many_rows = block_coded && cfg->n > 64 && cfg->comp.block >= 512 && want.tile_plan < 0;
+        if (can_stream && (!fits || want.variant == 1 || many_rows)) {
             h->tile_candidates.assign(1, sp);
             h->msg_half = (uint64_t)cfg->n * h->msg_row_bytes;
         } else if (!fits) {

@@ -897,6 +897,18 @@ def test_row_streaming_variant(w):
     ds.ds_destroy()
 
 
+@pytest.mark.parametrize("n,block", [(64, 512), (65, 512), (65, 256), (70, 1024)])
+def test_more_rows_than_registers_hold(n, block):
+    """One worker more than any fused launch shape holds: streaming from blocks of 512 columns on, the fused kernel that forms
+    the rows twice for narrower ones and where a launch shape is pinned; the same step everywhere."""
+    w = small(wl.KIND_QUANT_MAXABS, n, 1024 * 2 + 5, bits=2, block=block)
+    for plan in (None, {"tile_plan": 0}):
+        ds = b.DeepSqueeze.from_workload(w, plan)
+        assert ds.ds_plan_name().startswith("stream/") == (plan is None and n > 64 and block >= 512), ds.ds_plan_name()
+        ds.ds_destroy()
+        lock_step(w, steps=2, plan=plan)
+
+
 @pytest.mark.parametrize("w", [small(wl.KIND_QUANT_MAXABS, 700, 512 * 2 + 77, bits=4, block=512),
                                small(wl.KIND_SIGN_MEANABS, 1300, 2048 + 5, block=2048),
                                small(wl.KIND_IDENTITY, 200, 1000)], ids=lambda w: w.name)
