@@ -68,6 +68,9 @@ struct TileArgs {
                                        // to hand out, counted from the grid size); [32 (1+c)], c < 64: finished
                                        // workgroups with blockIdx % 64 == c.
                                        // Cells [1], [16] and [32 (1+c)] are zero between launches.
+    // Fused tile kernel without anything in device memory beside the caller's arrays (t_ptr and rowptr nullptr):
+    uint32_t t_given;                  // the step's number, low word
+    int given_topo, given_rows, given_cols;   // DS_TOPO_RING or DS_TOPO_TORUS2D: each workgroup works W - I out for itself
 };
 
 // A compiled variant of the fused tile kernel, chosen once at init.

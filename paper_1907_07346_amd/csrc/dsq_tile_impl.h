@@ -28,6 +28,41 @@ namespace dsq {
 namespace {
 
 constexpr uint32_t kQuantStreamTag = 0x51554E54u;   // 4th counter word of the rounding stream
+// The step counter's low word.
+__device__ __forceinline__ uint32_t step_word(const TileArgs& a) { return a.t_ptr ? (uint32_t)*a.t_ptr : a.t_given; }
+
+// Word q of the CSR of W - I (rowptr | col | coef, neighbours ascending) of a ring or a 2-D torus, for a launch that has no
+// graph in memory (TileArgs::given_topo).
+__device__ __forceinline__ int32_t given_graph_word(const TileArgs& a, int q) {
+    const int deg = a.given_topo == DS_TOPO_RING ? 3 : 5, n = a.n;
+    if (q <= n) return deg * q;
+    const int p = q - (n + 1), e = p < deg * n ? p : p - deg * n, i = e / deg;
+    int nb[5];
+    if (a.given_topo == DS_TOPO_RING) {
+        nb[0] = i == 0 ? n - 1 : i - 1; nb[1] = i; nb[2] = i == n - 1 ? 0 : i + 1;
+        nb[3] = nb[4] = n;                                    // behind every neighbour
+    } else {
+        const int R = a.given_rows, C = a.given_cols, r = i / C, c = i - r * C;
+        nb[0] = i;
+        nb[1] = (r == R - 1 ? 0 : r + 1) * C + c;
+        nb[2] = (r == 0 ? R - 1 : r - 1) * C + c;
+        nb[3] = r * C + (c == C - 1 ? 0 : c + 1);
+        nb[4] = r * C + (c == 0 ? C - 1 : c - 1);
+    }
+    const int rank = e - i * deg;                             // the neighbours are different workers: one of them has this rank
+    int at = i;
+#pragma unroll
+    for (int u = 0; u < 5; ++u) {
+        int below = 0;
+#pragma unroll
+        for (int w = 0; w < 5; ++w) below += nb[w] < nb[u] ? 1 : 0;
+        if (nb[u] < n && below == rank) at = nb[u];
+    }
+    if (p < deg * n) return at;
+    const float w = a.given_topo == DS_TOPO_RING ? 1.0f / 3.0f : 1.0f / 5.0f;
+    return __float_as_int(at == i ? w - 1.0f : w);
+}
+
 constexpr uint32_t kSparseStreamTag = 0x53504152u;  // ... and of the stream that draws the random sparsifier's mask
 
 // 16-byte streaming accesses.  x, g and delta are touched exactly once per step, so they are
@@ -200,7 +235,7 @@ struct Tile {
                                                                const float4 (&base)[SW], uint8_t* msg_row, uint8_t* lds_row, float* lds_units, float* dout) {
         const int grp = lane / G, in_blk = lane % G;                  // block of the sweep, lane-slot inside the block
         [[maybe_unused]] uint32_t t_lo = 0;
-        if constexpr (KIND == DS_COMP_QUANT_MAXABS) t_lo = (uint32_t)*a.t_ptr;
+        if constexpr (KIND == DS_COMP_QUANT_MAXABS) t_lo = step_word(a);
 #pragma unroll
         for (int s = 0; s < SW; ++s) {
             const uint64_t j = col0 + (uint64_t)s * kSweep + 4 * lane;
@@ -341,7 +376,7 @@ struct Tile {
             uint8_t* msg_blk = msg_row + (bcol0 / B) * MSG_BLOCK_BYTES;
 
             if constexpr (KIND == DS_COMP_QUANT_MAXABS) {
-                const uint32_t t_lo = (uint32_t)*a.t_ptr;            // step counter, low word (Philox counter word 2)
+                const uint32_t t_lo = step_word(a);                  // (Philox counter word 2)
                 float mx = 0.f;
 #pragma unroll
                 for (int s = b * SPB; s < (b + 1) * SPB; ++s)
@@ -627,9 +662,13 @@ struct Tile {
 #pragma unroll
         for (int k = 0; k < GPRE; ++k) {
             const int q = threadIdx.x + k * NW * kWave;
-            gpre[k] = (q < gtotal) ? a.rowptr[q] : 0;
+            gpre[k] = (q < gtotal && a.rowptr) ? a.rowptr[q] : 0;
         }
         auto park_graph = [&]() {
+            if (!a.rowptr) {                                  // uniform
+                for (int q = threadIdx.x; q < gtotal; q += NW * kWave) lds_graph[q] = given_graph_word(a, q);
+                return;
+            }
 #pragma unroll
             for (int k = 0; k < GPRE; ++k) {
                 const int q = threadIdx.x + k * NW * kWave;
@@ -779,8 +818,8 @@ __global__ void __launch_bounds__(NW* kWave) fused_tile_kernel(TileArgs a, int r
     // atomics on a single address serialise: with ~10^5 workgroups one shared counter doubled the
     // kernel time on MI355X, 64 cells cost < 0.5 %.  Relaxed atomics on purpose: a release fence
     // would write back the XCD's L2 once per workgroup; the end of the kernel publishes the new t.
-    // All cells are zero again when the kernel ends.
-    if (threadIdx.x == 0) {
+    // All cells are zero again when the kernel ends.  A launch that was given its step number has no counter to advance.
+    if (threadIdx.x == 0 && a.t_ptr) {
         const unsigned long long blocks = (unsigned long long)gridDim.x * gridDim.y;
         const unsigned cell = (unsigned)(tile & 63u);
         const unsigned long long members = (blocks >> 6) + (cell < (blocks & 63u) ? 1u : 0u);
