@@ -14,6 +14,7 @@ from typing import Optional
 import numpy as np
 import torch  # noqa: F401  (must be loaded before libdsq.so: one HIP runtime per process)
 
+from .detgen import GRAD_KINDS
 from .workloads import (KIND_IDENTITY, KIND_QUANT_MAXABS, KIND_SIGN_MEANABS, KIND_TOPK, KIND_QUANT_L2NORM, KIND_RAND_SPARSE, KIND_GSPAR,  # noqa: F401
                         TOPO_CSR, TOPO_RING, TOPO_TORUS2D, Config)
 
@@ -26,6 +27,19 @@ EXPORTS = ["ds_validate_config", "ds_build_topology", "ds_message_bytes", "ds_in
            "ds_read_state", "ds_write_state", "ds_read_messages", "ds_state_ptrs", "ds_message_ptr",
            "ds_step_count", "ds_plan_name", "ds_last_error", "ds_destroy", "ds_bench_copy",
            "ds_topk_candidate_rows", "ds_set_mixing", "ds_diagnostics", "ds_set_rates", "ds_workload_gradient", "ds_bench_stream", "ds_build_id", "ds_step_static", "ds_init_ex"]
+
+
+# torch's current stream as the pointer the library takes.  torch.cuda.current_stream() makes a Stream object for it: 2.9 us of
+# the 10 to 18 us that a small problem's step costs the caller; the raw pointer takes 0.3.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream_pointer(stream: Optional["torch.cuda.Stream"]) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 class ds_comp(ctypes.Structure):
@@ -126,11 +140,9 @@ def make_config(n: int, N: int, topo: int, kind: int, gamma: float, eta: float, 
 def ds_workload_gradient(kind: str, n: int, N: int, scale: float, seed: int, t: int, g: "torch.Tensor", x_ptr: int = 0,
                          x_ld: int = 0, stream: Optional["torch.cuda.Stream"] = None):
     """Fills the CUDA float32 tensor g (n, >= N) with the deterministic gradients of step t (see detgen.py)."""
-    from .detgen import GRAD_KINDS
     assert g.is_cuda and g.dtype == torch.float32 and g.dim() == 2 and g.shape[0] == n and g.stride(1) == 1
     w = ds_workload(n, GRAD_KINDS[kind], N, scale, 0.0, seed)
-    s = stream if stream is not None else torch.cuda.current_stream()
-    st = lib().ds_workload_gradient(ctypes.byref(w), t, x_ptr, x_ld, g.data_ptr(), g.stride(0), s.cuda_stream)
+    st = lib().ds_workload_gradient(ctypes.byref(w), t, x_ptr, x_ld, g.data_ptr(), g.stride(0), _stream_pointer(stream))
     if st != DS_OK:
         raise RuntimeError(f"ds_workload_gradient failed with status {st}")
 
@@ -168,8 +180,7 @@ def ds_bench_copy(dst: "torch.Tensor", src: "torch.Tensor", stream=None):
     """Plain device copy of src into dst (same byte size, multiple of 16) with the library's copy kernel."""
     nbytes = src.numel() * src.element_size()
     assert dst.numel() * dst.element_size() == nbytes and dst.is_cuda and src.is_cuda
-    s = stream if stream is not None else torch.cuda.current_stream()
-    st = lib().ds_bench_copy(dst.data_ptr(), src.data_ptr(), nbytes, s.cuda_stream)
+    st = lib().ds_bench_copy(dst.data_ptr(), src.data_ptr(), nbytes, _stream_pointer(stream))
     if st != DS_OK:
         raise DsqError(st, "ds_bench_copy")
 
@@ -180,8 +191,7 @@ def ds_bench_stream(x: "torch.Tensor", d: "Optional[torch.Tensor]", g: "torch.Te
     nbytes = x.numel() * x.element_size()
     assert (d is None or d.numel() * d.element_size() == nbytes) and g.numel() * g.element_size() == nbytes
     assert x.is_cuda and (d is None or d.is_cuda) and g.is_cuda
-    s = stream if stream is not None else torch.cuda.current_stream()
-    st = lib().ds_bench_stream(x.data_ptr(), d.data_ptr() if d is not None else None, g.data_ptr(), nbytes, s.cuda_stream)
+    st = lib().ds_bench_stream(x.data_ptr(), d.data_ptr() if d is not None else None, g.data_ptr(), nbytes, _stream_pointer(stream))
     if st != DS_OK:
         raise DsqError(st, "ds_bench_stream")
 
@@ -193,10 +203,9 @@ def ds_step_static(cfg: ds_config, x: "torch.Tensor", delta: "torch.Tensor", g: 
         assert a.is_cuda and a.dtype == torch.float32 and a.dim() == 2 and a.stride(1) == 1
     assert msg.is_cuda and msg.dtype == torch.uint8 and msg.is_contiguous() and msg.numel() >= ds_message_bytes(cfg)
     assert x.stride(0) == delta.stride(0)
-    s = stream if stream is not None else torch.cuda.current_stream()
     buf = ctypes.create_string_buffer(256)
     st = lib().ds_step_static(ctypes.byref(cfg), x.data_ptr(), delta.data_ptr(), x.stride(0), g.data_ptr(), g.stride(0),
-                              msg.data_ptr(), t, s.cuda_stream, buf, 256)
+                              msg.data_ptr(), t, _stream_pointer(stream), buf, 256)
     if st != DS_OK:
         raise DsqError(st, "ds_step_static", buf.value.decode())
 
@@ -233,9 +242,8 @@ class DeepSqueeze:
         """g: CUDA float32 tensor (n, >=N) with unit column stride; runs on `stream` (default: current)."""
         assert g.is_cuda and g.dtype == torch.float32 and g.dim() == 2 and g.shape[0] == self.n
         assert g.stride(1) == 1 and g.shape[1] >= self.N
-        s = stream if stream is not None else torch.cuda.current_stream()
         self._check(lib().ds_step(self._h, g.data_ptr(), g.stride(0) if self.n > 1 else max(g.stride(0), g.shape[1]),
-                                  s.cuda_stream), "ds_step")
+                                  _stream_pointer(stream)), "ds_step")
 
     def ds_step_raw(self, g_ptr: int, g_ld: int, stream_ptr: int = 0) -> int:
         return lib().ds_step(self._h, g_ptr, g_ld, stream_ptr)
