@@ -1179,12 +1179,16 @@ __global__ void __launch_bounds__(TK_THREADS) gs_write_dense(TopkArgs a, Scratch
 __global__ void gs_close(unsigned long long* t_ptr) { atomicAdd(t_ptr, 1ull); }      // one step taken
 
 // ---- the deferred sparse tail of a step, applied in place (when the state must be complete now) --
-// One workgroup per (row, chunk): the neighbours' pairs that fall into the chunk are contiguous in
-// their messages (out_off), so they are accumulated in ascending neighbour order into an LDS copy
-// of the chunk and then applied once per touched column.
+// One workgroup per (row, chunk): the neighbours' pairs that fall into the chunk are contiguous in their messages
+// (out_off), so they are accumulated in ascending neighbour order into an LDS copy of the chunk.  Bound by memory: with
+// 1 % sent and three neighbours 62 % of x's 128-byte lines are touched, and writing single words of them cost as much as
+// writing them whole (1116 us for 32 workers x 25,557,032 parameters, and 1146 with one wave per chunk and four times as many
+// chunks in flight).  So the touched sectors of 64 bytes, and those of delta with a sent column, are read and written
+// whole, asked for before the sum is made: 1015 us (1038 with lines of 128 bytes).
 __global__ void __launch_bounds__(TK_THREADS) topk_gossip(TopkArgs a, Scratch s) {
     __shared__ float acc[TK_CHUNK];
-    __shared__ uint32_t taken[TK_CHUNK / 32];
+    __shared__ uint32_t touched[TK_CHUNK / 512];            // a bit per sector of 16 columns
+    __shared__ uint32_t own[TK_CHUNK / 32];                 // half a word per sector: the columns this worker sent
     const int row = blockIdx.y;
     const uint32_t c = blockIdx.x;
     const uint32_t nchunks = s.nchunks;
@@ -1196,35 +1200,80 @@ __global__ void __launch_bounds__(TK_THREADS) topk_gossip(TopkArgs a, Scratch s)
         any |= (off[0] != off[1]);
     }
     if (!any) return;                                       // uniform
-    for (int q = threadIdx.x; q < TK_CHUNK; q += TK_THREADS) acc[q] = 0.f;
-    for (int q = threadIdx.x; q < TK_CHUNK / 32; q += TK_THREADS) taken[q] = 0u;
+    // the first pair per thread of the first neighbours, all asked for together
+    constexpr int EB = 4;
+    uint2 ahead[EB];
+#pragma unroll
+    for (int u = 0; u < EB; ++u) {
+        ahead[u] = make_uint2(0xFFFFFFFFu, 0u);
+        if (e0 + u < e1) {
+            const int nb = a.col[e0 + u];
+            const uint32_t* off = s.out_off + (size_t)nb * (nchunks + 1) + c;
+            if (off[0] + threadIdx.x < off[1]) ahead[u] = reinterpret_cast<const uint2*>(a.msg + (uint64_t)nb * a.k * 8)[off[0] + threadIdx.x];
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < TK_ITERS; ++it) reinterpret_cast<float4*>(acc)[it * TK_THREADS + threadIdx.x] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (threadIdx.x < TK_CHUNK / 32) own[threadIdx.x] = 0u;
+    if (threadIdx.x < TK_CHUNK / 512) touched[threadIdx.x] = 0u;
     __syncthreads();
-    for (int e = e0; e < e1; ++e) {
+    // f(pair, neighbour's edge) for all pairs of edge e that fall into the chunk
+    auto pairs_of = [&](int e, const uint2& first, bool have_first, auto f) {
         const int nb = a.col[e];
-        const float w = a.coef[e];
         const uint32_t* off = s.out_off + (size_t)nb * (nchunks + 1) + c;
         const uint2* in = reinterpret_cast<const uint2*>(a.msg + (uint64_t)nb * a.k * 8);
-        for (uint32_t p = off[0] + threadIdx.x; p < off[1]; p += TK_THREADS) {
-            const uint2 pr = in[p];
+        for (uint32_t p = off[0] + threadIdx.x, end = off[1]; p < end; p += TK_THREADS) {
+            const uint2 pr = have_first && p < off[0] + TK_THREADS ? first : in[p];
             const uint32_t q = (uint32_t)((uint64_t)pr.x - c0);
-            if (q < (uint32_t)TK_CHUNK) acc[q] = fmaf(w, __uint_as_float(pr.y), acc[q]);
+            if (q < (uint32_t)TK_CHUNK && pr.x < a.N) f(q, __uint_as_float(pr.y), nb);
         }
+    };
+    auto mark = [&](uint32_t q, float, int nb) {
+        atomicOr(&touched[q >> 9], 1u << ((q >> 4) & 31));
+        if (nb == row) atomicOr(&own[q >> 5], 1u << (q & 31));
+    };
+#pragma unroll
+    for (int u = 0; u < EB; ++u)
+        if (e0 + u < e1) pairs_of(e0 + u, ahead[u], true, mark);
+    for (int e = e0 + EB; e < e1; ++e) pairs_of(e, ahead[0], false, mark);
+    __syncthreads();
+    float* xr = a.x + (uint64_t)row * a.ld + c0;
+    float* dr = a.delta + (uint64_t)row * a.ld + c0;
+    float4 xv[TK_ITERS], dv[TK_ITERS];
+#pragma unroll
+    for (int it = 0; it < TK_ITERS; ++it) {
+        const uint32_t q = (uint32_t)it * TK_VEC + 4 * threadIdx.x;               // rows are padded to whole chunks
+        if ((touched[q >> 9] >> ((q >> 4) & 31)) & 1u) xv[it] = ld4_stream(xr + q);
+        if ((own[q >> 5] >> (q & 16)) & 0xFFFFu) dv[it] = ld4_stream(dr + q);
+    }
+#pragma unroll
+    for (int u = 0; u < EB; ++u)
+        if (e0 + u < e1) {                                                        // uniform
+            const float w = a.coef[e0 + u];
+            pairs_of(e0 + u, ahead[u], true, [&](uint32_t q, float val, int) { acc[q] = fmaf(w, val, acc[q]); });
+            __syncthreads();
+        }
+    for (int e = e0 + EB; e < e1; ++e) {
+        const float w = a.coef[e];
+        pairs_of(e, ahead[0], false, [&](uint32_t q, float val, int) { acc[q] = fmaf(w, val, acc[q]); });
         __syncthreads();
     }
-    float* xr = a.x + (uint64_t)row * a.ld;
-    float* dr = a.delta + (uint64_t)row * a.ld;
-    for (int e = e0; e < e1; ++e) {
-        const int nb = a.col[e];
-        const uint32_t* off = s.out_off + (size_t)nb * (nchunks + 1) + c;
-        const uint2* in = reinterpret_cast<const uint2*>(a.msg + (uint64_t)nb * a.k * 8);
-        for (uint32_t p = off[0] + threadIdx.x; p < off[1]; p += TK_THREADS) {
-            const uint32_t jj = in[p].x;
-            const uint32_t q = (uint32_t)((uint64_t)jj - c0);
-            if (q >= (uint32_t)TK_CHUNK || jj >= a.N) continue;
-            if (nb == row) dr[jj] = 0.f;                    // line 6: delta = v - C[v] = 0 where v was sent
-            const uint32_t bit = 1u << (q & 31);
-            const uint32_t old = atomicOr(&taken[q >> 5], bit);
-            if (!(old & bit)) xr[jj] = fmaf(a.eta, acc[q], xr[jj]);
+#pragma unroll
+    for (int it = 0; it < TK_ITERS; ++it) {
+        const uint32_t q = (uint32_t)it * TK_VEC + 4 * threadIdx.x;
+        if ((touched[q >> 9] >> ((q >> 4) & 31)) & 1u) {                         // x holds no -0: adding eta * 0 leaves the others as they are
+            const float4 sum = *reinterpret_cast<const float4*>(acc + q);
+            xv[it].x = fmaf(a.eta, sum.x, xv[it].x); xv[it].y = fmaf(a.eta, sum.y, xv[it].y);
+            xv[it].z = fmaf(a.eta, sum.z, xv[it].z); xv[it].w = fmaf(a.eta, sum.w, xv[it].w);
+            st4_stream(xr + q, xv[it]);
+        }
+        if ((own[q >> 5] >> (q & 16)) & 0xFFFFu) {                                // line 6: delta = v - C[v] = 0 where v was sent
+            const uint32_t sent = own[q >> 5] >> (q & 31);
+            if (sent & 1u) dv[it].x = 0.f;
+            if (sent & 2u) dv[it].y = 0.f;
+            if (sent & 4u) dv[it].z = 0.f;
+            if (sent & 8u) dv[it].w = 0.f;
+            st4_stream(dr + q, dv[it]);
         }
     }
 }

@@ -130,3 +130,31 @@ def test_two_resident_handles_on_two_streams(other):
         x, d = ds.ds_read_state()
         ds.ds_destroy()
         assert assert_close(f"{w.name} x", x, st.x) + assert_close(f"{w.name} delta", d, st.delta) == 0
+
+
+@pytest.mark.parametrize("k", [1, 64, 65, 128, 129, 300])
+@pytest.mark.parametrize("n,torus", [(5, None), (9, (3, 3)), (8, "dense")])
+def test_sparse_tail_by_fullness_of_a_chunk(k, n, torus):
+    """Everything that is sent lies in one chunk of four, in some of the same columns for all workers: the tail on its own with
+    one pair per lane, two, and more than a wave takes at once; with 3, 5 and 8 neighbours."""
+    w = small(wl.KIND_TOPK, n, 4096 * 3 + 1001, k=k, **({"topo": wl.TOPO_TORUS2D, "torus": torus} if isinstance(torus, tuple) else {}))
+    W = np.full((n, n), 1.0 / n, np.float32) if torus == "dense" else None
+    if W is not None:
+        cfg, keep = b.make_config(n, w.N, wl.TOPO_CSR, w.kind, w.gamma, w.eta, k=k, seed=w.seed,
+                                  W_csr=(np.arange(n + 1, dtype=np.int32) * n, np.tile(np.arange(n, dtype=np.int32), n), W.reshape(-1)))
+        ds = b.DeepSqueeze(cfg, keep, _plan(2))
+    else:
+        ds = b.DeepSqueeze.from_workload(w, _plan(2))
+    st = oracle_state(w, W)
+    rng = np.random.default_rng(k)
+    st.delta = rng.normal(size=(n, w.N)).astype(np.float32)
+    st.delta[:, 4096 + 7:4096 + 7 + 2 * k:2] *= 1000.0
+    ds.ds_write_state(st.x, st.delta, st.t)
+    for t in range(3):
+        g = wl.gradient(w, t)
+        ds.ds_step(upload(g))
+        _, msg = oracle.step(st, g, want_cv=False)
+        assert np.array_equal(ds.ds_read_messages(), msg), f"step {t}: messages differ"
+        x, d = ds.ds_read_state()
+        assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0, f"step {t}"
+    ds.ds_destroy()
