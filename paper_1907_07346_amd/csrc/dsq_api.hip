@@ -491,13 +491,18 @@ ds_status ds_init_ex(const ds_config* cfg, const ds_plan_request* plan, char* er
         // hold in registers (every shape ends at 64 rows) and a tile of 512 columns or more makes those rows a serial
         // chain of 2 KB loads, formed twice: 256 workers x 272,474 parameters at 4 bits and blocks of 512, state complete
         // after every step, 416 us fused and 349 streaming (28.5 B per element either way, but no last wave of 21
-        // tiles), 250 back to back; 100 workers x 12,000, 30 and 15 us.  With blocks of up to 256 columns the fused kernel
-        // stays ahead while the state fits in the memory-side cache (100 x 100,000 at 4 bits: 52 us against 65).
+        // tiles), 250 back to back; 100 workers x 12,000, 30 and 15 us.  Measured over 66 .. 256 workers and blocks of 512 ..
+        // 2048: up to 128 tiles (half of the compute units) streaming takes 0.5 to 0.9 of the fused kernel's time, beyond
+        // 512 tiles 0.8 to 0.95 from about 200 workers on; in between it depends on how full the last wave is (0.7 to
+        // 1.3) and on how much of the second forming comes from the memory-side cache, and the fused kernel stays.  So it does
+        // with blocks of up to 256 columns (100 x 100,000 at 4 bits: 52 us against 65).
         dsq::TilePlan sp;
         const bool can_stream = dsq::stream_plan(h->cfg, sp);
         const bool fits = dsq::choose_tile_plans(h->cfg, (int)h->graph.col.size(), h->tile_candidates, err);
         const bool block_coded = cfg->comp.kind == DS_COMP_QUANT_MAXABS || cfg->comp.kind == DS_COMP_SIGN_MEANABS;
-        const bool many_rows = block_coded && cfg->n > 64 && cfg->comp.block >= 512 && want.tile_plan < 0;
+        const uint64_t tiles = block_coded ? (cfg->N + cfg->comp.block - 1) / cfg->comp.block : 0;
+        const bool few_tiles = tiles <= 128, many_tiles = tiles > 512 && cfg->n >= 192;
+        const bool many_rows = block_coded && cfg->n > 64 && cfg->comp.block >= 512 && (few_tiles || many_tiles) && want.tile_plan < 0;
         if (can_stream && (!fits || want.variant == 1 || many_rows)) {
             h->tile_candidates.assign(1, sp);
             h->msg_half = (uint64_t)cfg->n * h->msg_row_bytes;

@@ -899,7 +899,7 @@ def test_row_streaming_variant(w):
 
 @pytest.mark.parametrize("n,block", [(64, 512), (65, 512), (65, 256), (70, 1024)])
 def test_more_rows_than_registers_hold(n, block):
-    """One worker more than any fused launch shape holds: streaming from blocks of 512 columns on, the fused kernel that forms
+    """One worker more than any fused launch shape holds: streaming from blocks of 512 columns on (few tiles), the fused kernel that forms
     the rows twice for narrower ones and where a launch shape is pinned; the same step everywhere."""
     w = small(wl.KIND_QUANT_MAXABS, n, 1024 * 2 + 5, bits=2, block=block)
     for plan in (None, {"tile_plan": 0}):
