@@ -353,7 +353,7 @@ __global__ void __launch_bounds__(256) stream_2r1w_kernel(f32x4* __restrict__ x,
     }
 }
 
-constexpr int kStaticMaxWorkers = 1024;                       // ds_step_static
+constexpr int kStaticMaxWorkers = 1024;                       // ds_step_static: what its declaration promises (nothing in the kernel ends there)
 
 }  // namespace
 
@@ -391,16 +391,17 @@ ds_status ds_step_static(const ds_config* cfg, float* x_dev, float* delta_dev, u
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     // One launch: the kernel takes the step number by value and works the graph out for itself.  (A kernel of its own that
     // put both into device memory took 2.4 us and a second launch of a 12.4 us call: 8 workers x 4,645 parameters.)
-    dsq::TileArgs a{};
+    dsq::GivenTileArgs a{};
     a.x = x_dev; a.delta = delta_dev; a.g = g_dev; a.msg = static_cast<uint8_t*>(msg_dev);
     a.ld = ld; a.g_ld = g_ld; a.N = cfg->N; a.msg_row_bytes = dsq::message_row_bytes(cfg);
     a.n = cfg->n; a.nnz = nnz;
     a.gamma = cfg->gamma; a.eta = cfg->eta;
     a.seed_lo = (uint32_t)cfg->seed; a.seed_hi = (uint32_t)(cfg->seed >> 32);
-    a.t_given = (uint32_t)t;
-    a.given_topo = cfg->topo; a.given_rows = cfg->torus_rows; a.given_cols = cfg->torus_cols;
+    a.t = (uint32_t)t;
+    a.topo = cfg->topo; a.torus_rows = cfg->torus_rows; a.torus_cols = cfg->torus_cols;
     const dsq::TilePlan& plan = plans.front();
-    plan.launch(a, plan.rows_per_wave, stream);
+    if (!plan.launch_given) return fail_with(DS_EINVAL, "internal: the first launch shape has no form that is given its graph");
+    plan.launch_given(a, plan.rows_per_wave, stream);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail_with(DS_EHIP, std::string("launching the step failed: ") + hipGetErrorString(e));
     if (errbuf && errbuf_len) std::snprintf(errbuf, (size_t)errbuf_len, "%s", warn.c_str());

@@ -68,15 +68,19 @@ struct TileArgs {
                                        // to hand out, counted from the grid size); [32 (1+c)], c < 64: finished
                                        // workgroups with blockIdx % 64 == c.
                                        // Cells [1], [16] and [32 (1+c)] are zero between launches.
-    // Fused tile kernel without anything in device memory beside the caller's arrays (t_ptr and rowptr nullptr):
-    uint32_t t_given;                  // the step's number, low word
-    int given_topo, given_rows, given_cols;   // DS_TOPO_RING or DS_TOPO_TORUS2D: each workgroup works W - I out for itself
+};
+
+// The fused tile kernel without anything in device memory beside the caller's arrays (t_ptr and rowptr are nullptr).
+struct GivenTileArgs : TileArgs {
+    uint32_t t;                        // the step's number, low word
+    int topo, torus_rows, torus_cols;  // DS_TOPO_RING or DS_TOPO_TORUS2D: each workgroup works W - I out for itself
 };
 
 // A compiled variant of the fused tile kernel, chosen once at init.
 struct TilePlan {
     const char* name = "";
     void (*launch)(const TileArgs&, int rows_per_wave, hipStream_t) = nullptr;
+    void (*launch_given)(const GivenTileArgs&, int rows_per_wave, hipStream_t) = nullptr;   // nullptr: not built for this shape
     int tile_cols = 0;         // columns per workgroup
     int waves = 0;             // waves per workgroup
     int rows_per_wave = 0;     // rows each wave owns (held in registers when the variant says so)

@@ -21,6 +21,8 @@
 
 #pragma once
 
+#include <type_traits>
+
 #include "dsq_internal.h"
 #include "dsq_philox.h"
 
@@ -28,21 +30,19 @@ namespace dsq {
 namespace {
 
 constexpr uint32_t kQuantStreamTag = 0x51554E54u;   // 4th counter word of the rounding stream
-// The step counter's low word.
-__device__ __forceinline__ uint32_t step_word(const TileArgs& a) { return a.t_ptr ? (uint32_t)*a.t_ptr : a.t_given; }
 
 // Word q of the CSR of W - I (rowptr | col | coef, neighbours ascending) of a ring or a 2-D torus, for a launch that has no
-// graph in memory (TileArgs::given_topo).
-__device__ __forceinline__ int32_t given_graph_word(const TileArgs& a, int q) {
-    const int deg = a.given_topo == DS_TOPO_RING ? 3 : 5, n = a.n;
+// graph in memory.
+__device__ __forceinline__ int32_t given_graph_word(const GivenTileArgs& a, int q) {
+    const int deg = a.topo == DS_TOPO_RING ? 3 : 5, n = a.n;
     if (q <= n) return deg * q;
     const int p = q - (n + 1), e = p < deg * n ? p : p - deg * n, i = e / deg;
     int nb[5];
-    if (a.given_topo == DS_TOPO_RING) {
+    if (a.topo == DS_TOPO_RING) {
         nb[0] = i == 0 ? n - 1 : i - 1; nb[1] = i; nb[2] = i == n - 1 ? 0 : i + 1;
         nb[3] = nb[4] = n;                                    // behind every neighbour
     } else {
-        const int R = a.given_rows, C = a.given_cols, r = i / C, c = i - r * C;
+        const int R = a.torus_rows, C = a.torus_cols, r = i / C, c = i - r * C;
         nb[0] = i;
         nb[1] = (r == R - 1 ? 0 : r + 1) * C + c;
         nb[2] = (r == 0 ? R - 1 : r - 1) * C + c;
@@ -59,7 +59,7 @@ __device__ __forceinline__ int32_t given_graph_word(const TileArgs& a, int q) {
         if (nb[u] < n && below == rank) at = nb[u];
     }
     if (p < deg * n) return at;
-    const float w = a.given_topo == DS_TOPO_RING ? 1.0f / 3.0f : 1.0f / 5.0f;
+    const float w = a.topo == DS_TOPO_RING ? 1.0f / 3.0f : 1.0f / 5.0f;
     return __float_as_int(at == i ? w - 1.0f : w);
 }
 
@@ -132,8 +132,18 @@ template <> struct CodeTraits<DS_COMP_RAND_SPARSE, 32> { using lane_t = float4; 
 __device__ __forceinline__ float comp(const float4& v, int c) { return c == 0 ? v.x : c == 1 ? v.y : c == 2 ? v.z : v.w; }
 __device__ __forceinline__ void set_comp(float4& v, int c, float f) { if (c == 0) v.x = f; else if (c == 1) v.y = f; else if (c == 2) v.z = f; else v.w = f; }
 
-template <int KIND, int BITS, int B, int SW, int NW>
+// GIVEN: a launch of GivenTileArgs, with the step's number and the graph by value.  A kernel of its own, and not a test of
+// a pointer in the one that handles launch: there the test and the graph's integer divisions cost 14 scalar and 2 vector
+// registers of the sign kernel (60 -> 74, 26 -> 28).
+template <int KIND, int BITS, int B, int SW, int NW, bool GIVEN = false>
 struct Tile {
+    using Args = std::conditional_t<GIVEN, GivenTileArgs, TileArgs>;
+    // The step counter's low word.
+    static __device__ __forceinline__ uint32_t step_word(const TileArgs& a) {
+        if constexpr (GIVEN) return static_cast<const GivenTileArgs&>(a).t;
+        else return (uint32_t)*a.t_ptr;
+    }
+
     static constexpr int TC = SW * kSweep;                 // columns per tile
     static constexpr bool SUB = B < kSweep;                // several scale blocks share one sweep
     static constexpr int BPS = SUB ? kSweep / B : 1;       // scale blocks per sweep (SUB)
@@ -647,7 +657,7 @@ struct Tile {
     }
 
     template <int RPW, bool FULL>
-    static __device__ __forceinline__ void run(const TileArgs& a, int rpw_runtime, uint64_t col0, uint8_t* lds) {
+    static __device__ __forceinline__ void run(const Args& a, int rpw_runtime, uint64_t col0, uint8_t* lds) {
         const int lane = threadIdx.x & (kWave - 1);
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         uint8_t* lds_codes = lds;
@@ -658,23 +668,23 @@ struct Tile {
         // hides behind the row streams.  Read only after the barrier.
         constexpr int GPRE = 2;
         const int gtotal = a.n + 1 + 2 * a.nnz;
-        int32_t gpre[GPRE];
+        [[maybe_unused]] int32_t gpre[GPRE];
 #pragma unroll
         for (int k = 0; k < GPRE; ++k) {
             const int q = threadIdx.x + k * NW * kWave;
-            gpre[k] = (q < gtotal && a.rowptr) ? a.rowptr[q] : 0;
+            if constexpr (!GIVEN) gpre[k] = (q < gtotal) ? a.rowptr[q] : 0;
         }
         auto park_graph = [&]() {
-            if (!a.rowptr) {                                  // uniform
+            if constexpr (GIVEN) {
                 for (int q = threadIdx.x; q < gtotal; q += NW * kWave) lds_graph[q] = given_graph_word(a, q);
-                return;
-            }
+            } else {
 #pragma unroll
-            for (int k = 0; k < GPRE; ++k) {
-                const int q = threadIdx.x + k * NW * kWave;
-                if (q < gtotal) lds_graph[q] = gpre[k];
+                for (int k = 0; k < GPRE; ++k) {
+                    const int q = threadIdx.x + k * NW * kWave;
+                    if (q < gtotal) lds_graph[q] = gpre[k];
+                }
+                for (int q = threadIdx.x + GPRE * NW * kWave; q < gtotal; q += NW * kWave) lds_graph[q] = a.rowptr[q];
             }
-            for (int q = threadIdx.x + GPRE * NW * kWave; q < gtotal; q += NW * kWave) lds_graph[q] = a.rowptr[q];
         };
         if constexpr (RPW > 0) {
             float4 xh[RPW][SW];
@@ -801,9 +811,9 @@ __global__ void __launch_bounds__(1024) keep_scan_kernel(TileArgs a, uint32_t* _
     }
 }
 
-template <int KIND, int BITS, int B, int SW, int NW, int RPW>
-__global__ void __launch_bounds__(NW* kWave) fused_tile_kernel(TileArgs a, int rpw_runtime) {
-    using T = Tile<KIND, BITS, B, SW, NW>;
+template <int KIND, int BITS, int B, int SW, int NW, int RPW, bool GIVEN>
+__global__ void __launch_bounds__(NW* kWave) fused_tile_kernel(typename Tile<KIND, BITS, B, SW, NW, GIVEN>::Args a, int rpw_runtime) {
+    using T = Tile<KIND, BITS, B, SW, NW, GIVEN>;
     extern __shared__ __align__(16) uint8_t lds[];
     // tiles are numbered along x first; the grid has a second row only when x alone would pass the
     // 2^32 work-items a launch dimension can hold, and its last row may then have spare workgroups
@@ -819,7 +829,8 @@ __global__ void __launch_bounds__(NW* kWave) fused_tile_kernel(TileArgs a, int r
     // kernel time on MI355X, 64 cells cost < 0.5 %.  Relaxed atomics on purpose: a release fence
     // would write back the XCD's L2 once per workgroup; the end of the kernel publishes the new t.
     // All cells are zero again when the kernel ends.  A launch that was given its step number has no counter to advance.
-    if (threadIdx.x == 0 && a.t_ptr) {
+    if constexpr (GIVEN) return;
+    if (threadIdx.x == 0) {
         const unsigned long long blocks = (unsigned long long)gridDim.x * gridDim.y;
         const unsigned cell = (unsigned)(tile & 63u);
         const unsigned long long members = (blocks >> 6) + (cell < (blocks & 63u) ? 1u : 0u);
@@ -954,16 +965,16 @@ bool stream_plan_for_block(int block, TilePlan& plan) {
     }
 }
 
-template <int KIND, int BITS, int B, int SW, int NW, int RPW>
-void launch_tile(const TileArgs& a, int rpw_runtime, hipStream_t stream) {
-    using T = Tile<KIND, BITS, B, SW, NW>;
+template <int KIND, int BITS, int B, int SW, int NW, int RPW, bool GIVEN>
+void launch_tile(const typename Tile<KIND, BITS, B, SW, NW, GIVEN>::Args& a, int rpw_runtime, hipStream_t stream) {
+    using T = Tile<KIND, BITS, B, SW, NW, GIVEN>;
     const uint64_t tiles = (a.N + T::TC - 1) / T::TC;
     // a launch dimension holds fewer than 2^32 work-items: very long vectors get a second grid row
     const uint64_t max_x = 0xFFFFFFFFull / (NW * kWave);
     const unsigned gx = (unsigned)(tiles < max_x ? tiles : max_x);
     const unsigned gy = (unsigned)((tiles + gx - 1) / gx);
     const size_t lds = T::lds_bytes(a.n, a.nnz);
-    auto kern = fused_tile_kernel<KIND, BITS, B, SW, NW, RPW>;
+    auto kern = fused_tile_kernel<KIND, BITS, B, SW, NW, RPW, GIVEN>;
     // more than the default dynamic LDS has to be asked for once per kernel and device (handles are
     // bound to one device, but a process may hold handles on several)
     static unsigned long long attr_devices = 0;
@@ -983,7 +994,9 @@ template <int KIND, int BITS, int B, int SW, int NW, int RPW>
 TilePlan make_plan(const char* name) {
     TilePlan p;
     p.name = name;
-    p.launch = &launch_tile<KIND, BITS, B, SW, NW, RPW>;
+    p.launch = &launch_tile<KIND, BITS, B, SW, NW, RPW, false>;
+    // the shapes that can stand first in a list of candidates: ds_step_static takes the first
+    if constexpr (KIND != DS_COMP_RAND_SPARSE && (NW == 8 || RPW == 0)) p.launch_given = &launch_tile<KIND, BITS, B, SW, NW, RPW, true>;
     p.tile_cols = SW * kSweep;
     p.waves = NW;
     p.rows_per_wave = RPW;

@@ -1,5 +1,5 @@
-"""ds_step_static (one step on caller-owned arrays, nothing allocated, scratch in a static device array)
-against ds_step on a handle: bit for bit, on two calls in a row, the second with a smaller input."""
+"""ds_step_static (one step on caller-owned arrays, nothing allocated, nothing in device memory beside them) against
+ds_step on a handle: bit for bit, on calls in a row, later ones with a smaller input, and on two streams at once."""
 import numpy as np
 import pytest
 import torch
@@ -64,7 +64,54 @@ def test_static_step_equals_handle_step_twice_second_smaller():
         assert np.array_equal(got[1].view(np.uint32), want[1].view(np.uint32)), f"{w.name}: delta differs"
 
 
-def test_static_step_rejects_what_its_scratch_cannot_hold():
+Q4 = (wl.KIND_QUANT_MAXABS, 4, 512)
+
+
+@pytest.mark.parametrize("n,torus,comp,N", [
+    (9, (3, 3), Q4, 700), (15, (3, 5), Q4, 512 * 3 + 1), (15, (5, 3), Q4, 512 * 3 + 1), (24, (4, 6), (wl.KIND_SIGN_MEANABS, 0, 64), 901),
+    (3, None, Q4, 1), (16, None, Q4, 512 * 2), (33, None, (wl.KIND_QUANT_MAXABS, 2, 1024), 1500), (65, None, Q4, 1100),
+    (17, None, (wl.KIND_QUANT_MAXABS, 8, 2048), 2049), (300, None, Q4, 600), (300, (15, 20), Q4, 600), (500, None, (wl.KIND_SIGN_MEANABS, 0, 256), 513),
+    (1024, None, (wl.KIND_SIGN_MEANABS, 0, 64), 300), (40, (5, 8), (wl.KIND_IDENTITY, 0, 0), 777)])
+def test_static_step_by_graph_and_launch_shape(n, torus, comp, N):
+    """The graph that the kernel works out for itself: sides of three (where the wrap-around changes the neighbours' order),
+    rows and columns that differ, more entries than threads, the largest number of workers; and every rows-per-wave shape."""
+    w, x0, d0, g, t = _case(n, N, wl.TOPO_TORUS2D if torus else wl.TOPO_RING, torus or (0, 0), *comp, seed=n, t=5)
+    print("case", w.name, flush=True)
+    want, got = _by_handle(w, x0, d0, g, t), _static(w, x0, d0, g, t)
+    assert np.array_equal(got[2], want[2]), "messages differ"
+    assert np.array_equal(got[0].view(np.uint32), want[0].view(np.uint32)) and np.array_equal(got[1].view(np.uint32), want[1].view(np.uint32))
+
+
+def test_static_steps_on_two_streams_share_nothing():
+    """Two problems of different graphs, sizes and step numbers, a stream each, ten steps of both under way together."""
+    steps = 10
+    cases = [_case(15, 512 * 40 + 3, wl.TOPO_TORUS2D, (3, 5), *Q4, seed=11, t=0), _case(8, 256 * 90 + 1, wl.TOPO_RING, (0, 0), wl.KIND_QUANT_MAXABS, 2, 256, seed=12, t=100)]
+    sides = []
+    for w, x0, d0, g, t in cases:
+        cfg, _ = b.config_from_workload(w)
+        ld = (w.N + 4095) // 4096 * 4096
+        rows = [torch.zeros((w.n, ld), device="cuda") for _ in range(3)]
+        for a, v in zip(rows, (x0, d0, g)):
+            a[:, :w.N] = torch.from_numpy(v).cuda()
+        sides.append((cfg, rows, torch.zeros(b.ds_message_bytes(cfg), dtype=torch.uint8, device="cuda"), t, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for q in range(steps):
+        for cfg, (x, d, g), msg, t, stream in sides:
+            b.ds_step_static(cfg, x, d, g, msg, t + q, stream)
+    torch.cuda.synchronize()
+    for (w, x0, d0, _, t), (_, (x, d, g), msg, _, _) in zip(cases, sides):
+        ds = b.DeepSqueeze.from_workload(w)
+        ds.ds_write_state(x0, d0, t)
+        for _ in range(steps):
+            ds.ds_step(g)
+        xw, dw = ds.ds_read_state()
+        assert np.array_equal(msg.cpu().numpy(), ds.ds_read_messages()), f"{w.name}: messages differ"
+        assert np.array_equal(x[:, :w.N].cpu().numpy().view(np.uint32), xw.view(np.uint32)), f"{w.name}: x differs"
+        assert np.array_equal(d[:, :w.N].cpu().numpy().view(np.uint32), dw.view(np.uint32)), f"{w.name}: delta differs"
+        ds.ds_destroy()
+
+
+def test_static_step_refuses_what_it_does_not_serve():
     x = torch.zeros((4, 4096 + 2560), dtype=torch.float32, device="cuda")
     msg = torch.zeros(1 << 16, dtype=torch.uint8, device="cuda")
 
