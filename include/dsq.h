@@ -182,8 +182,12 @@ typedef struct {
                           /*    takes one row of a tile, no LDS exchange; what serves more workers than the     */
                           /*    fused kernel's LDS holds is chosen automatically anyway)                        */
                           /* 2: no resident kernel: compressors that take a small problem's step in one launch use   */
-                          /*    the launches they use for large ones.  3: that kernel, but its workgroups do not     */
-                          /*    wait for each other at all, so that the last one does the step alone (tests)         */
+                          /*    the launches they use for large ones.  That is also what such a handle does by itself */
+                          /*    while the streams that others like it step on fill the GPU; ask for it where the      */
+                          /*    library cannot see that (several processes, graphs replayed on more than two streams,  */
+                          /*    streams that may not use every compute unit): a step whose workgroups cannot all run   */
+                          /*    waits for 10 ms and then takes some 10 ms more.  3: that kernel, but its workgroups do */
+                          /*    not wait for each other at all, so that the last one does the step alone (tests)       */
     int32_t tile_plan;    /* -1: automatic; i >= 0 pins the i-th candidate launch shape of the fused kernel      */
                           /*    (an index past the last candidate leaves the choice automatic)                   */
     int64_t pitch_skew;   /* -1: automatic; else floats added to the padded row length of x and delta:          */

@@ -3,6 +3,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 
 #include "dsq_internal.h"
@@ -29,6 +30,10 @@ struct ds_handle {
     std::vector<dsq::TilePlan> tile_candidates;
     dsq::TopkState* topk = nullptr;
     dsq::L2State* l2q = nullptr;
+    bool resident = false;               // steps may take one launch ...
+    uint32_t share = 0;                  // ... whose workgroups wait for each other and fill this part of the GPU
+    int seat = -1;                       // row of g_seats this handle holds, and the stream it holds it for
+    hipStream_t seat_stream = nullptr;
     uint32_t* d_keep = nullptr;          // random sparsifier, one allocation: n x nsweeps offsets inside groups,
                                          // n x ngroups group offsets, n previous counts, one overflow flag,
                                          // 2 x n x nsweeps raw counts (steps of even / odd t)
@@ -54,8 +59,65 @@ ds_status hip_fail(ds_handle* h, hipError_t e, const char* what) {
         if (e_ != hipSuccess) return hip_fail((h), e_, #call);        \
     } while (0)
 
+// ---- who may step in one launch --------------------------------------------------------------------
+// The workgroups of a resident kernel (dsq_resident.h) wait for each other, so all of them have to be running at some
+// time.  Launches on one stream follow each other; those on several share the GPU, and where they are more than it holds each
+// can keep the last workgroups of the others out, until the patience of one ends and one workgroup does that step alone:
+// three handles of 8 workers x 272,474 parameters that started their steps together on three streams took 14.6 ms for it
+// (norm-rescaled codes; top-k 27.8, GSpar 25.6), and 0.08 ms (0.15, 0.15) in the launches of large problems.  So a stream
+// on which handles step in one launch has a seat, of the largest share any of them takes, and a handle whose stream
+// finds no room takes those launches.  A handle gives its seat up when it steps on another
+// stream and when it is destroyed.  Not seen from here: other processes, graphs replayed on streams of their own, and
+// streams that may not use every compute unit; there the meeting's patience decides.
+constexpr int kSeats = 64;
+struct Seat {
+    int device, handles;                 // handles == 0: free
+    hipStream_t stream;
+    uint32_t share;
+};
+Seat g_seats[kSeats];
+std::mutex g_seats_lock;
+
+void leave_seat_locked(ds_handle* h) {
+    if (h->seat >= 0) g_seats[h->seat].handles -= 1;         // the share stays until the last one leaves
+    h->seat = -1;
+}
+
+void take_seat(ds_handle* h, hipStream_t stream) {
+    std::lock_guard<std::mutex> hold(g_seats_lock);
+    leave_seat_locked(h);
+    int at = -1, spare = -1;
+    uint32_t others = 0;
+    for (int q = 0; q < kSeats; ++q) {
+        const Seat& s = g_seats[q];
+        if (s.handles == 0) spare = q;
+        else if (s.device != h->device) continue;
+        else if (s.stream == stream) at = q;
+        else others += s.share;
+    }
+    const uint32_t share = at >= 0 && g_seats[at].share > h->share ? g_seats[at].share : h->share;
+    if (others + share > dsq::kWholeDevice || (at < 0 && spare < 0)) return;
+    if (at < 0) g_seats[at = spare] = Seat{h->device, 0, stream, 0};
+    g_seats[at].handles += 1;
+    g_seats[at].share = share;
+    h->seat = at;
+    h->seat_stream = stream;
+}
+
+// May this step of the handle be one launch?
+bool seated(ds_handle* h, hipStream_t stream) {
+    if (!h->resident) return false;
+    if (h->share == 0) return true;                          // its workgroups never wait
+    if (h->seat < 0 || h->seat_stream != stream) take_seat(h, stream);
+    return h->seat >= 0;
+}
+
 void release(ds_handle* h) {
     if (!h) return;
+    if (h->seat >= 0) {
+        std::lock_guard<std::mutex> hold(g_seats_lock);
+        leave_seat_locked(h);
+    }
     if (h->topk) dsq::topk_destroy(h->topk);
     if (h->l2q) dsq::l2q_destroy(h->l2q);
     if (h->x) (void)hipFree(h->x);
@@ -478,14 +540,15 @@ ds_status ds_init_ex(const ds_config* cfg, const ds_plan_request* plan, char* er
 
     const bool sparse_pairs = cfg->comp.kind == DS_COMP_TOPK || cfg->comp.kind == DS_COMP_GSPAR;   // (column, value) messages
     const bool tiled = !sparse_pairs && cfg->comp.kind != DS_COMP_QUANT_L2NORM;
-    bool resident = false;                                 // a whole step in one launch (small problems)
+    // small problems of these compressors: a whole step in one launch
+    if (sparse_pairs || cfg->comp.kind == DS_COMP_QUANT_L2NORM) h->share = want.variant == 2 ? 0 : sparse_pairs ? dsq::topk_resident_share(*cfg) : dsq::l2q_resident_share(*cfg);
+    h->resident = h->share != 0;
+    if (want.variant == 3) h->share = 0;                   // the first meeting is called off at once: nothing waits
     if (sparse_pairs) {
-        resident = want.variant != 2 && dsq::topk_fits_resident(*cfg);
-        h->plan_name = cfg->comp.kind == DS_COMP_GSPAR ? (resident ? "gspar/resident" : "gspar/sift-scan-write") : resident ? "topk/resident" : "topk/radix-select";
+        h->plan_name = cfg->comp.kind == DS_COMP_GSPAR ? (h->resident ? "gspar/resident" : "gspar/sift-scan-write") : h->resident ? "topk/resident" : "topk/radix-select";
     } else if (cfg->comp.kind == DS_COMP_QUANT_L2NORM) {
-        resident = want.variant != 2 && dsq::l2q_fits_resident(*cfg);
-        h->plan_name = resident ? "l2norm/resident" : "l2norm/speculative-codes";
-        if (!resident) h->msg_half = (uint64_t)cfg->n * h->msg_row_bytes;     // the first pass writes codes while the old ones are still read
+        h->plan_name = h->resident ? "l2norm/resident" : "l2norm/speculative-codes";
+        if (!h->resident) h->msg_half = (uint64_t)cfg->n * h->msg_row_bytes;     // the first pass writes codes while the old ones are still read
     } else {
         // The row-streaming variant of the block compressors on request; it is also what serves a number of workers whose
         // codes do not fit in LDS, and the faster one where the fused kernel's waves would own more rows than they can
@@ -565,11 +628,11 @@ ds_status ds_init_ex(const ds_config* cfg, const ds_plan_request* plan, char* er
     h->plan_name += "/pitch+" + std::to_string(skew);
 
     if (sparse_pairs) {
-        const ds_status st = dsq::topk_create(h->cfg, h->ld, resident, want.variant == 3, &h->topk, err);
+        const ds_status st = dsq::topk_create(h->cfg, h->ld, h->resident, want.variant == 3, &h->topk, err);
         if (st != DS_OK) return bail(st, err);
     }
     if (cfg->comp.kind == DS_COMP_QUANT_L2NORM) {
-        const ds_status st = dsq::l2q_create(h->cfg, h->ld, resident, want.variant == 3, &h->l2q, err);
+        const ds_status st = dsq::l2q_create(h->cfg, h->ld, h->resident, want.variant == 3, &h->l2q, err);
         if (st != DS_OK) return bail(st, err);
     }
     h->err = warn;
@@ -589,10 +652,10 @@ ds_status ds_step(ds_handle* h, const float* g_dev, uint64_t g_ld, void* hip_str
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
 
     if (h->topk) {
-        const ds_status st = dsq::topk_step(h->topk, topk_args(h, g_dev, g_ld), stream);
+        const ds_status st = dsq::topk_step(h->topk, topk_args(h, g_dev, g_ld), seated(h, stream), stream);
         if (st != DS_OK) return fail(h, st, "launching the sparsifying step failed");
     } else if (h->cfg.comp.kind == DS_COMP_QUANT_L2NORM) {
-        const ds_status st = dsq::l2q_step(h->l2q, l2_args(h, g_dev, g_ld), stream);
+        const ds_status st = dsq::l2q_step(h->l2q, l2_args(h, g_dev, g_ld), seated(h, stream), stream);
         if (st != DS_OK) return fail(h, st, "launching the norm-rescaled step failed");
     } else {
         const dsq::TileArgs a = tile_args(h, g_dev, g_ld);

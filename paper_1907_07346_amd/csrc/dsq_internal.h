@@ -19,6 +19,7 @@ constexpr uint64_t kPitchSkew = 2560;     // ... plus 10 KB, so that rows do not
                                           // of a column tile in flight at once, HBM channel hashing made a 16 MiB pitch
                                           // 12 % slower than this one on MI355X (measured, 64 rows x 4 Mi columns)
 constexpr int kMinBlock = 64, kMaxBlock = 2048;
+constexpr uint32_t kWholeDevice = 1u << 16;   // see topk_resident_share
 constexpr size_t kStepCells = 32 * 65;    // 64-bit cells behind the step counter (see TileArgs::t_ptr)
 
 // Host-side description of W - I in CSR form (diagonal always present, columns ascending).
@@ -128,13 +129,15 @@ struct TopkArgs {
 };
 
 struct TopkState;              // device scratch of the radix select (histograms, per-chunk counts)
-// True if the problem is small enough for the kernel that takes a whole step in one launch (dsq_topk_resident.hip).
-bool topk_fits_resident(const ds_config& cfg);
-// resident: steps take that kernel; impatient: its first meeting calls itself off at once (tests of what follows then).
+// The part of the current device, in units of 1 / kWholeDevice, that the kernel which takes a whole step in one launch
+// (dsq_topk_resident.hip) fills; 0 if the problem is not small enough for it.
+uint32_t topk_resident_share(const ds_config& cfg);
+// resident: steps may take that kernel; impatient: its first meeting calls itself off at once (tests of what follows then).
 ds_status topk_create(const ds_config& cfg, uint64_t ld, bool resident, bool impatient, TopkState** out, std::string& err);
 void topk_destroy(TopkState* s);
-ds_status topk_step(TopkState* s, const TopkArgs& a, hipStream_t stream);
-// Unless the handle is resident, topk_step leaves the sparse part of the gossip update of x to the next step's first pass;
+// one_launch: with that kernel (the state has to be made for it), else with the launches that large problems take.
+ds_status topk_step(TopkState* s, const TopkArgs& a, bool one_launch, hipStream_t stream);
+// Unless the state is made for one launch, topk_step leaves the sparse part of the gossip update of x to the next step's first pass;
 // topk_flush applies it now (no-op if nothing is pending).  Call before x is read or replaced, with the
 // buffers, mixing matrix and eta the last step ran with (a.g is not used).
 ds_status topk_flush(TopkState* s, const TopkArgs& a, hipStream_t stream);
@@ -154,7 +157,7 @@ struct L2Args {
     const float* coef;
     uint64_t ld, g_ld, N, msg_row_bytes;
     uint64_t msg_half;         // msg holds two buffers of this many bytes; a step writes the one the last step did not
-                               // (resident kernel: 0, one buffer)
+                               // (0, one buffer, where nothing is left to the next step: states made for one launch)
     int n;
     float gamma, eta;
     unsigned long long* t_ptr;  // step cells in device memory: [0] the step counter (advanced once per step), [4] the
@@ -163,13 +166,12 @@ struct L2Args {
 };
 
 struct L2State;                // device scratch: per-row scales, per-chunk partial reductions
-// True if the problem is small enough for the kernel that takes a whole step in one launch (dsq_resident.h).
-bool l2q_fits_resident(const ds_config& cfg);
-// resident: steps take that kernel; impatient: its first meeting calls itself off at once (tests of what follows then).
+// As for the top-k path.
+uint32_t l2q_resident_share(const ds_config& cfg);
 ds_status l2q_create(const ds_config& cfg, uint64_t ld, bool resident, bool impatient, L2State** out, std::string& err);
 void l2q_destroy(L2State* s);
-ds_status l2q_step(L2State* s, const L2Args& a, hipStream_t stream);
-// Unless the handle is resident, l2q_step leaves delta = v - C[v] and the gossip update of x to the next step's first pass;
+ds_status l2q_step(L2State* s, const L2Args& a, bool one_launch, hipStream_t stream);
+// Unless the state is made for one launch, l2q_step leaves delta = v - C[v] and the gossip update of x to the next step's first pass;
 // l2q_flush applies them now (no-op if nothing is pending).  Call before the state is read or replaced, with
 // the buffers, mixing matrix and eta the last step ran with (a.g is not used).
 ds_status l2q_flush(L2State* s, const L2Args& a, hipStream_t stream);

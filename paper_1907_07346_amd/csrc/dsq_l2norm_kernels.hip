@@ -81,7 +81,7 @@ struct L2Scratch {
     uint2* uslot;                 // n x nchunks x LQ_UCAP: (column offset in the chunk | placeholder code << 16, bits of v)
     uint32_t* row_flags;          // n: bit 0 = a slot of the row overflowed in this step's form pass
     uint32_t nchunks;
-    // resident kernel only (which needs none of pending, ucount, uslot, row_flags):
+    // resident kernel only:
     uint32_t* meetings;           // two meetings of all workgroups (dsq_resident.h) ...
     unsigned long long* epoch;    // ... and the number of launches so far
     uint64_t* codes;              // n x nchunks x 256 x words: the sixteen codes of each thread's columns, for the neighbours
@@ -753,8 +753,8 @@ __global__ void __launch_bounds__(LQ_THREADS, 5) l2q_resident(L2Args a, L2Scratc
 struct L2State {
     L2Scratch s{};
     int n = 0, bits = 0;
-    bool stepped = false;          // a step has been enqueued (or may have been, by a replayed graph)
-    bool resident = false;         // steps run in one launch each and leave nothing pending
+    bool pending = false;          // a step has been enqueued (or may have been, by a replayed graph) that left its tail
+    bool resident = false;         // steps may run in one launch each; none leaves its tail then
     uint64_t patience = 0;         // of the resident kernel's first meeting
 };
 
@@ -767,12 +767,11 @@ void l2q_destroy(L2State* st) {
     delete st;
 }
 
-bool l2q_fits_resident(const ds_config& cfg) {
-    const uint64_t nchunks = (cfg.N + LQ_CHUNK - 1) / LQ_CHUNK;
-    if (nchunks > 4ull * LQ_THREADS) return false;            // row_scale() takes four chunks per thread
-    const uint32_t limit = cfg.comp.bits == 2 ? resident_limit(l2q_resident<2>, LQ_THREADS)
-                         : cfg.comp.bits == 4 ? resident_limit(l2q_resident<4>, LQ_THREADS) : resident_limit(l2q_resident<8>, LQ_THREADS);
-    return (uint64_t)cfg.n * nchunks <= limit;
+uint32_t l2q_resident_share(const ds_config& cfg) {
+    const uint64_t nchunks = (cfg.N + LQ_CHUNK - 1) / LQ_CHUNK, blocks = (uint64_t)cfg.n * nchunks;
+    if (nchunks > 4ull * LQ_THREADS) return 0;                // row_scale() takes four chunks per thread
+    return cfg.comp.bits == 2 ? resident_share(l2q_resident<2>, LQ_THREADS, blocks)
+         : cfg.comp.bits == 4 ? resident_share(l2q_resident<4>, LQ_THREADS, blocks) : resident_share(l2q_resident<8>, LQ_THREADS, blocks);
 }
 
 ds_status l2q_create(const ds_config& cfg, uint64_t ld, bool resident, bool impatient, L2State** out, std::string& err) {
@@ -798,16 +797,15 @@ ds_status l2q_create(const ds_config& cfg, uint64_t ld, bool resident, bool impa
              hipMemset(s.meetings, 0, 2 * kMeetWords * sizeof(uint32_t)) == hipSuccess &&
              hipMalloc(&s.epoch, sizeof(unsigned long long)) == hipSuccess && hipMemset(s.epoch, 0, sizeof(unsigned long long)) == hipSuccess &&
              hipMalloc(&s.codes, code_bytes) == hipSuccess && hipMalloc(&s.norms, n * sizeof(float)) == hipSuccess;
-    } else {
-        ok = ok && hipMalloc(&s.pending, sizeof(uint32_t)) == hipSuccess &&
-             hipMalloc(&s.ucount, n * nc * sizeof(uint32_t)) == hipSuccess &&
-             hipMalloc(&s.uslot, n * nc * LQ_UCAP * sizeof(uint2)) == hipSuccess &&
-             hipMalloc(&s.row_flags, n * sizeof(uint32_t)) == hipSuccess &&
-             hipMemset(s.ucount, 0, n * nc * sizeof(uint32_t)) == hipSuccess &&
-             hipMemset(s.row_flags, 0, n * sizeof(uint32_t)) == hipSuccess &&
-             hipMemset(s.pending, 0, sizeof(uint32_t)) == hipSuccess;
     }
-    ok = ok && hipDeviceSynchronize() == hipSuccess;
+    ok = ok && hipMalloc(&s.pending, sizeof(uint32_t)) == hipSuccess &&
+         hipMalloc(&s.ucount, n * nc * sizeof(uint32_t)) == hipSuccess &&
+         hipMalloc(&s.uslot, n * nc * LQ_UCAP * sizeof(uint2)) == hipSuccess &&
+         hipMalloc(&s.row_flags, n * sizeof(uint32_t)) == hipSuccess &&
+         hipMemset(s.ucount, 0, n * nc * sizeof(uint32_t)) == hipSuccess &&
+         hipMemset(s.row_flags, 0, n * sizeof(uint32_t)) == hipSuccess &&
+         hipMemset(s.pending, 0, sizeof(uint32_t)) == hipSuccess &&
+         hipDeviceSynchronize() == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         err = "scratch allocation for the norm-rescaled compressor failed";
@@ -818,9 +816,21 @@ ds_status l2q_create(const ds_config& cfg, uint64_t ld, bool resident, bool impa
     return DS_OK;
 }
 
-ds_status l2q_step(L2State* st, const L2Args& a, hipStream_t stream) {
+static ds_status apply_tail(L2State* st, const L2Args& a, hipStream_t stream) {
     const L2Scratch& s = st->s;
-    if (st->resident) {
+    const dim3 grid(s.nchunks, a.n), block(LQ_THREADS);
+    // the kernels look at the device's pending flag themselves: a replayed graph of ds_step sets it
+    // without this code noticing
+    if (st->bits == 2)      hipLaunchKernelGGL(l2q_tail<2>, grid, block, 0, stream, a, s);
+    else if (st->bits == 4) hipLaunchKernelGGL(l2q_tail<4>, grid, block, 0, stream, a, s);
+    else                    hipLaunchKernelGGL(l2q_tail<8>, grid, block, 0, stream, a, s);
+    hipLaunchKernelGGL(l2q_clear_pending, dim3(1), dim3(1), 0, stream, s);
+    return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
+}
+
+ds_status l2q_step(L2State* st, const L2Args& a, bool one_launch, hipStream_t stream) {
+    const L2Scratch& s = st->s;
+    if (one_launch) {
         const dim3 grid(s.nchunks * (uint32_t)a.n), block(LQ_THREADS);
         if (st->bits == 2)      hipLaunchKernelGGL(l2q_resident<2>, grid, block, 0, stream, a, s, st->patience);
         else if (st->bits == 4) hipLaunchKernelGGL(l2q_resident<4>, grid, block, 0, stream, a, s, st->patience);
@@ -840,21 +850,15 @@ ds_status l2q_step(L2State* st, const L2Args& a, hipStream_t stream) {
     else if (st->bits == 4) hipLaunchKernelGGL(l2q_quantize<4>, grid, block, 0, stream, a, s);
     else                    hipLaunchKernelGGL(l2q_quantize<8>, grid, block, 0, stream, a, s);
     hipLaunchKernelGGL(l2q_row_unit, rows, rblock, 0, stream, a, s, hl);
-    st->stepped = true;
+    // A state made for one launch gets the tail at once: the next step may be the resident kernel, in a graph that was
+    // captured long ago even, and that expects x and delta complete.
+    if (st->resident) return apply_tail(st, a, stream);
+    st->pending = true;
     return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
 }
 
 ds_status l2q_flush(L2State* st, const L2Args& a, hipStream_t stream) {
-    if (!st || !st->stepped) return DS_OK;                    // (never set by the resident kernel)
-    const L2Scratch& s = st->s;
-    const dim3 grid(s.nchunks, a.n), block(LQ_THREADS);
-    // the kernels look at the device's pending flag themselves: a replayed graph of ds_step sets it
-    // without this code noticing
-    if (st->bits == 2)      hipLaunchKernelGGL(l2q_tail<2>, grid, block, 0, stream, a, s);
-    else if (st->bits == 4) hipLaunchKernelGGL(l2q_tail<4>, grid, block, 0, stream, a, s);
-    else                    hipLaunchKernelGGL(l2q_tail<8>, grid, block, 0, stream, a, s);
-    hipLaunchKernelGGL(l2q_clear_pending, dim3(1), dim3(1), 0, stream, s);
-    return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
+    return st && st->pending ? apply_tail(st, a, stream) : DS_OK;
 }
 
 ds_status l2q_speculated_rows(L2State* st, hipStream_t stream, uint32_t* count) {

@@ -7,8 +7,8 @@
 //
 // Waiting inside a kernel needs every workgroup of the launch to be running.  Three things see to it that every wait
 // ends, whatever else the GPU is doing:
-//   * a resident plan is only made if its workgroups fill at most half of what the GPU holds at once (two such kernels
-//     on two streams fit next to each other);
+//   * a resident plan is only made if its workgroups fill at most half of what the GPU holds at once, and ds_step only
+//     takes it while the streams that such handles step on fit next to each other (Seat in dsq_api.hip);
 //   * the first meeting (meet_or_part) has a time limit, and its outcome is decided on ONE word: either all arrive
 //     (from then on every workgroup runs, and later meetings end), or one workgroup's limit passes first and
 //     all part.  Nothing but scratch memory has been written by then;
@@ -27,6 +27,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "dsq_internal.h"
+
 namespace dsq {
 namespace {
 
@@ -35,7 +37,9 @@ constexpr uint32_t kMeetLine = 64;                          // words between the
 constexpr uint32_t kMeetWords = (1 + 2 * kMeetGroups) * kMeetLine;   // root | arrival counters | flags
 constexpr uint32_t kPartBit = 0x80000000u;                  // in a flag: called off
 constexpr unsigned long long kPartRoot = 1ull << 63;        // in a root
-constexpr uint64_t kMeetPatience = 1'000'000;               // ticks of the 100 MHz clock: 10 ms
+// Ticks of the 100 MHz clock: 10 ms.  About what the step costs one workgroup alone (8 workers x 272,474 parameters: norm-rescaled
+// 4.5 ms, GSpar 10 to 15, top-k 17), so that a wait that would have ended soon is not given up for something dearer.
+constexpr uint64_t kMeetPatience = 1'000'000;
 
 template <typename V> __device__ __forceinline__ V agent_load(const V* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 template <typename V> __device__ __forceinline__ void agent_store(V* p, V v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -272,16 +276,41 @@ struct ResidentChunk {
     }
 };
 
-// How many workgroups a resident kernel may have: half of what the current device holds at once.
+// The smallest number of pieces of `size` that a memory of `whole` can hold with no room left for one more, whatever lies
+// or lay between them: gaps of up to size - step on either side of each.
+inline uint64_t sure_pieces(uint64_t whole, uint64_t size, uint64_t step) {
+    const uint64_t gap = size - step;
+    return whole <= gap ? 0 : (whole - gap + size + gap - 1) / (size + gap);
+}
+
+// The part of the current device that `blocks` workgroups of a resident kernel fill, in units of 1 / kWholeDevice and rounded
+// up; 0 if a resident plan is not made: more than half of what an empty device holds at once.  The whole is what the device
+// holds for sure, next to anything that ends by itself: registers and LDS are given out in one piece each, and where other
+// kernels' waves have come and gone between them five waves of 96 registers need not fit into the 512 of a SIMD, three
+// do.  (Two kernels of 536 workgroups started together with a third kernel whose waves take 80 registers did not fit on the
+// 256 compute units in 24 of 30 attempts; on an otherwise idle device they do.)
 template <typename K>
-uint32_t resident_limit(K kernel, int threads) {
-    int per_cu = 0, cus = 0, dev = 0;
+uint32_t resident_share(K kernel, int threads, uint64_t blocks) {
+    int per_cu = 0, cus = 0, lds = 0, dev = 0;
+    hipFuncAttributes attr{};
     if (hipGetDevice(&dev) != hipSuccess || hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || per_cu < 1 || cus < 1) {
+        hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(kernel)) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess || per_cu < 1 || cus < 1) {
         (void)hipGetLastError();
         return 0;
     }
-    return (uint32_t)(per_cu * cus / 2);
+    constexpr uint64_t kRegisters = 512, kRegisterStep = 8;   // of a SIMD, per lane; a workgroup has a wave on each of four
+    const uint64_t regs = ((uint64_t)(attr.numRegs > 0 ? attr.numRegs : 1) + kRegisterStep - 1) / kRegisterStep * kRegisterStep;
+    uint64_t sure = sure_pieces(kRegisters, regs, kRegisterStep);
+    if (attr.sharedSizeBytes > 0) {
+        const uint64_t pieces = sure_pieces((uint64_t)lds, (uint64_t)attr.sharedSizeBytes, 1);
+        sure = pieces < sure ? pieces : sure;
+    }
+    if (sure > (uint64_t)per_cu) sure = (uint64_t)per_cu;
+    const uint64_t whole = sure * (uint64_t)cus;
+    if (2 * blocks > (uint64_t)per_cu * (uint64_t)cus || blocks > whole) return 0;
+    return (uint32_t)((blocks * kWholeDevice + whole - 1) / whole);
 }
 
 }  // namespace

@@ -36,7 +36,7 @@ struct TopkRow {
 
 // The one-launch form of a step, on the rows of the state that owns it.
 struct SparseResidentState;
-bool sparse_fits_resident(const ds_config& cfg);
+uint32_t sparse_resident_share(const ds_config& cfg);
 // impatient: the kernel's first meeting calls itself off at once (tests of what follows then).
 ds_status sparse_resident_create(const ds_config& cfg, bool impatient, TopkRow* rows, uint32_t* overflow, SparseResidentState** out);
 void sparse_resident_destroy(SparseResidentState* st);

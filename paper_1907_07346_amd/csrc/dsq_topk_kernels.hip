@@ -1302,7 +1302,7 @@ struct TopkState {
     bool gspar = false;            // the GSpar operator runs on this state (its own select-free chain of kernels)
     bool pending = false;          // a step has been enqueued since the last flush (or may have been, by a
                                    // replayed graph): its sparse tail may not have been applied yet
-    SparseResidentState* resident = nullptr;   // a small problem's step is one launch and leaves nothing pending
+    SparseResidentState* resident = nullptr;   // a small problem's step may be one launch; no step leaves anything pending then
 };
 
 void topk_destroy(TopkState* st) {
@@ -1315,7 +1315,7 @@ void topk_destroy(TopkState* st) {
     delete st;
 }
 
-bool topk_fits_resident(const ds_config& cfg) { return sparse_fits_resident(cfg); }
+uint32_t topk_resident_share(const ds_config& cfg) { return sparse_resident_share(cfg); }
 
 ds_status topk_create(const ds_config& cfg, uint64_t ld, bool resident, bool impatient, TopkState** out, std::string& err) {
     TopkState* st = new TopkState();
@@ -1329,7 +1329,7 @@ ds_status topk_create(const ds_config& cfg, uint64_t ld, bool resident, bool imp
     bool ok = hipMalloc(&s.rows, n * sizeof(TopkRow)) == hipSuccess && hipMalloc(&s.gs_overflow, sizeof(uint32_t)) == hipSuccess &&
               hipMemset(s.gs_overflow, 0, sizeof(uint32_t)) == hipSuccess;
     if (resident) ok = ok && sparse_resident_create(cfg, impatient, s.rows, s.gs_overflow, &st->resident) == DS_OK;
-    else ok = ok && hipMalloc(&s.hist, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
+    ok = ok && hipMalloc(&s.hist, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc(&s.hist_part, n * TK_HPARTS * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc(&s.hist2, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
               hipMalloc(&s.hist3, n * BINS3 * sizeof(uint32_t)) == hipSuccess &&
@@ -1371,16 +1371,27 @@ ds_status topk_candidate_rows(TopkState* st, hipStream_t stream, uint32_t* count
     return DS_OK;
 }
 
-ds_status topk_flush(TopkState* st, const TopkArgs& a, hipStream_t stream) {
-    if (!st || !st->pending) return DS_OK;
+static ds_status apply_tail(TopkState* st, const TopkArgs& a, hipStream_t stream) {
     const dim3 grid(st->s.nchunks, a.n), block(TK_THREADS);
     hipLaunchKernelGGL(topk_gossip, grid, block, 0, stream, a, st->s);
     // the tail is applied: no message offsets, nothing for the next first pass to apply again (a kernel, not a
     // memset: the caller may be capturing the stream)
     const size_t words = (size_t)st->n * (st->s.nchunks + 1);
     hipLaunchKernelGGL(topk_zero_words, dim3((unsigned)((words + 1023) / 1024)), dim3(256), 0, stream, st->s.out_off, words);
+    return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
+}
+
+ds_status topk_flush(TopkState* st, const TopkArgs& a, hipStream_t stream) {
     // `pending` stays set: a captured graph of ds_step may be replayed without this code noticing, and a flush
     // with nothing to apply is a grid of workgroups that return at once
+    return st && st->pending ? apply_tail(st, a, stream) : DS_OK;
+}
+
+// The chain of launches has been enqueued.  A state made for one launch gets the tail at once: the next step may be a
+// resident kernel, in a graph that was captured long ago even, and that expects x and delta complete.
+static ds_status chain_enqueued(TopkState* st, const TopkArgs& a, hipStream_t stream) {
+    if (st->resident) return apply_tail(st, a, stream);
+    st->pending = true;
     return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
 }
 
@@ -1392,8 +1403,8 @@ ds_status gspar_overflowed(TopkState* st, hipStream_t stream, bool* overflowed) 
     return DS_OK;
 }
 
-ds_status topk_step(TopkState* st, const TopkArgs& a, hipStream_t stream) {
-    if (st->resident) return sparse_resident_step(st->resident, a, stream);
+ds_status topk_step(TopkState* st, const TopkArgs& a, bool one_launch, hipStream_t stream) {
+    if (one_launch) return sparse_resident_step(st->resident, a, stream);
     const Scratch& s = st->s;
     const dim3 grid(s.nchunks, a.n), block(TK_THREADS), rblock(TK_RTHREADS);
     if (st->gspar) {
@@ -1409,8 +1420,7 @@ ds_status topk_step(TopkState* st, const TopkArgs& a, hipStream_t stream) {
         hipLaunchKernelGGL(gs_write, wgrid, wblock, 0, stream, a, s);
         hipLaunchKernelGGL(gs_write_dense, dgrid, block, 0, stream, a, s);
         hipLaunchKernelGGL(gs_close, dim3(1), dim3(1), 0, stream, a.t_ptr);
-        st->pending = true;
-        return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
+        return chain_enqueued(st, a, stream);
     }
     const dim3 wgrid((s.nchunks + TK_WPW - 1) / TK_WPW, a.n);
     // full mode walks a row's chunks with a fixed number of workgroups, so that a step in which no row needs it
@@ -1432,8 +1442,7 @@ ds_status topk_step(TopkState* st, const TopkArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL(topk_finish, rows, rblock, 0, stream, s, k, a.t_ptr);
     hipLaunchKernelGGL(topk_write_cand, wgrid, dim3(64), 0, stream, a, s);
     hipLaunchKernelGGL(topk_write_full, fgrid, block, 0, stream, a, s);
-    st->pending = true;
-    return DS_OK;
+    return chain_enqueued(st, a, stream);
 }
 
 }  // namespace dsq

@@ -907,10 +907,10 @@ void sparse_resident_destroy(SparseResidentState* st) {
     delete st;
 }
 
-bool sparse_fits_resident(const ds_config& cfg) {
-    const uint64_t nchunks = (cfg.N + kResChunk - 1) / kResChunk;
-    if (nchunks > RS_MAX_CHUNKS) return false;
-    return (uint64_t)cfg.n * nchunks <= (cfg.comp.kind == DS_COMP_GSPAR ? resident_limit(gspar_resident, kResThreads) : resident_limit(topk_resident, kResThreads));
+uint32_t sparse_resident_share(const ds_config& cfg) {
+    const uint64_t nchunks = (cfg.N + kResChunk - 1) / kResChunk, blocks = (uint64_t)cfg.n * nchunks;
+    if (nchunks > RS_MAX_CHUNKS) return 0;
+    return cfg.comp.kind == DS_COMP_GSPAR ? resident_share(gspar_resident, kResThreads, blocks) : resident_share(topk_resident, kResThreads, blocks);
 }
 
 ds_status sparse_resident_create(const ds_config& cfg, bool impatient, TopkRow* rows, uint32_t* overflow, SparseResidentState** out) {

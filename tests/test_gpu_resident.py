@@ -112,7 +112,7 @@ def test_resident_topk_many_equal_magnitudes(k, variant):
 
 @pytest.mark.parametrize("other", [small(wl.KIND_QUANT_L2NORM, 8, 4096 * 40 + 1001, bits=4, seed=9), TOPK[4], GSPAR[4]], ids=lambda w: w.name)
 def test_two_resident_handles_on_two_streams(other):
-    """Two handles step side by side on streams of their own: their workgroups fit next to each other."""
+    """Two handles step side by side on streams of their own; the second takes one launch or the chain, as there is room."""
     import torch
     ws = [CASES[4], other]
     dss = [b.DeepSqueeze.from_workload(w) for w in ws]
@@ -130,6 +130,87 @@ def test_two_resident_handles_on_two_streams(other):
         x, d = ds.ds_read_state()
         ds.ds_destroy()
         assert assert_close(f"{w.name} x", x, st.x) + assert_close(f"{w.name} delta", d, st.delta) == 0
+
+
+def _crowd(kind, variants, **kw):
+    """Handles of 536 workgroups each, a stream for each."""
+    import torch
+    ws = [small(kind, 8, 272_474, seed=5 + q, **kw) for q in range(len(variants))]
+    return ws, [b.DeepSqueeze.from_workload(w, _plan(v)) for w, v in zip(ws, variants)], [torch.cuda.Stream() for _ in ws]
+
+
+KINDS = [(wl.KIND_QUANT_L2NORM, {"bits": 4}), (wl.KIND_TOPK, {"k": 2724}), (wl.KIND_GSPAR, {"k": 27_247})]
+
+
+@pytest.mark.parametrize("kind,kw", KINDS)
+@pytest.mark.parametrize("variants", [(0, 0, 0), (0, 0, 2), (0, 0, 0, 0)], ids=str)
+def test_steps_that_start_together_on_several_streams(kind, kw, variants):
+    """Three or four steps that the GPU has not got the room (or, next to another kernel's registers, not in the right pieces) to
+    run in one launch each, set off together.  None may wait for its meeting in vain: that takes 10 ms, and a step of all of them
+    some 0.1 ms."""
+    import time
+
+    import torch
+    ws, dss, streams = _crowd(kind, variants, **kw)
+    gs = [torch.randn((w.n, (w.N + 3) // 4 * 4), device="cuda") * 0.5 for w in ws]
+    a = torch.randn((4096, 4096), device="cuda")
+    out = torch.empty_like(a)
+    torch.cuda.synchronize()
+    took = []
+    for _ in range(25):
+        torch.mm(a, a, out=out)                                # the steps are enqueued while this keeps the GPU busy
+        torch.mm(a, a, out=out)
+        go = torch.cuda.Event()
+        go.record()
+        for ds, g, s in zip(dss, gs, streams):
+            s.wait_event(go)
+            ds.ds_step(g, s)
+        go.synchronize()
+        began = time.perf_counter()
+        torch.cuda.synchronize()
+        took.append(time.perf_counter() - began)
+    for ds in dss:
+        assert ds.ds_step_count() == 25
+        ds.ds_destroy()
+    took = sorted(took[3:])
+    say("ms:", [round(1e3 * t, 3) for t in took])
+    assert took[-3] < 5e-3, took                               # two of 22 may have been held up by something else
+
+
+@pytest.mark.parametrize("kind,kw", KINDS)
+def test_one_launch_and_chain_take_turns(kind, kw):
+    """A handle whose stream finds no room next to two others takes the launches of large problems, and one launch again on a stream
+    that has room: both work on the same state.  Messages after every step, x and delta after every other one."""
+    import torch
+    _, others, streams = _crowd(kind, (0, 0), **kw)
+    w = small(kind, 8, 272_474, seed=3, **kw)
+    st = oracle_state(w)
+    ds = b.DeepSqueeze.from_workload(w)
+    third = torch.cuda.Stream()
+    g0 = upload(wl.gradient(w, 0))
+    for ds_, s in zip(others, streams):
+        ds_.ds_step(g0, s)                                   # takes its seat
+    for t, s in enumerate([third, streams[0], streams[0], third, third, streams[1], third, streams[0]]):
+        g = wl.gradient(w, t)
+        gd = upload(g)
+        torch.cuda.synchronize()
+        ds.ds_step(gd, s)
+        _, msg = oracle.step(st, g, want_cv=False)
+        torch.cuda.synchronize()
+        assert np.array_equal(ds.ds_read_messages(), msg), f"step {t}: messages differ"
+        if t % 2:
+            x, d = ds.ds_read_state()
+            assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0, f"step {t}"
+    for ds_ in others:
+        ds_.ds_destroy()
+    g = wl.gradient(w, 8)
+    ds.ds_step(upload(g), third)                             # there is room now
+    _, msg = oracle.step(st, g, want_cv=False)
+    assert np.array_equal(ds.ds_read_messages(), msg)
+    x, d = ds.ds_read_state()
+    assert ds.ds_step_count() == 9
+    ds.ds_destroy()
+    assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
 
 
 @pytest.mark.parametrize("k", [1, 64, 65, 128, 129, 300])
