@@ -259,6 +259,29 @@ uint64_t autotune(ds_handle* h, uint64_t base_ld, size_t state_bytes, size_t msg
     return ok ? best_skew : dsq::kPitchSkew;
 }
 
+// Is the row-streaming variant the faster one where the fused kernel would serve too?  It can be where the fused kernel's
+// waves own more rows than they hold in registers (every shape ends at 64 rows), and a tile of 512 columns or more makes those
+// rows a serial chain of 2 KB loads, formed twice.  Measured with the state complete after every step over 65 .. 800 workers,
+// blocks of 512 .. 2048, all codes and circulant graphs (3100 points), as streaming's time in units of the fused kernel's:
+//   up to 128 tiles, half of the compute units have no tile: 0.1 to 0.99 for any graph, but 1.07 at the line itself where there are
+//     fewer than 96 workers with nine neighbours each (112 tiles: 0.96);
+//   beyond 512 tiles from 192 workers on the fused kernel's time is that of whole waves of 256 tiles and streaming's that of
+//     the tiles, which decode the neighbours from memory: with up to 5 neighbours (own included) 0.75 to 1.00 while the
+//     last wave leaves a sixteenth of them all free (one point of 544 at 1.03) and up to 1.12 when it is full; with 9, 0.79
+//     to 0.99 while three sixteenths are free; with 17 up to 1.22.  256 workers x 272,474, torus, 4 bits: 412
+//     us fused, 345 streaming.
+// In between, and with blocks of up to 256 columns (100 x 100,000 at 4 bits: 52 us fused, 65 streaming), the fused kernel stays.
+// The graph is the one the handle is made with: a later ds_set_mixing changes no plan.
+bool streams_faster(const ds_config& cfg, uint64_t entries) {
+    if (cfg.comp.kind != DS_COMP_QUANT_MAXABS && cfg.comp.kind != DS_COMP_SIGN_MEANABS) return false;
+    if (cfg.n <= 64 || cfg.comp.block < 512) return false;
+    const uint64_t n = (uint64_t)cfg.n, tiles = (cfg.N + cfg.comp.block - 1) / cfg.comp.block;
+    const bool near = entries <= 5 * n;
+    if (tiles <= 128) return tiles <= 112 || n >= 96 || near;
+    if (tiles <= 512 || n < 192 || entries > 9 * n) return false;
+    return 16 * tiles <= (near ? 15u : 13u) * ((tiles + 255) / 256 * 256);
+}
+
 // Diagnostics (off the hot path); fp64 accumulation, the three sums of a workgroup added to `out`.
 __device__ __forceinline__ void add_diagnostics(double cons, double dsq_, double mixed, double (*part)[4], double* out) {
     double v[3] = {cons, dsq_, mixed};
@@ -551,22 +574,11 @@ ds_status ds_init_ex(const ds_config* cfg, const ds_plan_request* plan, char* er
         if (!h->resident) h->msg_half = (uint64_t)cfg->n * h->msg_row_bytes;     // the first pass writes codes while the old ones are still read
     } else {
         // The row-streaming variant of the block compressors on request; it is also what serves a number of workers whose
-        // codes do not fit in LDS, and the faster one where the fused kernel's waves would own more rows than they can
-        // hold in registers (every shape ends at 64 rows) and a tile of 512 columns or more makes those rows a serial
-        // chain of 2 KB loads, formed twice: 256 workers x 272,474 parameters at 4 bits and blocks of 512, state complete
-        // after every step, 416 us fused and 349 streaming (28.5 B per element either way, but no last wave of 21
-        // tiles), 250 back to back; 100 workers x 12,000, 30 and 15 us.  Measured over 66 .. 256 workers and blocks of 512 ..
-        // 2048: up to 128 tiles (half of the compute units) streaming takes 0.5 to 0.9 of the fused kernel's time, beyond
-        // 512 tiles 0.8 to 0.95 from about 200 workers on; in between it depends on how full the last wave is (0.7 to
-        // 1.3) and on how much of the second forming comes from the memory-side cache, and the fused kernel stays.  So it does
-        // with blocks of up to 256 columns (100 x 100,000 at 4 bits: 52 us against 65).
+        // codes do not fit in LDS, and what is faster for some sizes (streams_faster)
         dsq::TilePlan sp;
         const bool can_stream = dsq::stream_plan(h->cfg, sp);
         const bool fits = dsq::choose_tile_plans(h->cfg, (int)h->graph.col.size(), h->tile_candidates, err);
-        const bool block_coded = cfg->comp.kind == DS_COMP_QUANT_MAXABS || cfg->comp.kind == DS_COMP_SIGN_MEANABS;
-        const uint64_t tiles = block_coded ? (cfg->N + cfg->comp.block - 1) / cfg->comp.block : 0;
-        const bool few_tiles = tiles <= 128, many_tiles = tiles > 512 && cfg->n >= 192;
-        const bool many_rows = block_coded && cfg->n > 64 && cfg->comp.block >= 512 && (few_tiles || many_tiles) && want.tile_plan < 0;
+        const bool many_rows = want.tile_plan < 0 && streams_faster(*cfg, h->graph.col.size());
         if (can_stream && (!fits || want.variant == 1 || many_rows)) {
             h->tile_candidates.assign(1, sp);
             h->msg_half = (uint64_t)cfg->n * h->msg_row_bytes;

@@ -135,10 +135,10 @@ SMALL = [
     small(wl.KIND_QUANT_MAXABS, 5, 100, bits=2, block=256),                       # one ragged block
     small(wl.KIND_QUANT_MAXABS, 20, 1024 * 2 + 1, bits=4, block=1024),            # 2 rows per wave
     small(wl.KIND_QUANT_MAXABS, 64, 512 * 3 + 300, bits=4, block=512, topo=wl.TOPO_TORUS2D, torus=(8, 8)),
-    small(wl.KIND_QUANT_MAXABS, 70, 512 * 2 + 5, bits=2, block=512),              # looped rows (re-read x, g)
+    small(wl.KIND_QUANT_MAXABS, 70, 512 * 2 + 5, bits=2, block=512),              # more rows than registers hold: streaming
     small(wl.KIND_QUANT_MAXABS, 12, 2048 * 2 + 2000, bits=4, block=2048),         # 8-wave looped variant
     small(wl.KIND_QUANT_MAXABS, 15, 512 * 4 + 4, bits=2, block=512, topo=wl.TOPO_TORUS2D, torus=(3, 5)),
-    small(wl.KIND_QUANT_MAXABS, 300, 512 + 5, bits=4, block=512),                 # 87 KB of LDS (above the 64 KB default)
+    small(wl.KIND_QUANT_MAXABS, 300, 512 + 5, bits=4, block=512),                 # streaming (pinned below: 87 KB of LDS)
     small(wl.KIND_SIGN_MEANABS, 8, 256 * 7 + 40, block=256),
     small(wl.KIND_SIGN_MEANABS, 16, 1024 * 2 + 999, block=1024),
     small(wl.KIND_SIGN_MEANABS, 3, 2, block=256),
@@ -196,6 +196,59 @@ SMALL_GSPAR = [
 def test_lock_step_small_shapes(w):
     say("case", w.name)
     lock_step(w, steps=3)
+
+
+@pytest.mark.parametrize("w", [SMALL[6], SMALL[9], small(wl.KIND_SIGN_MEANABS, 100, 1024 * 3 + 7, block=1024),
+                               small(wl.KIND_QUANT_MAXABS, 130, 2048 + 9, bits=8, block=512, topo=wl.TOPO_TORUS2D, torus=(10, 13))],
+                         ids=lambda w: w.name)
+def test_fused_kernel_with_looped_rows(w):
+    """More rows than registers hold in the fused kernel, which re-forms them (and above 64 KB of LDS for 300 workers): at
+    these sizes it is taken only when it is asked for, at 129 to 512 tiles by itself."""
+    say("case", w.name)
+    ds = b.DeepSqueeze.from_workload(w, {"tile_plan": 0})
+    assert "looped" in ds.ds_plan_name(), ds.ds_plan_name()
+    ds.ds_destroy()
+    lock_step(w, steps=2, plan={"tile_plan": 0})
+
+
+def _circulant(n, degree):
+    """Every worker averages with the `degree` - 1 nearest (an even number) and itself."""
+    rp = np.arange(n + 1, dtype=np.int32) * degree
+    co = np.concatenate([np.sort((i + np.arange(-(degree // 2), degree // 2 + 1)) % n) for i in range(n)]).astype(np.int32)
+    return rp, co, np.full(n * degree, 1.0 / degree, np.float32)
+
+
+@pytest.mark.parametrize("n,tiles,degree,streams", [
+    (64, 10, 3, False), (65, 112, 17, True), (65, 113, 5, True), (65, 128, 9, False), (95, 128, 9, False), (96, 128, 9, True), (96, 129, 3, False),
+    (192, 512, 3, False), (191, 513, 3, False), (192, 513, 3, True), (192, 720, 5, True), (192, 721, 5, False), (192, 768, 3, False),
+    (192, 624, 9, True), (192, 625, 9, False), (192, 513, 11, False)])
+def test_which_sizes_stream(n, tiles, degree, streams):
+    cfg, keep = b.make_config(n, (tiles - 1) * 512 + 1, wl.TOPO_CSR, wl.KIND_SIGN_MEANABS, 0.1, 0.4, block=512, W_csr=_circulant(n, degree))
+    ds = b.DeepSqueeze(cfg, keep, {"autotune": 0})
+    assert ds.ds_plan_name().startswith("stream/") == streams, ds.ds_plan_name()
+    ds.ds_destroy()
+
+
+def test_streaming_of_many_tiles():
+    """The large end of the streaming rule: 192 workers, 513 tiles, the last one ragged, nine neighbours; a free run of two steps
+    with the state read at its end."""
+    w = small(wl.KIND_SIGN_MEANABS, 192, 512 * 512 + 77, block=512)
+    rp, co, va = _circulant(w.n, 9)
+    W = np.zeros((w.n, w.n))
+    W[np.repeat(np.arange(w.n), 9), co] = va
+    cfg, keep = b.make_config(w.n, w.N, wl.TOPO_CSR, w.kind, w.gamma, w.eta, block=w.block, seed=w.seed, W_csr=(rp, co, va))
+    ds = b.DeepSqueeze(cfg, keep)
+    assert ds.ds_plan_name().startswith("stream/"), ds.ds_plan_name()
+    st = oracle_state(w, W)
+    rng = np.random.default_rng(8)
+    for t in range(2):
+        g = rng.standard_normal((w.n, w.N), dtype=np.float32)
+        ds.ds_step(upload(g))
+        _, msg = oracle.step(st, g, want_cv=False)
+        assert np.array_equal(ds.ds_read_messages(), msg), f"step {t}: messages differ"
+    x, d = ds.ds_read_state()
+    ds.ds_destroy()
+    assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
 
 
 def _random_cases(count, seed):
