@@ -480,6 +480,29 @@ def test_diagnostics_at_the_edges_of_their_tiles(n, N, dense):
         assert abs(got[key] - want[key]) <= 1e-9 * abs(want[key]) + 1e-30, (key, got[key], want[key])
 
 
+@pytest.mark.parametrize("variant", [0, 2])
+@pytest.mark.parametrize("w", [small(wl.KIND_QUANT_MAXABS, 8, 512 * 5 + 37, bits=4, block=512), small(wl.KIND_QUANT_MAXABS, 70, 1030, bits=2, block=512),
+                               small(wl.KIND_SIGN_MEANABS, 5, 101, block=64), small(wl.KIND_IDENTITY, 9, 333), small(wl.KIND_RAND_SPARSE, 8, 1001, k=90),
+                               small(wl.KIND_TOPK, 8, 4096 + 3, k=80), small(wl.KIND_GSPAR, 8, 4096 + 3, k=80), small(wl.KIND_QUANT_L2NORM, 8, 4096 + 5, bits=4),
+                               replace(small(wl.KIND_QUANT_MAXABS, 8, 777, bits=4, block=256), algo=wl.ALGO_CHOCO_SGD, name="choco"),
+                               replace(small(wl.KIND_SIGN_MEANABS, 8, 777, block=256), algo=wl.ALGO_DCD_PSGD, name="dcd")], ids=lambda w: w.name)
+def test_diagnostics_after_steps_with_ragged_rows(w, variant):
+    """The diagnostics read whole tiles, so the columns behind N have to be zero after every kernel that writes the state: here
+    the gradients' columns behind N are not, and three steps go ahead of the diagnostics."""
+    ds = b.DeepSqueeze.from_workload(w, {"variant": variant})
+    st = oracle_state(w)
+    for t in range(3):
+        g = wl.gradient(w, t)
+        gd = torch.full((w.n, (w.N + 3) // 4 * 4 + 8), 1e6, device="cuda")
+        gd[:, :w.N] = torch.from_numpy(g).cuda()
+        ds.ds_step(gd)
+        oracle.step(st, g, want_cv=False, want_msg=False)
+    got, want = ds.ds_diagnostics(), oracle.diagnostics(st)
+    ds.ds_destroy()
+    for key in ("consensus_sq", "delta_sq", "delta_mixed_sq"):
+        assert abs(got[key] - want[key]) <= 1e-9 * abs(want[key]) + 1e-30, (key, got[key], want[key])
+
+
 # ------------------------------------------------------------------------------------ worked examples
 
 def test_hand_expanded_example_on_gpu(golden_dir):
