@@ -293,8 +293,9 @@ ds_status ds_diagnostics(ds_handle* h, double* out4);
  * while forming v under a guessed band for max|v| stood (the band held the real maximum and no slot of undecided
  * elements overflowed), instead of the exact second pass.  GSpar: everything that was kept was among the elements
  * collected while forming v under an upper bound of lambda taken from the step before.  Small problems, whose step is
- * one launch that keeps v in registers, report whether the band would have held.  Results are identical
- * either way.  Synchronises; 0
+ * one launch: v stays in registers, which counts for all workers of the norm-rescaled codes and of GSpar and, with top-k, for those whose
+ * threshold was found among the keys counted while v was formed; 0 where the workgroups could not all run at once and one of
+ * them did the step.  Results are identical either way.  Synchronises; 0
  * for other compressors; DS_ESTATE before the first step. */
 ds_status ds_topk_candidate_rows(ds_handle* h, uint32_t* count);
 

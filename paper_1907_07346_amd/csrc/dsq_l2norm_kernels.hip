@@ -64,7 +64,8 @@ struct L2Row {
     float s_lo, s_hi, inv_lo_s, inv_hi_s;   // inv_lo_s = (L/2)/s_lo (the larger one), inv_hi_s = (L/2)/s_hi
     float s_prev;     // s of the step before (0: none)
     float drift;      // recent relative movement of s from step to step (decaying maximum)
-    uint32_t mode;    // this step: 1 = the codes `form` wrote stand (once the undecided ones are settled), 0 = exact second pass
+    uint32_t mode;    // this step: 1 = the codes `form` wrote stand (once the undecided ones are settled), 0 = exact second pass;
+                      // resident kernel: 1 = v stayed in registers, 0 = one workgroup did the step
     uint32_t overflowed;   // this step: a chunk had more undecided elements than its slot holds
     uint32_t streak;  // consecutive speculating steps that overflowed
     uint32_t wait;    // steps to sit out before the next guess (backs off when the slots keep overflowing)
@@ -697,17 +698,9 @@ struct L2Resident : ResidentChunk<L2Args> {
         }
     }
 
-    // What ds_topk_candidate_rows reports: would the range have stayed in the band the steps before suggest?  (Here v is
-    // in registers, nothing is guessed.)
-    __device__ __forceinline__ void keep_book() {
-        if (chunk != 0 || threadIdx.x != 0) return;
-        L2Row r = s.rows[row];
-        r.s = range;
-        r.nrm = nrm;
-        r.overflowed = 0u;
-        r.mode = (r.s_hi > 0.f && range >= r.s_lo && range <= r.s_hi) ? 1u : 0u;
-        next_band(r, 0.5f * (float)L);
-        s.rows[row] = r;
+    // What ds_topk_candidate_rows reports: v has stayed in registers, unless one workgroup did the step.
+    __device__ __forceinline__ void keep_book(bool alone) {
+        if (chunk == 0 && threadIdx.x == 0) s.rows[row].mode = alone ? 0u : 1u;
     }
 };
 
@@ -737,7 +730,7 @@ __global__ void __launch_bounds__(LQ_THREADS, 5) l2q_resident(L2Args a, L2Scratc
     for (uint32_t i = first; i < last; ++i) {
         if (alone) op.load(i);
         op.encode();
-        op.keep_book();
+        op.keep_book(alone);
     }
     if (alone) op.phase_end();
     else (void)meet<false, true>(s.meetings + kMeetWords, blocks, epoch, 0, s.epoch, a.t_ptr);

@@ -669,7 +669,7 @@ struct TopkResident : SparseResident {
             if (chunk == 0) {
                 select_alone();
                 tlo = s.rows[row].tlo;
-                keep_book();
+                keep_book(true);
                 clear_counts();
                 ties = 0;
             }
@@ -697,8 +697,8 @@ struct TopkResident : SparseResident {
         emit_mask(mask);
     }
 
-    // The guess of the next step.
-    __device__ __forceinline__ void keep_book() {
+    // The guess of the next step.  exact: a radix select found the threshold, not the keys counted while v was formed.
+    __device__ __forceinline__ void keep_book(bool exact) {
         if (chunk != 0 || threadIdx.x != 0) return;
         TopkRow r = s.rows[row];
         r.tau = tau;
@@ -709,7 +709,7 @@ struct TopkResident : SparseResident {
         // the number of keys above tlo is exact, whether they could be gathered or not: it always serves the next guess
         r.cand_mode = (tlo != 0xFFFFFFFFu && collected >= (uint32_t)a.k) ? 1u : 0u;
         r.tlo = next_candidate_threshold(r, tau, (uint32_t)a.k);
-        if (radix && s.gather != 0u) r.cand_mode = 0u;
+        r.cand_mode = exact ? 0u : 1u;                        // from here on what ds_topk_candidate_rows reports
         r.tied = equal > RS_INSIDE ? 1u : 0u;
         // the forecast lies in the window's second quarter or so: 512 to 1023 bins above tlo
         const uint32_t dist = r.forecast > r.tlo ? r.forecast - r.tlo : 1u;
@@ -750,7 +750,7 @@ __global__ void __launch_bounds__(kResThreads, 5) topk_resident(SparseLaunch lau
         if (!uniform(op.select_tied())) op.select_radix();
         op.emit_masked();
     }
-    op.keep_book();
+    op.keep_book(op.radix);
     (void)meet<false, true>(s.meetings + kMeetWords, blocks, epoch, 0, s.epoch, a.t_ptr);
     (void)op.sum_neighbours<false>(0);
     op.finish();
@@ -819,13 +819,9 @@ struct GsparResident : SparseResident {
         emit_mask(mask);
     }
 
-    // What ds_topk_candidate_rows reports: would the bound that the step before suggests have held?
-    __device__ __forceinline__ void keep_book() {
-        if (chunk != 0 || threadIdx.x != 0) return;
-        const float used = s.rows[row].lambda_hi;
-        s.rows[row].lambda = lambda;
-        s.rows[row].gs_mode = (used > 0.f && lambda <= used) ? 1u : 0u;
-        s.rows[row].lambda_hi = (lambda > 0.f && lambda < 1.0e30f) ? lambda * 1.05f : 0.f;
+    // What ds_topk_candidate_rows reports: v has stayed in registers, unless one workgroup did the step.
+    __device__ __forceinline__ void keep_book(bool alone) {
+        if (chunk == 0 && threadIdx.x == 0) s.rows[row].gs_mode = alone ? 0u : 1u;
     }
 
     // The header, and zeros behind a message shorter than the last one.
@@ -847,7 +843,7 @@ struct GsparResident : SparseResident {
             locate(i);
             if (chunk == 0) {
                 row_lambda();
-                keep_book();
+                keep_book(true);
             }
             emit_alone([&](uint64_t j, float val) {
                 uint32_t rnd[4];
@@ -884,7 +880,7 @@ __global__ void __launch_bounds__(kResThreads, 5) gspar_resident(SparseLaunch la
     }
     op.row_lambda();
     op.mark();
-    op.keep_book();
+    op.keep_book(false);
     (void)meet<false, true>(s.meetings + kMeetWords, blocks, epoch, 0, s.epoch, a.t_ptr);
     const uint32_t kept = op.sum_neighbours<true>(op.room());
     op.finish();

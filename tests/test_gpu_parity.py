@@ -769,14 +769,17 @@ def test_l2norm_free_run_messages_every_step(bits):
 
 
 @pytest.mark.parametrize("bits,grad", [(2, "normal"), (2, "quadratic"), (4, "normal"), (8, "normal")])
-def test_l2norm_speculative_codes_steady_state(bits, grad):
+@pytest.mark.parametrize("variant", [2, 0])
+def test_l2norm_speculative_codes_steady_state(bits, grad, variant):
     """The norm-rescaled path writes codes from its first pass under a guessed band for the row's range and settles
     the undecided elements once the range is known (or falls back to the exact second pass).  A free run long enough
     for the guesses to settle: messages after every step, and -- at 2 bits, where few elements sit next to a level
     boundary -- every row on the speculative path in the later steps.  Then the range is moved from outside (the
-    state scaled by 3), which the band cannot hold: the next step must take the exact pass and still agree."""
+    state scaled by 3), which the band cannot hold: the next step must take the exact pass and still agree.  (Variant 0: the
+    same steps in one launch each, where nothing is guessed.)"""
     w = small(wl.KIND_QUANT_L2NORM, 8, 4096 * 40 + 1001, bits=bits, grad=grad, gamma=0.05, eta=0.3)
-    ds = b.DeepSqueeze.from_workload(w)
+    ds = b.DeepSqueeze.from_workload(w, {"variant": variant})
+    assert ds.ds_plan_name().startswith("l2norm/speculative-codes" if variant == 2 else "l2norm/resident")
     st = oracle_state(w)
     c = wl.centres(w) if grad == "quadratic" else None
     fast = []
@@ -787,7 +790,9 @@ def test_l2norm_speculative_codes_steady_state(bits, grad):
         assert np.array_equal(ds.ds_read_messages(), msg), f"step {t}: messages differ"
         fast.append(ds.ds_topk_candidate_rows())
     say(w.name, "rows on the speculative path per step:", fast)
-    if bits == 2 and grad == "normal":
+    if variant == 0:
+        assert fast == [w.n] * 16
+    elif bits == 2 and grad == "normal":
         assert sum(fast[-6:]) >= 5 * w.n, fast          # a row's maximum may leave its band now and then
     x, d = ds.ds_read_state()
     assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
@@ -800,18 +805,20 @@ def test_l2norm_speculative_codes_steady_state(bits, grad):
         _, msg = oracle.step(st, g, want_cv=False)
         assert np.array_equal(ds.ds_read_messages(), msg), f"step {t} (after the jump): messages differ"
         if t == 16:
-            assert ds.ds_topk_candidate_rows() == 0
+            assert ds.ds_topk_candidate_rows() == (0 if variant == 2 else w.n)
     x, d = ds.ds_read_state()
     assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
     ds.ds_destroy()
 
 
-def test_gspar_free_runs_messages_every_step():
+@pytest.mark.parametrize("variant", [2, 0])
+def test_gspar_free_runs_messages_every_step(variant):
     """GSpar without anything read back in between: every step's tail goes through the next step's first pass, a
     shorter message clears what the longer one before it left behind; heavy-tailed gradients cut some p_j off at 1."""
     for w in (small(wl.KIND_GSPAR, 8, 4096 * 6 + 1001, k=700, grad="quadratic"),
               small(wl.KIND_GSPAR, 9, 50_021, k=2500, grad="student_t3", topo=wl.TOPO_TORUS2D, torus=(3, 3))):
-        ds = b.DeepSqueeze.from_workload(w)
+        ds = b.DeepSqueeze.from_workload(w, {"variant": variant})
+        assert ds.ds_plan_name().startswith("gspar/sift-scan-write" if variant == 2 else "gspar/resident")
         st = oracle_state(w)
         c = wl.centres(w) if w.grad == "quadratic" else None
         counts, fast = [], []
@@ -826,7 +833,10 @@ def test_gspar_free_runs_messages_every_step():
         assert len(set(counts)) > 1                                  # the count moves, so stale pairs had to be cleared
         # from the second step on the first pass collects under an upper bound of lambda and the bound holds
         say(w.name, "rows whose first pass collected the kept elements:", fast)
-        assert fast[0] == 0 and sum(fast[-5:]) >= 5 * w.n - 2, fast
+        if variant == 2:
+            assert fast[0] == 0 and sum(fast[-5:]) >= 5 * w.n - 2, fast
+        else:
+            assert fast == [w.n] * 10, fast                          # nothing is collected under a bound, v stays in registers
         x, d = ds.ds_read_state()
         assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
         ds.ds_destroy()

@@ -24,8 +24,8 @@ CASES = [
     small(wl.KIND_QUANT_L2NORM, 3, 4096 * 180 + 1, bits=2),
     small(wl.KIND_QUANT_L2NORM, 35, 4096 * 2 + 2, bits=8),
 ]
-# top-k: the same sizes; everything sent; k whose keys are gathered and k that takes the radix select; one, a few and more
-# sent columns per thread than a record holds
+# top-k: the same sizes; everything sent; k whose keys are gathered and k that takes the radix select; chunks that send nothing, a
+# few pairs, one per thread and more
 TOPK = [
     small(wl.KIND_TOPK, 3, 1, k=1),
     small(wl.KIND_TOPK, 5, 4095, k=41),
@@ -58,12 +58,18 @@ def test_resident_lock_step(w, variant):
     say("case", w.name, "variant", variant)
     ds = b.DeepSqueeze.from_workload(w, _plan(variant))
     assert ("resident" in ds.ds_plan_name()) == (variant != 2), ds.ds_plan_name()
+    for t in range(2):                                         # which way the step went: variant 3 must have been done by one workgroup
+        ds.ds_step(upload(wl.gradient(w, t)))
+        if variant == 3:
+            assert ds.ds_topk_candidate_rows() == 0
+        elif variant == 0 and w.kind != wl.KIND_TOPK:
+            assert ds.ds_topk_candidate_rows() == w.n
     ds.ds_destroy()
     lock_step(w, steps=2, plan=_plan(variant))
 
 
 @pytest.mark.parametrize("w", [CASES[3], CASES[4]] + TOPK + GSPAR, ids=lambda w: w.name)
-@pytest.mark.parametrize("variant", [0, 3])
+@pytest.mark.parametrize("variant", [0, 3, 2])
 def test_resident_free_run(w, variant):
     """Nothing read or written between the steps but the messages (the guesses of one step serve the next)."""
     ds = b.DeepSqueeze.from_workload(w, _plan(variant))
