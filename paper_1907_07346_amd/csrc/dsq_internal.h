@@ -30,6 +30,34 @@ struct Graph {
     int max_degree = 0;        // entries per row, diagonal included
 };
 
+// Many device arrays in one allocation: the same list is placed twice, for the sizes and for the addresses.  (An allocation
+// or a memset takes 10 us or so of making a handle, and a state made for one launch has 25 arrays.)
+struct Slab {
+    static constexpr size_t kPage = 2u << 20;             // large arrays start where an allocation of their own would
+    uint8_t* base = nullptr;
+    size_t bytes = 0;
+    template <typename T>
+    void place(T*& p, size_t count) {
+        const size_t size = count * sizeof(T), step = size >= kPage ? kPage : 256;
+        bytes = (bytes + step - 1) / step * step;
+        if (base) p = reinterpret_cast<T*>(base + bytes);
+        bytes += (size + 255) / 256 * 256;
+    }
+    // `list(slab)` places the arrays and returns how many bytes from the start on have to be zero.
+    template <typename F>
+    bool make(F list) {
+        size_t zero = list(*this);
+        if (hipMalloc(&base, bytes) != hipSuccess) { base = nullptr; return false; }
+        bytes = 0;
+        zero = list(*this);
+        return hipMemset(base, 0, zero) == hipSuccess;
+    }
+    void drop() {
+        if (base) (void)hipFree(base);
+        base = nullptr;
+    }
+};
+
 // Validation and topology construction (pure host code, usable without a GPU).
 ds_status validate_config(const ds_config* cfg, std::string& err, std::string* warn);
 ds_status build_graph(const ds_config* cfg, Graph& g, std::string& err);

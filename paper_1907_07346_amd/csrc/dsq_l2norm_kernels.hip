@@ -745,6 +745,7 @@ __global__ void __launch_bounds__(LQ_THREADS, 5) l2q_resident(L2Args a, L2Scratc
 
 struct L2State {
     L2Scratch s{};
+    Slab slab;                     // holds all of it
     int n = 0, bits = 0;
     bool pending = false;          // a step has been enqueued (or may have been, by a replayed graph) that left its tail
     bool resident = false;         // steps may run in one launch each; none leaves its tail then
@@ -753,10 +754,7 @@ struct L2State {
 
 void l2q_destroy(L2State* st) {
     if (!st) return;
-    L2Scratch& s = st->s;
-    void* ptrs[] = {s.rows, s.cmax, s.csq, s.csy2, s.pending, s.ucount, s.uslot, s.row_flags, s.meetings, s.epoch, s.codes, s.norms};
-    for (void* p : ptrs)
-        if (p) (void)hipFree(p);
+    st->slab.drop();
     delete st;
 }
 
@@ -780,25 +778,22 @@ ds_status l2q_create(const ds_config& cfg, uint64_t ld, bool resident, bool impa
     const size_t n = (size_t)cfg.n, nc = s.nchunks;
     // rows start with no guess (s_hi = 0): the first two steps are exact (the first has no s_prev and counts as a
     // movement of 20 %, too wide a band), speculation starts with the third if s moved little between them
-    bool ok = hipMalloc(&s.rows, n * sizeof(L2Row)) == hipSuccess && hipMemset(s.rows, 0, n * sizeof(L2Row)) == hipSuccess &&
-              hipMalloc(&s.cmax, n * nc * sizeof(float)) == hipSuccess &&
-              hipMalloc(&s.csq, n * nc * sizeof(double)) == hipSuccess &&
-              hipMalloc(&s.csy2, n * nc * sizeof(uint32_t)) == hipSuccess;
-    if (resident) {
-        const size_t code_bytes = n * nc * LQ_THREADS * (st->bits == 8 ? 2 : 1) * sizeof(uint64_t);
-        ok = ok && hipMalloc(&s.meetings, 2 * kMeetWords * sizeof(uint32_t)) == hipSuccess &&
-             hipMemset(s.meetings, 0, 2 * kMeetWords * sizeof(uint32_t)) == hipSuccess &&
-             hipMalloc(&s.epoch, sizeof(unsigned long long)) == hipSuccess && hipMemset(s.epoch, 0, sizeof(unsigned long long)) == hipSuccess &&
-             hipMalloc(&s.codes, code_bytes) == hipSuccess && hipMalloc(&s.norms, n * sizeof(float)) == hipSuccess;
-    }
-    ok = ok && hipMalloc(&s.pending, sizeof(uint32_t)) == hipSuccess &&
-         hipMalloc(&s.ucount, n * nc * sizeof(uint32_t)) == hipSuccess &&
-         hipMalloc(&s.uslot, n * nc * LQ_UCAP * sizeof(uint2)) == hipSuccess &&
-         hipMalloc(&s.row_flags, n * sizeof(uint32_t)) == hipSuccess &&
-         hipMemset(s.ucount, 0, n * nc * sizeof(uint32_t)) == hipSuccess &&
-         hipMemset(s.row_flags, 0, n * sizeof(uint32_t)) == hipSuccess &&
-         hipMemset(s.pending, 0, sizeof(uint32_t)) == hipSuccess &&
-         hipDeviceSynchronize() == hipSuccess;
+    const bool ok = st->slab.make([&](Slab& m) {
+        m.place(s.rows, n);
+        m.place(s.pending, 1);
+        m.place(s.ucount, n * nc);
+        m.place(s.row_flags, n);
+        m.place(s.meetings, resident ? 2 * kMeetWords : 0);
+        m.place(s.epoch, resident ? 1 : 0);
+        const size_t zero = m.bytes;
+        m.place(s.cmax, n * nc);
+        m.place(s.csq, n * nc);
+        m.place(s.csy2, n * nc);
+        m.place(s.uslot, n * nc * LQ_UCAP);
+        m.place(s.codes, resident ? n * nc * LQ_THREADS * (st->bits == 8 ? 2 : 1) : 0);
+        m.place(s.norms, resident ? n : 0);
+        return zero;
+    }) && hipDeviceSynchronize() == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         err = "scratch allocation for the norm-rescaled compressor failed";

@@ -1298,6 +1298,7 @@ __global__ void topk_init_rows(TopkRow* rows, int n) {
 
 struct TopkState {
     Scratch s{};
+    Slab slab;                     // holds all of it
     int n = 0;
     bool gspar = false;            // the GSpar operator runs on this state (its own select-free chain of kernels)
     bool pending = false;          // a step has been enqueued since the last flush (or may have been, by a
@@ -1308,10 +1309,7 @@ struct TopkState {
 void topk_destroy(TopkState* st) {
     if (!st) return;
     sparse_resident_destroy(st->resident);
-    void* ptrs[] = {st->s.hist, st->s.hist_part, st->s.hist2, st->s.hist3, st->s.rows, st->s.cnt_gt, st->s.cnt_eq, st->s.eq_before, st->s.out_off, st->s.cand_cnt, st->s.slot_val, st->s.slot_idx,
-                    st->s.list, st->s.csum, st->s.gs_overflow};
-    for (void* p : ptrs)
-        if (p) (void)hipFree(p);
+    st->slab.drop();
     delete st;
 }
 
@@ -1326,28 +1324,26 @@ ds_status topk_create(const ds_config& cfg, uint64_t ld, bool resident, bool imp
     // the first pass reads and writes whole chunks of x and delta
     if ((uint64_t)s.nchunks * TK_CHUNK > ld) { err = "internal: row pitch smaller than the chunked row"; delete st; return DS_EINVAL; }
     const size_t n = (size_t)cfg.n, nc = s.nchunks;
-    bool ok = hipMalloc(&s.rows, n * sizeof(TopkRow)) == hipSuccess && hipMalloc(&s.gs_overflow, sizeof(uint32_t)) == hipSuccess &&
-              hipMemset(s.gs_overflow, 0, sizeof(uint32_t)) == hipSuccess;
+    bool ok = st->slab.make([&](Slab& m) {
+        m.place(s.gs_overflow, 1);
+        m.place(s.hist, n * HIST_BINS);
+        m.place(s.hist_part, n * TK_HPARTS * HIST_BINS);
+        m.place(s.hist2, n * HIST_BINS);
+        m.place(s.hist3, n * BINS3);
+        m.place(s.out_off, n * (nc + 1));
+        m.place(s.cand_cnt, n * nc);
+        const size_t zero = m.bytes;
+        m.place(s.rows, n);
+        m.place(s.cnt_gt, n * nc);
+        m.place(s.cnt_eq, n * nc);
+        m.place(s.eq_before, n * nc);
+        m.place(s.slot_val, n * nc * TK_CAP);
+        m.place(s.slot_idx, n * nc * TK_CAP);
+        m.place(s.list, n * TK_LIST_CAP);
+        m.place(s.csum, st->gspar ? n * nc : 1);
+        return zero;
+    });
     if (resident) ok = ok && sparse_resident_create(cfg, impatient, s.rows, s.gs_overflow, &st->resident) == DS_OK;
-    ok = ok && hipMalloc(&s.hist, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.hist_part, n * TK_HPARTS * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.hist2, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.hist3, n * BINS3 * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.cnt_gt, n * nc * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.cnt_eq, n * nc * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.eq_before, n * nc * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.out_off, n * (nc + 1) * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.cand_cnt, n * nc * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.slot_val, n * nc * TK_CAP * sizeof(uint32_t)) == hipSuccess &&
-              hipMalloc(&s.slot_idx, n * nc * TK_CAP * sizeof(uint16_t)) == hipSuccess &&
-              hipMalloc(&s.list, n * TK_LIST_CAP * sizeof(uint2)) == hipSuccess &&
-              hipMalloc(&s.csum, (st->gspar ? n * nc : 1) * sizeof(double)) == hipSuccess &&
-         hipMemset(s.hist, 0, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
-         hipMemset(s.hist_part, 0, n * TK_HPARTS * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
-         hipMemset(s.hist2, 0, n * HIST_BINS * sizeof(uint32_t)) == hipSuccess &&
-         hipMemset(s.hist3, 0, n * BINS3 * sizeof(uint32_t)) == hipSuccess &&
-         hipMemset(s.out_off, 0, n * (nc + 1) * sizeof(uint32_t)) == hipSuccess &&
-         hipMemset(s.cand_cnt, 0, n * nc * sizeof(uint32_t)) == hipSuccess;
     if (ok) {
         hipLaunchKernelGGL(topk_init_rows, dim3((cfg.n + 63) / 64), dim3(64), 0, 0, s.rows, cfg.n);
         ok = hipDeviceSynchronize() == hipSuccess;

@@ -22,7 +22,6 @@
 // 4.4 and 3.7.  8 workers x 272,474 parameters, k = 1 %, the state complete after every step: 22 us (load 3.8, collect 2,
 // the meetings 2 each, launch 2.5); the fourteen launches it takes otherwise: 61 us.
 #include <new>
-#include <type_traits>
 
 #include "dsq_internal.h"
 #include "dsq_resident.h"
@@ -892,14 +891,14 @@ static_assert(sizeof(SparseShared) <= 31 * 1024, "five workgroups share the 160 
 
 struct SparseResidentState {
     SparseScratch s{};
-    uint8_t* slab = nullptr;      // one allocation holds all of the scratch
+    Slab slab;                    // holds all of the scratch
     bool gspar = false;
     uint64_t patience = 0;
 };
 
 void sparse_resident_destroy(SparseResidentState* st) {
     if (!st) return;
-    if (st->slab) (void)hipFree(st->slab);
+    st->slab.drop();
     delete st;
 }
 
@@ -922,29 +921,22 @@ ds_status sparse_resident_create(const ds_config& cfg, bool impatient, TopkRow* 
     // about 1.6 k keys are collected; a chunk's have to fit in its slot with room for an uneven row
     s.gather = cfg.comp.k * kResChunk <= cfg.N * (RS_SLOT / 2) ? 1u : 0u;
     s.deep = cfg.comp.k * kResChunk > cfg.N * (uint64_t)(kResThreads * 3 / 4) ? 1u : 0u;   // most chunks send more pairs than there are threads
-    size_t bytes = 0;
-    auto place = [&](auto*& p, size_t count) {                // two passes: sizes, then addresses
-        if (st->slab) p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(st->slab + bytes);
-        bytes += (count * sizeof(*p) + 255) / 256 * 256;
-    };
-    size_t zero = 0;
-    for (int pass = 0; pass < 2; ++pass) {
-        bytes = 0;
-        place(s.meetings, 2 * kMeetWords);
-        place(s.epoch, 1);
-        place(s.window, st->gspar ? 0 : n * RS_WINDOW);
-        place(s.row_arrivals, st->gspar ? 0 : n * kMeetLine);
-        place(s.row_hist, st->gspar ? 0 : n * RS_LEVELS * RS_LEVEL_BINS);
-        zero = bytes;                                         // what lies before this has to be zero at the first launch
-        place(s.reach, all);
-        place(s.split, all);
-        place(s.sent, all);
-        place(s.csum, st->gspar ? all : 0);
-        place(s.keys, st->gspar ? 0 : all * RS_SLOT);
-        place(s.pairs, all * kResChunk);
-        if (pass == 0 && hipMalloc(&st->slab, bytes) != hipSuccess) break;
-    }
-    if (!st->slab || hipMemset(st->slab, 0, zero) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+    const bool ok = st->slab.make([&](Slab& m) {
+        m.place(s.meetings, 2 * kMeetWords);
+        m.place(s.epoch, 1);
+        m.place(s.window, st->gspar ? 0 : n * RS_WINDOW);
+        m.place(s.row_arrivals, st->gspar ? 0 : n * kMeetLine);
+        m.place(s.row_hist, st->gspar ? 0 : n * RS_LEVELS * RS_LEVEL_BINS);
+        const size_t zero = m.bytes;                          // at the first launch
+        m.place(s.reach, all);
+        m.place(s.split, all);
+        m.place(s.sent, all);
+        m.place(s.csum, st->gspar ? all : 0);
+        m.place(s.keys, st->gspar ? 0 : all * RS_SLOT);
+        m.place(s.pairs, all * kResChunk);
+        return zero;
+    });
+    if (!ok) {                                                // (the caller waits for the memset)
         (void)hipGetLastError();
         sparse_resident_destroy(st);
         return DS_ENOMEM;
