@@ -87,6 +87,8 @@ struct L2Scratch {
     unsigned long long* epoch;    // ... and the number of launches so far
     uint64_t* codes;              // n x nchunks x 256 x words: the sixteen codes of each thread's columns, for the neighbours
     float* norms;                 // n: the norms that are sent, for the neighbours
+    uint32_t expected;            // workgroups the first meeting waits for: all, and without patience one more than there are,
+                                  // so that it is called off whichever way they arrive (tests of what follows)
 };
 
 // Code of one element for a given inv = (L/2)/s: nearest level, ties to even; NaN goes to level 0.
@@ -720,7 +722,7 @@ __global__ void __launch_bounds__(LQ_THREADS, 5) l2q_resident(L2Args a, L2Scratc
             if (alone) op.load(i);
             op.measure();
         }
-        if (alone || meet<true, false>(s.meetings, blocks, epoch, patience)) break;
+        if (alone || meet<true, false>(s.meetings, s.expected, epoch, patience)) break;
         if (!leave(a.t_ptr, blocks)) return;
         alone = true;
         first = 0u;
@@ -774,6 +776,7 @@ ds_status l2q_create(const ds_config& cfg, uint64_t ld, bool resident, bool impa
     st->patience = impatient ? 0 : kMeetPatience;
     L2Scratch& s = st->s;
     s.nchunks = (uint32_t)((cfg.N + LQ_CHUNK - 1) / LQ_CHUNK);
+    s.expected = (uint32_t)cfg.n * s.nchunks + (impatient ? 1u : 0u);
     if ((uint64_t)s.nchunks * LQ_CHUNK > ld) { err = "internal: row pitch smaller than the chunked row"; l2q_destroy(st); return DS_EINVAL; }
     const size_t n = (size_t)cfg.n, nc = s.nchunks;
     // rows start with no guess (s_hi = 0): the first two steps are exact (the first has no s_prev and counts as a

@@ -53,8 +53,7 @@ __device__ __forceinline__ uint32_t meet_groups(uint32_t blocks) { return blocks
 
 // Counts this workgroup in and waits for the others; called by all threads.  The words are never cleared: `epoch` launches
 // have come this way before, so each counter stands at epoch times its arrivals.  MAY_PART: returns false if `patience`
-// ran out for some workgroup before all had arrived -- the same answer in every workgroup; with no patience at all
-// it always does, as workgroup 0 does not count itself in (tests of what follows).  CLOSING: the last meeting
+// ran out for some workgroup before all had arrived -- the same answer in every workgroup.  CLOSING: the last meeting
 // of a launch; the workgroup that completes it advances the epoch and the step counter, which all have read by then.
 template <bool MAY_PART, bool CLOSING>
 __device__ __forceinline__ bool meet(uint32_t* w, uint32_t blocks, unsigned long long epoch, uint64_t patience, unsigned long long* epoch_cell = nullptr,
@@ -68,8 +67,7 @@ __device__ __forceinline__ bool meet(uint32_t* w, uint32_t blocks, unsigned long
         const unsigned long long complete = groups * (epoch + 1ull);
         unsigned long long* root = reinterpret_cast<unsigned long long*>(w);
         uint32_t* flags = w + (size_t)(1 + kMeetGroups) * kMeetLine;
-        const bool counted = !MAY_PART || patience != 0 || blockIdx.x != 0;
-        if (counted && agent_add(w + (size_t)(1 + g) * kMeetLine, 1u) + 1u == meet_members(blocks, g) * (uint32_t)(epoch + 1ull)) {
+        if (agent_add(w + (size_t)(1 + g) * kMeetLine, 1u) + 1u == meet_members(blocks, g) * (uint32_t)(epoch + 1ull)) {
             if (__hip_atomic_fetch_add(root, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1ull == complete) {
                 // the last group, and nobody has called it off
                 for (uint32_t q = 0; q < groups; ++q) agent_store(flags + (size_t)q * kMeetLine, now);

@@ -55,6 +55,8 @@ struct SparseScratch {
     double* csum;                 // GSpar: n x nchunks tree sums of |v| over the chunks
     uint32_t* overflow;           // GSpar: set once a row kept more than its message holds
     uint32_t nchunks;
+    uint32_t expected;            // workgroups the first meeting waits for: all, and without patience one more than there are,
+                                  // so that it is called off whichever way they arrive (tests of what follows)
     uint32_t gather;              // 1: keys are exchanged; 0: the radix select is always taken
     uint32_t deep;                // 1: two pairs of a neighbour per thread are asked for together, not one
 };
@@ -737,7 +739,7 @@ __global__ void __launch_bounds__(kResThreads, 5) topk_resident(SparseLaunch lau
     op.expect(blockIdx.x);
     op.load(blockIdx.x);
     op.collect();
-    if (!uniform(meet<true, false>(s.meetings, blocks, epoch, launch.patience))) {
+    if (!uniform(meet<true, false>(s.meetings, s.expected, epoch, launch.patience))) {
         if (!uniform(leave(a.t_ptr, blocks))) return;
         op.step_alone(blocks);
         close_alone(s.meetings, 2, blocks, epoch, s.epoch, a.t_ptr);
@@ -871,7 +873,7 @@ __global__ void __launch_bounds__(kResThreads, 5) gspar_resident(SparseLaunch la
     op.t_lo = (uint32_t)*a.t_ptr;
     op.load(blockIdx.x);
     op.measure();
-    if (!uniform(meet<true, false>(s.meetings, blocks, epoch, launch.patience))) {
+    if (!uniform(meet<true, false>(s.meetings, s.expected, epoch, launch.patience))) {
         if (!uniform(leave(a.t_ptr, blocks))) return;
         op.step_alone(blocks);
         close_alone(s.meetings, 2, blocks, epoch, s.epoch, a.t_ptr);
@@ -917,6 +919,7 @@ ds_status sparse_resident_create(const ds_config& cfg, bool impatient, TopkRow* 
     s.rows = rows;
     s.overflow = overflow;
     s.nchunks = (uint32_t)((cfg.N + kResChunk - 1) / kResChunk);
+    s.expected = (uint32_t)cfg.n * s.nchunks + (impatient ? 1u : 0u);
     const size_t n = (size_t)cfg.n, all = n * s.nchunks;
     // about 1.6 k keys are collected; a chunk's have to fit in its slot with room for an uneven row
     s.gather = cfg.comp.k * kResChunk <= cfg.N * (RS_SLOT / 2) ? 1u : 0u;
