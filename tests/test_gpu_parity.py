@@ -120,6 +120,17 @@ def free_run(w: wl.Config, steps, W=None):
     return nbits
 
 
+# The sparsifiers and the norm-rescaled codes step small problems in one launch; variant 2 keeps such a handle on the launches that large
+# problems take, with their deferred tails and guesses.
+CHAINED = {wl.KIND_TOPK: "topk/radix-select", wl.KIND_GSPAR: "gspar/sift-scan-write", wl.KIND_QUANT_L2NORM: "l2norm/speculative-codes"}
+both_plans = pytest.mark.parametrize("variant", [0, 2])
+
+
+def assert_plan(ds, w, variant):
+    if w.kind in CHAINED:
+        assert ds.ds_plan_name().startswith(CHAINED[w.kind]) == (variant == 2), ds.ds_plan_name()
+
+
 def small(kind, n, N, *, topo=wl.TOPO_RING, torus=(0, 0), bits=0, block=0, k=0, grad="normal", seed=5,
           gamma=0.1, eta=0.4):
     return wl.Config(f"small_k{kind}_n{n}_N{N}_b{bits}_B{block}", n=n, N=N, topo=topo, torus=torus, kind=kind,
@@ -196,6 +207,12 @@ SMALL_GSPAR = [
 def test_lock_step_small_shapes(w):
     say("case", w.name)
     lock_step(w, steps=3)
+
+
+@pytest.mark.parametrize("w", [w for w in SMALL + SMALL_GSPAR if w.kind in CHAINED], ids=lambda w: w.name)
+def test_lock_step_small_shapes_in_the_launches_of_large_ones(w):
+    say("case", w.name)
+    lock_step(w, steps=3, plan={"variant": 2})
 
 
 @pytest.mark.parametrize("w", [SMALL[6], SMALL[9], small(wl.KIND_SIGN_MEANABS, 100, 1024 * 3 + 7, block=1024),
@@ -275,27 +292,35 @@ def _random_cases(count, seed):
     return cases
 
 
-def test_randomized_small_configs():
+@both_plans
+def test_randomized_small_configs(variant):
     """120 seeded random configurations (sizes around the tile, sweep and chunk edges; rings and tori; every
     compressor): two lock-step iterations each, everything compared bit for bit."""
     for w in _random_cases(120, seed=2024):
+        if variant == 2 and w.kind not in CHAINED:
+            continue
         say("case", w.name)
-        lock_step(w, steps=2)
+        lock_step(w, steps=2, plan={"variant": variant})
 
 
-def test_randomized_free_runs_on_random_graphs():
+@both_plans
+def test_randomized_free_runs_on_random_graphs(variant):
     """40 seeded random configurations on random connected graphs (Metropolis weights, given as CSR): five steps
     without touching the state in between -- so deferred tails go through the next step's first pass -- with W,
     gamma and eta changed once on the way; messages compared after every step, the state at the end."""
     r = np.random.default_rng(77)
-    for w in _random_cases(40, seed=4048):
+    for w in _random_cases(40, seed=4048) + [small(wl.KIND_GSPAR, 9, 4096 * 2 + 5, k=300), small(wl.KIND_GSPAR, 30, 3000, k=2000, grad="student_t3")]:
+        if variant == 2 and w.kind not in CHAINED:
+            continue
         n = w.n
         Ws = [_random_graph(n, int(r.integers(0, 2 * n)), seed=int(r.integers(0, 1 << 30))) for _ in range(2)]
         say("case", w.name)
         rp, co, va = oracle.dense_to_csr(Ws[0])
         cfg, keep = b.make_config(n, w.N, wl.TOPO_CSR, w.kind, w.gamma, w.eta, bits=w.bits, block=w.block, k=w.k,
                                   seed=w.seed, W_csr=(rp, co, va.astype(np.float32)))
-        ds = b.DeepSqueeze(cfg, keep)
+        ds = b.DeepSqueeze(cfg, keep, {"variant": variant})
+        if variant == 2:
+            assert_plan(ds, w, 2)
         st = oracle_state(w, Ws[0])
         for t in range(5):
             if t == 3:
@@ -365,14 +390,16 @@ def test_general_graph_csr():
         lock_step(w, steps=2, W=W, csr=(rp, co, va.astype(np.float32)))
 
 
-def test_rates_change_between_steps():
+@both_plans
+def test_rates_change_between_steps(variant):
     # gamma decays during a run (the paper's experiments divide the learning rate by 5 every 60 epochs) and
     # eta is retuned; top-k and the norm-rescaled codes carry a deferred tail that belongs to the old eta
     for w in (small(wl.KIND_QUANT_MAXABS, 8, 512 * 3 + 9, bits=4, block=512),
-              small(wl.KIND_TOPK, 8, 12_345, k=77),
+              small(wl.KIND_TOPK, 8, 12_345, k=77), small(wl.KIND_GSPAR, 8, 12_345, k=77),
               small(wl.KIND_QUANT_L2NORM, 8, 4096 + 77, bits=4)):
         say("case", w.name)
-        ds = b.DeepSqueeze.from_workload(w)
+        ds = b.DeepSqueeze.from_workload(w, {"variant": variant})
+        assert_plan(ds, w, variant)
         st = oracle_state(w)
         for t in range(6):
             if t in (2, 4):
@@ -407,15 +434,17 @@ def _random_graph(n, extra, seed):
     return W
 
 
-def test_time_varying_graph():
+@both_plans
+def test_time_varying_graph(variant):
     # W is swapped between steps (ds_set_mixing); top-k has a deferred tail that must use the old W
     n = 12
     for w in (small(wl.KIND_QUANT_MAXABS, n, 512 * 3 + 9, bits=4, block=512),
               small(wl.KIND_SIGN_MEANABS, n, 777, block=256),
-              small(wl.KIND_TOPK, n, 12_345, k=77),
+              small(wl.KIND_TOPK, n, 12_345, k=77), small(wl.KIND_GSPAR, n, 12_345, k=77),
               small(wl.KIND_QUANT_L2NORM, n, 4096 * 2 + 77, bits=4)):
         say("case", w.name)
-        ds = b.DeepSqueeze.from_workload(w)
+        ds = b.DeepSqueeze.from_workload(w, {"variant": variant})
+        assert_plan(ds, w, variant)
         st = oracle_state(w)
         for t in range(5):
             if t > 0:
@@ -589,7 +618,8 @@ def test_all_zero_and_denormal_blocks():
         assert_close("delta", dg, st.delta)
 
 
-def test_negative_zeros():
+@both_plans
+def test_negative_zeros(variant):
     # the sign compressor sends the IEEE sign bit, so -0.0 counts as negative; a zero keeps its sign through
     # v = (x - gamma g) + delta only if delta's zero has it too
     N = 300
@@ -602,9 +632,11 @@ def test_negative_zeros():
     d0[1] = -0.0                                               # a block of negative zeros: scale 0, all bits set
     for w in (small(wl.KIND_SIGN_MEANABS, 4, N, block=256, gamma=0.0), small(wl.KIND_SIGN_MEANABS, 4, N, block=64, gamma=0.0),
               small(wl.KIND_QUANT_MAXABS, 4, N, bits=2, block=128, gamma=0.0), small(wl.KIND_TOPK, 4, N, k=150, gamma=0.0),
+              small(wl.KIND_TOPK, 4, N, k=3, gamma=0.0), small(wl.KIND_GSPAR, 4, N, k=20, gamma=0.0),    # whole sectors are written for a sent column
               small(wl.KIND_QUANT_L2NORM, 4, N, bits=4, gamma=0.0), small(wl.KIND_RAND_SPARSE, 4, N, k=150, gamma=0.0)):
         say("case", w.name)
-        ds = b.DeepSqueeze.from_workload(w)
+        ds = b.DeepSqueeze.from_workload(w, {"variant": variant})
+        assert_plan(ds, w, variant)
         st = oracle_state(w, x=x0.copy(), delta=d0.copy())
         ds.ds_write_state(x0, d0, 0)
         g = np.zeros((4, N), np.float32)
@@ -618,9 +650,11 @@ def test_negative_zeros():
         ds.ds_destroy()
 
 
-def test_topk_ties_take_the_lower_index():
+@both_plans
+def test_topk_ties_take_the_lower_index(variant):
     w = small(wl.KIND_TOPK, 3, 20_000, k=333)
-    ds = b.DeepSqueeze.from_workload(w)
+    ds = b.DeepSqueeze.from_workload(w, {"variant": variant})
+    assert_plan(ds, w, variant)
     st = oracle_state(w)
     r = np.random.default_rng(4)
     x = r.integers(-3, 4, (3, w.N)).astype(np.float32)    # massive ties at the threshold
@@ -710,10 +744,12 @@ def test_two_handles_interleaved():
                                replace(small(wl.KIND_QUANT_MAXABS, 8, 512 * 9 + 37, bits=2, block=512), algo=wl.ALGO_DCD_PSGD, name="dcd_graph"),
                                replace(small(wl.KIND_SIGN_MEANABS, 8, 256 * 9 + 37, block=256), algo=wl.ALGO_CHOCO_SGD, name="choco_graph")],
                          ids=lambda w: w.name)
-def test_hip_graph_replay(w):
+@both_plans
+def test_hip_graph_replay(w, variant):
     """ds_step captured once into a HIP graph and replayed: the step counter lives on the device, so every
     replay draws fresh rounding words; each replay is checked against the oracle, with eager work between."""
-    ds = b.DeepSqueeze.from_workload(w)
+    ds = b.DeepSqueeze.from_workload(w, {"variant": variant})
+    assert_plan(ds, w, variant)
     st = oracle_state(w)
     pitch = (w.N + 3) // 4 * 4
     g_static = torch.zeros((w.n, pitch), dtype=torch.float32, device="cuda")
@@ -748,12 +784,14 @@ def test_hip_graph_replay(w):
     ds.ds_destroy()
 
 
-@pytest.mark.parametrize("bits", [2, 4])
-def test_l2norm_free_run_messages_every_step(bits):
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@both_plans
+def test_l2norm_free_run_messages_every_step(bits, variant):
     # nothing reads the state between the steps, so every step's tail (delta = v - C[v] and the gossip
     # update) is applied by the next step's first pass; the messages are compared after every step
     w = small(wl.KIND_QUANT_L2NORM, 8, 4096 * 6 + 1001, bits=bits, grad="quadratic")
-    ds = b.DeepSqueeze.from_workload(w)
+    ds = b.DeepSqueeze.from_workload(w, {"variant": variant})
+    assert_plan(ds, w, variant)
     st = oracle_state(w)
     c = wl.centres(w)
     for t in range(8):
@@ -765,6 +803,52 @@ def test_l2norm_free_run_messages_every_step(bits):
     assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
     x2, d2 = ds.ds_read_state()                               # a second read finds nothing pending
     assert np.array_equal(x, x2) and np.array_equal(d, d2)
+    ds.ds_destroy()
+
+
+@pytest.mark.parametrize("w", [small(wl.KIND_QUANT_L2NORM, 8, 4096 * 3 + 1001, bits=2), small(wl.KIND_QUANT_L2NORM, 8, 4096 * 3 + 1001, bits=4),
+                               small(wl.KIND_QUANT_L2NORM, 8, 4096 * 3 + 1001, bits=8), small(wl.KIND_TOPK, 8, 4096 * 3 + 1001, k=130),
+                               small(wl.KIND_GSPAR, 8, 4096 * 3 + 1001, k=900)], ids=lambda w: w.name)
+@pytest.mark.parametrize("order", ["ssr", "srssr", "sessr", "swssr", "ggr", "sggsr", "grgsger", "gwgger"])
+def test_deferred_tails_by_what_meets_them(w, order):
+    """The launches of large problems leave the tail of a step (of which the norm-rescaled codes know two kinds, by whether delta was
+    rewritten) to the next step, a read (r), a change of eta (e) or of W (w), after an eager step (s) or the replay of a graph (g)."""
+    ds = b.DeepSqueeze.from_workload(w, {"variant": 2})
+    assert_plan(ds, w, 2)
+    st = oracle_state(w)
+    gd = torch.zeros((w.n, (w.N + 3) // 4 * 4), dtype=torch.float32, device="cuda")
+    graph, side, t = None, torch.cuda.Stream(), 0
+    for what in order:
+        if what in "sg":
+            g = wl.gradient(w, t)
+            gd[:, :w.N].copy_(torch.from_numpy(g).cuda())
+            torch.cuda.synchronize()
+            if what == "s":
+                ds.ds_step(gd)
+            else:
+                if graph is None:                              # (a graph keeps the eta and the W it was captured with: captured anew below)
+                    graph = torch.cuda.CUDAGraph()
+                    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+                        ds.ds_step(gd, side)
+                graph.replay()
+                torch.cuda.synchronize()
+            _, msg = oracle.step(st, g, want_cv=False)
+            t += 1
+            assert np.array_equal(ds.ds_read_messages(), msg), f"{order} step {t}: messages differ"
+        elif what == "e":
+            st.eta *= 0.75
+            ds.ds_set_rates(st.gamma, st.eta)
+            graph = None
+        elif what == "w":
+            W = _random_graph(w.n, 5, seed=t)
+            rp, co, va = oracle.dense_to_csr(W)
+            ds.ds_set_mixing((rp, co, va.astype(np.float32)))
+            st.set_W(W)
+            graph = None
+        else:
+            x, d = ds.ds_read_state()
+            assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0, order
+    assert ds.ds_step_count() == t
     ds.ds_destroy()
 
 
