@@ -138,7 +138,7 @@ __global__ void __launch_bounds__(256) workload_gradient_kernel(ds_workload w, u
 __global__ void __launch_bounds__(256) workload_quadratic_kernel(ds_workload w, uint64_t t, const float* __restrict__ x, uint64_t x_ld,
                                                                  float* __restrict__ g, uint64_t g_ld) {
     const uint32_t row = blockIdx.y;
-    const uint64_t lane2 = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint64_t lane2 = ((uint64_t)blockIdx.z * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
     const uint64_t c = lane2 >> 1;
     const bool noise = (lane2 & 1u) != 0u;
     const uint64_t j = 4 * c + (noise ? 2 : 0);                // the two columns this lane writes
@@ -167,8 +167,10 @@ __global__ void __launch_bounds__(256) workload_quadratic_kernel(ds_workload w, 
 ds_status launch_workload_gradient(const ds_workload& w, uint64_t t, const float* x, uint64_t x_ld, float* g, uint64_t g_ld,
                                    hipStream_t stream) {
     const uint64_t quads = (g_ld + 3) / 4;
+    // a launch dimension holds fewer than 2^32 work-items: very long rows get a second layer
+    const uint64_t blocks = (2 * quads + 255) / 256, most = 0xFFFFFFFFull / 256, layers = (blocks + most - 1) / most;
     if (w.kind == DS_GRAD_QUADRATIC)
-        hipLaunchKernelGGL(workload_quadratic_kernel, dim3((unsigned)((2 * quads + 255) / 256), w.n), dim3(256), 0, stream, w, t, x, x_ld, g, g_ld);
+        hipLaunchKernelGGL(workload_quadratic_kernel, dim3((unsigned)(blocks < most ? blocks : most), w.n, (unsigned)layers), dim3(256), 0, stream, w, t, x, x_ld, g, g_ld);
     else
         hipLaunchKernelGGL(workload_gradient_kernel, dim3((unsigned)((quads + 255) / 256), w.n), dim3(256), 0, stream, w, t, g, g_ld);
     return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;

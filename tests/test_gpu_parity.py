@@ -998,6 +998,23 @@ def test_device_gradient_generator_matches_the_host_one_bit_for_bit(kind):
         assert np.all(got[:, N:] == 0)
 
 
+def test_device_gradient_with_a_pitch_of_2_33_columns():
+    """One row of 1003 parameters whose pitch is the longest that the quadratic gradient took when a thread did four columns:
+    values as with a short pitch, zeros behind them to the end."""
+    N, pitch = 1003, 1 << 33
+    if torch.cuda.mem_get_info()[0] < 5 * pitch:
+        pytest.skip("needs 43 GB of device memory")
+    x = torch.randn((1, 1004), device="cuda")
+    short = torch.empty((1, 1004), device="cuda")
+    b.ds_workload_gradient("quadratic", 1, N, 0.5, 7, 3, short, x.data_ptr(), 1004)
+    g = torch.empty((1, pitch), dtype=torch.float32, device="cuda")
+    g[0, 1000:1 << 20] = 1.0
+    g[0, -(1 << 20):] = 1.0
+    b.ds_workload_gradient("quadratic", 1, N, 0.5, 7, 3, g, x.data_ptr(), 1004)
+    assert torch.equal(g[0, :1004], short[0])
+    assert not g[0, 1004:1 << 20].any() and not g[0, -(1 << 20):].any() and not g[0, (1 << 32) - 4096:(1 << 32) + 4096].any()
+
+
 def test_free_run_with_gradients_drawn_on_the_device():
     """Config 0 at full size for its 100 steps, plus a sign and a top-k run on the same quadratic: the GPU side
     draws its gradients on the device from its own state (no host-device traffic inside the run), the oracle side
