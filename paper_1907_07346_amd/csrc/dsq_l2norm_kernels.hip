@@ -499,7 +499,7 @@ __global__ void l2q_clear_pending(L2Scratch s) { *s.pending = 0u; }
 //   meeting
 //   finish    the decode units of the neighbours, delta = v - C[v], x = xh + eta sum_j a_ij C[v_j]
 // What bounds it is the chain of two meetings and four round trips to memory.  8 workers x 272,474 parameters at 4 bits
-// with the state complete after every step: 20.3 us, of which loads and measure 4.4, the meetings 1.5-2 each, encode 2.5,
+// with the state complete after every step: 20 us, of which loads and measure 4.4, the meetings 1.5-2 each, encode 2.5,
 // finish 4, launch 2.7; the six launches it takes otherwise: 40 us.
 template <int BITS>
 struct L2Resident : ResidentChunk<L2Args> {

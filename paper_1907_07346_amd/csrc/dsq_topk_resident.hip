@@ -19,8 +19,8 @@
 // 4 to 5 us: what bounds the kernel, next to the meetings and four round trips to memory, is the number of instructions.
 // Gathering all the row's keys in LDS and a histogram over them in every workgroup took 10 us, and records per thread
 // (which of its sixteen columns a neighbour sends) instead of the LDS sum 11 us, where the present forms take
-// 4.4 and 3.7.  8 workers x 272,474 parameters, k = 1 %, the state complete after every step: 22 us (load 3.8, collect 2,
-// the meetings 2 each, launch 2.5); the fourteen launches it takes otherwise: 61 us.
+// 4.4 and 3.7.  8 workers x 272,474 parameters, k = 1 %: the kernel 22 us (load 3.8, collect 2, the meetings 2 each), the loop
+// with the state complete after every step 26, and 61 in the fourteen launches it takes otherwise.
 #include <new>
 
 #include "dsq_internal.h"
@@ -765,8 +765,8 @@ __global__ void __launch_bounds__(kResThreads, 5) topk_resident(SparseLaunch lau
 //             order                                                                                -> scratch
 //   meeting
 //   finish    as for top-k; the message's header and the zeros behind it by the workgroups of chunk 0
-// 8 workers x 272,474 parameters, 10 % kept, the state complete after every step: 26.4 us; the ten launches it takes
-// otherwise: 52 us.
+// 8 workers x 272,474 parameters, 10 % kept, the state complete after every step: 25.3 us (kernel 24.7); the ten launches it
+// takes otherwise: 52 us.
 struct GsparResident : SparseResident {
     using SparseResident::SparseResident;
     uint32_t t_lo = 0;                                        // the step's counter, read before it is advanced
