@@ -184,7 +184,7 @@ typedef struct {
                           /* 2: no resident kernel: compressors that take a small problem's step in one launch use   */
                           /*    the launches they use for large ones.  That is also what such a handle does by itself */
                           /*    while the streams that others like it step on fill the GPU; ask for it where the      */
-                          /*    library cannot see that (several processes, graphs replayed on more than two streams,  */
+                          /*    library cannot see that (several processes, graphs replayed on more than one stream,   */
                           /*    streams that may not use every compute unit): a step whose workgroups cannot all run   */
                           /*    waits for 10 ms and then takes some 10 ms more.  3: that kernel, but its workgroups do */
                           /*    not wait for each other at all, so that the last one does the step alone (tests)       */

@@ -108,6 +108,8 @@ void take_seat(ds_handle* h, hipStream_t stream) {
 bool seated(ds_handle* h, hipStream_t stream) {
     if (!h->resident) return false;
     if (h->share == 0) return true;                          // its workgroups never wait
+    static thread_local char own_stream;                     // hipStreamPerThread is one name for a stream of every thread
+    if (stream == hipStreamPerThread) stream = reinterpret_cast<hipStream_t>(&own_stream);
     if (h->seat < 0 || h->seat_stream != stream) take_seat(h, stream);
     return h->seat >= 0;
 }

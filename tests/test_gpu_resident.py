@@ -183,6 +183,47 @@ def test_steps_that_start_together_on_several_streams(kind, kw, variants):
     assert took[-3] < 5e-3, took                               # two of 22 may have been held up by something else
 
 
+def test_steps_on_the_per_thread_default_streams():
+    """hipStreamPerThread names another stream in every thread: four threads step a handle each, all at once."""
+    import threading
+    import time
+
+    import torch
+    ws, dss, _ = _crowd(wl.KIND_QUANT_L2NORM, (0, 0, 0, 0), bits=4)
+    ups = [[upload(wl.gradient(w, t)) for t in range(2)] for w in ws]
+    torch.cuda.synchronize()
+    steps, meet, took, failed = 20, threading.Barrier(len(ws)), [], []
+
+    def work(ds, gs, first):
+        torch.cuda.set_device(0)
+        for t in range(steps):
+            meet.wait(30)
+            began = time.perf_counter()
+            if ds.ds_step_raw(gs[t % 2].data_ptr(), gs[t % 2].stride(0), 2) != b.DS_OK:
+                failed.append(t)
+            meet.wait(30)
+            if first:
+                torch.cuda.synchronize()
+                took.append(time.perf_counter() - began)
+
+    threads = [threading.Thread(target=work, args=(ds, gs, q == 0)) for q, (ds, gs) in enumerate(zip(dss, ups))]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join(60)
+    assert not failed and not any(th.is_alive() for th in threads)
+    say("ms:", [round(1e3 * t, 2) for t in took])
+    assert sorted(took[2:])[-3] < 5e-3, took
+    st = oracle_state(ws[3])
+    for t in range(steps):
+        oracle.step(st, wl.gradient(ws[3], t % 2), want_cv=False, want_msg=False)
+    x, d = dss[3].ds_read_state()
+    for ds in dss:
+        assert ds.ds_step_count() == steps
+        ds.ds_destroy()
+    assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
+
+
 @pytest.mark.parametrize("kind,kw", KINDS)
 def test_one_launch_and_chain_take_turns(kind, kw):
     """A handle whose stream finds no room next to two others takes the launches of large problems, and one launch again on a stream
