@@ -26,7 +26,7 @@
 // L2 hits), quantize 4 B read + b/8 B written: 24 B + codes against the 20 B + b/8 B any
 // implementation must move.  Where the state is completed after every step (a training loop), form moves 16 B and the tail
 // another 16 B: 32 B + codes.  16 workers x 11,173,962 parameters at 2 bits: form 612 -> 474 us since delta stays in place,
-// tail 562 -> 522 us with all loads ahead of the stores (5.5 TB/s), the whole step 1207 -> 1048 us.
+// tail 562 -> 522 us with all loads ahead of the stores (5.5 TB/s; not everywhere, see tail_ahead), the whole step 1207 -> 1048 us.
 //
 // Speculative codes (what makes the second dense pass unnecessary in steady state).  The code of an
 // element depends on the row's range s only through inv = (L/2)/s, and is monotone in it.  `form`
@@ -459,9 +459,11 @@ __global__ void __launch_bounds__(LQ_ROW_THREADS) l2q_row_unit(L2Args a, L2Scrat
     }
 }
 
-// The tail on its own (l2q_flush): delta = v - C[v], x = xh + eta sum_j a_ij C[v_j].
-template <int BITS>
+// The tail on its own (l2q_flush): delta = v - C[v], x = xh + eta sum_j a_ij C[v_j].  AHEAD: iterations whose loads go out
+// ahead of the first store of theirs, all four (70 registers, seven workgroups on a compute unit) or two (48, eight); see tail_ahead.
+template <int BITS, int AHEAD>
 __global__ void __launch_bounds__(LQ_THREADS) l2q_tail(L2Args a, L2Scratch s) {
+    static_assert(LQ_ITERS % AHEAD == 0, "whole groups of iterations");
     const uint32_t pending = *s.pending;
     if (pending == 0u) return;
     const int row = blockIdx.y;
@@ -469,21 +471,24 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_tail(L2Args a, L2Scratch s) {
     const uint8_t* msg_last = a.msg + (uint64_t)last_half(a) * a.msg_half;
     float* xr = a.x + (uint64_t)row * a.ld;
     float* dr = a.delta + (uint64_t)row * a.ld;
-    float4 xs[LQ_ITERS], ds[LQ_ITERS];                    // all loads ahead of the first store, as in l2q_form
 #pragma unroll
-    for (int it = 0; it < LQ_ITERS; ++it) {
-        const uint64_t col = col0 + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x;   // rows are padded to whole chunks
-        xs[it] = ld4_stream(xr + col);
-        ds[it] = ld4_stream(dr + col);
-    }
+    for (int i0 = 0; i0 < LQ_ITERS; i0 += AHEAD) {
+        float4 xs[AHEAD], ds[AHEAD];
 #pragma unroll
-    for (int it = 0; it < LQ_ITERS; ++it) {
-        const uint64_t col = col0 + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x;
-        if (col >= a.N) continue;
-        if (pending == 2u) add4(ds[it], xs[it]);
-        apply_tail4<BITS>(a, s, msg_last, row, col, xs[it], ds[it]);
-        st4_stream(xr + col, xs[it]);
-        st4_stream(dr + col, ds[it]);
+        for (int u = 0; u < AHEAD; ++u) {
+            const uint64_t col = col0 + (uint64_t)(i0 + u) * (4 * LQ_THREADS) + 4u * threadIdx.x;   // rows are padded to whole chunks
+            xs[u] = ld4_stream(xr + col);
+            ds[u] = ld4_stream(dr + col);
+        }
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const uint64_t col = col0 + (uint64_t)(i0 + u) * (4 * LQ_THREADS) + 4u * threadIdx.x;
+            if (col >= a.N) continue;
+            if (pending == 2u) add4(ds[u], xs[u]);
+            apply_tail4<BITS>(a, s, msg_last, row, col, xs[u], ds[u]);
+            st4_stream(xr + col, xs[u]);
+            st4_stream(dr + col, ds[u]);
+        }
     }
 }
 
@@ -807,15 +812,33 @@ ds_status l2q_create(const ds_config& cfg, uint64_t ld, bool resident, bool impa
     return DS_OK;
 }
 
-static ds_status apply_tail(L2State* st, const L2Args& a, hipStream_t stream) {
-    const L2Scratch& s = st->s;
+// How many iterations' loads the tail of so many workgroups asks for together.  Step with the state complete after it, in
+// units of the time with one iteration at a time: four are ahead while the GPU holds all workgroups at once (11 x 400,000: 0.90,
+// two 1.00) and, where bytes bound it, at 2 and 4 bits (16 x 11,173,962: 0.86 and 0.98, two 0.88 and 0.99).  Two are ahead where
+// only eight to a compute unit hold all (8 x 1,000,000 at 8 bits: 1.00 to 1.02, four 1.03), and at 8 bits, whose codes are the
+// most bytes asked for on top, beyond two rounds of seven (8 x 2,000,000: 1.01, four 1.03; 31 x 3,298,574 with five neighbours: 1.00
+// and 1.03; but 60 x 200,000, in less than two rounds: 0.99 and 0.97).
+static int tail_ahead(uint64_t workgroups, int bits) {
+    constexpr uint64_t kCus = 256, kFour = 7 * kCus, kTwo = 8 * kCus;        // workgroups the GPU holds at once
+    if (workgroups <= kFour) return 4;
+    if (workgroups <= kTwo) return 2;
+    return bits == 8 && workgroups > 2 * kFour ? 2 : 4;
+}
+
+template <int BITS>
+static void launch_tail(const L2Args& a, const L2Scratch& s, hipStream_t stream) {
     const dim3 grid(s.nchunks, a.n), block(LQ_THREADS);
+    if (tail_ahead((uint64_t)s.nchunks * (uint64_t)a.n, BITS) == 4) hipLaunchKernelGGL((l2q_tail<BITS, 4>), grid, block, 0, stream, a, s);
+    else hipLaunchKernelGGL((l2q_tail<BITS, 2>), grid, block, 0, stream, a, s);
+}
+
+static ds_status apply_tail(L2State* st, const L2Args& a, hipStream_t stream) {
     // the kernels look at the device's pending flag themselves: a replayed graph of ds_step sets it
     // without this code noticing
-    if (st->bits == 2)      hipLaunchKernelGGL(l2q_tail<2>, grid, block, 0, stream, a, s);
-    else if (st->bits == 4) hipLaunchKernelGGL(l2q_tail<4>, grid, block, 0, stream, a, s);
-    else                    hipLaunchKernelGGL(l2q_tail<8>, grid, block, 0, stream, a, s);
-    hipLaunchKernelGGL(l2q_clear_pending, dim3(1), dim3(1), 0, stream, s);
+    if (st->bits == 2)      launch_tail<2>(a, st->s, stream);
+    else if (st->bits == 4) launch_tail<4>(a, st->s, stream);
+    else                    launch_tail<8>(a, st->s, stream);
+    hipLaunchKernelGGL(l2q_clear_pending, dim3(1), dim3(1), 0, stream, st->s);
     return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
 }
 

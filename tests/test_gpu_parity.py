@@ -852,6 +852,13 @@ def test_deferred_tails_by_what_meets_them(w, order):
     ds.ds_destroy()
 
 
+@pytest.mark.parametrize("n,N,bits", [(64, 4096 * 27 + 5, 4), (64, 4096 * 28 + 5, 4), (64, 4096 * 32 + 5, 4), (64, 4096 * 32 + 5, 8), (64, 4096 * 56 + 5, 8),
+                                      (64, 4096 * 28 + 5, 2)])
+def test_l2norm_tails_by_number_of_workgroups(n, N, bits):
+    """The tail on its own, by how many of its workgroups the GPU holds at once: up to 1792, up to 2048, up to 3584 and more."""
+    lock_step(small(wl.KIND_QUANT_L2NORM, n, N, bits=bits), steps=2, plan={"variant": 2})
+
+
 @pytest.mark.parametrize("bits,grad", [(2, "normal"), (2, "quadratic"), (4, "normal"), (8, "normal")])
 @pytest.mark.parametrize("variant", [2, 0])
 def test_l2norm_speculative_codes_steady_state(bits, grad, variant):
