@@ -187,9 +187,13 @@ typedef struct {
                           /*    library cannot see that (several processes, graphs replayed on more than one stream,   */
                           /*    streams that may not use every compute unit): a step whose workgroups cannot all run   */
                           /*    waits for 10 ms and then takes some 10 ms more.  3: that kernel, but its workgroups do */
-                          /*    not wait for each other at all, so that the last one does the step alone (tests)       */
-    int32_t tile_plan;    /* -1: automatic; i >= 0 pins the i-th candidate launch shape of the fused kernel      */
-                          /*    (an index past the last candidate leaves the choice automatic)                   */
+                          /*    not wait for each other at all, so that the last one does the step alone; where the rows   */
+                          /*    of a tile are split over workgroups, one of them does them all (tests)                 */
+    int32_t tile_plan;    /* -1: automatic; i >= 0 pins the i-th candidate launch shape of the fused kernel, and behind  */
+                          /*    those the shapes that split the rows of a tile over several workgroups (an index past     */
+                          /*    the last candidate leaves the choice automatic).  With the row-streaming variant: 0: no    */
+                          /*    step is finished in its own launch; i >= 1: the i-th split shape finishes steps after each   */
+                          /*    of which x is read                                                               */
     int64_t pitch_skew;   /* -1: automatic; else floats added to the padded row length of x and delta:          */
                           /*    a multiple of 4, at most 12288                                                   */
     int32_t autotune;     /* 1: time the candidates at init (large problems only); 0: first candidate, default   */

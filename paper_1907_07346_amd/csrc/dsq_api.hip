@@ -28,6 +28,13 @@ struct ds_handle {
                                          // step's kernels; the rest: the tile kernel's finished-workgroup counters
     dsq::TilePlan tile;
     std::vector<dsq::TilePlan> tile_candidates;
+    dsq::TilePlan team;                  // row-streaming plan: what takes a step whole (launch == nullptr: nothing does)
+    unsigned long long* d_team = nullptr;    // arrival counters of the team kernels
+    bool impatient = false;              // ... whose workgroups then look for parts nobody works on at once (tests)
+    // Row-streaming plan: steps since x and delta were last asked for, and how many there were between the last two times.
+    uint64_t run = 0, period = 1;
+    bool complete = true;                // x and delta are complete once everything enqueued has run
+    enum { kFree, kWhole, kStreamed } captured = kFree;   // how the steps go that a graph may replay unseen, and all others with them
     dsq::TopkState* topk = nullptr;
     dsq::L2State* l2q = nullptr;
     bool resident = false;               // steps may take one launch ...
@@ -127,6 +134,7 @@ void release(ds_handle* h) {
     if (h->msg) (void)hipFree(h->msg);
     if (h->d_rowptr) (void)hipFree(h->d_rowptr);   // d_col and d_coef point into the same allocation
     if (h->d_t) (void)hipFree(h->d_t);
+    if (h->d_team) (void)hipFree(h->d_team);
     if (h->d_keep) (void)hipFree(h->d_keep);
     delete h;
 }
@@ -167,7 +175,11 @@ ds_status flush_deferred(ds_handle* h) {
     if (h->topk) return dsq::topk_flush(h->topk, topk_args(h, nullptr, 0), h->last_stream);
     if (h->l2q) return dsq::l2q_flush(h->l2q, l2_args(h, nullptr, 0), h->last_stream);
     if (h->tile.streaming && h->stepped) {
+        if (h->run) h->period = h->run;
+        h->run = 0;
+        if (h->complete && h->captured != ds_handle::kStreamed) return DS_OK;
         h->tile.flush(tile_args(h, nullptr, 0), h->last_stream);
+        h->complete = true;
         return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
     }
     return DS_OK;
@@ -183,6 +195,9 @@ dsq::TileArgs tile_args(const ds_handle* h, const float* g_dev, uint64_t g_ld) {
     a.seed_lo = (uint32_t)h->cfg.seed; a.seed_hi = (uint32_t)(h->cfg.seed >> 32); a.t_ptr = h->d_t;
     a.msg_half = h->msg_half;
     a.pending = reinterpret_cast<uint32_t*>(h->d_t + 3);        // cell 3: the row-streaming variant's pending flag
+    a.team_cells = h->d_team;
+    a.team_patience = h->impatient ? 0 : dsq::kTeamPatienceTicks;
+    a.team_solo = h->impatient ? 1u : 0u;
     if (h->cfg.comp.kind == DS_COMP_RAND_SPARSE) {
         a.keep_off = h->d_keep;
         a.keep_group_off = h->d_keep + (size_t)h->cfg.n * h->nsweeps;
@@ -195,6 +210,14 @@ dsq::TileArgs tile_args(const ds_handle* h, const float* g_dev, uint64_t g_ld) {
     return a;
 }
 
+dsq::TileArgs plan_args(const ds_handle* h, const dsq::TilePlan& plan, const float* g_dev, uint64_t g_ld) {
+    dsq::TileArgs a = tile_args(h, g_dev, g_ld);
+    a.team_rows = plan.team_rows;
+    a.team_slots = plan.team_slots;
+    a.team_edges = plan.team_edges;
+    return a;
+}
+
 // Row pitch candidates (floats added to N rounded up to kPitchAlign).  A tile kernel has all n rows
 // of a column window in flight at once, so how the row pitch falls on the HBM channel hash decides
 // up to 12 % of the achieved bandwidth, and the best pitch differs between shapes and GPUs.  ds_init
@@ -202,9 +225,24 @@ dsq::TileArgs tile_args(const ds_handle* h, const float* g_dev, uint64_t g_ld) {
 const uint64_t kPitchCandidates[] = {0, 2560, 4096, 6656, 8192, 12288};
 constexpr uint64_t kMaxPitchSkew = 12288;
 
+// Arrival counters for the narrowest tiles of any candidate.
+size_t team_bytes(const ds_handle* h) {
+    uint64_t tiles = 0;
+    auto most = [&](const dsq::TilePlan& p) {
+        if (!p.team) return;
+        const uint64_t t = (h->cfg.N + p.tile_cols - 1) / p.tile_cols;
+        tiles = t > tiles ? t : tiles;
+    };
+    for (const dsq::TilePlan& p : h->tile_candidates) most(p);
+    most(h->tile);
+    most(h->team);
+    return tiles ? (size_t)(tiles + 1) * dsq::kTeamCellBytes : 0;
+}
+
 // Times `plan` at the current h->ld on the all-zero state (3 launches, twice, after a warm-up); < 0 on failure.
 float time_plan(ds_handle* h, const dsq::TilePlan& plan, const float* g, hipEvent_t e0, hipEvent_t e1) {
-    const dsq::TileArgs a = tile_args(h, g, h->ld);
+    const dsq::TileArgs a = plan_args(h, plan, g, h->ld);
+    if (plan.team && hipMemset(h->d_team, 0, team_bytes(h)) != hipSuccess) return -1.f;   // another plan's parts may be another number
     plan.launch(a, plan.rows_per_wave, nullptr);
     float best = 1e30f;
     for (int rep = 0; rep < 2; ++rep) {                        // the better of two timings: less noise in the choice
@@ -256,6 +294,7 @@ uint64_t autotune(ds_handle* h, uint64_t base_ld, size_t state_bytes, size_t msg
     (void)hipMemset(h->msg, 0, msg_bytes ? msg_bytes : 4);
     (void)hipMemset(h->d_t, 0, dsq::kStepCells * sizeof(unsigned long long));   // the timed launches advanced t
     (void)hipMemset(h->d_t + 2, 0xFF, sizeof(unsigned long long));              // ... and no keep counts are valid
+    if (h->d_team) (void)hipMemset(h->d_team, 0, team_bytes(h));
     (void)hipDeviceSynchronize();
     if (!ok) h->tile = h->tile_candidates.front();
     return ok ? best_skew : dsq::kPitchSkew;
@@ -271,8 +310,8 @@ uint64_t autotune(ds_handle* h, uint64_t base_ld, size_t state_bytes, size_t msg
 //     the tiles, which decode the neighbours from memory: with up to 5 neighbours (own included) 0.75 to 1.00 while the
 //     last wave leaves a sixteenth of them all free (one point of 544 at 1.03) and up to 1.12 when it is full; with 9, 0.79
 //     to 0.99 while three sixteenths are free; with 17 up to 1.22.  256 workers x 272,474, torus, 4 bits: 412
-//     us fused, 345 streaming.
-// In between, and with blocks of up to 256 columns (100 x 100,000 at 4 bits: 52 us fused, 65 streaming), the fused kernel stays.
+//     us fused, 345 streaming (246 back to back).  Such a handle takes a step whole where that is faster: whole_steps_faster.
+// In between, and with blocks of up to 256 columns (100 x 100,000 at 4 bits: 52 us fused, 65 streaming), nothing is left to the next step.
 // The graph is the one the handle is made with: a later ds_set_mixing changes no plan.
 bool streams_faster(const ds_config& cfg, uint64_t entries) {
     if (cfg.comp.kind != DS_COMP_QUANT_MAXABS && cfg.comp.kind != DS_COMP_SIGN_MEANABS) return false;
@@ -282,6 +321,38 @@ bool streams_faster(const ds_config& cfg, uint64_t entries) {
     if (tiles <= 128) return tiles <= 112 || n >= 96 || near;
     if (tiles <= 512 || n < 192 || entries > 9 * n) return false;
     return 16 * tiles <= (near ? 15u : 13u) * ((tiles + 255) / 256 * 256);
+}
+
+// The team shape for a handle: most rows in a workgroup while there are two workgroups per compute unit, or four where a lane
+// holds sixteen float4 of x - gamma g.  (4 bits, blocks of 512, rows in a workgroup 8 / 16 / 32, state complete after every step: 100 workers x
+// 2,621 10.8 / 13.6 / 17.4 us, 256 x 16,384 29.3 / 24.4 / 26.3, 256 x 262,144 319 / 277 / 271.)
+dsq::TilePlan best_team(const std::vector<dsq::TilePlan>& teams, const ds_config& cfg) {
+    for (const dsq::TilePlan& p : teams) {
+        const uint64_t tiles = (cfg.N + p.tile_cols - 1) / p.tile_cols, parts = (cfg.n + p.team_rows - 1) / p.team_rows;
+        if (tiles * parts >= (p.rows_per_wave * p.sweeps > 8 ? 1024u : 512u)) return p;
+    }
+    return teams.empty() ? dsq::TilePlan() : teams.back();
+}
+
+// A handle of the row-streaming plan whose x is read after every step: is the step in one launch faster than the streaming pass and
+// the gossip sum on its own?  4 bits, blocks of 512: 100 workers x 41,943 26.1 us and 26.9, 280 x 3,744 15.1 and 13.1, 280 x 59,918 80
+// and 91, 256 x 272,474 293 and 345; blocks of 2048, which leave one workgroup or two to a compute unit: 100 x 167,772 94 and 92, x 671,088
+// 292 and 332.
+bool whole_steps_faster(const ds_config& cfg, const dsq::TilePlan& stream) {
+    return (uint64_t)cfg.n * cfg.N >= (stream.sweeps == 8 ? 32ull << 20 : 8ull << 20);
+}
+
+// Is it faster than the fused kernel of shape `fused`?  Where that forms its rows twice: 100 x 671,088 357 us fused, 265 as teams; 256 x
+// 1,024 61 and 12; but 124 and 139 (64 x 400,000, 8 bits, blocks of 2048) and 76 and 78 (256 x 65,536, sign, blocks of 64) where
+// there is a workgroup for nearly every compute unit and the second forming reads the memory-side cache (100 x 500,000 does
+// not fit there: 240 and 213).  Where registers hold the rows, only if
+// there are few tiles of many rows: 64 x 16,384 (32 tiles) 19 and 11, 48 x 87,381 (171 tiles) 18 and 25; not for tiles of one
+// sweep, whose sixteen-wave shape takes 7 to 8 us (9 as teams).
+bool teams_faster(const ds_config& cfg, const dsq::TilePlan& fused) {
+    const uint64_t tiles = (cfg.N + fused.tile_cols - 1) / fused.tile_cols;
+    const bool cached = (uint64_t)cfg.n * cfg.N <= (28u << 20);              // x and g fit in the memory-side cache
+    if (std::strstr(fused.name, "looped")) return !((fused.sweeps == 1 || fused.sweeps == 8) && tiles >= 160 && tiles <= 256 && cached);
+    return cfg.n > 32 && fused.sweeps >= 2 && tiles <= 64;
 }
 
 // Diagnostics (off the hot path); fp64 accumulation.  The three sums of a workgroup are added to one of kDiagCells cells of
@@ -584,15 +655,27 @@ ds_status ds_init_ex(const ds_config* cfg, const ds_plan_request* plan, char* er
         const bool can_stream = dsq::stream_plan(h->cfg, sp);
         const bool fits = dsq::choose_tile_plans(h->cfg, (int)h->graph.col.size(), h->tile_candidates, err);
         const bool many_rows = want.tile_plan < 0 && streams_faster(*cfg, h->graph.col.size());
+        std::vector<dsq::TilePlan> teams;
         if (can_stream && (!fits || want.variant == 1 || many_rows)) {
             h->tile_candidates.assign(1, sp);
             h->msg_half = (uint64_t)cfg->n * h->msg_row_bytes;
+            dsq::team_plans(h->cfg, h->graph, teams);
+            if (want.tile_plan > 0 && (size_t)want.tile_plan <= teams.size()) h->team = teams[(size_t)want.tile_plan - 1];
+            else if (want.tile_plan != 0 && whole_steps_faster(*cfg, sp)) h->team = best_team(teams, *cfg);
         } else if (!fits) {
             return bail(DS_EINVAL, err);
+        } else {
+            dsq::team_plans(h->cfg, h->graph, teams);
+            const size_t pinnable = h->tile_candidates.size() + teams.size();
+            if (want.tile_plan >= 0 && (size_t)want.tile_plan < pinnable)
+                for (const dsq::TilePlan& p : teams) h->tile_candidates.push_back(p);
+            else if (!teams.empty() && teams_faster(*cfg, h->tile_candidates.front()))
+                h->tile_candidates.assign(1, best_team(teams, *cfg));
         }
+        h->impatient = want.variant == 3;
         h->tile = h->tile_candidates.front();
         // a pinned candidate launch shape (tests walk through all of them; an index past the end leaves the choice automatic)
-        if (want.tile_plan >= 0 && (size_t)want.tile_plan < h->tile_candidates.size()) {
+        if (!h->tile.streaming && want.tile_plan >= 0 && (size_t)want.tile_plan < h->tile_candidates.size()) {
             h->tile = h->tile_candidates[(size_t)want.tile_plan];
             h->tile_candidates.assign(1, h->tile);
         }
@@ -620,6 +703,12 @@ ds_status ds_init_ex(const ds_config* cfg, const ds_plan_request* plan, char* er
               hipMemcpy(h->d_coef, h->graph.coef.data(), nnz * sizeof(float), hipMemcpyHostToDevice) == hipSuccess &&
               hipDeviceSynchronize() == hipSuccess;
     if (!ok) return bail(DS_EHIP, "device initialisation failed");
+    if (const size_t bytes = team_bytes(h)) {
+        if (hipMalloc(&h->d_team, bytes) != hipSuccess || hipMemset(h->d_team, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+            (void)hipGetLastError();
+            return bail(DS_ENOMEM, "allocating the arrival counters failed");
+        }
+    }
     if (cfg->comp.kind == DS_COMP_RAND_SPARSE) {
         h->nsweeps = (cfg->N + dsq::kSweep - 1) / dsq::kSweep;
         h->ngroups = (h->nsweeps + 15) / 16;
@@ -675,13 +764,28 @@ ds_status ds_step(ds_handle* h, const float* g_dev, uint64_t g_ld, void* hip_str
         const ds_status st = dsq::l2q_step(h->l2q, l2_args(h, g_dev, g_ld), seated(h, stream), stream);
         if (st != DS_OK) return fail(h, st, "launching the norm-rescaled step failed");
     } else {
-        const dsq::TileArgs a = tile_args(h, g_dev, g_ld);
         if (h->cfg.comp.kind == DS_COMP_RAND_SPARSE) {
+            const dsq::TileArgs a = tile_args(h, g_dev, g_ld);
             uint32_t* groups = h->d_keep + (size_t)h->cfg.n * h->nsweeps;
             uint32_t* prev = groups + (size_t)h->cfg.n * h->ngroups;
             dsq::launch_keep_offsets(a, h->d_keep, groups, prev, prev + h->cfg.n, stream);
         }
-        h->tile.launch(a, h->tile.rows_per_wave, stream);
+        if (h->tile.streaming) {
+            // Where x is read after every step, a step is taken whole; where several follow one another, each leaves its gossip
+            // sum to the next one's pass, which reads x anyway.  A step that is captured may be replayed between any others:
+            // the way of the first one that is captured is the way of all that follow.
+            hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(stream, &status) != hipSuccess) { (void)hipGetLastError(); status = hipStreamCaptureStatusActive; }
+            h->run += 1;
+            bool whole = h->team.launch && h->complete && h->run == 1 && h->period == 1;
+            if (h->captured != ds_handle::kFree) whole = h->captured == ds_handle::kWhole;
+            else if (status != hipStreamCaptureStatusNone) h->captured = whole ? ds_handle::kWhole : ds_handle::kStreamed;
+            const dsq::TilePlan& plan = whole ? h->team : h->tile;
+            plan.launch(plan_args(h, plan, g_dev, g_ld), plan.rows_per_wave, stream);
+            h->complete = whole;
+        } else {
+            h->tile.launch(plan_args(h, h->tile, g_dev, g_ld), h->tile.rows_per_wave, stream);
+        }
     }
     DSQ_HIP(h, hipGetLastError());
     h->t += 1;
@@ -704,7 +808,9 @@ ds_status ds_set_mixing(ds_handle* h, const int32_t* W_rowptr, const int32_t* W_
         // the launch shape was chosen for the old graph; the new CSR only has to fit in LDS next to the codes
         std::vector<dsq::TilePlan> plans;
         if (!dsq::choose_tile_plans(h->cfg, (int)nnz, plans, err)) return fail(h, DS_EINVAL, err);
+        if (h->tile.team && !dsq::fit_team(g, h->tile)) h->tile = plans.front();
     }
+    if (h->team.launch && !dsq::fit_team(g, h->team) && h->captured != ds_handle::kWhole) h->team = dsq::TilePlan();
     // a deferred tail belongs to the old W: apply it first
     if (flush_deferred(h) != DS_OK) return fail(h, DS_EHIP, "applying the deferred tail of the last step failed");
     DSQ_HIP(h, hipStreamSynchronize(h->last_stream));

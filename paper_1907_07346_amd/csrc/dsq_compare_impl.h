@@ -231,7 +231,7 @@ __global__ void __launch_bounds__(NW* kWave) compare_tile_kernel(TileArgs a, int
     // The step counter (read by the rounding words of phase 1 / phase 2) is advanced by the last workgroup to
     // finish; every wave of this workgroup must be done with it first.
     __syncthreads();
-    step_counter_bump<KIND, BITS, B, SW, NW>(a, tile, (unsigned long long)gridDim.x * gridDim.y, false);
+    step_counter_bump<KIND, BITS, B, SW, NW>(a, tile, (unsigned long long)gridDim.x * gridDim.y, -1);
 }
 
 template <int KIND, int BITS, int B, int SW, int NW, int RPW, int ALGO>
@@ -367,7 +367,7 @@ __global__ void __launch_bounds__(NW* kWave) dcd_ahead_kernel(TileArgs a) {
     if (whole * C::TC < a.N && blockIdx.x == (unsigned)(whole % gridDim.x))            // uniform over the workgroup
         C::template run<kAlgoDcd, RPW, false>(a, 0, whole * C::TC, lds);
     __syncthreads();                                                 // every wave has read the step counter for the last time
-    step_counter_bump<KIND, BITS, B, SW, NW>(a, blockIdx.x, gridDim.x, false, queue);
+    step_counter_bump<KIND, BITS, B, SW, NW>(a, blockIdx.x, gridDim.x, -1, queue);
 }
 
 template <int KIND, int BITS, int B, int SW, int NW, int RPW, bool SPARE>

@@ -63,6 +63,8 @@ ds_status validate_config(const ds_config* cfg, std::string& err, std::string* w
 ds_status build_graph(const ds_config* cfg, Graph& g, std::string& err);
 uint64_t message_row_bytes(const ds_config* cfg);
 
+constexpr uint64_t kTeamCellBytes = 512;  // see TileArgs::team_cells
+
 // Arguments of the fused tile kernels (block quantiser / sign / identity).
 struct TileArgs {
     float* x;                  // n x ld
@@ -97,6 +99,13 @@ struct TileArgs {
                                        // to hand out, counted from the grid size); [32 (1+c)], c < 64: finished
                                        // workgroups with blockIdx % 64 == c.
                                        // Cells [1], [16] and [32 (1+c)] are zero between launches.
+    // teams of workgroups only (dsq_team_impl.h):
+    unsigned long long* team_cells;    // kTeamCellBytes for the launch and for each tile: counters that are never set back
+    uint64_t team_patience;            // ticks a workgroup waits before it looks for parts nobody has claimed
+    uint32_t team_parts;               // workgroups that share a tile (set by the launch) ...
+    int team_rows;                     // ... the rows of each, ...
+    int team_slots, team_edges;        // ... the neighbours it has room to fetch, and the entries of W - I it has room for
+    uint32_t team_solo;                // tests: one workgroup of each tile works, and finds the other parts unclaimed
 };
 
 // The fused tile kernel without anything in device memory beside the caller's arrays (t_ptr and rowptr are nullptr).
@@ -119,6 +128,10 @@ struct TilePlan {
     // pending sum now.
     bool streaming = false;
     void (*flush)(const TileArgs&, hipStream_t) = nullptr;
+    // The rows of a tile are split over several workgroups: see TileArgs::team_*.
+    bool team = false;
+    int team_rows = 0, team_slots = 0, team_edges = 0;
+    size_t (*lds)(int n, int rows, int slots, int edges) = nullptr;
 };
 
 // Random sparsifier: makes sure the kept-element counts of this step's 256-column sweeps are in keep_raw (the tile
@@ -133,6 +146,14 @@ uint64_t rand_sparse_capacity(uint64_t N, uint64_t k);
 
 // The row-streaming plan of a block compressor (quantiser or sign); false if the compressor has none.
 bool stream_plan(const ds_config& cfg, TilePlan& plan);
+
+// The shapes that split the rows of a tile over several workgroups, most rows per workgroup first; none where one holds them all
+// or a tile has too many.
+void team_plans(const ds_config& cfg, const Graph& graph, std::vector<TilePlan>& plans);
+// Makes the shape's LDS large enough for the graph; false if there is not that much.
+bool fit_team(const Graph& graph, TilePlan& plan);
+extern const uint64_t kTeamPatienceTicks;
+constexpr size_t kMaxLds = 160 * 1024;    // of a workgroup
 
 // Lists the variants that fit (n, compressor), best guess first; returns false with `err` set if none does.
 bool choose_tile_plans(const ds_config& cfg, int nnz, std::vector<TilePlan>& plans, std::string& err);

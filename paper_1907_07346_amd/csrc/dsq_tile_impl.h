@@ -162,8 +162,14 @@ struct Tile {
     }
 
     // ---- line 9 of the PREVIOUS step for one row of a tile, decoding the neighbours' codes from that step's
-    //      messages in HBM (row-streaming variant: nothing is shared through LDS): x = xh + eta sum_j a_ij C[v_j]
-    template <bool FULL>
+    //      messages in HBM (row-streaming variant: nothing is shared through LDS): x = xh + eta sum_j a_ij C[v_j].  NOW: line 9
+    //      of this step, from messages that other workgroups have stored in this launch.
+    template <bool NOW, typename V>
+    static __device__ __forceinline__ V fetched(const V* p) {
+        if constexpr (NOW) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else return *p;
+    }
+    template <bool FULL, bool NOW = false>
     static __device__ __forceinline__ void gossip_from_messages(const TileArgs& a, int i, uint64_t col0, int lane, float4 (&x)[SW]) {
         static_assert(KIND == DS_COMP_QUANT_MAXABS || KIND == DS_COMP_SIGN_MEANABS || KIND == DS_COMP_IDENTITY,
                       "messages of this operator cannot be decoded per column");
@@ -174,7 +180,7 @@ struct Tile {
         for (int e = e0; e < e1; ++e) {                         // ascending neighbour index, own index included
             const int nb = a.col[e];
             const float w = a.coef[e];
-            const uint8_t* nrow = a.msg_prev + (uint64_t)nb * a.msg_row_bytes;
+            const uint8_t* nrow = (NOW ? a.msg : a.msg_prev) + (uint64_t)nb * a.msg_row_bytes;
 #pragma unroll
             for (int s = 0; s < SW; ++s) {
                 const uint64_t j = col0 + (uint64_t)s * kSweep + 4 * lane;
@@ -183,7 +189,7 @@ struct Tile {
                     const float* vrow = reinterpret_cast<const float*>(nrow);
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        const float cv = (FULL || j + c < a.N) ? vrow[j + c] : 0.f;
+                        const float cv = (FULL || j + c < a.N) ? fetched<NOW>(vrow + j + c) : 0.f;
                         acc[s][c] = fmaf(w, cv, acc[s][c]);
                     }
                     continue;
@@ -191,12 +197,12 @@ struct Tile {
                 const uint64_t bcol0 = SUB ? col0 + (uint64_t)s * kSweep + (uint64_t)(lane / G) * B
                                            : col0 + (uint64_t)(s / SPB) * B;
                 const uint8_t* blk = nrow + (bcol0 / B) * MSG_BLOCK_BYTES;
-                const float scale = *reinterpret_cast<const float*>(blk);
+                const float scale = fetched<NOW>(reinterpret_cast<const float*>(blk));
                 const int slot = SUB ? lane % G : (s % SPB) * kWave + lane;     // lane-slot inside the block
                 if constexpr (KIND == DS_COMP_QUANT_MAXABS) {
                     using lane_t = typename CT::lane_t;
                     const float unit = scale / (float)L;
-                    const uint32_t codes = reinterpret_cast<const lane_t*>(blk + 4)[slot];
+                    const uint32_t codes = fetched<NOW>(reinterpret_cast<const lane_t*>(blk + 4) + slot);
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
                         const int q = (int)((codes >> (BITS * c)) & (uint32_t)L);
@@ -205,7 +211,7 @@ struct Tile {
                         acc[s][c] = fmaf(w, cv, acc[s][c]);
                     }
                 } else {
-                    const uint32_t word = reinterpret_cast<const uint32_t*>(blk + 4)[slot >> 3];
+                    const uint32_t word = fetched<NOW>(reinterpret_cast<const uint32_t*>(blk + 4) + (slot >> 3));
                     const uint32_t nib = word >> (4 * (lane & 7));
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
@@ -234,10 +240,18 @@ struct Tile {
     // What a row keeps of an element after C[v] is known.  MODE 0, Algorithm 1 line 6: the residual v - C[v].
     // MODE 1 and 2 serve the comparison updates (dsq_compare_impl.h): `base` + C[v], where base is the worker's
     // public copy (MODE 1, the new copy also goes to LDS as fp32 for the gossip phase) or its model (MODE 2).
+    // MODE 3 is MODE 0 in a launch whose other workgroups read the message (dsq_team_impl.h).
+    static constexpr bool residual(int mode) { return mode == 0 || mode == 3; }
     template <int MODE>
     static __device__ __forceinline__ float kept(float vc, float cv, float base) {
-        if constexpr (MODE == 0) return vc - cv;                     // line 6: delta = v - C[v]
+        if constexpr (residual(MODE)) return vc - cv;                // line 6: delta = v - C[v]
         else return base + cv;
+    }
+    // A store to the message.  MODE 3: past this XCD's L2, which is not coherent with the others' before the kernel ends.
+    template <int MODE, typename V>
+    static __device__ __forceinline__ void put(V* p, V v) {
+        if constexpr (MODE == 3) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else *p = v;
     }
 
     template <bool FULL, int MODE = 0>
@@ -261,8 +275,8 @@ struct Tile {
                 const float unit = scale / (float)L;
                 const float inv = (scale > 0.f) ? hl / scale : 0.f;
                 if (in_blk == 0) {
-                    if constexpr (MODE == 0) lds_units[li * BPT + s * BPS + grp] = unit;
-                    if (block_live) *reinterpret_cast<float*>(msg_blk) = scale;
+                    if constexpr (residual(MODE)) lds_units[li * BPT + s * BPS + grp] = unit;
+                    if (block_live) put<MODE>(reinterpret_cast<float*>(msg_blk), scale);
                 }
                 uint32_t rnd[4];
                 philox4x32_10((uint32_t)(j >> 2), (uint32_t)i, t_lo, kQuantStreamTag, a.seed_lo, a.seed_hi, rnd);
@@ -287,16 +301,16 @@ struct Tile {
                 }
                 st4(dout + s * kSweep, dnew);
                 using lane_t = typename CT::lane_t;
-                if constexpr (MODE == 0) reinterpret_cast<lane_t*>(lds_row)[s * kWave + lane] = (lane_t)codes;
+                if constexpr (residual(MODE)) reinterpret_cast<lane_t*>(lds_row)[s * kWave + lane] = (lane_t)codes;
                 if constexpr (MODE == 1) reinterpret_cast<float4*>(lds_row)[s * kWave + lane] = dnew;
                 const uint32_t word = (uint32_t)in_blk * (uint32_t)sizeof(lane_t) / 4u;
-                if (FULL || word < nwords) reinterpret_cast<lane_t*>(msg_blk + 4)[in_blk] = (lane_t)codes;
+                if (FULL || word < nwords) put<MODE>(reinterpret_cast<lane_t*>(msg_blk + 4) + in_blk, (lane_t)codes);
             } else if constexpr (KIND == DS_COMP_SIGN_MEANABS) {
                 const float sum = group_sum_tree<G>((fabsf(v[s].x) + fabsf(v[s].y)) + (fabsf(v[s].z) + fabsf(v[s].w)));
                 const float scale = block_live ? sum / (float)m : 0.f;
                 if (in_blk == 0) {
-                    if constexpr (MODE == 0) lds_units[li * BPT + s * BPS + grp] = scale;
-                    if (block_live) *reinterpret_cast<float*>(msg_blk) = scale;
+                    if constexpr (residual(MODE)) lds_units[li * BPT + s * BPS + grp] = scale;
+                    if (block_live) put<MODE>(reinterpret_cast<float*>(msg_blk), scale);
                 }
                 uint32_t nib = 0;
                 float4 dnew;
@@ -316,21 +330,28 @@ struct Tile {
                 word |= __shfl_xor(word, 2);
                 word |= __shfl_xor(word, 4);
                 if ((lane & 7) == 0) {
-                    if constexpr (MODE == 0) reinterpret_cast<uint32_t*>(lds_row)[s * 8 + (lane >> 3)] = word;
+                    if constexpr (residual(MODE)) reinterpret_cast<uint32_t*>(lds_row)[s * 8 + (lane >> 3)] = word;
                     const uint32_t widx = (uint32_t)in_blk >> 3;
-                    if (FULL || widx < nwords) reinterpret_cast<uint32_t*>(msg_blk + 4)[widx] = word;
+                    if (FULL || widx < nwords) put<MODE>(reinterpret_cast<uint32_t*>(msg_blk + 4) + widx, word);
                 }
             }
         }
     }
 
+    template <bool FULL>
+    static __device__ __forceinline__ float4 ld_g(const TileArgs& a, const float* p, uint64_t j) {
+        if (FULL) return ld4(p);
+        float4 v;
+        v.x = (j + 0 < a.N) ? p[0] : 0.f;
+        v.y = (j + 1 < a.N) ? p[1] : 0.f;
+        v.z = (j + 2 < a.N) ? p[2] : 0.f;
+        v.w = (j + 3 < a.N) ? p[3] : 0.f;
+        return v;
+    }
+
     // ---- phase 1 for one row: returns xh (x - gamma g) in registers ---------------------------
-    // `li` is the slot of the row in the LDS arrays (the row itself in the fused kernel).  TAIL: x holds the
-    // previous step's x - gamma g and that step's gossip sum is still due (row-streaming variant).
-    template <bool FULL, bool TAIL = false>
-    static __device__ __forceinline__ void compress_row(const TileArgs& a, int i, int li, uint64_t col0, int lane,
-                                                        uint8_t* lds_codes, float* lds_units, float4 (&xh)[SW]) {
-        float4 xv[SW], gv[SW], dv[SW];
+    template <bool FULL>
+    static __device__ __forceinline__ void load_row(const TileArgs& a, int i, uint64_t col0, int lane, float4 (&xv)[SW], float4 (&gv)[SW], float4 (&dv)[SW]) {
         const float* xr = a.x + (uint64_t)i * a.ld + col0 + 4 * lane;
         const float* dr = a.delta + (uint64_t)i * a.ld + col0 + 4 * lane;
         const float* gr = a.g + (uint64_t)i * a.g_ld + col0 + 4 * lane;
@@ -338,16 +359,23 @@ struct Tile {
         for (int s = 0; s < SW; ++s) {
             xv[s] = ld4(xr + s * kSweep);
             dv[s] = ld4(dr + s * kSweep);
-            if (FULL) {
-                gv[s] = ld4(gr + s * kSweep);
-            } else {
-                const uint64_t j = col0 + (uint64_t)s * kSweep + 4 * lane;
-                gv[s].x = (j + 0 < a.N) ? gr[s * kSweep + 0] : 0.f;
-                gv[s].y = (j + 1 < a.N) ? gr[s * kSweep + 1] : 0.f;
-                gv[s].z = (j + 2 < a.N) ? gr[s * kSweep + 2] : 0.f;
-                gv[s].w = (j + 3 < a.N) ? gr[s * kSweep + 3] : 0.f;
-            }
+            gv[s] = ld_g<FULL>(a, gr + s * kSweep, col0 + (uint64_t)s * kSweep + 4 * lane);
         }
+    }
+
+    // `li` is the slot of the row in the LDS arrays (the row itself in the fused kernel).  TAIL: x holds the
+    // previous step's x - gamma g and that step's gossip sum is still due (row-streaming variant).
+    template <bool FULL, bool TAIL = false, int MODE = 0>
+    static __device__ __forceinline__ void compress_row(const TileArgs& a, int i, int li, uint64_t col0, int lane,
+                                                        uint8_t* lds_codes, float* lds_units, float4 (&xh)[SW]) {
+        float4 xv[SW], gv[SW], dv[SW];
+        load_row<FULL>(a, i, col0, lane, xv, gv, dv);
+        compress_loaded<FULL, TAIL, MODE>(a, i, li, col0, lane, xv, gv, dv, lds_codes, lds_units, xh);
+    }
+
+    template <bool FULL, bool TAIL, int MODE>
+    static __device__ __forceinline__ void compress_loaded(const TileArgs& a, int i, int li, uint64_t col0, int lane, float4 (&xv)[SW], const float4 (&gv)[SW],
+                                                           const float4 (&dv)[SW], uint8_t* lds_codes, float* lds_units, float4 (&xh)[SW]) {
         if constexpr (TAIL) {
             if (*a.pending != 0u) gossip_from_messages<FULL>(a, i, col0, lane, xv);
         }
@@ -362,7 +390,7 @@ struct Tile {
 
         uint8_t* lds_row = lds_codes + (size_t)li * ROW_CODE_BYTES;
         float* dout = a.delta + (uint64_t)i * a.ld + col0 + 4 * lane;
-        encode_row<FULL, 0>(a, i, li, col0, lane, v, v, lds_row, lds_units, dout);
+        encode_row<FULL, MODE>(a, i, li, col0, lane, v, v, lds_row, lds_units, dout);
     }
 
     // ---- line 6 and line 7 for one row of a tile whose v is in registers: scales, codes, the packed message,
@@ -370,7 +398,7 @@ struct Tile {
     template <bool FULL, int MODE>
     static __device__ __forceinline__ void encode_row(const TileArgs& a, int i, int li, uint64_t col0, int lane, const float4 (&v)[SW],
                                                       const float4 (&base)[SW], uint8_t* lds_row, float* lds_units, float* dout) {
-        static_assert(MODE == 0 || KIND == DS_COMP_QUANT_MAXABS || KIND == DS_COMP_SIGN_MEANABS,
+        static_assert(residual(MODE) || KIND == DS_COMP_QUANT_MAXABS || KIND == DS_COMP_SIGN_MEANABS,
                       "the comparison updates are built for the block compressors");
         uint8_t* msg_row = a.msg + (uint64_t)i * a.msg_row_bytes;
         if constexpr (SUB) {
@@ -396,8 +424,8 @@ struct Tile {
                 const float unit = scale / (float)L;
                 const float inv = (scale > 0.f) ? hl / scale : 0.f;
                 if (lane == 0) {
-                    if constexpr (MODE == 0) lds_units[li * BPT + b] = unit;
-                    if (block_live) *reinterpret_cast<float*>(msg_blk) = scale;
+                    if constexpr (residual(MODE)) lds_units[li * BPT + b] = unit;
+                    if (block_live) put<MODE>(reinterpret_cast<float*>(msg_blk), scale);
                 }
 #pragma unroll
                 for (int s = b * SPB; s < (b + 1) * SPB; ++s) {
@@ -425,12 +453,11 @@ struct Tile {
                     }
                     st4(dout + s * kSweep, dnew);
                     using lane_t = typename CT::lane_t;
-                    if constexpr (MODE == 0) reinterpret_cast<lane_t*>(lds_row)[s * kWave + lane] = (lane_t)codes;
+                    if constexpr (residual(MODE)) reinterpret_cast<lane_t*>(lds_row)[s * kWave + lane] = (lane_t)codes;
                     if constexpr (MODE == 1) reinterpret_cast<float4*>(lds_row)[s * kWave + lane] = dnew;
                     const int in_blk = (s - b * SPB) * kWave + lane;  // lane-slot inside the block
                     const uint32_t word = (uint32_t)in_blk * (uint32_t)sizeof(lane_t) / 4u;
-                    if (FULL || word < nwords)
-                        reinterpret_cast<lane_t*>(msg_blk + 4)[in_blk] = (lane_t)codes;
+                    if (FULL || word < nwords) put<MODE>(reinterpret_cast<lane_t*>(msg_blk + 4) + in_blk, (lane_t)codes);
                 }
             } else if constexpr (KIND == DS_COMP_SIGN_MEANABS) {
                 // balanced pairwise tree over the block: inside the lane, across lanes, across sweeps
@@ -446,8 +473,8 @@ struct Tile {
                     for (int s = 0; s + w < SPB; s += 2 * w) part[s] = part[s] + part[s + w];
                 const float scale = block_live ? part[0] / (float)m : 0.f;
                 if (lane == 0) {
-                    if constexpr (MODE == 0) lds_units[li * BPT + b] = scale;
-                    if (block_live) *reinterpret_cast<float*>(msg_blk) = scale;
+                    if constexpr (residual(MODE)) lds_units[li * BPT + b] = scale;
+                    if (block_live) put<MODE>(reinterpret_cast<float*>(msg_blk), scale);
                 }
 #pragma unroll
                 for (int s = b * SPB; s < (b + 1) * SPB; ++s) {
@@ -470,9 +497,9 @@ struct Tile {
                     word |= __shfl_xor(word, 2);
                     word |= __shfl_xor(word, 4);
                     if ((lane & 7) == 0) {
-                        if constexpr (MODE == 0) reinterpret_cast<uint32_t*>(lds_row)[s * 8 + (lane >> 3)] = word;
+                        if constexpr (residual(MODE)) reinterpret_cast<uint32_t*>(lds_row)[s * 8 + (lane >> 3)] = word;
                         const uint32_t widx = (uint32_t)(s - b * SPB) * 8u + (uint32_t)(lane >> 3);
-                        if (FULL || widx < nwords) reinterpret_cast<uint32_t*>(msg_blk + 4)[widx] = word;
+                        if (FULL || widx < nwords) put<MODE>(reinterpret_cast<uint32_t*>(msg_blk + 4) + widx, word);
                     }
                 }
             } else if constexpr (KIND == DS_COMP_RAND_SPARSE) {
@@ -540,7 +567,7 @@ struct Tile {
                     float* mrow = reinterpret_cast<float*>(msg_row);
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
-                        if (FULL || j + c < a.N) mrow[j + c] = comp(v[s], c);
+                        if (FULL || j + c < a.N) put<MODE>(mrow + j + c, comp(v[s], c));
                 }
             }
         }
@@ -600,12 +627,19 @@ struct Tile {
         const float* g_coef = reinterpret_cast<const float*>(g_col + a.nnz);
         const int e0 = __builtin_amdgcn_readfirstlane(lds_graph[i]);
         const int e1 = __builtin_amdgcn_readfirstlane(lds_graph[i + 1]);
+        gossip_edges<FULL>(a, i, col0, lane, lds_codes, lds_units, e0, e1, [&](int e) { return __builtin_amdgcn_readfirstlane(g_col[e]); }, g_coef, xh);
+    }
+
+    // slot_of(e): where in the LDS arrays the codes of edge e's neighbour are
+    template <bool FULL, typename F>
+    static __device__ __forceinline__ void gossip_edges(const TileArgs& a, int i, uint64_t col0, int lane, const uint8_t* lds_codes, const float* lds_units,
+                                                        int e0, int e1, F slot_of, const float* lds_coef, const float4 (&xh)[SW]) {
         float acc[SW][4];
 #pragma unroll
         for (int s = 0; s < SW; ++s) acc[s][0] = acc[s][1] = acc[s][2] = acc[s][3] = 0.f;
         auto edge = [&](int e) {
-            const int nb = __builtin_amdgcn_readfirstlane(g_col[e]);
-            const float w = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(g_coef[e])));
+            const int nb = slot_of(e);
+            const float w = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(lds_coef[e])));
             gossip_accumulate(nb, w, lane, lds_codes, lds_units, acc);
         };
         const int deg = e1 - e0;
@@ -641,16 +675,7 @@ struct Tile {
 #pragma unroll
         for (int s = 0; s < SW; ++s) {
             const float4 xv = ld4(xr + s * kSweep);
-            float4 gv;
-            if (FULL) {
-                gv = ld4(gr + s * kSweep);
-            } else {
-                const uint64_t j = col0 + (uint64_t)s * kSweep + 4 * lane;
-                gv.x = (j + 0 < a.N) ? gr[s * kSweep + 0] : 0.f;
-                gv.y = (j + 1 < a.N) ? gr[s * kSweep + 1] : 0.f;
-                gv.z = (j + 2 < a.N) ? gr[s * kSweep + 2] : 0.f;
-                gv.w = (j + 3 < a.N) ? gr[s * kSweep + 3] : 0.f;
-            }
+            const float4 gv = ld_g<FULL>(a, gr + s * kSweep, col0 + (uint64_t)s * kSweep + 4 * lane);
             xh[s].x = fmaf(-a.gamma, gv.x, xv.x); xh[s].y = fmaf(-a.gamma, gv.y, xv.y);
             xh[s].z = fmaf(-a.gamma, gv.z, xv.z); xh[s].w = fmaf(-a.gamma, gv.w, xv.w);
         }
@@ -855,8 +880,9 @@ __global__ void __launch_bounds__(NW* kWave) fused_tile_kernel(typename Tile<KIN
 // workers fits; the price is reading (degree + 1) code streams per column (mostly cache hits) and a
 // deferred gossip sum that readers of x must flush.
 template <int KIND, int BITS, int B, int SW, int NW>
-__device__ __forceinline__ void step_counter_bump(const TileArgs& a, unsigned long long linear_block, unsigned long long blocks, bool set_pending,
-                                                  unsigned long long* also_clear = nullptr) {
+__device__ __forceinline__ void step_counter_bump(const TileArgs& a, unsigned long long linear_block, unsigned long long blocks, int pending_after,
+                                                  unsigned long long* also_clear = nullptr, unsigned long long* also_count = nullptr) {
+    // pending_after < 0: not a plan with two message buffers
     if (threadIdx.x == 0) {
         const unsigned cell = (unsigned)(linear_block & 63u);
         const unsigned long long members = (blocks >> 6) + (cell < (blocks & 63u) ? 1u : 0u);
@@ -869,9 +895,10 @@ __device__ __forceinline__ void step_counter_bump(const TileArgs& a, unsigned lo
                 __hip_atomic_store(done, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const unsigned long long t = __hip_atomic_fetch_add(a.t_ptr, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 // a cell the launch used as a work queue: every other workgroup has drawn its last number
+                if (also_count != nullptr) __hip_atomic_fetch_add(also_count, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);    // launches so far
                 if (also_clear != nullptr) __hip_atomic_store(also_clear, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (set_pending) {
-                    __hip_atomic_store(a.pending, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (pending_after >= 0) {
+                    __hip_atomic_store(a.pending, (uint32_t)pending_after, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     // which of the two message buffers this step wrote (readers must not infer it from t: the
                     // counter can be set from outside)
                     __hip_atomic_store(a.t_ptr + 4, t & 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -918,7 +945,7 @@ __global__ void __launch_bounds__(NW* kWave) stream_tile_kernel(TileArgs a) {
     if constexpr (!FLUSH) {
         __syncthreads();                                      // every wave of the workgroup has read t and pending
         const unsigned long long blocks = (unsigned long long)gridDim.x * gridDim.y * gridDim.z;
-        step_counter_bump<KIND, BITS, B, SW, NW>(a, ((unsigned long long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, blocks, true);
+        step_counter_bump<KIND, BITS, B, SW, NW>(a, ((unsigned long long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, blocks, 1);
     }
 }
 
@@ -965,6 +992,18 @@ bool stream_plan_for_block(int block, TilePlan& plan) {
     }
 }
 
+// More than the default dynamic LDS has to be asked for once per kernel and device (handles are bound to one device, but a
+// process may hold handles on several); `asked` has a bit per device.
+inline void raise_lds_limit(const void* kernel, size_t lds, unsigned long long& asked) {
+    if (lds <= 48 * 1024) return;
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    const unsigned long long bit = 1ull << (dev & 63);
+    if (asked & bit) return;
+    (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    asked |= bit;
+}
+
 template <int KIND, int BITS, int B, int SW, int NW, int RPW, bool GIVEN>
 void launch_tile(const typename Tile<KIND, BITS, B, SW, NW, GIVEN>::Args& a, int rpw_runtime, hipStream_t stream) {
     using T = Tile<KIND, BITS, B, SW, NW, GIVEN>;
@@ -975,18 +1014,8 @@ void launch_tile(const typename Tile<KIND, BITS, B, SW, NW, GIVEN>::Args& a, int
     const unsigned gy = (unsigned)((tiles + gx - 1) / gx);
     const size_t lds = T::lds_bytes(a.n, a.nnz);
     auto kern = fused_tile_kernel<KIND, BITS, B, SW, NW, RPW, GIVEN>;
-    // more than the default dynamic LDS has to be asked for once per kernel and device (handles are
-    // bound to one device, but a process may hold handles on several)
-    static unsigned long long attr_devices = 0;
-    if (lds > 48 * 1024) {
-        int dev = 0;
-        (void)hipGetDevice(&dev);
-        const unsigned long long bit = 1ull << (dev & 63);
-        if (!(attr_devices & bit)) {
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            attr_devices |= bit;
-        }
-    }
+    static unsigned long long asked = 0;
+    raise_lds_limit(reinterpret_cast<const void*>(kern), lds, asked);
     hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(NW * kWave), lds, stream, a, rpw_runtime);
 }
 
@@ -1003,8 +1032,6 @@ TilePlan make_plan(const char* name) {
     p.sweeps = SW;
     return p;
 }
-
-constexpr size_t kMaxLds = 160 * 1024;
 
 // Variant table for one (KIND, BITS, B): every launch shape that fits n, best guess first.
 // Measured on MI355X: 8-wave workgroups whose waves each own several rows usually beat 16-wave

@@ -1,5 +1,5 @@
 // Instantiations of the tile kernels (dsq_tile_impl.h) for one family of compressors.
-#include "dsq_tile_impl.h"
+#include "dsq_team_impl.h"
 
 namespace dsq {
 
@@ -12,6 +12,11 @@ bool stream_plan_quant4(int block, TilePlan& plan);
 bool stream_plan_quant2(int block, TilePlan& plan);
 bool stream_plan_quant8(int block, TilePlan& plan);
 bool stream_plan_sign(int block, TilePlan& plan);
+// teams of workgroups (dsq_team_*.hip)
+void team_plans_quant4(int block, int n, std::vector<TilePlan>& plans);
+void team_plans_quant2(int block, int n, std::vector<TilePlan>& plans);
+void team_plans_quant8(int block, int n, std::vector<TilePlan>& plans);
+void team_plans_sign(int block, int n, std::vector<TilePlan>& plans);
 // the comparison updates (dsq_compare_*.hip)
 bool compare_plans_quant4(int algo, int block, int n, int nnz, std::vector<TilePlan>& plans, std::string& err);
 bool compare_plans_quant2(int algo, int block, int n, int nnz, std::vector<TilePlan>& plans, std::string& err);
@@ -36,6 +41,37 @@ bool stream_plan(const ds_config& cfg, TilePlan& plan) {
     if (cfg.comp.kind == DS_COMP_SIGN_MEANABS) return stream_plan_sign(cfg.comp.block, plan);
     if (cfg.comp.kind == DS_COMP_IDENTITY) { plan = make_stream_plan<DS_COMP_IDENTITY, 32, 512>(); return true; }
     return false;
+}
+
+const uint64_t kTeamPatienceTicks = kTeamPatience;
+
+bool fit_team(const Graph& graph, TilePlan& plan) {
+    const int n = (int)graph.rowptr.size() - 1;
+    std::vector<int> seen_by((size_t)n, -1);
+    plan.team_slots = plan.team_edges = 0;
+    for (int row0 = 0, part = 0; row0 < n; row0 += plan.team_rows, ++part) {
+        const int row1 = row0 + plan.team_rows < n ? row0 + plan.team_rows : n;
+        int fetched = 0;
+        for (int e = graph.rowptr[(size_t)row0]; e < graph.rowptr[(size_t)row1]; ++e) {
+            const int nb = graph.col[(size_t)e];
+            if ((nb < row0 || nb >= row1) && seen_by[(size_t)nb] != part) { seen_by[(size_t)nb] = part; ++fetched; }
+        }
+        const int edges = graph.rowptr[(size_t)row1] - graph.rowptr[(size_t)row0];
+        if (fetched > plan.team_slots) plan.team_slots = fetched;
+        if (edges > plan.team_edges) plan.team_edges = edges;
+    }
+    return plan.lds(n, plan.team_rows, plan.team_slots, plan.team_edges) <= kMaxLds;
+}
+
+void team_plans(const ds_config& cfg, const Graph& graph, std::vector<TilePlan>& plans) {
+    if (cfg.algo != DS_ALGO_DEEPSQUEEZE) return;
+    std::vector<TilePlan> all;
+    if (cfg.comp.kind == DS_COMP_QUANT_MAXABS && cfg.comp.bits == 4) team_plans_quant4(cfg.comp.block, cfg.n, all);
+    else if (cfg.comp.kind == DS_COMP_QUANT_MAXABS && cfg.comp.bits == 2) team_plans_quant2(cfg.comp.block, cfg.n, all);
+    else if (cfg.comp.kind == DS_COMP_QUANT_MAXABS && cfg.comp.bits == 8) team_plans_quant8(cfg.comp.block, cfg.n, all);
+    else if (cfg.comp.kind == DS_COMP_SIGN_MEANABS) team_plans_sign(cfg.comp.block, cfg.n, all);
+    for (TilePlan& p : all)
+        if (fit_team(graph, p)) plans.push_back(p);
 }
 
 bool choose_tile_plans(const ds_config& cfg, int nnz, std::vector<TilePlan>& plan, std::string& err) {
