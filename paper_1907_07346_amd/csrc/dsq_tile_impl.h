@@ -338,14 +338,15 @@ struct Tile {
         }
     }
 
+    // The gradient at columns j .. j+3: nothing behind column N-1 is read, and only the one lane whose quad the row's end cuts
+    // reads word by word (all lanes did: four loads a quad in the last tile, which the whole launch waits for where tiles are few).
     template <bool FULL>
     static __device__ __forceinline__ float4 ld_g(const TileArgs& a, const float* p, uint64_t j) {
-        if (FULL) return ld4(p);
-        float4 v;
-        v.x = (j + 0 < a.N) ? p[0] : 0.f;
-        v.y = (j + 1 < a.N) ? p[1] : 0.f;
-        v.z = (j + 2 < a.N) ? p[2] : 0.f;
-        v.w = (j + 3 < a.N) ? p[3] : 0.f;
+        if (FULL || j + 3 < a.N) return ld4(p);
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (j + 0 < a.N) v.x = p[0];
+        if (j + 1 < a.N) v.y = p[1];
+        if (j + 2 < a.N) v.z = p[2];
         return v;
     }
 
@@ -1025,7 +1026,7 @@ TilePlan make_plan(const char* name) {
     p.name = name;
     p.launch = &launch_tile<KIND, BITS, B, SW, NW, RPW, false>;
     // the shapes that can stand first in a list of candidates: ds_step_static takes the first
-    if constexpr (KIND != DS_COMP_RAND_SPARSE && (NW == 8 || RPW == 0)) p.launch_given = &launch_tile<KIND, BITS, B, SW, NW, RPW, true>;
+    if constexpr (KIND != DS_COMP_RAND_SPARSE && (NW >= 8 || RPW == 0)) p.launch_given = &launch_tile<KIND, BITS, B, SW, NW, RPW, true>;
     p.tile_cols = SW * kSweep;
     p.waves = NW;
     p.rows_per_wave = RPW;
@@ -1087,6 +1088,18 @@ bool pick_for_block(int n, int nnz, std::vector<TilePlan>& plans, std::string& e
         plans.push_back(plan);
     }
     return true;
+}
+
+// Up to two workgroups per compute unit the time is that of one wave's rows, one after the other: sixteen waves share them then.  (8
+// waves and 16, 4 bits, blocks of 512: 48 workers x 5,461 17.2 and 13.8 us, x 87,381 20.3 and 17.7; 64 x 65,536 25.5 and 22.5; with
+// more tiles the eight-wave workgroups overlap: 12 x 349,525 17.2 and 18.2.)
+inline void sixteen_waves_first(uint64_t N, std::vector<TilePlan>& plans) {
+    if (plans.empty() || (N + plans[0].tile_cols - 1) / plans[0].tile_cols > 512) return;
+    for (size_t q = 1; q < plans.size(); ++q)
+        if (plans[q].waves == 16 && plans[q].tile_cols == plans[0].tile_cols && plans[0].waves == 8 && plans[0].rows_per_wave > 1) {
+            std::swap(plans[0], plans[q]);
+            return;
+        }
 }
 
 template <int KIND, int BITS>

@@ -74,7 +74,7 @@ void team_plans(const ds_config& cfg, const Graph& graph, std::vector<TilePlan>&
         if (fit_team(graph, p)) plans.push_back(p);
 }
 
-bool choose_tile_plans(const ds_config& cfg, int nnz, std::vector<TilePlan>& plan, std::string& err) {
+static bool list_tile_plans(const ds_config& cfg, int nnz, std::vector<TilePlan>& plan, std::string& err) {
     if (cfg.algo != DS_ALGO_DEEPSQUEEZE) {
         if (cfg.comp.kind == DS_COMP_SIGN_MEANABS) return compare_plans_sign(cfg.algo, cfg.comp.block, cfg.n, nnz, plan, err);
         if (cfg.comp.kind == DS_COMP_QUANT_MAXABS && cfg.comp.bits == 4) return compare_plans_quant4(cfg.algo, cfg.comp.block, cfg.n, nnz, plan, err);
@@ -100,6 +100,12 @@ bool choose_tile_plans(const ds_config& cfg, int nnz, std::vector<TilePlan>& pla
             err = "no tile kernel for this compressor";
             return false;
     }
+}
+
+bool choose_tile_plans(const ds_config& cfg, int nnz, std::vector<TilePlan>& plan, std::string& err) {
+    if (!list_tile_plans(cfg, nnz, plan, err)) return false;
+    if (cfg.algo == DS_ALGO_DEEPSQUEEZE) sixteen_waves_first(cfg.N, plan);
+    return true;
 }
 
 }  // namespace dsq
