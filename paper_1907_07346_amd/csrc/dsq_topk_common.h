@@ -75,12 +75,12 @@ __device__ __forceinline__ uint32_t gs_keep4(const TopkArgs& a, int row, uint64_
 // from step to step (early in a run delta grows fast and then settles).  Without usable candidates (full
 // mode) a fixed distance of two million keys (a quarter of a binade) is taken.  Only speed depends on this
 // guess; a bad one sends the row through the exact full path.
-__device__ __forceinline__ uint32_t next_candidate_threshold(TopkRow& r, uint32_t tau, uint32_t k) {
+__device__ __forceinline__ uint32_t next_candidate_threshold(TopkRow& r, uint32_t tau, uint32_t k, float target = TK_TARGET) {
     const float d0 = 2.f * (float)(1u << SHIFT1);
     float dist = d0;
     if (r.cand_mode && r.cand_total > k && tau > r.tlo_used) {
         const float ratio = (float)r.cand_total / (float)k;
-        dist = (float)(tau - r.tlo_used) * (logf(TK_TARGET) / logf(ratio));
+        dist = (float)(tau - r.tlo_used) * (logf(target) / logf(ratio));
         dist = fminf(fmaxf(dist, 65536.f), 4.f * d0);
     }
     const float mag = __uint_as_float(tau);

@@ -23,6 +23,7 @@
 //       topk_bin_collect    per chunk: candidates above that bin counted; the few inside it listed per row
 //       topk_finish         per row: exact tau and r_tie from the list, per-chunk counts, scan over chunks
 //       topk_write_cand     per chunk: the ordered message from the slot
+//     Rows with few candidates take topk_select_row, one workgroup each, in place of all but the last.
 //   * full mode (always exact, used on the first step and whenever the guess fails): an MSB-first radix
 //     select over v itself, 11 + 11 + 9 bits, workgroup histograms in LDS, every workgroup of a pass
 //     working out the previous level's bin for itself.  Its kernels run on a small grid-stride grid and
@@ -38,6 +39,7 @@
 // applied by topk_flush before anyone else looks at the state.
 
 #include "dsq_internal.h"
+#include "dsq_resident.h"
 #include "dsq_topk_common.h"
 
 namespace dsq {
@@ -48,12 +50,12 @@ constexpr int TK_THREADS = 256;
 constexpr int TK_VEC = 4 * TK_THREADS;       // elements per workgroup iteration
 constexpr int TK_ITERS = 4;
 constexpr int TK_CHUNK = TK_VEC * TK_ITERS;  // columns per chunk (one workgroup of the streaming passes)
-constexpr int TK_CAP = 512;                  // candidate slots per chunk (12.5 % of the chunk)
+constexpr uint32_t TK_CAP = 512;             // room in a chunk's slot: 12.5 % of the chunk at least (Scratch::cap)
 constexpr int TK_H1 = 256;                   // level-1 bins the first pass tracks, counted from tlo's bin upwards
-constexpr int TK_HWG = 16;                   // workgroups per row in topk_hist_cand2 and topk_bin_collect
+constexpr uint32_t TK_HWG = 16;              // most workgroups per row in topk_hist_cand2 and topk_bin_collect
 constexpr int TK_HTHREADS = 1024;            // threads of those workgroups
 constexpr int TK_FWG = 64;                   // full-mode workgroups per row (grid-stride over the row's chunks)
-constexpr int TK_WPW = 8;                    // chunks per wave (= workgroup) in topk_write_cand
+constexpr int write_chunks(int lanes) { return lanes == 16 ? 8 : 2; }   // chunks per wave (= workgroup) of topk_write_cand
 constexpr int TK_RTHREADS = 1024;            // threads of the per-row kernels
 constexpr int BINS2 = 2048, SHIFT2 = 9;      // level 2: key bits 19..9
 constexpr int BINS3 = 512;                   // level 3: key bits 8..0
@@ -113,13 +115,17 @@ struct Scratch {               // device pointers of the select's scratch (all o
     uint32_t* eq_before;       // n x nchunks: ties in earlier chunks of the row
     uint32_t* out_off;         // n x (nchunks+1): message offset of each chunk
     uint32_t* cand_cnt;        // n x nchunks: candidates stored in the chunk's slot
-    uint32_t* slot_val;        // n x nchunks x TK_CAP candidate values (fp32 bits), unordered inside a slot; the select
+    uint32_t* slot_val;        // n x nchunks x cap candidate values (fp32 bits), unordered inside a slot; the select
                                // passes read only these
     uint16_t* slot_idx;        // same shape: the candidates' columns, relative to the start of the chunk
     uint2* list;               // n x TK_LIST_CAP: (key, chunk) of the candidates inside the threshold's histogram bin
     double* csum;              // GSpar: n x nchunks tree sums of |v| over the chunks
     uint32_t* gs_overflow;     // GSpar: set once a row kept more than its message holds
     uint32_t nchunks;
+    uint32_t cap;              // candidates a chunk's slot has room for
+    uint32_t row_select;       // a row's select is one workgroup's work (topk_select_row)
+    uint32_t hist_wgs;         // workgroups per row of topk_hist_cand2 and topk_bin_collect
+    float target;              // candidates aimed at, in units of k
 };
 
 // Scans over the TK_RTHREADS threads of a per-row workgroup.
@@ -170,10 +176,10 @@ __device__ __forceinline__ unsigned long long block_exclusive_scan4(unsigned lon
     return base + inc - v;
 }
 
-// The elements of one chunk whose mask bit is set, in column order, into the chunk's slot (the first TK_CAP of
+// The elements of one chunk whose mask bit is set, in column order, into the chunk's slot (the first `cap` of
 // them); returns their number.  vin: the lane's four float4 of the chunk, keep: their four 4-bit masks.
 __device__ __forceinline__ uint32_t gs_collect(const float4 (&vin)[TK_ITERS], const uint32_t (&keep)[TK_ITERS], uint32_t* slot_val,
-                                               uint16_t* slot_idx, unsigned long long* wave_sums) {
+                                               uint16_t* slot_idx, uint32_t cap, unsigned long long* wave_sums) {
     unsigned long long packed = 0;
 #pragma unroll
     for (int it = 0; it < TK_ITERS; ++it) packed |= (unsigned long long)__popc(keep[it]) << (16 * it);
@@ -188,7 +194,7 @@ __device__ __forceinline__ uint32_t gs_collect(const float4 (&vin)[TK_ITERS], co
 #pragma unroll
         for (int c = 0; c < 4; ++c)
             if (keep[it] & (1u << c)) {
-                if (pos < (uint32_t)TK_CAP) { slot_val[pos] = __float_as_uint(vv[c]); slot_idx[pos] = (uint16_t)(q0 + c); }
+                if (pos < cap) { slot_val[pos] = __float_as_uint(vv[c]); slot_idx[pos] = (uint16_t)(q0 + c); }
                 ++pos;
             }
         run += (uint32_t)((tot >> (16 * it)) & 0xFFFFu);
@@ -206,12 +212,13 @@ __device__ __forceinline__ double wave_tree_sum_f64(double v) {   // adjacent pa
 // ---- pass 1: pending gossip of the previous step, Algorithm 1 line 5, candidate collection ------
 // GS (the GSpar operator shares this pass and the message conventions): no candidates; instead the chunk's sum of
 // |v| in double, as the balanced adjacent-pairs tree the operator's lambda is defined with.
-template <bool GS>
+// PAIRS: pairs of a neighbour in the chunk that a thread asks for ahead.
+template <bool GS, int PAIRS>
 __global__ void __launch_bounds__(TK_THREADS) topk_form_collect(TopkArgs a, Scratch s) {
     __shared__ float acc[TK_CHUNK];
     [[maybe_unused]] __shared__ double sweep_abs[TK_ITERS * (TK_THREADS / 64)];
     [[maybe_unused]] __shared__ unsigned long long wave_sums4[TK_THREADS / 64];
-    [[maybe_unused]] float4 gs_v[TK_ITERS];
+    float4 vs[TK_ITERS];
     __shared__ uint32_t own[TK_CHUNK / 32];       // columns this worker itself sent in the previous step
     __shared__ uint32_t h[TK_H1];                              // level-1 digits of the candidates, relative to tlo's
     __shared__ uint32_t cand_count;
@@ -265,22 +272,28 @@ __global__ void __launch_bounds__(TK_THREADS) topk_form_collect(TopkArgs a, Scra
             // Neighbours in ascending order, four at a time: their pair loads go out together (memory operations
             // complete in issue order, so a load issued only after the previous neighbour was accumulated would
             // show its whole latency with nothing else of this workgroup in flight), then they are accumulated one
-            // after the other.  A neighbour with more than one pair per thread in this chunk takes the loop below.
+            // after the other.  A neighbour with more than PAIRS pairs per thread in this chunk takes the loop below.
             constexpr int EB = 4;
             for (int eb = e0; eb < e1; eb += EB) {
-                uint2 pr[EB];
-                bool have[EB], wide[EB];
+                uint2 pr[EB][PAIRS];
+                uint32_t have[EB];                             // a bit per pair
+                bool wide[EB];
 #pragma unroll
                 for (int u = 0; u < EB; ++u) {
-                    have[u] = wide[u] = false;
+                    have[u] = 0u;
+                    wide[u] = false;
                     if (eb + u < e1) {
                         const int nb = a.col[eb + u];
                         const uint32_t* off = s.out_off + (size_t)nb * (s.nchunks + 1) + chunk;
                         const uint32_t p0 = off[0], p1 = off[1];
-                        wide[u] = p1 - p0 > (uint32_t)TK_THREADS;                    // uniform
-                        if (!wide[u] && p0 + threadIdx.x < p1) {
-                            pr[u] = reinterpret_cast<const uint2*>(a.msg + (uint64_t)nb * a.k * 8)[p0 + threadIdx.x];
-                            have[u] = true;
+                        wide[u] = p1 - p0 > (uint32_t)(PAIRS * TK_THREADS);          // uniform
+#pragma unroll
+                        for (int h = 0; h < PAIRS; ++h) {
+                            const uint32_t p = p0 + h * TK_THREADS + threadIdx.x;
+                            if (!wide[u] && p < p1) {
+                                pr[u][h] = reinterpret_cast<const uint2*>(a.msg + (uint64_t)nb * a.k * 8)[p];
+                                have[u] |= 1u << h;
+                            }
                         }
                     }
                 }
@@ -300,11 +313,14 @@ __global__ void __launch_bounds__(TK_THREADS) topk_form_collect(TopkArgs a, Scra
                                     if (nb == row) atomicOr(&own[q >> 5], 1u << (q & 31));
                                 }
                             }
-                        } else if (have[u]) {
-                            const uint32_t q = (uint32_t)((uint64_t)pr[u].x - c0);
-                            if (q < (uint32_t)TK_CHUNK) {
-                                acc[q] = fmaf(w, __uint_as_float(pr[u].y), acc[q]);
-                                if (nb == row) atomicOr(&own[q >> 5], 1u << (q & 31));
+                        } else {
+#pragma unroll
+                            for (int h = 0; h < PAIRS; ++h) {
+                                const uint32_t q = (uint32_t)((uint64_t)pr[u][h].x - c0);
+                                if ((have[u] >> h & 1u) && q < (uint32_t)TK_CHUNK) {
+                                    acc[q] = fmaf(w, __uint_as_float(pr[u][h].y), acc[q]);
+                                    if (nb == row) atomicOr(&own[q >> 5], 1u << (q & 31));
+                                }
                             }
                         }
                         __syncthreads();
@@ -317,8 +333,8 @@ __global__ void __launch_bounds__(TK_THREADS) topk_form_collect(TopkArgs a, Scra
     const uint32_t tlo = s.rows[row].tlo;
     const uint32_t bin0 = tlo >> SHIFT1;                       // (0xfff for "collect nothing")
     bool far = false;                                          // a candidate beyond the tracked bins
-    uint32_t* slot_val = s.slot_val + ((size_t)row * s.nchunks + chunk) * TK_CAP;
-    uint16_t* slot_idx = s.slot_idx + ((size_t)row * s.nchunks + chunk) * TK_CAP;
+    uint32_t* slot_val = s.slot_val + ((size_t)row * s.nchunks + chunk) * s.cap;
+    uint16_t* slot_idx = s.slot_idx + ((size_t)row * s.nchunks + chunk) * s.cap;
 #pragma unroll
     for (int it = 0; it < TK_ITERS; ++it) {
         const uint32_t q0 = (uint32_t)it * TK_VEC + 4 * threadIdx.x;
@@ -346,18 +362,38 @@ __global__ void __launch_bounds__(TK_THREADS) topk_form_collect(TopkArgs a, Scra
         if constexpr (GS) {                                    // padding columns hold v = 0
             const double sw = wave_tree_sum_f64(((double)fabsf(v.x) + (double)fabsf(v.y)) + ((double)fabsf(v.z) + (double)fabsf(v.w)));
             if ((threadIdx.x & 63) == 0) sweep_abs[it * (TK_THREADS / 64) + (threadIdx.x >> 6)] = sw;   // sweep index = column order
-            gs_v[it] = v;
-            continue;
         }
-        const float vv[4] = {v.x, v.y, v.z, v.w};
+        vs[it] = v;
+    }
+    if constexpr (!GS) {
+        // The lane's candidates one after the other behind those of the lanes before it, the waves in any order: one returning
+        // atomic per wave.
+        uint32_t mine = 0;
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if (j + c < a.N && key_of(vv[c]) >= tlo) {
-                const uint32_t idx = atomicAdd(&cand_count, 1u);
-                if (idx < (uint32_t)TK_CAP) { slot_val[idx] = __float_as_uint(vv[c]); slot_idx[idx] = (uint16_t)(q0 + c); }
-                const uint32_t rel = (key_of(vv[c]) >> SHIFT1) - bin0;
-                if (rel < (uint32_t)TK_H1) atomicAdd(&h[rel], 1u); else far = true;
-            }
+        for (int it = 0; it < TK_ITERS; ++it) {
+            const uint64_t j = c0 + (uint64_t)it * TK_VEC + 4 * threadIdx.x;
+            const float vv[4] = {vs[it].x, vs[it].y, vs[it].z, vs[it].w};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) mine |= (j + c < a.N && key_of(vv[c]) >= tlo ? 1u : 0u) << (4 * it + c);
+        }
+        const uint32_t upto = wave_inclusive_u32((uint32_t)__popc(mine));
+        uint32_t idx = 0;
+        if ((threadIdx.x & 63) == 63 && upto != 0u) idx = atomicAdd(&cand_count, upto);
+        idx = (uint32_t)__builtin_amdgcn_readlane((int)idx, 63) + upto - (uint32_t)__popc(mine);
+#pragma unroll
+        for (int it = 0; it < TK_ITERS; ++it) {
+            const uint32_t q0 = (uint32_t)it * TK_VEC + 4 * threadIdx.x;
+            const float vv[4] = {vs[it].x, vs[it].y, vs[it].z, vs[it].w};
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (mine >> (4 * it + c) & 1u) {
+                    if (idx < s.cap) { slot_val[idx] = __float_as_uint(vv[c]); slot_idx[idx] = (uint16_t)(q0 + c); }
+                    ++idx;
+                    if (s.row_select) continue;
+                    const uint32_t rel = (key_of(vv[c]) >> SHIFT1) - bin0;
+                    if (rel < (uint32_t)TK_H1) atomicAdd(&h[rel], 1u); else far = true;
+                }
+        }
     }
     __syncthreads();
     if constexpr (GS) {
@@ -369,8 +405,8 @@ __global__ void __launch_bounds__(TK_THREADS) topk_form_collect(TopkArgs a, Scra
             const uint32_t t_lo = (uint32_t)*a.t_ptr;
             uint32_t keep[TK_ITERS];
 #pragma unroll
-            for (int it = 0; it < TK_ITERS; ++it) keep[it] = gs_keep4(a, row, c0 + (uint64_t)it * TK_VEC + 4 * threadIdx.x, t_lo, lambda_hi, gs_v[it]);
-            const uint32_t n = gs_collect(gs_v, keep, slot_val, slot_idx, wave_sums4);
+            for (int it = 0; it < TK_ITERS; ++it) keep[it] = gs_keep4(a, row, c0 + (uint64_t)it * TK_VEC + 4 * threadIdx.x, t_lo, lambda_hi, vs[it]);
+            const uint32_t n = gs_collect(vs, keep, slot_val, slot_idx, s.cap, wave_sums4);
             if (threadIdx.x == 0) s.cand_cnt[(size_t)row * s.nchunks + chunk] = n;
         }
         if (threadIdx.x == 0) {
@@ -388,13 +424,14 @@ __global__ void __launch_bounds__(TK_THREADS) topk_form_collect(TopkArgs a, Scra
     // the row histogram is used if the row ends up in candidate mode and wiped by topk_decide_select either way;
     // a candidate beyond the tracked bins (256 bins = 2^32 in magnitude above tlo) sends the row the exact way
     uint32_t* hrow = s.hist_part + ((size_t)row * TK_HPARTS + (chunk & (uint32_t)(TK_HPARTS - 1))) * HIST_BINS;
-    for (int b = threadIdx.x; b < TK_H1; b += TK_THREADS)
-        if (h[b]) atomicAdd(&hrow[bin0 + b], h[b]);
+    if (!s.row_select)
+        for (int b = threadIdx.x; b < TK_H1; b += TK_THREADS)
+            if (h[b]) atomicAdd(&hrow[bin0 + b], h[b]);
     if (far) atomicOr(&s.rows[row].overflow, 1u);
     if (threadIdx.x == 0) {
         const uint32_t c = cand_count;
-        s.cand_cnt[(size_t)row * s.nchunks + chunk] = c < (uint32_t)TK_CAP ? c : (uint32_t)TK_CAP;
-        if (c > (uint32_t)TK_CAP) atomicOr(&s.rows[row].overflow, 1u);
+        s.cand_cnt[(size_t)row * s.nchunks + chunk] = c < s.cap ? c : s.cap;
+        if (c > s.cap) atomicOr(&s.rows[row].overflow, 1u);
     }
 }
 
@@ -473,7 +510,7 @@ __global__ void __launch_bounds__(TK_HTHREADS) topk_hist_cand2(Scratch s) {
     const uint32_t prefix = s.rows[row].prefix1;
     constexpr int TPC = 16, SIDE = TK_HTHREADS / TPC;          // lanes per chunk, chunks side by side
     const int sub = threadIdx.x % TPC;
-    const uint32_t per_wg = (s.nchunks + TK_HWG - 1) / TK_HWG;
+    const uint32_t per_wg = (s.nchunks + s.hist_wgs - 1) / s.hist_wgs;
     const uint32_t first = blockIdx.x * per_wg;
     const uint32_t last = (first + per_wg < s.nchunks) ? first + per_wg : s.nchunks;
     const uint32_t* cand_cnt = s.cand_cnt + (size_t)row * s.nchunks;
@@ -481,7 +518,7 @@ __global__ void __launch_bounds__(TK_HTHREADS) topk_hist_cand2(Scratch s) {
     uint32_t cnt = chunk < last ? cand_cnt[chunk] : 0u;        // the next chunk's count is asked for one turn ahead
     for (; chunk < last; chunk += SIDE) {
         const uint32_t cnt_next = (chunk + SIDE < last) ? cand_cnt[chunk + SIDE] : 0u;
-        const uint32_t* slot = s.slot_val + ((size_t)row * s.nchunks + chunk) * TK_CAP;
+        const uint32_t* slot = s.slot_val + ((size_t)row * s.nchunks + chunk) * s.cap;
         for (uint32_t p0 = sub; p0 < cnt; p0 += 8 * TPC) {
             uint32_t key[8];
 #pragma unroll
@@ -632,7 +669,7 @@ __global__ void __launch_bounds__(TK_HTHREADS) topk_bin_collect(Scratch s) {
     const uint32_t lo = s.rows[row].bin_lo;
     constexpr int TPC = 16, SIDE = TK_HTHREADS / TPC;
     const int sub = threadIdx.x % TPC;
-    const uint32_t per_wg = (s.nchunks + TK_HWG - 1) / TK_HWG;
+    const uint32_t per_wg = (s.nchunks + s.hist_wgs - 1) / s.hist_wgs;
     const uint32_t first = blockIdx.x * per_wg;
     const uint32_t last = (first + per_wg < s.nchunks) ? first + per_wg : s.nchunks;
     const uint32_t* cand_cnt = s.cand_cnt + (size_t)row * s.nchunks;
@@ -642,7 +679,7 @@ __global__ void __launch_bounds__(TK_HTHREADS) topk_bin_collect(Scratch s) {
     for (; chunk < last; chunk += SIDE) {                 // the 16 lanes of a chunk leave the loop together
         const uint32_t cnt_next = (chunk + SIDE < last) ? cand_cnt[chunk + SIDE] : 0u;
         const size_t cidx = (size_t)row * s.nchunks + chunk;
-        const uint32_t* slot = s.slot_val + cidx * TK_CAP;
+        const uint32_t* slot = s.slot_val + cidx * s.cap;
         uint32_t gt = 0;
         for (uint32_t p0 = sub; p0 < cnt; p0 += 8 * TPC) {
             uint32_t key[8];
@@ -680,6 +717,7 @@ __global__ void __launch_bounds__(TK_RTHREADS) topk_finish(Scratch s, uint32_t k
     TopkRow& r = s.rows[row];
     uint32_t* gtw = s.cnt_gt + (size_t)row * nchunks;
     uint32_t* eqw = s.cnt_eq + (size_t)row * nchunks;
+    if (r.cand_mode && s.row_select) return;                        // topk_select_row has done it
     if (r.cand_mode) {                                              // uniform
         const uint32_t lo = r.bin_lo, need = r.bin_need;
         const uint32_t nlist = r.list_count < TK_LIST_CAP ? r.list_count : TK_LIST_CAP;
@@ -703,8 +741,8 @@ __global__ void __launch_bounds__(TK_RTHREADS) topk_finish(Scratch s, uint32_t k
             else if (en.x == tau) atomicAdd(&eqw[en.y], 1u);
         }
         if (threadIdx.x == 0) { r.tau = tau; r.r_tie = sel[1]; }
-        __threadfence();                                            // the corrected counts, before the scan reads them
-        __syncthreads();
+        drain();                                                    // the corrected counts, before the scan reads them (a fence would also
+        __syncthreads();                                            // write the L2 back, which 200 rows waited 40 us for)
     } else {
         // full mode: topk_fix_full left tau and the tie quota; the level-1 histogram of all keys must not meet the
         // next first pass's candidates
@@ -780,8 +818,145 @@ __global__ void __launch_bounds__(TK_RTHREADS) topk_finish(Scratch s, uint32_t k
     if (threadIdx.x == 0) {
         off[nchunks] = tot_o;
         r.total = tot_o;
-        r.tlo = next_candidate_threshold(r, tau_row, k);
+        r.tlo = next_candidate_threshold(r, tau_row, k, s.target);
         r.tau_prev = tau_row;
+    }
+}
+
+// ---- candidate mode of rows with few candidates: the whole select in one workgroup per row ---------
+// What topk_decide_select, topk_hist_cand2, topk_select2_cand, topk_bin_collect and topk_finish do for long rows, without their
+// global histograms: four launches less, and no atomics that many rows queue for.  Bound by its three walks over the slots, eight
+// loads of a lane in flight.
+// (form to flush, us, by sixteen workgroups a row and by one: 200 x 20,971, 1 % sent, 131 and 56; 48 x 349,525 137 and 120; but 8 x
+// 2,097,152, 0.1 %, 106 and 124; 48 x 1,398,101, 1 %, 359 and 371; 8 x 524,288 63 and 64.)
+constexpr uint32_t TK_SEL_CHUNKS = 128;       // chunks of such a row ...
+constexpr uint32_t TK_SEL_K = 16384;          // ... and its k
+constexpr uint32_t TK_SEL_LIST = 2048;        // candidates inside the threshold's level-2 bin that are listed in LDS
+
+// The bin of an LDS histogram of HIST_BINS where the count from the top crosses `need`, all threads; res as in select_digit.
+__device__ __forceinline__ void select_digit_row(const uint32_t* h, uint32_t need, uint32_t* wave_sums, uint32_t* res) {
+    constexpr int PER = HIST_BINS / TK_RTHREADS;
+    uint32_t mine[PER], sum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) { mine[q] = h[HIST_BINS - 1 - (threadIdx.x * PER + q)]; sum += mine[q]; }
+    uint32_t total;
+    uint32_t above = row_exclusive_scan(sum, wave_sums, &total);
+    if (threadIdx.x == 0) { res[0] = 0; res[1] = 0; res[2] = 0; res[3] = total; }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        if (above < need && need <= above + mine[q]) { res[0] = HIST_BINS - 1 - (threadIdx.x * PER + q); res[1] = need - above; res[2] = mine[q]; }
+        above += mine[q];
+    }
+    __syncthreads();
+}
+
+__global__ void __launch_bounds__(TK_RTHREADS) topk_select_row(Scratch s, uint32_t k) {
+    __shared__ uint32_t h[HIST_BINS];
+    __shared__ uint32_t gt[TK_SEL_CHUNKS], eq[TK_SEL_CHUNKS];
+    __shared__ uint2 list[TK_SEL_LIST];
+    __shared__ uint32_t wave_sums[TK_RTHREADS / 64];
+    __shared__ uint32_t res[4], sel[2], listed;
+    const int row = blockIdx.x;
+    const uint32_t nchunks = s.nchunks;
+    TopkRow& r = s.rows[row];
+    const uint32_t tlo = r.tlo;
+    const uint32_t* cand_cnt = s.cand_cnt + (size_t)row * nchunks;
+    const uint32_t* slots = s.slot_val + (size_t)row * nchunks * s.cap;
+    constexpr uint32_t TPC = 32, SIDE = TK_RTHREADS / TPC;     // lanes per chunk, chunks side by side
+    auto walk = [&](auto f) {                                  // f(key, chunk) for every candidate of the row
+        const uint32_t sub = threadIdx.x % TPC;
+        uint32_t chunk = threadIdx.x / TPC;
+        uint32_t cnt = chunk < nchunks ? cand_cnt[chunk] : 0u; // asked for one turn ahead
+        for (; chunk < nchunks; chunk += SIDE) {
+            const uint32_t cnt_next = chunk + SIDE < nchunks ? cand_cnt[chunk + SIDE] : 0u;
+            const uint32_t* slot = slots + (size_t)chunk * s.cap;
+            for (uint32_t p0 = sub; p0 < cnt; p0 += 8 * TPC) {
+                uint32_t key[8];
+#pragma unroll
+                for (uint32_t u = 0; u < 8; ++u) key[u] = p0 + u * TPC < cnt ? slot[p0 + u * TPC] & 0x7FFFFFFFu : 0xFFFFFFFFu;
+#pragma unroll
+                for (uint32_t u = 0; u < 8; ++u)
+                    if (key[u] != 0xFFFFFFFFu) f(key[u], chunk);
+            }
+            cnt = cnt_next;
+        }
+    };
+    auto clear = [&]() {
+        for (int b = threadIdx.x; b < HIST_BINS; b += TK_RTHREADS) h[b] = 0u;
+        __syncthreads();
+    };
+    bool cand = tlo != 0xFFFFFFFFu && r.overflow == 0u;        // uniform
+    uint32_t total = 0, lo = 0, need = 0;
+    if (threadIdx.x == 0) listed = 0u;
+    if (threadIdx.x < TK_SEL_CHUNKS) gt[threadIdx.x] = eq[threadIdx.x] = 0u;
+    static_assert(TK_SEL_CHUNKS <= TK_RTHREADS, "a thread per chunk");
+    clear();
+    if (cand) {
+        walk([&](uint32_t key, uint32_t) { atomicAdd(&h[key >> SHIFT1], 1u); });
+        __syncthreads();
+        select_digit_row(h, k, wave_sums, res);
+        total = res[3];
+        cand = total >= k;
+    }
+    if (cand) {
+        const uint32_t prefix = res[0];
+        need = res[1];
+        clear();                                               // (with a barrier: everybody has read res)
+        walk([&](uint32_t key, uint32_t) { if (key >> SHIFT1 == prefix) atomicAdd(&h[key >> SHIFT2 & (BINS2 - 1)], 1u); });
+        __syncthreads();
+        select_digit_row(h, need, wave_sums, res);
+        lo = (prefix << (SHIFT1 - SHIFT2) | res[0]) << SHIFT2;
+        need = res[1];
+        cand = res[2] <= TK_SEL_LIST;                          // many equal or nearly equal keys: the exact way
+        clear();
+    }
+    if (threadIdx.x == 0) { r.cand_mode = cand ? 1u : 0u; r.cand_total = total; r.overflow = 0u; r.tlo_used = tlo; }
+    if (!cand) {                                               // full mode needs its histograms clean
+        for (int b = threadIdx.x; b < HIST_BINS; b += TK_RTHREADS) { s.hist[(size_t)row * HIST_BINS + b] = 0u; s.hist2[(size_t)row * HIST_BINS + b] = 0u; }
+        for (int b = threadIdx.x; b < BINS3; b += TK_RTHREADS) s.hist3[(size_t)row * BINS3 + b] = 0u;
+        return;
+    }
+    walk([&](uint32_t key, uint32_t chunk) {
+        if (key < lo) return;
+        if (key - lo >= FINE_SPAN) atomicAdd(&gt[chunk], 1u);
+        else {
+            list[atomicAdd(&listed, 1u)] = make_uint2(key, chunk);          // as many as the bin holds
+            atomicAdd(&h[key - lo], 1u);
+        }
+    });
+    __syncthreads();
+    {                                                          // exact threshold and tie quota: one value per thread, largest first
+        const uint32_t b = threadIdx.x < FINE_SPAN ? FINE_SPAN - 1 - threadIdx.x : 0u;
+        const uint32_t mine = threadIdx.x < FINE_SPAN ? h[b] : 0u;
+        uint32_t tot;
+        const uint32_t above = row_exclusive_scan(mine, wave_sums, &tot);
+        if (threadIdx.x < FINE_SPAN && above < need && need <= above + mine) { sel[0] = lo + b; sel[1] = need - above; }
+        __syncthreads();
+    }
+    const uint32_t tau = sel[0], r_tie = sel[1], nlist = listed;
+    for (uint32_t e = threadIdx.x; e < nlist; e += TK_RTHREADS) {
+        if (list[e].x > tau) atomicAdd(&gt[list[e].y], 1u);
+        else if (list[e].x == tau) atomicAdd(&eq[list[e].y], 1u);
+    }
+    __syncthreads();
+    const uint32_t c = threadIdx.x, my_eq = c < nchunks ? eq[c] : 0u, my_gt = c < nchunks ? gt[c] : 0u;
+    uint32_t tot_e, tot_o;
+    const uint32_t before = row_exclusive_scan(my_eq, wave_sums, &tot_e);
+    const uint32_t quota = before < r_tie ? r_tie - before : 0u;
+    const uint32_t off = row_exclusive_scan(my_gt + (my_eq < quota ? my_eq : quota), wave_sums, &tot_o);
+    if (c < nchunks) {
+        s.cnt_eq[(size_t)row * nchunks + c] = my_eq;
+        s.eq_before[(size_t)row * nchunks + c] = before;
+        s.out_off[(size_t)row * (nchunks + 1) + c] = off;
+    }
+    if (threadIdx.x == 0) {
+        s.out_off[(size_t)row * (nchunks + 1) + nchunks] = tot_o;
+        r.tau = tau;
+        r.r_tie = r_tie;
+        r.total = tot_o;
+        r.tlo = next_candidate_threshold(r, tau, k, s.target);
+        r.tau_prev = tau;
     }
 }
 
@@ -846,15 +1021,15 @@ __global__ void __launch_bounds__(TK_THREADS) topk_write_full(TopkArgs a, Scratc
         write_full_chunk(a, s, row, chunk, wave_sums);
 }
 
-// Candidate mode: 16 lanes per chunk, so a wave (= a workgroup) writes four chunks side by side, TK_WPW / 4
-// times in a row.  A slot is unordered, so order comes from two bitmaps over the chunk's columns (selected,
+// Candidate mode: 16 lanes per chunk, so a wave (= a workgroup) writes four chunks side by side, twice in a row; where slots
+// hold more than a few hundred candidates a chunk has the whole wave, twice in a row.  A slot is unordered, so order comes from two bitmaps over the chunk's columns (selected,
 // tied): the place of a pair in the message is the number of selected columns below it, and the ties that
 // belong to the set are the `quota` lowest tied columns.
 constexpr int TK_WORDS = TK_CHUNK / 32;                        // bitmap words per chunk
-constexpr int TK_GL = 16;                                      // lanes per chunk
-constexpr int TK_WPL = TK_WORDS / TK_GL;                       // bitmap words per lane (consecutive)
 // prefix[w] = number of set bits in words [0, w) of one chunk's bitmap; the TK_GL lanes of the chunk call together
+template <int TK_GL>
 __device__ __forceinline__ void bitmap_prefix(const uint32_t* bits, uint32_t* prefix, int sub) {
+    constexpr int TK_WPL = TK_WORDS / TK_GL;                   // bitmap words per lane (consecutive)
     uint32_t c[TK_WPL], sum = 0;
 #pragma unroll
     for (int q = 0; q < TK_WPL; ++q) { c[q] = __popc(bits[sub * TK_WPL + q]); sum += c[q]; }
@@ -872,10 +1047,12 @@ __device__ __forceinline__ uint32_t bitmap_rank(const uint32_t* bits, const uint
     return prefix[q >> 5] + __popc(bits[q >> 5] & ((1u << (q & 31)) - 1u));
 }
 
+template <int TK_GL>
 __global__ void __launch_bounds__(64) topk_write_cand(TopkArgs a, Scratch s) {
+    constexpr int TK_WPL = TK_WORDS / TK_GL;
     constexpr int GROUPS = 64 / TK_GL;                         // chunks side by side in the wave
-    constexpr int TURNS = TK_WPW / GROUPS;
-    constexpr int SPEC = 8;                                    // slot entries per lane held in registers: 128 per chunk
+    constexpr int TURNS = write_chunks(TK_GL) / GROUPS;
+    constexpr int SPEC = 8;                                    // slot entries per lane held in registers: 128 per chunk, 512 if it has the wave
     __shared__ uint32_t sel_all[GROUPS][TK_WORDS], eq_all[GROUPS][TK_WORDS], prefix_all[GROUPS][TK_WORDS];
     const int row = blockIdx.y;
     if (!s.rows[row].cand_mode) return;                     // uniform
@@ -892,13 +1069,13 @@ __global__ void __launch_bounds__(64) topk_write_cand(TopkArgs a, Scratch s) {
     uint32_t cnt[TURNS], off0[TURNS], off1[TURNS], eqb[TURNS], ceq[TURNS];
 #pragma unroll
     for (int tn = 0; tn < TURNS; ++tn) {
-        const uint32_t want = blockIdx.x * TK_WPW + tn * GROUPS + grp;
+        const uint32_t want = blockIdx.x * write_chunks(TK_GL) + tn * GROUPS + grp;
         const uint32_t chunk = want < nchunks ? want : nchunks - 1;              // a clamped chunk is skipped below
         const size_t cidx = (size_t)row * nchunks + chunk;
 #pragma unroll
         for (int u = 0; u < SPEC; ++u) {
             const uint32_t p = (uint32_t)u * TK_GL + sub;
-            ent[tn][u] = make_uint2(s.slot_idx[cidx * TK_CAP + p], s.slot_val[cidx * TK_CAP + p]);   // .x: column in the chunk
+            ent[tn][u] = make_uint2(s.slot_idx[cidx * s.cap + p], s.slot_val[cidx * s.cap + p]);   // .x: column in the chunk
         }
         cnt[tn] = s.cand_cnt[cidx];
         off0[tn] = s.out_off[(size_t)row * (nchunks + 1) + chunk];
@@ -910,11 +1087,11 @@ __global__ void __launch_bounds__(64) topk_write_cand(TopkArgs a, Scratch s) {
     for (int tn = 0; tn < TURNS; ++tn) {
         // every lane walks through all barriers of a turn (one wave: they only order its LDS accesses); a group
         // with nothing to write idles through them
-        const uint32_t chunk = blockIdx.x * TK_WPW + tn * GROUPS + grp;
+        const uint32_t chunk = blockIdx.x * write_chunks(TK_GL) + tn * GROUPS + grp;
         const bool active = chunk < nchunks && off0[tn] != off1[tn];
         const size_t cidx = (size_t)row * nchunks + (chunk < nchunks ? chunk : 0u);
-        const uint32_t* slot_val = s.slot_val + cidx * TK_CAP;
-        const uint16_t* slot_idx = s.slot_idx + cidx * TK_CAP;
+        const uint32_t* slot_val = s.slot_val + cidx * s.cap;
+        const uint16_t* slot_idx = s.slot_idx + cidx * s.cap;
         const uint64_t c0 = (uint64_t)chunk * TK_CHUNK;
         const uint32_t quota = (eqb[tn] < r_tie) ? (r_tie - eqb[tn]) : 0u;        // ties of this chunk that belong to the set
         const bool ties = active && ceq[tn] != 0 && quota != 0;
@@ -932,7 +1109,7 @@ __global__ void __launch_bounds__(64) topk_write_cand(TopkArgs a, Scratch s) {
             if ((uint32_t)u * TK_GL + sub < n_ent) mark(ent[tn][u].x, ent[tn][u].y);
         for (uint32_t p = SPEC * TK_GL + sub; p < n_ent; p += TK_GL) mark(slot_idx[p], slot_val[p]);   // a fuller slot than usual
         __syncthreads();
-        if (ties) bitmap_prefix(eq_bits, prefix, sub);          // all lanes of the group together
+        if (ties) bitmap_prefix<TK_GL>(eq_bits, prefix, sub);          // all lanes of the group together
         __syncthreads();
         if (ties) {
 #pragma unroll
@@ -951,7 +1128,7 @@ __global__ void __launch_bounds__(64) topk_write_cand(TopkArgs a, Scratch s) {
             }
         }
         __syncthreads();
-        bitmap_prefix(sel_bits, prefix, sub);
+        bitmap_prefix<TK_GL>(sel_bits, prefix, sub);
         __syncthreads();
         auto emit = [&](uint32_t q, uint32_t bits) {
             if (sel_bits[q >> 5] & (1u << (q & 31))) {
@@ -1021,7 +1198,7 @@ static_assert(TK_RTHREADS / 64 == 16, "the wave tree above is written for 16 wav
 // bound that held, are left to gs_count_dense.
 constexpr int GS_WAVES = 4;                                   // chunks per workgroup
 __device__ __forceinline__ bool gs_chunk_is_sifted(const Scratch& s, int row, size_t slot) {
-    return s.rows[row].gs_mode && s.cand_cnt[slot] <= (uint32_t)TK_CAP;
+    return s.rows[row].gs_mode && s.cand_cnt[slot] <= s.cap;
 }
 __global__ void __launch_bounds__(GS_WAVES * 64) gs_sift(TopkArgs a, Scratch s) {
     const int row = blockIdx.y;
@@ -1036,8 +1213,8 @@ __global__ void __launch_bounds__(GS_WAVES * 64) gs_sift(TopkArgs a, Scratch s) 
     const uint64_t c0 = (uint64_t)chunk * TK_CHUNK;
     const float lambda = s.rows[row].lambda;
     const uint32_t t_lo = (uint32_t)*a.t_ptr;
-    uint32_t* slot_val = s.slot_val + slot * TK_CAP;
-    uint16_t* slot_idx = s.slot_idx + slot * TK_CAP;
+    uint32_t* slot_val = s.slot_val + slot * s.cap;
+    uint16_t* slot_idx = s.slot_idx + slot * s.cap;
     const uint32_t have = s.cand_cnt[slot];
     const unsigned long long below = (1ull << lane) - 1ull;
     uint32_t kept = 0;
@@ -1086,10 +1263,10 @@ __global__ void __launch_bounds__(TK_THREADS) gs_count_dense(TopkArgs a, Scratch
         for (int it = 0; it < TK_ITERS; ++it) vin[it] = ld4_stream(dr + c0 + (uint64_t)it * TK_VEC + 4 * threadIdx.x);   // rows are padded to whole chunks
 #pragma unroll
         for (int it = 0; it < TK_ITERS; ++it) keep[it] = gs_keep4(a, row, c0 + (uint64_t)it * TK_VEC + 4 * threadIdx.x, t_lo, lambda, vin[it]);
-        const uint32_t n = gs_collect(vin, keep, s.slot_val + slot * TK_CAP, s.slot_idx + slot * TK_CAP, wave_sums4);
+        const uint32_t n = gs_collect(vin, keep, s.slot_val + slot * s.cap, s.slot_idx + slot * s.cap, s.cap, wave_sums4);
         if (threadIdx.x == 0) {
             s.cnt_gt[slot] = n;
-            if (n > (uint32_t)TK_CAP) atomicAdd(&s.rows[row].gs_need_write, 1u);
+            if (n > s.cap) atomicAdd(&s.rows[row].gs_need_write, 1u);
         }
     }
 }
@@ -1133,13 +1310,13 @@ __global__ void __launch_bounds__(GS_WAVES * 64) gs_write(TopkArgs a, Scratch s)
     if (chunk >= s.nchunks) return;
     const size_t slot = (size_t)row * s.nchunks + chunk;
     const uint32_t cnt = s.cnt_gt[slot];
-    if (cnt > (uint32_t)TK_CAP) return;                        // uniform over the wave
+    if (cnt > s.cap) return;                        // uniform over the wave
     const uint64_t c0 = (uint64_t)chunk * TK_CHUNK;
     const uint32_t limit = (uint32_t)a.k;                     // pair positions of the row: [1, limit)
     const uint32_t base = s.out_off[(size_t)row * (s.nchunks + 1) + chunk];
     uint2* mrow = reinterpret_cast<uint2*>(a.msg + (uint64_t)row * a.k * 8);
-    const uint32_t* slot_val = s.slot_val + slot * TK_CAP;
-    const uint16_t* slot_idx = s.slot_idx + slot * TK_CAP;
+    const uint32_t* slot_val = s.slot_val + slot * s.cap;
+    const uint16_t* slot_idx = s.slot_idx + slot * s.cap;
     for (uint32_t p = threadIdx.x & 63; p < cnt; p += 64)
         if (base + p < limit) mrow[base + p] = make_uint2((uint32_t)(c0 + slot_idx[p]), slot_val[p]);
 }
@@ -1155,7 +1332,7 @@ __global__ void __launch_bounds__(TK_THREADS) gs_write_dense(TopkArgs a, Scratch
     const uint32_t t_lo = (uint32_t)*a.t_ptr;                 // the step's counter: advanced only after this kernel
     const float* dr = a.delta + (uint64_t)row * a.ld;
     for (uint32_t chunk = blockIdx.x; chunk < s.nchunks; chunk += gridDim.x) {
-        if (s.cnt_gt[(size_t)row * s.nchunks + chunk] <= (uint32_t)TK_CAP) continue;    // uniform
+        if (s.cnt_gt[(size_t)row * s.nchunks + chunk] <= s.cap) continue;    // uniform
         const uint64_t c0 = (uint64_t)chunk * TK_CHUNK;
         uint32_t run = s.out_off[(size_t)row * (s.nchunks + 1) + chunk];
         for (int it = 0; it < TK_ITERS; ++it) {
@@ -1321,6 +1498,18 @@ ds_status topk_create(const ds_config& cfg, uint64_t ld, bool resident, bool imp
     st->gspar = cfg.comp.kind == DS_COMP_GSPAR;
     Scratch& s = st->s;
     s.nchunks = (uint32_t)((cfg.N + TK_CHUNK - 1) / TK_CHUNK);
+    // Room for 1.6 k candidates up to 3 % of N.  Beyond that 1.3 k are aimed at, and a slot has room for twice the chunk's share of
+    // them: with 512 places for any k such rows went the exact way in every step (8 x 33,554,432, 10 % sent: 7216 us a step).
+    s.cap = TK_CAP;
+    s.target = TK_TARGET;
+    if (!st->gspar && cfg.comp.k > cfg.N / 32) {
+        s.target = 1.3f;
+        const double want = 2.0 * (double)s.target * (double)cfg.comp.k / (double)cfg.N * TK_CHUNK;
+        s.cap = want < TK_CHUNK ? ((uint32_t)want + 63u) / 64u * 64u : (uint32_t)TK_CHUNK;
+        if (s.cap < TK_CAP) s.cap = TK_CAP;
+    }
+    s.row_select = s.nchunks <= TK_SEL_CHUNKS && cfg.comp.k <= TK_SEL_K ? 1u : 0u;
+    s.hist_wgs = s.nchunks >= 64u * TK_HWG ? TK_HWG : (s.nchunks + 63u) / 64u;   // 64 chunks side by side in each
     // the first pass reads and writes whole chunks of x and delta
     if ((uint64_t)s.nchunks * TK_CHUNK > ld) { err = "internal: row pitch smaller than the chunked row"; delete st; return DS_EINVAL; }
     const size_t n = (size_t)cfg.n, nc = s.nchunks;
@@ -1337,8 +1526,8 @@ ds_status topk_create(const ds_config& cfg, uint64_t ld, bool resident, bool imp
         m.place(s.cnt_gt, n * nc);
         m.place(s.cnt_eq, n * nc);
         m.place(s.eq_before, n * nc);
-        m.place(s.slot_val, n * nc * TK_CAP);
-        m.place(s.slot_idx, n * nc * TK_CAP);
+        m.place(s.slot_val, n * nc * s.cap);
+        m.place(s.slot_idx, n * nc * s.cap);
         m.place(s.list, n * TK_LIST_CAP);
         m.place(s.csum, st->gspar ? n * nc : 1);
         return zero;
@@ -1403,10 +1592,12 @@ ds_status topk_step(TopkState* st, const TopkArgs& a, bool one_launch, hipStream
     if (one_launch) return sparse_resident_step(st->resident, a, stream);
     const Scratch& s = st->s;
     const dim3 grid(s.nchunks, a.n), block(TK_THREADS), rblock(TK_RTHREADS);
+    const bool many = a.k * (uint64_t)TK_CHUNK > 200ull * a.N;            // more pairs of a neighbour in a chunk than threads, or nearly
     if (st->gspar) {
         // form (tail of the last step, line 5, sums of |v|, what can be kept at all) -> lambda -> kept elements and
         // their number per chunk -> offsets -> pairs
-        hipLaunchKernelGGL(topk_form_collect<true>, grid, block, 0, stream, a, s);
+        const auto form = many ? topk_form_collect<true, 2> : topk_form_collect<true, 1>;
+        hipLaunchKernelGGL(form, grid, block, 0, stream, a, s);
         hipLaunchKernelGGL(gs_row_lambda, dim3(a.n), rblock, 0, stream, s, (double)a.k_expected);
         const dim3 wgrid((s.nchunks + GS_WAVES - 1) / GS_WAVES, a.n), wblock(GS_WAVES * 64);
         const dim3 dgrid(s.nchunks < (uint32_t)TK_FWG ? s.nchunks : (uint32_t)TK_FWG, a.n);
@@ -1418,25 +1609,32 @@ ds_status topk_step(TopkState* st, const TopkArgs& a, bool one_launch, hipStream
         hipLaunchKernelGGL(gs_close, dim3(1), dim3(1), 0, stream, a.t_ptr);
         return chain_enqueued(st, a, stream);
     }
-    const dim3 wgrid((s.nchunks + TK_WPW - 1) / TK_WPW, a.n);
+    const uint32_t per_wave = write_chunks(s.cap > TK_CAP ? 64 : 16);
+    const dim3 wgrid((s.nchunks + per_wave - 1) / per_wave, a.n);
     // full mode walks a row's chunks with a fixed number of workgroups, so that a step in which no row needs it
     // pays little for the launches
     const dim3 fgrid(s.nchunks < (uint32_t)TK_FWG ? s.nchunks : (uint32_t)TK_FWG, a.n);
-    const dim3 hgrid(TK_HWG, a.n), hblock(TK_HTHREADS);
+    const dim3 hgrid(s.hist_wgs, a.n), hblock(TK_HTHREADS);
     const dim3 rows(a.n);
     const uint32_t k = (uint32_t)a.k;
     // after a flush (and at the start) all message offsets are zero, so the first pass finds no tail to apply
-    hipLaunchKernelGGL(topk_form_collect<false>, grid, block, 0, stream, a, s);
-    hipLaunchKernelGGL(topk_decide_select, rows, block, 0, stream, s, k);
-    hipLaunchKernelGGL(topk_hist_cand2, hgrid, hblock, 0, stream, s);
-    hipLaunchKernelGGL(topk_select2_cand, rows, block, 0, stream, s);
-    hipLaunchKernelGGL(topk_bin_collect, hgrid, hblock, 0, stream, s);
+    const auto form = many ? topk_form_collect<false, 2> : topk_form_collect<false, 1>;
+    hipLaunchKernelGGL(form, grid, block, 0, stream, a, s);
+    if (s.row_select) {
+        hipLaunchKernelGGL(topk_select_row, rows, rblock, 0, stream, s, k);
+    } else {
+        hipLaunchKernelGGL(topk_decide_select, rows, block, 0, stream, s, k);
+        hipLaunchKernelGGL(topk_hist_cand2, hgrid, hblock, 0, stream, s);
+        hipLaunchKernelGGL(topk_select2_cand, rows, block, 0, stream, s);
+        hipLaunchKernelGGL(topk_bin_collect, hgrid, hblock, 0, stream, s);
+    }
     hipLaunchKernelGGL(topk_hist_full<1>, fgrid, block, 0, stream, a.delta, a.ld, a.N, s, k);
     hipLaunchKernelGGL(topk_hist_full<2>, fgrid, block, 0, stream, a.delta, a.ld, a.N, s, k);
     hipLaunchKernelGGL(topk_hist_full<3>, fgrid, block, 0, stream, a.delta, a.ld, a.N, s, k);
     hipLaunchKernelGGL(topk_fix_full, fgrid, block, 0, stream, a.delta, a.ld, a.N, s);
     hipLaunchKernelGGL(topk_finish, rows, rblock, 0, stream, s, k, a.t_ptr);
-    hipLaunchKernelGGL(topk_write_cand, wgrid, dim3(64), 0, stream, a, s);
+    if (s.cap > TK_CAP) hipLaunchKernelGGL(topk_write_cand<64>, wgrid, dim3(64), 0, stream, a, s);
+    else                hipLaunchKernelGGL(topk_write_cand<16>, wgrid, dim3(64), 0, stream, a, s);
     hipLaunchKernelGGL(topk_write_full, fgrid, block, 0, stream, a, s);
     return chain_enqueued(st, a, stream);
 }
