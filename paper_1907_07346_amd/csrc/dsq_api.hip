@@ -35,6 +35,7 @@ struct ds_handle {
     uint64_t run = 0, period = 1;
     bool complete = true;                // x and delta are complete once everything enqueued has run
     enum { kFree, kWhole, kStreamed } captured = kFree;   // how the steps go that a graph may replay unseen, and all others with them
+    bool unseen = false;                 // a step has been captured: graphs may run steps that are not counted here
     dsq::TopkState* topk = nullptr;
     dsq::L2State* l2q = nullptr;
     bool resident = false;               // steps may take one launch ...
@@ -172,17 +173,27 @@ dsq::L2Args l2_args(const ds_handle* h, const float* g_dev, uint64_t g_ld) {
 // this applies it now, on the stream of the last step.  Callers that replace W, gamma or eta call it BEFORE the
 // replacement: the tail belongs to the values the step ran with.
 ds_status flush_deferred(ds_handle* h) {
-    if (h->topk) return dsq::topk_flush(h->topk, topk_args(h, nullptr, 0), h->last_stream);
-    if (h->l2q) return dsq::l2q_flush(h->l2q, l2_args(h, nullptr, 0), h->last_stream);
+    if (h->topk) return dsq::topk_flush(h->topk, topk_args(h, nullptr, 0), h->unseen, h->last_stream);
+    if (h->l2q) return dsq::l2q_flush(h->l2q, l2_args(h, nullptr, 0), h->unseen, h->last_stream);
     if (h->tile.streaming && h->stepped) {
         if (h->run) h->period = h->run;
         h->run = 0;
         if (h->complete && h->captured != ds_handle::kStreamed) return DS_OK;
-        h->tile.flush(tile_args(h, nullptr, 0), h->last_stream);
+        dsq::TileArgs a = tile_args(h, nullptr, 0);
+        a.known = h->unseen ? 0u : 1u;
+        h->tile.flush(a, h->last_stream);
         h->complete = true;
         return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
     }
     return DS_OK;
+}
+
+// Is the stream being captured into a graph?  (What cannot be found out counts as yes.)
+bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
 }
 
 dsq::TileArgs tile_args(const ds_handle* h, const float* g_dev, uint64_t g_ld) {
@@ -756,6 +767,9 @@ ds_status ds_step(ds_handle* h, const float* g_dev, uint64_t g_ld, void* hip_str
     if (hipGetDevice(&dev) != hipSuccess || dev != h->device)
         return fail(h, DS_ESTATE, "the current HIP device is not the one the handle was created on");
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    // Some plans leave part of a step to be done when x and delta are asked for, and whether there is such a part is known here only
+    // as long as no graph runs steps.
+    if ((h->topk || h->l2q || h->tile.streaming) && !h->unseen) h->unseen = capturing(stream);
 
     if (h->topk) {
         const ds_status st = dsq::topk_step(h->topk, topk_args(h, g_dev, g_ld), seated(h, stream), stream);
@@ -774,12 +788,10 @@ ds_status ds_step(ds_handle* h, const float* g_dev, uint64_t g_ld, void* hip_str
             // Where x is read after every step, a step is taken whole; where several follow one another, each leaves its gossip
             // sum to the next one's pass, which reads x anyway.  A step that is captured may be replayed between any others:
             // the way of the first one that is captured is the way of all that follow.
-            hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-            if (hipStreamIsCapturing(stream, &status) != hipSuccess) { (void)hipGetLastError(); status = hipStreamCaptureStatusActive; }
             h->run += 1;
             bool whole = h->team.launch && h->complete && h->run == 1 && h->period == 1;
             if (h->captured != ds_handle::kFree) whole = h->captured == ds_handle::kWhole;
-            else if (status != hipStreamCaptureStatusNone) h->captured = whole ? ds_handle::kWhole : ds_handle::kStreamed;
+            else if (h->unseen) h->captured = whole ? ds_handle::kWhole : ds_handle::kStreamed;
             const dsq::TilePlan& plan = whole ? h->team : h->tile;
             plan.launch(plan_args(h, plan, g_dev, g_ld), plan.rows_per_wave, stream);
             h->complete = whole;

@@ -82,6 +82,7 @@ struct TileArgs {
     const uint8_t* msg_prev;           // the previous step's messages: set by the kernels themselves (msg holds two
     uint64_t msg_half;                 // buffers of msg_half bytes; step t writes half t & 1 and reads the other)
     uint32_t* pending;                 // 1: the previous step's gossip sum has not been added to x yet
+    uint32_t known;                    // flush: 1 if the host knows that it has not; 0: the kernel looks at `pending`
     // random sparsifier only:
     const uint32_t* keep_off;          // n x nsweeps: kept values before each 256-column sweep inside its group of 16
     const uint32_t* keep_group_off;    // n x ngroups: values the row's message holds before each group
@@ -172,6 +173,7 @@ struct TopkArgs {
     int n;
     float gamma, eta;
     unsigned long long* t_ptr;  // step counter in device memory (advanced once per step)
+    uint32_t known;            // flush: 1 if the host knows that a tail is pending; 0: the kernels look at the device's mark
     // GSpar only:
     uint64_t k_expected;       // the operator's k (expected kept elements)
     uint32_t seed_lo, seed_hi; // key of the mask's random stream
@@ -188,8 +190,9 @@ void topk_destroy(TopkState* s);
 ds_status topk_step(TopkState* s, const TopkArgs& a, bool one_launch, hipStream_t stream);
 // Unless the state is made for one launch, topk_step leaves the sparse part of the gossip update of x to the next step's first pass;
 // topk_flush applies it now (no-op if nothing is pending).  Call before x is read or replaced, with the
-// buffers, mixing matrix and eta the last step ran with (a.g is not used).
-ds_status topk_flush(TopkState* s, const TopkArgs& a, hipStream_t stream);
+// buffers, mixing matrix and eta the last step ran with (a.g is not used).  unseen: a step of the handle has been captured, so
+// what is pending is not known here (a graph may have been replayed).
+ds_status topk_flush(TopkState* s, const TopkArgs& a, bool unseen, hipStream_t stream);
 // Number of rows whose last step selected from the candidate slots (the fast path).
 ds_status topk_candidate_rows(TopkState* s, hipStream_t stream, uint32_t* count);
 // GSpar: true if a row has kept more elements than its message has room for in some step since the handle was made.
@@ -212,6 +215,7 @@ struct L2Args {
     unsigned long long* t_ptr;  // step cells in device memory: [0] the step counter (advanced once per step), [4] the
                                 // message buffer (0 / 1) the last completed step wrote, [5] rows finished in the
                                 // step's last kernel (zero between launches)
+    uint32_t known;             // flush: what the device's mark of a pending tail holds, if the host knows; 0: the kernels look
 };
 
 struct L2State;                // device scratch: per-row scales, per-chunk partial reductions
@@ -223,7 +227,7 @@ ds_status l2q_step(L2State* s, const L2Args& a, bool one_launch, hipStream_t str
 // Unless the state is made for one launch, l2q_step leaves delta = v - C[v] and the gossip update of x to the next step's first pass;
 // l2q_flush applies them now (no-op if nothing is pending).  Call before the state is read or replaced, with
 // the buffers, mixing matrix and eta the last step ran with (a.g is not used).
-ds_status l2q_flush(L2State* s, const L2Args& a, hipStream_t stream);
+ds_status l2q_flush(L2State* s, const L2Args& a, bool unseen, hipStream_t stream);
 // Number of rows whose last step kept the codes its first pass wrote speculatively (no second dense pass).
 ds_status l2q_speculated_rows(L2State* s, hipStream_t stream, uint32_t* count);
 

@@ -119,39 +119,67 @@ __device__ __forceinline__ uint32_t load_codes4(const uint8_t* msg_row, uint64_t
     else return *reinterpret_cast<const uint32_t*>(msg_row + 4 + col);
 }
 
-// Lines 6 (second half) and 9 of Algorithm 1 for four adjacent columns of worker `row`, from the
-// codes in the message buffer: d holds v and becomes delta, xh becomes x.
-template <int BITS>
-__device__ __forceinline__ void apply_tail4(const L2Args& a, const L2Scratch& s, const uint8_t* msg, int row, uint64_t col,
-                                            float4& xh, float4& d) {
-    constexpr int L = (1 << BITS) - 1;
-    constexpr uint32_t MASK = (1u << BITS) - 1u;
-    float* xp = reinterpret_cast<float*>(&xh);
-    float* dp = reinterpret_cast<float*>(&d);
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    float own[4] = {0.f, 0.f, 0.f, 0.f};
-    const int e0 = a.rowptr[row], e1 = a.rowptr[row + 1];
-    for (int e = e0; e < e1; ++e) {                       // ascending neighbour index, own index included
-        const int nb = a.col[e];
-        const float coef = a.coef[e];
-        const float unit = s.rows[nb].unit;
-        const uint32_t codes = load_codes4<BITS>(msg + (uint64_t)nb * a.msg_row_bytes, col);
+// Lines 6 (second half) and 9 of Algorithm 1 for a lane's quads of adjacent columns of worker `row`, from the codes in the
+// message buffer: d holds v and becomes delta, xh becomes x.  The row's first neighbours and their codes of all quads are asked for
+// together with x and delta (`ask`): a neighbour at a time, quad after quad, each of them showed its latency, with the loads of
+// its index and its unit in front (16 x 11,173,962 at 2 bits: l2q_tail 524 -> 483 us, l2q_form with a tail to apply 639 -> 590; 8 x
+// 2,000,000 at 4 bits: l2q_tail 56 -> 47).
+template <int BITS, int QUADS>
+struct Tail {
+    static constexpr int L = (1 << BITS) - 1;
+    static constexpr uint32_t MASK = (1u << BITS) - 1u;
+    static constexpr int AHEAD = BITS == 8 ? 3 : 4;           // neighbours asked for ahead: a ring's, and one more where codes are small
+    int e0, e1;
+    int nb[AHEAD];
+    float coef[AHEAD], unit[AHEAD];
+    uint32_t codes[AHEAD][QUADS];
+
+    __device__ __forceinline__ void graph(const L2Args& a, const L2Scratch& s, int row) {
+        e0 = a.rowptr[row];
+        e1 = a.rowptr[row + 1];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            nb[u] = a.col[e0 + u < e1 ? e0 + u : e0];         // a row has its own entry at least
+            coef[u] = a.coef[e0 + u < e1 ? e0 + u : e0];
+        }
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) unit[u] = s.rows[nb[u]].unit;
+    }
+    __device__ __forceinline__ void ask(const L2Args& a, const uint8_t* msg, int quad, uint64_t col) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)
+            if (e0 + u < e1 && col < a.N) codes[u][quad] = load_codes4<BITS>(msg + (uint64_t)nb[u] * a.msg_row_bytes, col);
+    }
+    __device__ __forceinline__ void apply(const L2Args& a, const L2Scratch& s, const uint8_t* msg, int row, int quad, uint64_t col, float4& xh, float4& d) const {
+        float* xp = reinterpret_cast<float*>(&xh);
+        float* dp = reinterpret_cast<float*>(&d);
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+        float own[4] = {0.f, 0.f, 0.f, 0.f};
+        auto add = [&](uint32_t four, int from, float w, float scale) {            // ascending neighbour index, own index included
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int y = 2 * (int)((four >> (BITS * c)) & MASK) - L;
+                const float cv = (float)y * scale;
+                acc[c] = fmaf(w, cv, acc[c]);
+                if (from == row) own[c] = cv;
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)
+            if (e0 + u < e1) add(codes[u][quad], nb[u], coef[u], unit[u]);
+        for (int e = e0 + AHEAD; e < e1; ++e) {
+            const int from = a.col[e];
+            add(load_codes4<BITS>(msg + (uint64_t)from * a.msg_row_bytes, col), from, a.coef[e], s.rows[from].unit);
+        }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const int y = 2 * (int)((codes >> (BITS * c)) & MASK) - L;
-            const float cv = (float)y * unit;
-            acc[c] = fmaf(coef, cv, acc[c]);
-            if (nb == row) own[c] = cv;
+            if (col + c < a.N) {                              // padding columns stay zero
+                dp[c] = dp[c] - own[c];
+                xp[c] = fmaf(a.eta, acc[c], xp[c]);
+            }
         }
     }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        if (col + c < a.N) {                              // padding columns stay zero
-            dp[c] = dp[c] - own[c];
-            xp[c] = fmaf(a.eta, acc[c], xp[c]);
-        }
-    }
-}
+};
 
 __device__ __forceinline__ void add4(float4& d, const float4& x) {
     d.x = x.x + d.x; d.y = x.y + d.y; d.z = x.z + d.z; d.w = x.w + d.w;
@@ -198,6 +226,12 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_form(L2Args a, L2Scratch s) {
     // all twelve 16-byte loads of the lane go out before the first store: x and delta are updated in place, so the
     // compiler must otherwise keep every later load behind the stores of the iteration before
     float4 xs[LQ_ITERS], ds[LQ_ITERS], gs[LQ_ITERS];
+    Tail<BITS, LQ_ITERS> last;
+    if (tail) {                                           // uniform
+        last.graph(a, s, row);
+#pragma unroll
+        for (int it = 0; it < LQ_ITERS; ++it) last.ask(a, msg_prev, it, col0 + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x);
+    }
 #pragma unroll
     for (int it = 0; it < LQ_ITERS; ++it) {
         const uint64_t col = col0 + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x;   // < ld: ld is a multiple of the chunk
@@ -219,7 +253,7 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_form(L2Args a, L2Scratch s) {
             }
             if (tail) {
                 if (pending == 2u) add4(d4, x4);
-                apply_tail4<BITS>(a, s, msg_prev, row, col, x4, d4);
+                last.apply(a, s, msg_prev, row, it, col, x4, d4);
             }
         }
         float4 xh, v;
@@ -335,11 +369,12 @@ __global__ void __launch_bounds__(LQ_ROW_THREADS) l2q_row_scale(L2Scratch s, flo
 }
 static_assert(LQ_ROW_THREADS / 64 == 16, "the wave tree above is written for 16 waves");
 
-// Second pass, one workgroup per chunk.  Rows whose speculative codes stand: the chunk's undecided elements get
-// their exact code now that s is known (one slot entry per thread: an xor on the element's bits of the message
-// word, a correction of the chunk's sum of y^2).  Other rows: the codes of v (which `form` left in delta) and the
+// Second pass, a workgroup for settle_chunks() chunks.  Rows whose speculative codes stand: the chunk's undecided elements get
+// their exact code now that s is known (a wave per chunk: an xor on the element's bits of the message
+// word, a correction of the chunk's sum of y^2; with a workgroup per chunk most threads have no entry.  At 8 bits, where rows mostly
+// take the exact way, a workgroup keeps to one chunk: 16 x 2,000,000 50 us, with four 54).  Other rows: the codes of v (which `form` left in delta) and the
 // sum of y^2 per chunk, from scratch.
-static_assert(LQ_UCAP <= LQ_THREADS, "one slot entry per thread");
+constexpr uint32_t settle_chunks(int bits) { return bits == 8 ? 1 : LQ_THREADS / 64; }
 static_assert(LQ_THREADS == kResThreads && LQ_ITERS == kResIters, "the resident kernel works on the same chunks");
 template <int BITS>
 __global__ void __launch_bounds__(LQ_THREADS) l2q_quantize(L2Args a, L2Scratch s) {
@@ -347,20 +382,28 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_quantize(L2Args a, L2Scratch s
     __shared__ uint32_t wave_sy2[LQ_THREADS / 64];
     const int row = blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint64_t col0 = (uint64_t)blockIdx.x * LQ_CHUNK;
+    constexpr uint32_t PER = settle_chunks(BITS), LANES = LQ_THREADS / PER;
     if (s.rows[row].mode) {                                // uniform over the workgroup
-        const size_t chunk = (size_t)row * s.nchunks + blockIdx.x;
-        if (threadIdx.x >= s.ucount[chunk]) return;        // <= LQ_UCAP entries
-        const uint2 e = s.uslot[chunk * LQ_UCAP + threadIdx.x];
-        const int qb = (int)(e.x >> 16);
-        const int q = code_of<BITS>(__uint_as_float(e.y), s.rows[row].inv);
-        if (q != qb) {
-            uint32_t* words = reinterpret_cast<uint32_t*>(a.msg + (uint64_t)(last_half(a) ^ 1u) * a.msg_half + (uint64_t)row * a.msg_row_bytes + 4);
-            const uint64_t bit = (col0 + (e.x & 0xFFFFu)) * BITS;                         // position in the row's code stream
-            atomicXor(&words[bit >> 5], (uint32_t)(q ^ qb) << (bit & 31u));                // several threads may share a word
-            const int y = 2 * q - L, yb = 2 * qb - L;
-            atomicAdd(&s.csy2[chunk], (uint32_t)(y * y) - (uint32_t)(yb * yb));            // modulo 2^32: the sum itself fits
+        const uint32_t c = blockIdx.x * PER + threadIdx.x / LANES;
+        if (c >= s.nchunks) return;
+        const size_t chunk = (size_t)row * s.nchunks + c;
+        const uint32_t count = s.ucount[chunk];            // <= LQ_UCAP entries
+        uint32_t* words = reinterpret_cast<uint32_t*>(a.msg + (uint64_t)(last_half(a) ^ 1u) * a.msg_half + (uint64_t)row * a.msg_row_bytes + 4);
+        const float inv = s.rows[row].inv;
+        uint32_t moved = 0;
+        for (uint32_t p = threadIdx.x % LANES; p < count; p += LANES) {
+            const uint2 e = s.uslot[chunk * LQ_UCAP + p];
+            const int qb = (int)(e.x >> 16);
+            const int q = code_of<BITS>(__uint_as_float(e.y), inv);
+            if (q != qb) {
+                const uint64_t bit = ((uint64_t)c * LQ_CHUNK + (e.x & 0xFFFFu)) * BITS;    // position in the row's code stream
+                atomicXor(&words[bit >> 5], (uint32_t)(q ^ qb) << (bit & 31u));            // several lanes may share a word
+                const int y = 2 * q - L, yb = 2 * qb - L;
+                moved += (uint32_t)(y * y) - (uint32_t)(yb * yb);                          // modulo 2^32: the sum itself fits
+            }
         }
+        moved = wave_sum_u32(moved);
+        if (lane == 0 && moved != 0u) atomicAdd(&s.csy2[chunk], moved);
         return;
     }
     const float inv = s.rows[row].inv;
@@ -370,35 +413,38 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_quantize(L2Args a, L2Scratch s
     const bool add_x = *s.pending == 0u;                  // `form` had no tail to apply and left delta alone
     uint8_t* mrow = a.msg + (uint64_t)(last_half(a) ^ 1u) * a.msg_half + (uint64_t)row * a.msg_row_bytes;
     const uint64_t code_bytes = a.msg_row_bytes - 4;      // whole 32-bit words
-    uint32_t sy2 = 0;
+    for (uint32_t c = blockIdx.x * PER; c < (blockIdx.x + 1) * PER && c < s.nchunks; ++c) {
+        const uint64_t col0 = (uint64_t)c * LQ_CHUNK;
+        uint32_t sy2 = 0;
 #pragma unroll
-    for (int it = 0; it < LQ_ITERS; ++it) {
-        const uint64_t col = col0 + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x;
-        const uint64_t byte = col * BITS / 8;
-        if (byte >= code_bytes) continue;                 // behind the last code word of the row
-        float4 v4 = ld4_stream(dr + col);
-        if (add_x) add4(v4, ld4_stream(xr + col));
-        const float* vp = reinterpret_cast<const float*>(&v4);
-        uint32_t packed = 0;
+        for (int it = 0; it < LQ_ITERS; ++it) {
+            const uint64_t col = col0 + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x;
+            const uint64_t byte = col * BITS / 8;
+            if (byte >= code_bytes) continue;                 // behind the last code word of the row
+            float4 v4 = ld4_stream(dr + col);
+            if (add_x) add4(v4, ld4_stream(xr + col));
+            const float* vp = reinterpret_cast<const float*>(&v4);
+            uint32_t packed = 0;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            if (col + c < a.N) {                          // padding codes are 0 and do not count
-                const int q = zero_row ? 0 : code_of<BITS>(vp[c], inv);
-                const int y = 2 * q - L;
-                sy2 += (uint32_t)(y * y);
-                packed |= (uint32_t)q << (BITS * c);
+            for (int c = 0; c < 4; ++c) {
+                if (col + c < a.N) {                          // padding codes are 0 and do not count
+                    const int q = zero_row ? 0 : code_of<BITS>(vp[c], inv);
+                    const int y = 2 * q - L;
+                    sy2 += (uint32_t)(y * y);
+                    packed |= (uint32_t)q << (BITS * c);
+                }
             }
+            if constexpr (BITS == 2) mrow[4 + byte] = (uint8_t)packed;
+            else if constexpr (BITS == 4) *reinterpret_cast<uint16_t*>(mrow + 4 + byte) = (uint16_t)packed;
+            else *reinterpret_cast<uint32_t*>(mrow + 4 + byte) = packed;
         }
-        if constexpr (BITS == 2) mrow[4 + byte] = (uint8_t)packed;
-        else if constexpr (BITS == 4) *reinterpret_cast<uint16_t*>(mrow + 4 + byte) = (uint16_t)packed;
-        else *reinterpret_cast<uint32_t*>(mrow + 4 + byte) = packed;
-    }
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) sy2 += __shfl_xor(sy2, o);
-    if (lane == 0) wave_sy2[wave] = sy2;
-    __syncthreads();
-    if (threadIdx.x == 0)
-        s.csy2[(size_t)row * s.nchunks + blockIdx.x] = wave_sy2[0] + wave_sy2[1] + wave_sy2[2] + wave_sy2[3];
+        for (int o = 1; o < 64; o <<= 1) sy2 += __shfl_xor(sy2, o);
+        if (lane == 0) wave_sy2[wave] = sy2;
+        __syncthreads();
+        if (threadIdx.x == 0) s.csy2[(size_t)row * s.nchunks + c] = wave_sy2[0] + wave_sy2[1] + wave_sy2[2] + wave_sy2[3];
+        __syncthreads();
+    }
 }
 
 // The band the next step may assume for s: centred on this step's s, as wide as s has been moving lately.  A band too
@@ -459,24 +505,27 @@ __global__ void __launch_bounds__(LQ_ROW_THREADS) l2q_row_unit(L2Args a, L2Scrat
     }
 }
 
-// The tail on its own (l2q_flush): delta = v - C[v], x = xh + eta sum_j a_ij C[v_j].  AHEAD: iterations whose loads go out
+// The tail on its own (l2q_flush): delta = v - C[v], x = xh + eta sum_j a_ij C[v_j]; nothing is pending then.  AHEAD: iterations whose loads go out
 // ahead of the first store of theirs, all four (70 registers, seven workgroups on a compute unit) or two (48, eight); see tail_ahead.
 template <int BITS, int AHEAD>
 __global__ void __launch_bounds__(LQ_THREADS) l2q_tail(L2Args a, L2Scratch s) {
     static_assert(LQ_ITERS % AHEAD == 0, "whole groups of iterations");
-    const uint32_t pending = *s.pending;
+    const uint32_t pending = a.known ? a.known : *s.pending;
     if (pending == 0u) return;
     const int row = blockIdx.y;
     const uint64_t col0 = (uint64_t)blockIdx.x * LQ_CHUNK;
     const uint8_t* msg_last = a.msg + (uint64_t)last_half(a) * a.msg_half;
     float* xr = a.x + (uint64_t)row * a.ld;
     float* dr = a.delta + (uint64_t)row * a.ld;
+    Tail<BITS, AHEAD> last;
+    last.graph(a, s, row);
 #pragma unroll
     for (int i0 = 0; i0 < LQ_ITERS; i0 += AHEAD) {
         float4 xs[AHEAD], ds[AHEAD];
 #pragma unroll
         for (int u = 0; u < AHEAD; ++u) {
             const uint64_t col = col0 + (uint64_t)(i0 + u) * (4 * LQ_THREADS) + 4u * threadIdx.x;   // rows are padded to whole chunks
+            last.ask(a, msg_last, u, col);
             xs[u] = ld4_stream(xr + col);
             ds[u] = ld4_stream(dr + col);
         }
@@ -485,11 +534,12 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_tail(L2Args a, L2Scratch s) {
             const uint64_t col = col0 + (uint64_t)(i0 + u) * (4 * LQ_THREADS) + 4u * threadIdx.x;
             if (col >= a.N) continue;
             if (pending == 2u) add4(ds[u], xs[u]);
-            apply_tail4<BITS>(a, s, msg_last, row, col, xs[u], ds[u]);
+            last.apply(a, s, msg_last, row, u, col, xs[u], ds[u]);
             st4_stream(xr + col, xs[u]);
             st4_stream(dr + col, ds[u]);
         }
     }
+    if (a.known && blockIdx.x == 0 && row == 0 && threadIdx.x == 0) *s.pending = 0u;      // nobody in this launch looks at it
 }
 
 __global__ void l2q_clear_pending(L2Scratch s) { *s.pending = 0u; }
@@ -754,7 +804,7 @@ struct L2State {
     L2Scratch s{};
     Slab slab;                     // holds all of it
     int n = 0, bits = 0;
-    bool pending = false;          // a step has been enqueued (or may have been, by a replayed graph) that left its tail
+    uint32_t pending = 0;          // what L2Scratch::pending will hold when everything enqueued has run, replayed graphs apart
     bool resident = false;         // steps may run in one launch each; none leaves its tail then
     uint64_t patience = 0;         // of the resident kernel's first meeting
 };
@@ -832,13 +882,13 @@ static void launch_tail(const L2Args& a, const L2Scratch& s, hipStream_t stream)
     else hipLaunchKernelGGL((l2q_tail<BITS, 2>), grid, block, 0, stream, a, s);
 }
 
-static ds_status apply_tail(L2State* st, const L2Args& a, hipStream_t stream) {
-    // the kernels look at the device's pending flag themselves: a replayed graph of ds_step sets it
-    // without this code noticing
+static ds_status apply_tail(L2State* st, L2Args a, uint32_t known, hipStream_t stream) {
+    a.known = known;
     if (st->bits == 2)      launch_tail<2>(a, st->s, stream);
     else if (st->bits == 4) launch_tail<4>(a, st->s, stream);
     else                    launch_tail<8>(a, st->s, stream);
-    hipLaunchKernelGGL(l2q_clear_pending, dim3(1), dim3(1), 0, stream, st->s);
+    if (!known) hipLaunchKernelGGL(l2q_clear_pending, dim3(1), dim3(1), 0, stream, st->s);      // (5 us)
+    st->pending = 0u;
     return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
 }
 
@@ -860,19 +910,22 @@ ds_status l2q_step(L2State* st, const L2Args& a, bool one_launch, hipStream_t st
     else if (st->bits == 4) hipLaunchKernelGGL(l2q_form<4>, grid, block, 0, stream, a, s);
     else                    hipLaunchKernelGGL(l2q_form<8>, grid, block, 0, stream, a, s);
     hipLaunchKernelGGL(l2q_row_scale, rows, rblock, 0, stream, s, hl);
-    if (st->bits == 2)      hipLaunchKernelGGL(l2q_quantize<2>, grid, block, 0, stream, a, s);
-    else if (st->bits == 4) hipLaunchKernelGGL(l2q_quantize<4>, grid, block, 0, stream, a, s);
-    else                    hipLaunchKernelGGL(l2q_quantize<8>, grid, block, 0, stream, a, s);
+    const uint32_t per = settle_chunks(st->bits);
+    const dim3 qgrid((s.nchunks + per - 1) / per, a.n);
+    if (st->bits == 2)      hipLaunchKernelGGL(l2q_quantize<2>, qgrid, block, 0, stream, a, s);
+    else if (st->bits == 4) hipLaunchKernelGGL(l2q_quantize<4>, qgrid, block, 0, stream, a, s);
+    else                    hipLaunchKernelGGL(l2q_quantize<8>, qgrid, block, 0, stream, a, s);
     hipLaunchKernelGGL(l2q_row_unit, rows, rblock, 0, stream, a, s, hl);
     // A state made for one launch gets the tail at once: the next step may be the resident kernel, in a graph that was
     // captured long ago even, and that expects x and delta complete.
-    if (st->resident) return apply_tail(st, a, stream);
-    st->pending = true;
+    st->pending = st->pending ? 1u : 2u;
+    if (st->resident) return apply_tail(st, a, 2u, stream);
     return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
 }
 
-ds_status l2q_flush(L2State* st, const L2Args& a, hipStream_t stream) {
-    return st && st->pending ? apply_tail(st, a, stream) : DS_OK;
+ds_status l2q_flush(L2State* st, const L2Args& a, bool unseen, hipStream_t stream) {
+    if (!st || st->resident) return DS_OK;
+    return unseen ? apply_tail(st, a, 0u, stream) : st->pending ? apply_tail(st, a, st->pending, stream) : DS_OK;
 }
 
 ds_status l2q_speculated_rows(L2State* st, hipStream_t stream, uint32_t* count) {

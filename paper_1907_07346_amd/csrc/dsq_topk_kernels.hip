@@ -121,6 +121,7 @@ struct Scratch {               // device pointers of the select's scratch (all o
     uint2* list;               // n x TK_LIST_CAP: (key, chunk) of the candidates inside the threshold's histogram bin
     double* csum;              // GSpar: n x nchunks tree sums of |v| over the chunks
     uint32_t* gs_overflow;     // GSpar: set once a row kept more than its message holds
+    uint32_t* pending;         // 1: the last step's sparse tail has not been applied yet
     uint32_t nchunks;
     uint32_t cap;              // candidates a chunk's slot has room for
     uint32_t row_select;       // a row's select is one workgroup's work (topk_select_row)
@@ -257,7 +258,7 @@ __global__ void __launch_bounds__(TK_THREADS) topk_form_collect(TopkArgs a, Scra
         }
     }
     bool patch = false;
-    {
+    if (*s.pending != 0u) {                                    // uniform
         // eta * sum_j a_ij C[v_j] of the previous step for this chunk: the neighbours' pairs that fall
         // into the chunk are contiguous in their messages; accumulate neighbour after neighbour.
         const int e0 = a.rowptr[row], e1 = a.rowptr[row + 1];
@@ -711,7 +712,7 @@ __global__ void __launch_bounds__(TK_RTHREADS) topk_finish(Scratch s, uint32_t k
     __shared__ uint32_t wave_sums[TK_RTHREADS / 64];
     __shared__ uint32_t h[FINE_SPAN];
     __shared__ uint32_t sel[2];
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(t_ptr, 1ull);   // one step taken
+    if (blockIdx.x == 0 && threadIdx.x == 0) { atomicAdd(t_ptr, 1ull); *s.pending = 1u; }   // one step taken
     const int row = blockIdx.x;
     const uint32_t nchunks = s.nchunks;
     TopkRow& r = s.rows[row];
@@ -1294,6 +1295,7 @@ __global__ void __launch_bounds__(TK_RTHREADS) gs_scan(TopkArgs a, Scratch s) {
     const uint32_t last = s.rows[row].gs_total;
     for (uint32_t p = count + threadIdx.x; p < last; p += TK_RTHREADS) mrow[1 + p] = make_uint2(0u, 0u);
     __syncthreads();                                          // every thread has read gs_total
+    if (row == 0 && threadIdx.x == 0) { atomicAdd(a.t_ptr, 1ull); *s.pending = 1u; }     // one step taken
     if (threadIdx.x == 0) {
         off[nchunks] = 1u + count;
         mrow[0] = make_uint2(count, 0u);
@@ -1329,7 +1331,7 @@ __global__ void __launch_bounds__(TK_THREADS) gs_write_dense(TopkArgs a, Scratch
     const uint32_t limit = (uint32_t)a.k;
     uint2* mrow = reinterpret_cast<uint2*>(a.msg + (uint64_t)row * a.k * 8);
     const float lambda = s.rows[row].lambda;
-    const uint32_t t_lo = (uint32_t)*a.t_ptr;                 // the step's counter: advanced only after this kernel
+    const uint32_t t_lo = (uint32_t)*a.t_ptr - 1u;            // gs_scan has advanced it
     const float* dr = a.delta + (uint64_t)row * a.ld;
     for (uint32_t chunk = blockIdx.x; chunk < s.nchunks; chunk += gridDim.x) {
         if (s.cnt_gt[(size_t)row * s.nchunks + chunk] <= s.cap) continue;    // uniform
@@ -1353,7 +1355,6 @@ __global__ void __launch_bounds__(TK_THREADS) gs_write_dense(TopkArgs a, Scratch
     }
 }
 
-__global__ void gs_close(unsigned long long* t_ptr) { atomicAdd(t_ptr, 1ull); }      // one step taken
 
 // ---- the deferred sparse tail of a step, applied in place (when the state must be complete now) --
 // One workgroup per (row, chunk): the neighbours' pairs that fall into the chunk are contiguous in their messages
@@ -1371,12 +1372,21 @@ __global__ void __launch_bounds__(TK_THREADS) topk_gossip(TopkArgs a, Scratch s)
     const uint32_t nchunks = s.nchunks;
     const uint64_t c0 = (uint64_t)c * TK_CHUNK;
     const int e0 = a.rowptr[row], e1 = a.rowptr[row + 1];
+    if (!a.known && *s.pending == 0u) return;               // nothing to apply
+    // The mark goes when the host knows that it is there: nobody in this launch looks at it then.  (At the end: a store in front of them
+    // makes vector loads of the scalar loads of the graph and the offsets, 45 -> 82 us for 8 x 8,388,608 with 0.1 % sent.)
+    auto applied = [&]() {
+        if (a.known && c == 0 && row == 0 && threadIdx.x == 0) *s.pending = 0u;
+    };
     bool any = false;
     for (int e = e0; e < e1; ++e) {
         const uint32_t* off = s.out_off + (size_t)a.col[e] * (nchunks + 1) + c;
         any |= (off[0] != off[1]);
     }
-    if (!any) return;                                       // uniform
+    if (!any) {                                             // uniform
+        applied();
+        return;
+    }
     // the first pair per thread of the first neighbours, all asked for together
     constexpr int EB = 4;
     uint2 ahead[EB];
@@ -1453,13 +1463,10 @@ __global__ void __launch_bounds__(TK_THREADS) topk_gossip(TopkArgs a, Scratch s)
             st4_stream(dr + q, dv[it]);
         }
     }
+    applied();
 }
 
-__global__ void __launch_bounds__(256) topk_zero_words(uint32_t* p, size_t words) {
-    const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i + 3 < words) *reinterpret_cast<uint4*>(p + i) = make_uint4(0u, 0u, 0u, 0u);   // the array comes from hipMalloc: 16-byte aligned
-    else for (size_t q = i; q < words; ++q) p[q] = 0u;
-}
+__global__ void topk_clear_pending(Scratch s) { *s.pending = 0u; }
 
 __global__ void topk_init_rows(TopkRow* rows, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1478,8 +1485,7 @@ struct TopkState {
     Slab slab;                     // holds all of it
     int n = 0;
     bool gspar = false;            // the GSpar operator runs on this state (its own select-free chain of kernels)
-    bool pending = false;          // a step has been enqueued since the last flush (or may have been, by a
-                                   // replayed graph): its sparse tail may not have been applied yet
+    bool pending = false;          // the last enqueued step's sparse tail has not been applied, replayed graphs apart
     SparseResidentState* resident = nullptr;   // a small problem's step may be one launch; no step leaves anything pending then
 };
 
@@ -1515,6 +1521,7 @@ ds_status topk_create(const ds_config& cfg, uint64_t ld, bool resident, bool imp
     const size_t n = (size_t)cfg.n, nc = s.nchunks;
     bool ok = st->slab.make([&](Slab& m) {
         m.place(s.gs_overflow, 1);
+        m.place(s.pending, 1);
         m.place(s.hist, n * HIST_BINS);
         m.place(s.hist_part, n * TK_HPARTS * HIST_BINS);
         m.place(s.hist2, n * HIST_BINS);
@@ -1556,26 +1563,25 @@ ds_status topk_candidate_rows(TopkState* st, hipStream_t stream, uint32_t* count
     return DS_OK;
 }
 
-static ds_status apply_tail(TopkState* st, const TopkArgs& a, hipStream_t stream) {
+static ds_status apply_tail(TopkState* st, TopkArgs a, bool known, hipStream_t stream) {
     const dim3 grid(st->s.nchunks, a.n), block(TK_THREADS);
+    a.known = known ? 1u : 0u;
     hipLaunchKernelGGL(topk_gossip, grid, block, 0, stream, a, st->s);
-    // the tail is applied: no message offsets, nothing for the next first pass to apply again (a kernel, not a
-    // memset: the caller may be capturing the stream)
-    const size_t words = (size_t)st->n * (st->s.nchunks + 1);
-    hipLaunchKernelGGL(topk_zero_words, dim3((unsigned)((words + 1023) / 1024)), dim3(256), 0, stream, st->s.out_off, words);
+    if (!known) hipLaunchKernelGGL(topk_clear_pending, dim3(1), dim3(1), 0, stream, st->s);
+    st->pending = false;
     return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
 }
 
-ds_status topk_flush(TopkState* st, const TopkArgs& a, hipStream_t stream) {
-    // `pending` stays set: a captured graph of ds_step may be replayed without this code noticing, and a flush
-    // with nothing to apply is a grid of workgroups that return at once
-    return st && st->pending ? apply_tail(st, a, stream) : DS_OK;
+ds_status topk_flush(TopkState* st, const TopkArgs& a, bool unseen, hipStream_t stream) {
+    if (!st || st->resident) return DS_OK;
+    // where a graph may have been replayed, a flush with nothing to apply is a grid of workgroups that return at once
+    return unseen || st->pending ? apply_tail(st, a, !unseen, stream) : DS_OK;
 }
 
 // The chain of launches has been enqueued.  A state made for one launch gets the tail at once: the next step may be a
 // resident kernel, in a graph that was captured long ago even, and that expects x and delta complete.
 static ds_status chain_enqueued(TopkState* st, const TopkArgs& a, hipStream_t stream) {
-    if (st->resident) return apply_tail(st, a, stream);
+    if (st->resident) return apply_tail(st, a, true, stream);
     st->pending = true;
     return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
 }
@@ -1606,7 +1612,6 @@ ds_status topk_step(TopkState* st, const TopkArgs& a, bool one_launch, hipStream
         hipLaunchKernelGGL(gs_scan, dim3(a.n), rblock, 0, stream, a, s);
         hipLaunchKernelGGL(gs_write, wgrid, wblock, 0, stream, a, s);
         hipLaunchKernelGGL(gs_write_dense, dgrid, block, 0, stream, a, s);
-        hipLaunchKernelGGL(gs_close, dim3(1), dim3(1), 0, stream, a.t_ptr);
         return chain_enqueued(st, a, stream);
     }
     const uint32_t per_wave = write_chunks(s.cap > TK_CAP ? 64 : 16);
@@ -1617,7 +1622,6 @@ ds_status topk_step(TopkState* st, const TopkArgs& a, bool one_launch, hipStream
     const dim3 hgrid(s.hist_wgs, a.n), hblock(TK_HTHREADS);
     const dim3 rows(a.n);
     const uint32_t k = (uint32_t)a.k;
-    // after a flush (and at the start) all message offsets are zero, so the first pass finds no tail to apply
     const auto form = many ? topk_form_collect<false, 2> : topk_form_collect<false, 1>;
     hipLaunchKernelGGL(form, grid, block, 0, stream, a, s);
     if (s.row_select) {
