@@ -169,15 +169,28 @@ dsq::L2Args l2_args(const ds_handle* h, const float* g_dev, uint64_t g_ld) {
     return a;
 }
 
+// Is the stream being captured into a graph?  (What cannot be found out counts as yes.)
+bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // Three paths (top-k, norm-rescaled codes, the row-streaming block kernels) leave the tail of a step to the next step's first pass;
 // this applies it now, on the stream of the last step.  Callers that replace W, gamma or eta call it BEFORE the
 // replacement: the tail belongs to the values the step ran with.
 ds_status flush_deferred(ds_handle* h) {
+    // A flush that is captured runs in every replay, whatever is pending then: it has to be in the graph, and to look at the device's mark.
+    if ((h->topk || h->l2q || h->tile.streaming) && h->stepped && !h->unseen) h->unseen = capturing(h->last_stream);
     if (h->topk) return dsq::topk_flush(h->topk, topk_args(h, nullptr, 0), h->unseen, h->last_stream);
     if (h->l2q) return dsq::l2q_flush(h->l2q, l2_args(h, nullptr, 0), h->unseen, h->last_stream);
     if (h->tile.streaming && h->stepped) {
         if (h->run) h->period = h->run;
         h->run = 0;
+        // (A graph that begins with this call: its steps go the way of the steps so far, whole only if nothing is pending before it either.)
+        if (h->unseen && h->captured == ds_handle::kFree)
+            h->captured = h->team.launch && h->complete && h->period == 1 ? ds_handle::kWhole : ds_handle::kStreamed;
         if (h->complete && h->captured != ds_handle::kStreamed) return DS_OK;
         dsq::TileArgs a = tile_args(h, nullptr, 0);
         a.known = h->unseen ? 0u : 1u;
@@ -186,14 +199,6 @@ ds_status flush_deferred(ds_handle* h) {
         return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
     }
     return DS_OK;
-}
-
-// Is the stream being captured into a graph?  (What cannot be found out counts as yes.)
-bool capturing(hipStream_t stream) {
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return true;
 }
 
 dsq::TileArgs tile_args(const ds_handle* h, const float* g_dev, uint64_t g_ld) {
