@@ -46,6 +46,7 @@ struct Slab {
     // `list(slab)` places the arrays and returns how many bytes from the start on have to be zero.
     template <typename F>
     bool make(F list) {
+        bytes = 0;
         size_t zero = list(*this);
         if (hipMalloc(&base, bytes) != hipSuccess) { base = nullptr; return false; }
         bytes = 0;

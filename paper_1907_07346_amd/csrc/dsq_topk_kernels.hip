@@ -1519,7 +1519,7 @@ ds_status topk_create(const ds_config& cfg, uint64_t ld, bool resident, bool imp
     // the first pass reads and writes whole chunks of x and delta
     if ((uint64_t)s.nchunks * TK_CHUNK > ld) { err = "internal: row pitch smaller than the chunked row"; delete st; return DS_EINVAL; }
     const size_t n = (size_t)cfg.n, nc = s.nchunks;
-    bool ok = st->slab.make([&](Slab& m) {
+    auto place = [&](Slab& m) {
         m.place(s.gs_overflow, 1);
         m.place(s.pending, 1);
         m.place(s.hist, n * HIST_BINS);
@@ -1538,7 +1538,14 @@ ds_status topk_create(const ds_config& cfg, uint64_t ld, bool resident, bool imp
         m.place(s.list, n * TK_LIST_CAP);
         m.place(s.csum, st->gspar ? n * nc : 1);
         return zero;
-    });
+    };
+    bool ok = st->slab.make(place);
+    if (!ok && s.cap > TK_CAP) {                              // the least there is room for: such rows select from the state itself
+        (void)hipGetLastError();
+        st->slab.drop();
+        s.cap = TK_CAP;
+        ok = st->slab.make(place);
+    }
     if (resident) ok = ok && sparse_resident_create(cfg, impatient, s.rows, s.gs_overflow, &st->resident) == DS_OK;
     if (ok) {
         hipLaunchKernelGGL(topk_init_rows, dim3((cfg.n + 63) / 64), dim3(64), 0, 0, s.rows, cfg.n);
