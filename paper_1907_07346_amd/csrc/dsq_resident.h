@@ -97,27 +97,27 @@ __device__ __forceinline__ bool meet(uint32_t* w, uint32_t blocks, unsigned long
     return verdict == 0u;
 }
 
-// Counts workgroup `block` of `blocks` out (the finished-workgroup cells behind the step counter, as the tile kernel uses them: zero
-// again when the last is out); true in the one that leaves last.  Called by one thread, behind a barrier: what its workgroup
-// has read before is settled.
-__device__ __forceinline__ bool count_out(unsigned long long* t_ptr, unsigned long long block, unsigned long long blocks) {
-    const uint32_t cell = (uint32_t)block & 63u;
-    const unsigned long long members = (blocks >> 6) + (cell < (blocks & 63u) ? 1u : 0u);
-    unsigned long long* cnt = t_ptr + 32ull * (1 + cell);
-    if (__hip_atomic_fetch_add(cnt, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != members - 1ull) return false;
-    __hip_atomic_store(cnt, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long cells = blocks < 64u ? blocks : 64u;
-    if (__hip_atomic_fetch_add(t_ptr + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != cells - 1ull) return false;
-    __hip_atomic_store(t_ptr + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
-}
-
-// After parting: counts this workgroup out; true in the one workgroup that leaves last.  Called by all threads.
+// After parting: counts this workgroup out (the finished-workgroup cells behind the step counter, as the tile kernel uses
+// them); true in the one workgroup that leaves last.  Called by all threads.
 __device__ __forceinline__ bool leave(unsigned long long* t_ptr, uint32_t blocks) {
     __shared__ uint32_t is_last;
     drain();                                                // flags this workgroup has set land before it counts itself out
     __syncthreads();
-    if (threadIdx.x == 0) is_last = count_out(t_ptr, blockIdx.x, blocks) ? 1u : 0u;
+    if (threadIdx.x == 0) {
+        uint32_t last = 0;
+        const uint32_t cell = blockIdx.x & 63u;
+        const unsigned long long members = (blocks >> 6) + (cell < (blocks & 63u) ? 1u : 0u);
+        unsigned long long* cnt = t_ptr + 32ull * (1 + cell);
+        if (__hip_atomic_fetch_add(cnt, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == members - 1ull) {
+            __hip_atomic_store(cnt, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long cells = blocks < 64u ? blocks : 64u;
+            if (__hip_atomic_fetch_add(t_ptr + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == cells - 1ull) {
+                __hip_atomic_store(t_ptr + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                last = 1u;
+            }
+        }
+        is_last = last;
+    }
     __syncthreads();
     return is_last != 0u;
 }
