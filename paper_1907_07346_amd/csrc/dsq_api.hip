@@ -1,4 +1,5 @@
 // C ABI of libdsq: handle life cycle, state transfer and the ds_step dispatcher.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -31,7 +32,7 @@ struct ds_handle {
     dsq::TilePlan team;                  // row-streaming plan: what takes a step whole (launch == nullptr: nothing does)
     unsigned long long* d_team = nullptr;    // arrival counters of the team kernels
     bool impatient = false;              // ... whose workgroups then look for parts nobody works on at once (tests)
-    // Row-streaming plan: steps since x and delta were last asked for, and how many there were between the last two times.
+    // Steps since x and delta were last asked for, and how many there were between the last two times.
     uint64_t run = 0, period = 1;
     bool complete = true;                // x and delta are complete once everything enqueued has run
     enum { kFree, kWhole, kStreamed } captured = kFree;   // how the steps go that a graph may replay unseen, and all others with them
@@ -183,11 +184,11 @@ bool capturing(hipStream_t stream) {
 ds_status flush_deferred(ds_handle* h) {
     // A flush that is captured runs in every replay, whatever is pending then: it has to be in the graph, and to look at the device's mark.
     if ((h->topk || h->l2q || h->tile.streaming) && h->stepped && !h->unseen) h->unseen = capturing(h->last_stream);
+    if (h->run) h->period = h->run;
+    h->run = 0;
     if (h->topk) return dsq::topk_flush(h->topk, topk_args(h, nullptr, 0), h->unseen, h->last_stream);
     if (h->l2q) return dsq::l2q_flush(h->l2q, l2_args(h, nullptr, 0), h->unseen, h->last_stream);
     if (h->tile.streaming && h->stepped) {
-        if (h->run) h->period = h->run;
-        h->run = 0;
         // (A graph that begins with this call: its steps go the way of the steps so far, whole only if nothing is pending before it either.)
         if (h->unseen && h->captured == ds_handle::kFree)
             h->captured = h->team.launch && h->complete && h->period == 1 ? ds_handle::kWhole : ds_handle::kStreamed;
@@ -201,6 +202,21 @@ ds_status flush_deferred(ds_handle* h) {
     return DS_OK;
 }
 
+// The 64ths of the fused kernel's tiles whose x and delta stay in the memory-side cache: as many as fit into 192 MB of it beside the
+// messages, which go through it too.  Only in steps that follow one another: a caller that asks for x after every step reads
+// it, and draws the next gradient, in between, and plain loads that find nothing there are the slower ones (256 workers x 272,474 after a
+// pass over another state 313 us, non-temporal 286).
+// (us a step of a run, with nothing staying and so: 16 x 1,048,576 at 4 bits 64 and 57, 16 x 2,097,152 134 and 110; sign, 8 x 8,388,608 221
+// and 199, 8 x 25,557,032 722 and 675; 16 x 11,173,962 at 2 bits 637 and 616; 64 x 4,194,304 at 4 bits, whose messages are 134 MB,
+// 1009 and 973, with twice as much staying 1007 and three times 1064.)
+uint32_t stay_share(const ds_handle* h) {
+    if (h->run <= 1 && h->period <= 1) return 0;
+    constexpr uint64_t room = 192ull << 20;
+    const uint64_t messages = h->cfg.comp.kind == DS_COMP_IDENTITY ? 0 : h->msg_row_bytes * (uint64_t)h->cfg.n;
+    if (messages >= room) return 0;
+    return (uint32_t)std::min<uint64_t>(64, (room - messages) * 64 / ((uint64_t)h->cfg.n * h->cfg.N * 8));
+}
+
 dsq::TileArgs tile_args(const ds_handle* h, const float* g_dev, uint64_t g_ld) {
     dsq::TileArgs a{};
     a.x = h->x; a.delta = h->delta; a.g = g_dev; a.msg = h->msg;
@@ -210,6 +226,7 @@ dsq::TileArgs tile_args(const ds_handle* h, const float* g_dev, uint64_t g_ld) {
     a.gamma = h->cfg.gamma; a.eta = h->cfg.eta;
     a.seed_lo = (uint32_t)h->cfg.seed; a.seed_hi = (uint32_t)(h->cfg.seed >> 32); a.t_ptr = h->d_t;
     a.msg_half = h->msg_half;
+    a.stay = stay_share(h);
     a.pending = reinterpret_cast<uint32_t*>(h->d_t + 3);        // cell 3: the row-streaming variant's pending flag
     a.team_cells = h->d_team;
     a.team_patience = h->impatient ? 0 : dsq::kTeamPatienceTicks;
@@ -776,6 +793,7 @@ ds_status ds_step(ds_handle* h, const float* g_dev, uint64_t g_ld, void* hip_str
     // as long as no graph runs steps.
     if ((h->topk || h->l2q || h->tile.streaming) && !h->unseen) h->unseen = capturing(stream);
 
+    h->run += 1;
     if (h->topk) {
         const ds_status st = dsq::topk_step(h->topk, topk_args(h, g_dev, g_ld), seated(h, stream), stream);
         if (st != DS_OK) return fail(h, st, "launching the sparsifying step failed");
@@ -793,7 +811,6 @@ ds_status ds_step(ds_handle* h, const float* g_dev, uint64_t g_ld, void* hip_str
             // Where x is read after every step, a step is taken whole; where several follow one another, each leaves its gossip
             // sum to the next one's pass, which reads x anyway.  A step that is captured may be replayed between any others:
             // the way of the first one that is captured is the way of all that follow.
-            h->run += 1;
             bool whole = h->team.launch && h->complete && h->run == 1 && h->period == 1;
             if (h->captured != ds_handle::kFree) whole = h->captured == ds_handle::kWhole;
             else if (h->unseen) h->captured = whole ? ds_handle::kWhole : ds_handle::kStreamed;

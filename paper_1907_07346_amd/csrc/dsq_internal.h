@@ -77,6 +77,7 @@ struct TileArgs {
     const float* coef;
     uint64_t ld, g_ld, N, msg_row_bytes;
     int n, nnz;                // workers; stored entries of W - I
+    uint32_t stay;             // fused kernels: of 64 groups of tiles, those whose x and delta stay in the memory-side cache (stays())
     float gamma, eta;
     uint32_t seed_lo, seed_hi;
     // row-streaming variant only:

@@ -78,6 +78,31 @@ __device__ __forceinline__ void st4(float* p, const float4& v) {
     __builtin_nontemporal_store(w, reinterpret_cast<f32x4*>(p));
 }
 
+// ---- what stays in the memory-side cache from one step to the next ----------------------------------
+// A non-temporal load leaves nothing in the 256 MB in front of HBM, and with plain loads a pass over more than that finds none of
+// it again.  So in steps that follow one another x and delta of a fixed part of the tiles are read with plain loads: `stay` 64ths of
+// them, 0 to 64.  All else but the messages is marked non-temporal and does not push them out.  The part is spread over the
+// pass, eight tiles (one per XCD) at a time, so that the cache and HBM deliver side by side; in one stretch it gains a third of that.
+// (Where the line lies: see stay_share() in dsq_api.hip.)
+__device__ __forceinline__ bool stays(uint64_t tile, uint32_t stay) { return ((uint32_t)(tile >> 3) * stay & 63u) < stay; }
+template <bool STAY>
+__device__ __forceinline__ float4 ld4_state(const float* p) {
+    if constexpr (!STAY) return ld4(p);
+    const f32x4 v = *reinterpret_cast<const f32x4*>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+// f(std::true_type) or f(std::false_type).  (Without the barriers the compiler makes one plain load of the two kinds.)
+template <typename F>
+__device__ __forceinline__ void by_stay(bool stay, F f) {
+    if (stay) {
+        asm volatile("" ::: "memory");
+        f(std::true_type{});
+        asm volatile("" ::: "memory");
+    } else {
+        f(std::false_type{});
+    }
+}
+
 // ---- wave64 reductions on the DPP cross-lane path (no LDS traffic); the result is wave-uniform ----
 // row_shr:1,2,4,8 fold each row of 16 lanes into its lane 15, row_bcast15 folds row r into row r+1
 // (rows 1 and 3), row_bcast31 folds lane 31 into lane 63.  Lanes without a source keep `old`.
@@ -352,11 +377,24 @@ struct Tile {
     }
 
     // ---- phase 1 for one row: returns xh (x - gamma g) in registers ---------------------------
-    template <bool FULL>
+    // STAY: a.stay says what stays in the memory-side cache.
+    template <bool FULL, bool STAY = false>
     static __device__ __forceinline__ void load_row(const TileArgs& a, int i, uint64_t col0, int lane, float4 (&xv)[SW], float4 (&gv)[SW], float4 (&dv)[SW]) {
         const float* xr = a.x + (uint64_t)i * a.ld + col0 + 4 * lane;
         const float* dr = a.delta + (uint64_t)i * a.ld + col0 + 4 * lane;
         const float* gr = a.g + (uint64_t)i * a.g_ld + col0 + 4 * lane;
+        if constexpr (STAY) {
+#pragma unroll
+            for (int s = 0; s < SW; ++s) gv[s] = ld_g<FULL>(a, gr + s * kSweep, col0 + (uint64_t)s * kSweep + 4 * lane);
+            by_stay(stays(col0 / TC, a.stay), [&](auto stay) {
+#pragma unroll
+                for (int s = 0; s < SW; ++s) {
+                    xv[s] = ld4_state<stay()>(xr + s * kSweep);
+                    dv[s] = ld4_state<stay()>(dr + s * kSweep);
+                }
+            });
+            return;
+        }
 #pragma unroll
         for (int s = 0; s < SW; ++s) {
             xv[s] = ld4(xr + s * kSweep);
@@ -371,7 +409,7 @@ struct Tile {
     static __device__ __forceinline__ void compress_row(const TileArgs& a, int i, int li, uint64_t col0, int lane,
                                                         uint8_t* lds_codes, float* lds_units, float4 (&xh)[SW]) {
         float4 xv[SW], gv[SW], dv[SW];
-        load_row<FULL>(a, i, col0, lane, xv, gv, dv);
+        load_row<FULL, !TAIL && MODE == 0>(a, i, col0, lane, xv, gv, dv);
         compress_loaded<FULL, TAIL, MODE>(a, i, li, col0, lane, xv, gv, dv, lds_codes, lds_units, xh);
     }
 
@@ -569,7 +607,10 @@ struct Tile {
                     float* mrow = reinterpret_cast<float*>(msg_row);
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
-                        if (FULL || j + c < a.N) put<MODE>(mrow + j + c, comp(v[s], c));
+                        if (FULL || j + c < a.N) {           // as many bytes as x: nothing of it would stay
+                            if constexpr (MODE == 3) put<MODE>(mrow + j + c, comp(v[s], c));
+                            else __builtin_nontemporal_store(comp(v[s], c), mrow + j + c);
+                        }
                 }
             }
         }
