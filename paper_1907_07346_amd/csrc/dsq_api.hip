@@ -410,15 +410,16 @@ __device__ __forceinline__ void add_diagnostics(double cons, double dsq_, double
 
 // n rows of C columns at a time in LDS, so that x and delta are read once: the deviations from the mean and the mixed
 // errors, which need all rows of a column, come from there.  A quad of columns per lane; the C/4 lanes of a row side by
-// side, 1024/C rows in flight per load of the workgroup.  Bound by HBM: 64 workers x 4 Mi columns on a torus 1595 -> 540 us
-// (2.1 GB; the kernel below, which reads x twice and delta once more for every neighbour, mostly past the caches).
+// side, 1024/C rows in flight per load of the workgroup, the next tile's asked for while a tile is summed up.  Bound by HBM: the whole
+// call, 64 workers x 4 Mi columns on a torus (2.1 GB), 424 us, without the look-ahead 495; 8 x 8 Mi 195 and 259; 256 x 272,474 214 and
+// 239.  (The kernel below, which reads x twice and delta once more for every neighbour, mostly past the caches: 1595.)
 // LDS: [x: n x C][delta: n x C][column sums: 1024/C x C, then the means: C][rowptr n+1][col nnz][coef nnz]
 constexpr int kDiagGraphWords = 4096;
 constexpr size_t diagnostics_lds(int n, int C, size_t nnz) {
     return (size_t)n * C * 8 + (size_t)1024 * 8 + (size_t)C * 8 + ((size_t)n + 1 + 2 * nnz) * 4;
 }
 template <int C>
-__global__ void __launch_bounds__(256) diagnostics_tile_kernel(const float* __restrict__ x, const float* __restrict__ delta, uint64_t ld,
+__global__ void __launch_bounds__(256) diagnostics_tile_kernel(const float* x, const float* delta, uint64_t ld,
                                                                uint64_t tiles, int n, int nnz, const int32_t* __restrict__ graph, float eta,
                                                                double* __restrict__ out) {
     constexpr int LANES = C / 4, SIDE = 256 / LANES;             // lanes per row, rows side by side
@@ -434,31 +435,35 @@ __global__ void __launch_bounds__(256) diagnostics_tile_kernel(const float* __re
     for (int q = threadIdx.x; q < n + 1 + 2 * nnz; q += 256) rowptr[q] = graph[q];
     const int quad = threadIdx.x % LANES, side = threadIdx.x / LANES;
     double cons = 0.0, dsq_ = 0.0, mixed = 0.0;
-    for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {        // padding columns are zero: they add nothing
+    constexpr int OWN = 4;                                       // rows of a thread, at most
+    float4 xs[OWN], ds[OWN];
+    auto ask = [&](uint64_t tile) {                              // padding columns are zero: they add nothing
         const uint64_t j = tile * C + 4u * quad;
-        double sum[4] = {0.0, 0.0, 0.0, 0.0};
-        constexpr int AHEAD = 4;                                 // rows of a thread asked for together
-        for (int i0 = side; i0 < n; i0 += AHEAD * SIDE) {
-            float4 xs[AHEAD], ds[AHEAD];
 #pragma unroll
-            for (int u = 0; u < AHEAD; ++u) {
-                const int i = i0 + u * SIDE;
-                if (i < n) {
-                    xs[u] = *reinterpret_cast<const float4*>(x + (uint64_t)i * ld + j);
-                    ds[u] = *reinterpret_cast<const float4*>(delta + (uint64_t)i * ld + j);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < AHEAD; ++u) {
-                const int i = i0 + u * SIDE;
-                if (i < n) {
-                    lx[i * LANES + quad] = xs[u];
-                    ldel[i * LANES + quad] = ds[u];
-                    sum[0] += (double)xs[u].x; sum[1] += (double)xs[u].y; sum[2] += (double)xs[u].z; sum[3] += (double)xs[u].w;
-                    dsq_ += (double)ds[u].x * (double)ds[u].x + (double)ds[u].y * (double)ds[u].y + (double)ds[u].z * (double)ds[u].z + (double)ds[u].w * (double)ds[u].w;
-                }
+        for (int u = 0; u < OWN; ++u) {
+            const int i = side + u * SIDE;
+            if (i < n) {
+                xs[u] = *reinterpret_cast<const float4*>(x + (uint64_t)i * ld + j);
+                ds[u] = *reinterpret_cast<const float4*>(delta + (uint64_t)i * ld + j);
             }
         }
+    };
+    if (blockIdx.x < tiles) ask(blockIdx.x);
+    for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        double sum[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < OWN; ++u) {
+            const int i = side + u * SIDE;
+            if (i < n) {
+                lx[i * LANES + quad] = xs[u];
+                ldel[i * LANES + quad] = ds[u];
+                sum[0] += (double)xs[u].x; sum[1] += (double)xs[u].y; sum[2] += (double)xs[u].z; sum[3] += (double)xs[u].w;
+                dsq_ += (double)ds[u].x * (double)ds[u].x + (double)ds[u].y * (double)ds[u].y + (double)ds[u].z * (double)ds[u].z + (double)ds[u].w * (double)ds[u].w;
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0): so that no load below waits for the one before it
+        if (tile + gridDim.x < tiles) ask(tile + gridDim.x);     // in flight while this tile is summed up ...
+        asm volatile("" ::: "memory");                           // ... and not asked for where they are used
 #pragma unroll
         for (int c = 0; c < 4; ++c) sums[side * C + 4 * quad + c] = sum[c];
         __syncthreads();
