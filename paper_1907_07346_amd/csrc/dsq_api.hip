@@ -178,12 +178,15 @@ bool capturing(hipStream_t stream) {
     return true;
 }
 
+// Does a step leave part of itself to the next one?  (A state made for one launch never does.)
+bool defers(const ds_handle* h) { return h->tile.streaming || ((h->topk || h->l2q) && !h->resident); }
+
 // Three paths (top-k, norm-rescaled codes, the row-streaming block kernels) leave the tail of a step to the next step's first pass;
 // this applies it now, on the stream of the last step.  Callers that replace W, gamma or eta call it BEFORE the
 // replacement: the tail belongs to the values the step ran with.
 ds_status flush_deferred(ds_handle* h) {
     // A flush that is captured runs in every replay, whatever is pending then: it has to be in the graph, and to look at the device's mark.
-    if ((h->topk || h->l2q || h->tile.streaming) && h->stepped && !h->unseen) h->unseen = capturing(h->last_stream);
+    if (defers(h) && h->stepped && !h->unseen) h->unseen = capturing(h->last_stream);
     if (h->run) h->period = h->run;
     h->run = 0;
     if (h->topk) return dsq::topk_flush(h->topk, topk_args(h, nullptr, 0), h->unseen, h->last_stream);
@@ -796,7 +799,7 @@ ds_status ds_step(ds_handle* h, const float* g_dev, uint64_t g_ld, void* hip_str
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     // Some plans leave part of a step to be done when x and delta are asked for, and whether there is such a part is known here only
     // as long as no graph runs steps.
-    if ((h->topk || h->l2q || h->tile.streaming) && !h->unseen) h->unseen = capturing(stream);
+    if (defers(h) && !h->unseen) h->unseen = capturing(stream);
 
     h->run += 1;
     if (h->topk) {
