@@ -846,13 +846,15 @@ ds_status ds_set_mixing(ds_handle* h, const int32_t* W_rowptr, const int32_t* W_
     dsq::Graph g;
     if (dsq::build_graph(&probe, g, err) != DS_OK) return fail(h, DS_EINVAL, err);
     const size_t nnz = g.col.size();
+    dsq::TilePlan tile = h->tile, team = h->team;
     if (!h->topk && !h->l2q && !h->tile.streaming) {
         // the launch shape was chosen for the old graph; the new CSR only has to fit in LDS next to the codes
         std::vector<dsq::TilePlan> plans;
         if (!dsq::choose_tile_plans(h->cfg, (int)nnz, plans, err)) return fail(h, DS_EINVAL, err);
-        if (h->tile.team && !dsq::fit_team(g, h->tile)) h->tile = plans.front();
+        if (tile.team && !dsq::fit_team(g, tile)) tile = plans.front();
     }
-    if (h->team.launch && !dsq::fit_team(g, h->team) && h->captured != ds_handle::kWhole) h->team = dsq::TilePlan();
+    // (Where graphs may run whole steps all others have to be whole too: with the LDS of the old W, and rows that need more finished from memory.)
+    if (team.launch && !dsq::fit_team(g, team) && h->captured != ds_handle::kWhole) team = dsq::TilePlan();
     // a deferred tail belongs to the old W: apply it first
     if (flush_deferred(h) != DS_OK) return fail(h, DS_EHIP, "applying the deferred tail of the last step failed");
     DSQ_HIP(h, hipStreamSynchronize(h->last_stream));
@@ -873,6 +875,8 @@ ds_status ds_set_mixing(ds_handle* h, const int32_t* W_rowptr, const int32_t* W_
     h->d_col = packed + h->cfg.n + 1;
     h->d_coef = reinterpret_cast<float*>(h->d_col + nnz);
     h->graph = g;
+    h->tile = tile;
+    h->team = team;
     h->cfg.topo = DS_TOPO_CSR;
     return DS_OK;
 }

@@ -153,7 +153,7 @@ bool stream_plan(const ds_config& cfg, TilePlan& plan);
 // The shapes that split the rows of a tile over several workgroups, most rows per workgroup first; none where one holds them all
 // or a tile has too many.
 void team_plans(const ds_config& cfg, const Graph& graph, std::vector<TilePlan>& plans);
-// Makes the shape's LDS large enough for the graph; false if there is not that much.
+// Makes the shape's LDS large enough for the graph; false, and the shape as it was, if there is not that much.
 bool fit_team(const Graph& graph, TilePlan& plan);
 extern const uint64_t kTeamPatienceTicks;
 constexpr size_t kMaxLds = 160 * 1024;    // of a workgroup

@@ -48,7 +48,7 @@ const uint64_t kTeamPatienceTicks = kTeamPatience;
 bool fit_team(const Graph& graph, TilePlan& plan) {
     const int n = (int)graph.rowptr.size() - 1;
     std::vector<int> seen_by((size_t)n, -1);
-    plan.team_slots = plan.team_edges = 0;
+    int slots = 0, most_edges = 0;
     for (int row0 = 0, part = 0; row0 < n; row0 += plan.team_rows, ++part) {
         const int row1 = row0 + plan.team_rows < n ? row0 + plan.team_rows : n;
         int fetched = 0;
@@ -57,10 +57,13 @@ bool fit_team(const Graph& graph, TilePlan& plan) {
             if ((nb < row0 || nb >= row1) && seen_by[(size_t)nb] != part) { seen_by[(size_t)nb] = part; ++fetched; }
         }
         const int edges = graph.rowptr[(size_t)row1] - graph.rowptr[(size_t)row0];
-        if (fetched > plan.team_slots) plan.team_slots = fetched;
-        if (edges > plan.team_edges) plan.team_edges = edges;
+        if (fetched > slots) slots = fetched;
+        if (edges > most_edges) most_edges = edges;
     }
-    return plan.lds(n, plan.team_rows, plan.team_slots, plan.team_edges) <= kMaxLds;
+    if (plan.lds(n, plan.team_rows, slots, most_edges) > kMaxLds) return false;
+    plan.team_slots = slots;
+    plan.team_edges = most_edges;
+    return true;
 }
 
 void team_plans(const ds_config& cfg, const Graph& graph, std::vector<TilePlan>& plans) {

@@ -1,6 +1,6 @@
 """Tiles whose rows are split over a team of workgroups (csrc/dsq_team_impl.h): every shape at sizes with ragged tiles and uneven
 parts, the path of a workgroup that finds the other parts of its tile unclaimed, the row-streaming plan's steps in one launch,
-and a captured step whose graph is replaced by one with more to fetch.  State and messages bit for bit against the oracle."""
+a captured step whose graph is replaced by one with more to fetch, and graphs with more to fetch than a workgroup's LDS holds.  State and messages bit for bit against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -101,6 +101,65 @@ def test_captured_step_outlives_its_graph(plan):
                 if r != 2:
                     x, d = ds.ds_read_state()
                     assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0, (W is W1, r)
+    side.synchronize()
+    del graph
+    ds.ds_destroy()
+
+
+def _circulant(n, offsets):
+    W = np.zeros((n, n))
+    for i in range(n):
+        for d in offsets:
+            W[i, (i + d) % n] = 1 / len(offsets)
+    rp = np.concatenate([[0], np.cumsum((W != 0).sum(1))]).astype(np.int32)
+    return W, (rp, np.nonzero(W)[1].astype(np.int32), W[W != 0].astype(np.float32))
+
+
+@pytest.mark.parametrize("capture", [False, True])
+@pytest.mark.parametrize("wide", [[0, *range(5, 53, 6), *range(-47, 0, 6)], list(range(100))], ids=["as many entries", "dense"])
+def test_a_graph_too_wide_for_the_team(wide, capture):
+    """100 workers, blocks of 2048, 8 bits: a part's 15 rows and the 16 they fetch take 64 KB; with the wide graphs they fetch all others,
+    205 KB, which no workgroup has.  Steps go on after such a W, one by one and in runs, and after the way back."""
+    w = small(wl.KIND_QUANT_MAXABS, 100, 2048 * 2 + 9, bits=8, block=2048)
+    near = _circulant(w.n, range(-8, 9))
+    cfg, keep = b.make_config(w.n, w.N, wl.TOPO_CSR, w.kind, w.gamma, w.eta, bits=w.bits, block=w.block, seed=w.seed, W_csr=near[1])
+    ds = b.DeepSqueeze(cfg, keep, {"variant": 1, "tile_plan": 1})
+    st = oracle_state(w, near[0])
+    g = wl.gradient(w, 0)
+    gd = upload(g)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+
+    def compare(what):
+        x, d = ds.ds_read_state()
+        assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0, what
+
+    with torch.cuda.stream(side):
+        ds.ds_step(gd)
+        oracle.step(st, g, want_cv=False, want_msg=False)
+        compare("first")
+        graph = None
+        if capture:
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                ds.ds_state_ptrs()
+                ds.ds_step(gd)
+        for W, csr in (near, _circulant(w.n, wide), near):
+            ds.ds_set_mixing(csr)
+            now = oracle_state(w, W)
+            now.x, now.delta, now.t = st.x, st.delta, st.t
+            st = now
+            if len(wide) == 100 and W is not near[0]:
+                graph = None                                 # another number of entries: graphs are gone
+            for turn, steps in enumerate((1, 1, 3, 1)):
+                say("entries", len(csr[1]), "capture", capture, "turn", turn)
+                for s in range(steps):
+                    if graph is not None and turn == 1:
+                        graph.replay()
+                    else:
+                        ds.ds_step(gd)
+                    oracle.step(st, g, want_cv=False, want_msg=False)
+                compare((len(csr[1]), turn))
     side.synchronize()
     del graph
     ds.ds_destroy()
