@@ -209,15 +209,27 @@ ds_status flush_deferred(ds_handle* h) {
 // messages, which go through it too.  Only in steps that follow one another: a caller that asks for x after every step reads
 // it, and draws the next gradient, in between, and plain loads that find nothing there are the slower ones (256 workers x 272,474 after a
 // pass over another state 313 us, non-temporal 286).
-// (us a step of a run, with nothing staying and so: 16 x 1,048,576 at 4 bits 64 and 57, 16 x 2,097,152 134 and 110; sign, 8 x 8,388,608 221
-// and 199, 8 x 25,557,032 722 and 675; 16 x 11,173,962 at 2 bits 637 and 616; 64 x 4,194,304 at 4 bits, whose messages are 134 MB,
-// 1009 and 973, with twice as much staying 1007 and three times 1064.)
+// (us a step of a run, with nothing staying and so: 8 x 2,097,152 at 4 bits 66 and 54, 16 x 2,097,152 121 and 108; sign, 8 x 25,557,032 722
+// and 675; 16 x 11,173,962 at 2 bits 637 and 616; 64 x 4,194,304 at 4 bits, whose messages are 134 MB, 1009 and 973, with twice as much
+// staying 1007 and three times 1064.)
+// Where the line lies depends on what is smaller being in a cache either way: x and delta of 72 MiB (8 x 1,179,648: 4 bits 39.7 and 33.2, 2
+// bits 39.6 and 35.2, 8 bits 41.9 and 38, sign 40 and 36; 64 MiB in 24 rows: 31.2 and 33, 32.5 and 34.7, 33.8 and 33.8, 31.8 and 31.1), of 128
+// for the random sparsifier (24 x 696,320 75.8 and 74.8, x 524,288 56.2 and 56.9).  Signs, whose pass has little else to do, also where the
+// L2s hold most of it (8 x 262,144 8.4 and 7.3, 24 x 86,016 9.7 and 9.0, 8 x 393,216 12.5 and 11.5; but 8 x 524,288 15.6 and 17.1, 24 x
+// 40,960 5.7 and 6.0), and uncompressed values always: their messages are stored past the caches (8 x 16,384 4.4 and 4.3, x 262,144 10.0 and
+// 9.1, x 1,048,576 37 and 33, x 2,097,152 75 and 63).
+bool state_stays(int kind, uint64_t bytes) {
+    if (kind == DS_COMP_IDENTITY) return true;
+    if (kind == DS_COMP_SIGN_MEANABS && bytes >= (12ull << 20) && bytes <= (28ull << 20)) return true;
+    return bytes >= (kind == DS_COMP_RAND_SPARSE ? 128ull << 20 : 72ull << 20);
+}
 uint32_t stay_share(const ds_handle* h) {
     if (h->run <= 1 && h->period <= 1) return 0;
     constexpr uint64_t room = 192ull << 20;
+    const uint64_t state = (uint64_t)h->cfg.n * h->cfg.N * 8;
     const uint64_t messages = h->cfg.comp.kind == DS_COMP_IDENTITY ? 0 : h->msg_row_bytes * (uint64_t)h->cfg.n;
-    if (messages >= room) return 0;
-    return (uint32_t)std::min<uint64_t>(64, (room - messages) * 64 / ((uint64_t)h->cfg.n * h->cfg.N * 8));
+    if (messages >= room || !state_stays(h->cfg.comp.kind, state)) return 0;
+    return (uint32_t)std::min<uint64_t>(64, (room - messages) * 64 / state);
 }
 
 dsq::TileArgs tile_args(const ds_handle* h, const float* g_dev, uint64_t g_ld) {
