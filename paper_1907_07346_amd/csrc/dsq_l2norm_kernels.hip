@@ -369,11 +369,12 @@ __global__ void __launch_bounds__(LQ_ROW_THREADS) l2q_row_scale(L2Scratch s, flo
 }
 static_assert(LQ_ROW_THREADS / 64 == 16, "the wave tree above is written for 16 waves");
 
-// Second pass, a workgroup for settle_chunks() chunks.  Rows whose speculative codes stand: the chunk's undecided elements get
-// their exact code now that s is known (a wave per chunk: an xor on the element's bits of the message
-// word, a correction of the chunk's sum of y^2; with a workgroup per chunk most threads have no entry.  At 8 bits, where rows mostly
-// take the exact way, a workgroup keeps to one chunk: 16 x 2,000,000 50 us, with four 54).  Other rows: the codes of v (which `form` left in delta) and the
-// sum of y^2 per chunk, from scratch.
+// Second pass, a workgroup per chunk.  Rows whose speculative codes stand: the chunk's undecided elements get
+// their exact code now that s is known (an xor on the element's bits of the message word, a correction of the chunk's sum of y^2),
+// a wave per chunk, so that the first workgroups do it and the others leave at once: with a workgroup per chunk most threads have no
+// entry.  (At 8 bits, where rows mostly take the exact way, a workgroup keeps to one chunk.)  Other rows: the codes of v (which `form` left
+// in delta) and the sum of y^2 per chunk, from scratch, a chunk to every workgroup (four one after the other, in a quarter of the
+// workgroups: 8 x 650,000 at 4 bits 8.8 -> 15.9 us).
 constexpr uint32_t settle_chunks(int bits) { return bits == 8 ? 1 : LQ_THREADS / 64; }
 static_assert(LQ_THREADS == kResThreads && LQ_ITERS == kResIters, "the resident kernel works on the same chunks");
 template <int BITS>
@@ -407,44 +408,41 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_quantize(L2Args a, L2Scratch s
         return;
     }
     const float inv = s.rows[row].inv;
-    const bool zero_row = !(s.rows[row].s > 0.f);
-    const float* dr = a.delta + (uint64_t)row * a.ld;
+    const bool zero_row = inv == 0.f;                     // s = 0: every code is 0
     const float* xr = a.x + (uint64_t)row * a.ld;
+    const float* dr = a.delta + (uint64_t)row * a.ld;
     const bool add_x = *s.pending == 0u;                  // `form` had no tail to apply and left delta alone
     uint8_t* mrow = a.msg + (uint64_t)(last_half(a) ^ 1u) * a.msg_half + (uint64_t)row * a.msg_row_bytes;
     const uint64_t code_bytes = a.msg_row_bytes - 4;      // whole 32-bit words
-    for (uint32_t c = blockIdx.x * PER; c < (blockIdx.x + 1) * PER && c < s.nchunks; ++c) {
-        const uint64_t col0 = (uint64_t)c * LQ_CHUNK;
-        uint32_t sy2 = 0;
+    const uint64_t col0 = (uint64_t)blockIdx.x * LQ_CHUNK;
+    uint32_t sy2 = 0;
 #pragma unroll
-        for (int it = 0; it < LQ_ITERS; ++it) {
-            const uint64_t col = col0 + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x;
-            const uint64_t byte = col * BITS / 8;
-            if (byte >= code_bytes) continue;                 // behind the last code word of the row
-            float4 v4 = ld4_stream(dr + col);
-            if (add_x) add4(v4, ld4_stream(xr + col));
-            const float* vp = reinterpret_cast<const float*>(&v4);
-            uint32_t packed = 0;
+    for (int it = 0; it < LQ_ITERS; ++it) {
+        const uint64_t col = col0 + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x;
+        const uint64_t byte = col * BITS / 8;
+        if (byte >= code_bytes) continue;                 // behind the last code word of the row
+        float4 v4 = ld4_stream(dr + col);
+        if (add_x) add4(v4, ld4_stream(xr + col));
+        const float* vp = reinterpret_cast<const float*>(&v4);
+        uint32_t packed = 0;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if (col + c < a.N) {                          // padding codes are 0 and do not count
-                    const int q = zero_row ? 0 : code_of<BITS>(vp[c], inv);
-                    const int y = 2 * q - L;
-                    sy2 += (uint32_t)(y * y);
-                    packed |= (uint32_t)q << (BITS * c);
-                }
+        for (int c = 0; c < 4; ++c) {
+            if (col + c < a.N) {                          // padding codes are 0 and do not count
+                const int q = zero_row ? 0 : code_of<BITS>(vp[c], inv);
+                const int y = 2 * q - L;
+                sy2 += (uint32_t)(y * y);
+                packed |= (uint32_t)q << (BITS * c);
             }
-            if constexpr (BITS == 2) mrow[4 + byte] = (uint8_t)packed;
-            else if constexpr (BITS == 4) *reinterpret_cast<uint16_t*>(mrow + 4 + byte) = (uint16_t)packed;
-            else *reinterpret_cast<uint32_t*>(mrow + 4 + byte) = packed;
         }
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) sy2 += __shfl_xor(sy2, o);
-        if (lane == 0) wave_sy2[wave] = sy2;
-        __syncthreads();
-        if (threadIdx.x == 0) s.csy2[(size_t)row * s.nchunks + c] = wave_sy2[0] + wave_sy2[1] + wave_sy2[2] + wave_sy2[3];
-        __syncthreads();
+        if constexpr (BITS == 2) mrow[4 + byte] = (uint8_t)packed;
+        else if constexpr (BITS == 4) *reinterpret_cast<uint16_t*>(mrow + 4 + byte) = (uint16_t)packed;
+        else *reinterpret_cast<uint32_t*>(mrow + 4 + byte) = packed;
     }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) sy2 += __shfl_xor(sy2, o);
+    if (lane == 0) wave_sy2[wave] = sy2;
+    __syncthreads();
+    if (threadIdx.x == 0) s.csy2[(size_t)row * s.nchunks + blockIdx.x] = wave_sy2[0] + wave_sy2[1] + wave_sy2[2] + wave_sy2[3];
 }
 
 // The band the next step may assume for s: centred on this step's s, as wide as s has been moving lately.  A band too
@@ -910,11 +908,9 @@ ds_status l2q_step(L2State* st, const L2Args& a, bool one_launch, hipStream_t st
     else if (st->bits == 4) hipLaunchKernelGGL(l2q_form<4>, grid, block, 0, stream, a, s);
     else                    hipLaunchKernelGGL(l2q_form<8>, grid, block, 0, stream, a, s);
     hipLaunchKernelGGL(l2q_row_scale, rows, rblock, 0, stream, s, hl);
-    const uint32_t per = settle_chunks(st->bits);
-    const dim3 qgrid((s.nchunks + per - 1) / per, a.n);
-    if (st->bits == 2)      hipLaunchKernelGGL(l2q_quantize<2>, qgrid, block, 0, stream, a, s);
-    else if (st->bits == 4) hipLaunchKernelGGL(l2q_quantize<4>, qgrid, block, 0, stream, a, s);
-    else                    hipLaunchKernelGGL(l2q_quantize<8>, qgrid, block, 0, stream, a, s);
+    if (st->bits == 2)      hipLaunchKernelGGL(l2q_quantize<2>, grid, block, 0, stream, a, s);
+    else if (st->bits == 4) hipLaunchKernelGGL(l2q_quantize<4>, grid, block, 0, stream, a, s);
+    else                    hipLaunchKernelGGL(l2q_quantize<8>, grid, block, 0, stream, a, s);
     hipLaunchKernelGGL(l2q_row_unit, rows, rblock, 0, stream, a, s, hl);
     // A state made for one launch gets the tail at once: the next step may be the resident kernel, in a graph that was
     // captured long ago even, and that expects x and delta complete.
