@@ -26,7 +26,7 @@
 // L2 hits), quantize 4 B read + b/8 B written: 24 B + codes against the 20 B + b/8 B any
 // implementation must move.  Where the state is completed after every step (a training loop), form moves 16 B and the tail
 // another 16 B: 32 B + codes.  16 workers x 11,173,962 parameters at 2 bits: form 612 -> 474 us since delta stays in place,
-// tail 562 -> 522 us with all loads ahead of the stores (5.5 TB/s; not everywhere, see tail_ahead), the whole step 1207 -> 1048 us.
+// tail 562 -> 522 us with all loads ahead of the stores, -> 481 with the neighbours' codes among them, the whole step 1207 -> 984 us.
 //
 // Speculative codes (what makes the second dense pass unnecessary in steady state).  The code of an
 // element depends on the row's range s only through inv = (L/2)/s, and is monotone in it.  `form`
@@ -503,11 +503,13 @@ __global__ void __launch_bounds__(LQ_ROW_THREADS) l2q_row_unit(L2Args a, L2Scrat
     }
 }
 
-// The tail on its own (l2q_flush): delta = v - C[v], x = xh + eta sum_j a_ij C[v_j]; nothing is pending then.  AHEAD: iterations whose loads go out
-// ahead of the first store of theirs, all four (70 registers, seven workgroups on a compute unit) or two (48, eight); see tail_ahead.
-template <int BITS, int AHEAD>
+// The tail on its own (l2q_flush): delta = v - C[v], x = xh + eta sum_j a_ij C[v_j]; nothing is pending then.  All loads of a lane's four
+// iterations go out ahead of the first store (90 registers at 2 and 4 bits, 83 at 8: five workgroups on a compute unit).  With two
+// iterations at a time (55 registers, eight workgroups) a step with x read after it took 1.00 to 1.06 times as long over 1,078 to 43,664 workgroups,
+// 2, 4 and 8 bits (one point of 54 at 0.99): 11 x 400,000 at 4 bits 48.1 and 45.9 us, 8 x 1,000,000 68.4 and 67.5, 16 x 11,173,962 at 2 bits
+// 1012 and 984.
+template <int BITS>
 __global__ void __launch_bounds__(LQ_THREADS) l2q_tail(L2Args a, L2Scratch s) {
-    static_assert(LQ_ITERS % AHEAD == 0, "whole groups of iterations");
     const uint32_t pending = a.known ? a.known : *s.pending;
     if (pending == 0u) return;
     const int row = blockIdx.y;
@@ -515,27 +517,24 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_tail(L2Args a, L2Scratch s) {
     const uint8_t* msg_last = a.msg + (uint64_t)last_half(a) * a.msg_half;
     float* xr = a.x + (uint64_t)row * a.ld;
     float* dr = a.delta + (uint64_t)row * a.ld;
-    Tail<BITS, AHEAD> last;
+    Tail<BITS, LQ_ITERS> last;
     last.graph(a, s, row);
+    float4 xs[LQ_ITERS], ds[LQ_ITERS];
 #pragma unroll
-    for (int i0 = 0; i0 < LQ_ITERS; i0 += AHEAD) {
-        float4 xs[AHEAD], ds[AHEAD];
+    for (int it = 0; it < LQ_ITERS; ++it) {
+        const uint64_t col = col0 + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x;   // rows are padded to whole chunks
+        last.ask(a, msg_last, it, col);
+        xs[it] = ld4_stream(xr + col);
+        ds[it] = ld4_stream(dr + col);
+    }
 #pragma unroll
-        for (int u = 0; u < AHEAD; ++u) {
-            const uint64_t col = col0 + (uint64_t)(i0 + u) * (4 * LQ_THREADS) + 4u * threadIdx.x;   // rows are padded to whole chunks
-            last.ask(a, msg_last, u, col);
-            xs[u] = ld4_stream(xr + col);
-            ds[u] = ld4_stream(dr + col);
-        }
-#pragma unroll
-        for (int u = 0; u < AHEAD; ++u) {
-            const uint64_t col = col0 + (uint64_t)(i0 + u) * (4 * LQ_THREADS) + 4u * threadIdx.x;
-            if (col >= a.N) continue;
-            if (pending == 2u) add4(ds[u], xs[u]);
-            last.apply(a, s, msg_last, row, u, col, xs[u], ds[u]);
-            st4_stream(xr + col, xs[u]);
-            st4_stream(dr + col, ds[u]);
-        }
+    for (int it = 0; it < LQ_ITERS; ++it) {
+        const uint64_t col = col0 + (uint64_t)it * (4 * LQ_THREADS) + 4u * threadIdx.x;
+        if (col >= a.N) continue;
+        if (pending == 2u) add4(ds[it], xs[it]);
+        last.apply(a, s, msg_last, row, it, col, xs[it], ds[it]);
+        st4_stream(xr + col, xs[it]);
+        st4_stream(dr + col, ds[it]);
     }
     if (a.known && blockIdx.x == 0 && row == 0 && threadIdx.x == 0) *s.pending = 0u;      // nobody in this launch looks at it
 }
@@ -860,31 +859,12 @@ ds_status l2q_create(const ds_config& cfg, uint64_t ld, bool resident, bool impa
     return DS_OK;
 }
 
-// How many iterations' loads the tail of so many workgroups asks for together.  Step with the state complete after it, in
-// units of the time with one iteration at a time: four are ahead while the GPU holds all workgroups at once (11 x 400,000: 0.90,
-// two 1.00) and, where bytes bound it, at 2 and 4 bits (16 x 11,173,962: 0.86 and 0.98, two 0.88 and 0.99).  Two are ahead where
-// only eight to a compute unit hold all (8 x 1,000,000 at 8 bits: 1.00 to 1.02, four 1.03), and at 8 bits, whose codes are the
-// most bytes asked for on top, beyond two rounds of seven (8 x 2,000,000: 1.01, four 1.03; 31 x 3,298,574 with five neighbours: 1.00
-// and 1.03; but 60 x 200,000, in less than two rounds: 0.99 and 0.97).
-static int tail_ahead(uint64_t workgroups, int bits) {
-    constexpr uint64_t kCus = 256, kFour = 7 * kCus, kTwo = 8 * kCus;        // workgroups the GPU holds at once
-    if (workgroups <= kFour) return 4;
-    if (workgroups <= kTwo) return 2;
-    return bits == 8 && workgroups > 2 * kFour ? 2 : 4;
-}
-
-template <int BITS>
-static void launch_tail(const L2Args& a, const L2Scratch& s, hipStream_t stream) {
-    const dim3 grid(s.nchunks, a.n), block(LQ_THREADS);
-    if (tail_ahead((uint64_t)s.nchunks * (uint64_t)a.n, BITS) == 4) hipLaunchKernelGGL((l2q_tail<BITS, 4>), grid, block, 0, stream, a, s);
-    else hipLaunchKernelGGL((l2q_tail<BITS, 2>), grid, block, 0, stream, a, s);
-}
-
 static ds_status apply_tail(L2State* st, L2Args a, uint32_t known, hipStream_t stream) {
     a.known = known;
-    if (st->bits == 2)      launch_tail<2>(a, st->s, stream);
-    else if (st->bits == 4) launch_tail<4>(a, st->s, stream);
-    else                    launch_tail<8>(a, st->s, stream);
+    const dim3 grid(st->s.nchunks, a.n), block(LQ_THREADS);
+    if (st->bits == 2)      hipLaunchKernelGGL(l2q_tail<2>, grid, block, 0, stream, a, st->s);
+    else if (st->bits == 4) hipLaunchKernelGGL(l2q_tail<4>, grid, block, 0, stream, a, st->s);
+    else                    hipLaunchKernelGGL(l2q_tail<8>, grid, block, 0, stream, a, st->s);
     if (!known) hipLaunchKernelGGL(l2q_clear_pending, dim3(1), dim3(1), 0, stream, st->s);      // (5 us)
     st->pending = 0u;
     return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
