@@ -408,7 +408,7 @@ __global__ void __launch_bounds__(LQ_THREADS) l2q_quantize(L2Args a, L2Scratch s
         return;
     }
     const float inv = s.rows[row].inv;
-    const bool zero_row = inv == 0.f;                     // s = 0: every code is 0
+    const bool zero_row = !(s.rows[row].s > 0.f);         // (not by inv, which is 0 for an infinite s too)
     const float* xr = a.x + (uint64_t)row * a.ld;
     const float* dr = a.delta + (uint64_t)row * a.ld;
     const bool add_x = *s.pending == 0u;                  // `form` had no tail to apply and left delta alone

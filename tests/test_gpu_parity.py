@@ -852,6 +852,26 @@ def test_deferred_tails_by_what_meets_them(w, order):
     ds.ds_destroy()
 
 
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@both_plans
+def test_l2norm_codes_of_infinite_values(bits, variant):
+    """(L/2)/s is 0 where s is infinite, as it is set to where s = 0, but only in the second case are all codes 0: else finite elements
+    get the middle level."""
+    w = small(wl.KIND_QUANT_L2NORM, 4, 4096 + 1001, bits=bits)
+    ds = b.DeepSqueeze.from_workload(w, {"variant": variant})
+    assert_plan(ds, w, variant)
+    st = oracle_state(w)
+    g = wl.gradient(w, 0)
+    g[0, 17] = np.inf
+    g[1, 5000] = -np.inf
+    g[2, ::1000] = np.inf
+    g[3] = 0.0
+    ds.ds_step(upload(g))
+    _, msg = oracle.step(st, g, want_cv=False)
+    assert np.array_equal(ds.ds_read_messages(), msg)
+    ds.ds_destroy()
+
+
 @pytest.mark.parametrize("n,N,bits", [(64, 4096 * 27 + 5, 4), (64, 4096 * 28 + 5, 4), (64, 4096 * 32 + 5, 4), (64, 4096 * 32 + 5, 8), (64, 4096 * 56 + 5, 8),
                                       (64, 4096 * 28 + 5, 2)])
 def test_l2norm_tails_by_number_of_workgroups(n, N, bits):
