@@ -274,7 +274,12 @@ ds_status ds_read_messages(ds_handle* h, void* host_buf, uint64_t cap, uint64_t*
  * complete once the work enqueued so far on the stream of the last ds_step has finished (top-k,
  * the norm-rescaled codes and the row-streaming plans leave the last part of a step's update of x
  * and delta to the next step's first pass: this call enqueues it on that stream instead); call it
- * again after later steps before reading x. */
+ * again after later steps before reading x.
+ * In a stream capture: where the last ds_step ran on the stream that is being captured, the graph gets that
+ * last part.  Where it ran on another one, or there was none, the captured step that follows
+ * completes x and delta itself, and every later step of the handle does: graphs of steps alone that were captured before must then
+ * not be replayed between the graph's replays.  (That is also how steps go that are captured on another stream right after x
+ * was lent outside the capture.  A graph of steps alone, replayed back to back, is faster if one step is taken in between.) */
 ds_status ds_state_ptrs(ds_handle* h, float** x_dev, float** delta_dev, uint64_t* ld);
 
 /* Borrows the device buffer that holds the messages of the last ds_step (ds_message_bytes bytes, layout as

@@ -37,6 +37,8 @@ struct ds_handle {
     bool complete = true;                // x and delta are complete once everything enqueued has run
     enum { kFree, kWhole, kStreamed } captured = kFree;   // how the steps go that a graph may replay unseen, and all others with them
     bool unseen = false;                 // a step has been captured: graphs may run steps that are not counted here
+    bool asked = false;                  // x and delta were lent since the last step, and not seen to be lent inside a capture
+    bool completes = false;              // no step leaves anything to the next one (a graph relies on it: see ds_step)
     dsq::TopkState* topk = nullptr;
     dsq::L2State* l2q = nullptr;
     bool resident = false;               // steps may take one launch ...
@@ -182,13 +184,8 @@ bool capturing(hipStream_t stream) {
 bool defers(const ds_handle* h) { return h->tile.streaming || ((h->topk || h->l2q) && !h->resident); }
 
 // Three paths (top-k, norm-rescaled codes, the row-streaming block kernels) leave the tail of a step to the next step's first pass;
-// this applies it now, on the stream of the last step.  Callers that replace W, gamma or eta call it BEFORE the
-// replacement: the tail belongs to the values the step ran with.
-ds_status flush_deferred(ds_handle* h) {
-    // A flush that is captured runs in every replay, whatever is pending then: it has to be in the graph, and to look at the device's mark.
-    if (defers(h) && h->stepped && !h->unseen) h->unseen = capturing(h->last_stream);
-    if (h->run) h->period = h->run;
-    h->run = 0;
+// this applies it now, on the stream of the last step.
+ds_status apply_deferred(ds_handle* h) {
     if (h->topk) return dsq::topk_flush(h->topk, topk_args(h, nullptr, 0), h->unseen, h->last_stream);
     if (h->l2q) return dsq::l2q_flush(h->l2q, l2_args(h, nullptr, 0), h->unseen, h->last_stream);
     if (h->tile.streaming && h->stepped) {
@@ -203,6 +200,16 @@ ds_status flush_deferred(ds_handle* h) {
         return hipGetLastError() == hipSuccess ? DS_OK : DS_EHIP;
     }
     return DS_OK;
+}
+
+// The same for whoever looks at x and delta or changes them.  Callers that replace W, gamma or eta call it BEFORE the
+// replacement: the tail belongs to the values the step ran with.
+ds_status flush_deferred(ds_handle* h) {
+    // A flush that is captured runs in every replay, whatever is pending then: it has to be in the graph, and to look at the device's mark.
+    if (defers(h) && h->stepped && !h->unseen) h->unseen = capturing(h->last_stream);
+    if (h->run) h->period = h->run;
+    h->run = 0;
+    return apply_deferred(h);
 }
 
 // The 64ths of the fused kernel's tiles whose x and delta stay in the memory-side cache: as many as fit into 192 MB of it beside the
@@ -811,7 +818,15 @@ ds_status ds_step(ds_handle* h, const float* g_dev, uint64_t g_ld, void* hip_str
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     // Some plans leave part of a step to be done when x and delta are asked for, and whether there is such a part is known here only
     // as long as no graph runs steps.
-    if (defers(h) && !h->unseen) h->unseen = capturing(stream);
+    if (defers(h) && (!h->unseen || h->asked)) {
+        const bool captured = capturing(stream);
+        h->unseen |= captured;
+        // Was x lent for the graph that this step is part of?  On the stream of the last step that would have been seen; on another one, or
+        // with no step before it, the lending found nothing to enqueue, or enqueued it outside the graph.  Then the replays have to
+        // find x complete as they begin: this step completes it itself, and so do all others that may come in between.
+        if (h->asked && captured && (!h->stepped || h->last_stream != stream)) h->completes = true;
+    }
+    h->asked = false;
 
     h->run += 1;
     if (h->topk) {
@@ -830,10 +845,12 @@ ds_status ds_step(ds_handle* h, const float* g_dev, uint64_t g_ld, void* hip_str
         if (h->tile.streaming) {
             // Where x is read after every step, a step is taken whole; where several follow one another, each leaves its gossip
             // sum to the next one's pass, which reads x anyway.  A step that is captured may be replayed between any others:
-            // the way of the first one that is captured is the way of all that follow.
-            bool whole = h->team.launch && h->complete && h->run == 1 && h->period == 1;
+            // the way of the first one that is captured is the way of all that follow, and that of a graph of steps alone, whose
+            // replays may follow one another, is to stream (256 x 272,474: 246 us a replay, whole 291).
+            const bool able = h->team.launch && h->complete;
+            bool whole = able && h->run == 1 && h->period == 1;
+            if (h->captured == ds_handle::kFree && h->unseen) h->captured = able && h->completes ? ds_handle::kWhole : ds_handle::kStreamed;
             if (h->captured != ds_handle::kFree) whole = h->captured == ds_handle::kWhole;
-            else if (h->unseen) h->captured = whole ? ds_handle::kWhole : ds_handle::kStreamed;
             const dsq::TilePlan& plan = whole ? h->team : h->tile;
             plan.launch(plan_args(h, plan, g_dev, g_ld), plan.rows_per_wave, stream);
             h->complete = whole;
@@ -845,6 +862,7 @@ ds_status ds_step(ds_handle* h, const float* g_dev, uint64_t g_ld, void* hip_str
     h->t += 1;
     h->stepped = true;
     h->last_stream = stream;
+    if (h->completes && apply_deferred(h) != DS_OK) return fail(h, DS_EHIP, "applying the tail of the step failed");
     return DS_OK;
 }
 
@@ -978,6 +996,7 @@ ds_status ds_read_messages(ds_handle* h, void* host_buf, uint64_t cap, uint64_t*
 ds_status ds_state_ptrs(ds_handle* h, float** x_dev, float** delta_dev, uint64_t* ld) {
     if (!h) return DS_EINVAL;
     // top-k keeps the sparse part of the last gossip update pending; complete x before lending it
+    if (defers(h)) h->asked = !(h->stepped && capturing(h->last_stream));
     if (flush_deferred(h) != DS_OK) return fail(h, DS_EHIP, "applying the deferred tail of the last step failed");
     if (x_dev) *x_dev = h->x;
     if (delta_dev) *delta_dev = h->delta;

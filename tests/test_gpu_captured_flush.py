@@ -71,3 +71,55 @@ def test_borrow_and_step_in_a_graph(w, plan, warm):
     assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
     assert ds.ds_step_count() == t
     ds.ds_destroy()
+
+
+@pytest.mark.parametrize("warm", ["", "s", "sr", "ss"])
+@pytest.mark.parametrize("w,plan", CASES, ids=lambda v: v.name if hasattr(v, "name") else "-".join(map(str, v.values())) or "auto")
+def test_borrow_and_step_in_a_graph_of_another_stream(w, plan, warm):
+    """The same graph where the steps before it, if there are any, ran on another stream than the one that is captured: borrowing x enqueues
+    nothing into it, so that its step has to leave x complete, and so do the eager steps between the replays."""
+    say("case", w.name, plan, warm)
+    ds = b.DeepSqueeze.from_workload(w, plan)
+    st = oracle_state(w)
+    first, side = torch.cuda.Stream(), torch.cuda.Stream()
+    gd = upload(wl.gradient(w, 0))
+    torch.cuda.synchronize()
+    t = 0
+
+    def feed():
+        nonlocal t
+        g = wl.gradient(w, t)
+        gd[:, :w.N].copy_(torch.from_numpy(g).cuda())
+        torch.cuda.synchronize()
+        t += 1
+        return g
+
+    def eager(what, stream):
+        if what == "r":
+            ds.ds_state_ptrs()
+        else:
+            g = feed()
+            ds.ds_step(gd, stream)
+            oracle.step(st, g, want_cv=False, want_msg=False)
+        torch.cuda.synchronize()
+
+    for what in warm:
+        eager(what, first)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        xp, _, ld = ds.ds_state_ptrs()
+        seen = _device_view(xp, (w.n, ld))[:, :w.N].clone()
+        ds.ds_step(gd, side)
+    for after in ["", "", "r", "", "sr", "", "s", "", "ss", "", ""]:
+        before = st.x.copy()
+        g = feed()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert assert_close(f"{warm} {t} borrowed x", seen.cpu().numpy(), before) == 0
+        oracle.step(st, g, want_cv=False, want_msg=False)
+        for what in after:
+            eager(what, first)
+    x, d = ds.ds_read_state()
+    assert assert_close("x", x, st.x) + assert_close("delta", d, st.delta) == 0
+    assert ds.ds_step_count() == t
+    ds.ds_destroy()
