@@ -213,7 +213,8 @@ __device__ __forceinline__ double wave_tree_sum_f64(double v) {   // adjacent pa
 // ---- pass 1: pending gossip of the previous step, Algorithm 1 line 5, candidate collection ------
 // GS (the GSpar operator shares this pass and the message conventions): no candidates; instead the chunk's sum of
 // |v| in double, as the balanced adjacent-pairs tree the operator's lambda is defined with.
-// PAIRS: pairs of a neighbour in the chunk that a thread asks for ahead.
+// PAIRS: pairs of a neighbour in the chunk that a thread asks for ahead.  (74 registers with one, six waves a SIMD, and 82, five, with two.  GSpar's,
+// held to the 72 of seven, gained nothing: 32 x 1,048,576 at 1 %, four steps and the completion, 566 -> 571 us.)
 template <bool GS, int PAIRS>
 __global__ void __launch_bounds__(TK_THREADS) topk_form_collect(TopkArgs a, Scratch s) {
     __shared__ float acc[TK_CHUNK];
@@ -1374,9 +1375,10 @@ __global__ void __launch_bounds__(TK_THREADS) topk_gossip(TopkArgs a, Scratch s)
     const int e0 = a.rowptr[row], e1 = a.rowptr[row + 1];
     if (!a.known && *s.pending == 0u) return;               // nothing to apply
     // The mark goes when the host knows that it is there: nobody in this launch looks at it then.  (At the end: a store in front of them
-    // makes vector loads of the scalar loads of the graph and the offsets, 45 -> 82 us for 8 x 8,388,608 with 0.1 % sent.)
+    // makes vector loads of the scalar loads of the graph and the offsets, 45 -> 82 us for 8 x 8,388,608 with 0.1 % sent.  All threads of the
+    // workgroup store it: one thread of it alone takes the kernel to 66 registers, and 64 are eight waves a SIMD.)
     auto applied = [&]() {
-        if (a.known && c == 0 && row == 0 && threadIdx.x == 0) *s.pending = 0u;
+        if (a.known && c == 0 && row == 0) *s.pending = 0u;
     };
     bool any = false;
     for (int e = e0; e < e1; ++e) {
