@@ -188,7 +188,8 @@ typedef struct {
                           /*    streams that may not use every compute unit): a step whose workgroups cannot all run   */
                           /*    waits for 10 ms and then takes some 10 ms more.  3: that kernel, but its workgroups do */
                           /*    not wait for each other at all, so that the last one does the step alone; where the rows   */
-                          /*    of a tile are split over workgroups, one of them does them all (tests)                 */
+                          /*    of a tile are split over workgroups, one of them does them all; top-k in several launches keeps   */
+                          /*    the candidate slots it has where memory is short (tests)                               */
     int32_t tile_plan;    /* -1: automatic; i >= 0 pins the i-th candidate launch shape of the fused kernel, and behind  */
                           /*    those the shapes that split the rows of a tile over several workgroups (an index past     */
                           /*    the last candidate leaves the choice automatic).  With the row-streaming variant: 0: no    */

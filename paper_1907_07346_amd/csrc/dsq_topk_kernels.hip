@@ -1246,7 +1246,7 @@ __global__ void __launch_bounds__(GS_WAVES * 64) gs_sift(TopkArgs a, Scratch s) 
 }
 
 // The chunks gs_sift left out: decisions from v itself, the kept elements in column order into the slot (the first
-// TK_CAP of them), their number.  A fixed number of workgroups per row walks the chunks, so that a step in which
+// s.cap of them), their number.  A fixed number of workgroups per row walks the chunks, so that a step in which
 // every chunk was sifted pays little for the launch.
 __global__ void __launch_bounds__(TK_THREADS) gs_count_dense(TopkArgs a, Scratch s) {
     __shared__ unsigned long long wave_sums4[TK_THREADS / 64];
@@ -1507,14 +1507,15 @@ ds_status topk_create(const ds_config& cfg, uint64_t ld, bool resident, bool imp
     Scratch& s = st->s;
     s.nchunks = (uint32_t)((cfg.N + TK_CHUNK - 1) / TK_CHUNK);
     // Room for 1.6 k candidates up to 3 % of N.  Beyond that 1.3 k are aimed at, and a slot has room for twice the chunk's share of
-    // them: with 512 places for any k such rows went the exact way in every step (8 x 33,554,432, 10 % sent: 7216 us a step).
+    // them: with 512 places for any k such rows went the exact way in every step (8 x 33,554,432, 10 % sent: 7216 us a step).  6 bytes a place: 0.75
+    // bytes of device memory per worker-parameter with 512, and up to 6 where a slot is the whole chunk (k from 0.38 N on).
     s.cap = TK_CAP;
     s.target = TK_TARGET;
     if (!st->gspar && cfg.comp.k > cfg.N / 32) {
         s.target = 1.3f;
         const double want = 2.0 * (double)s.target * (double)cfg.comp.k / (double)cfg.N * TK_CHUNK;
         s.cap = want < TK_CHUNK ? ((uint32_t)want + 63u) / 64u * 64u : (uint32_t)TK_CHUNK;
-        if (s.cap < TK_CAP) s.cap = TK_CAP;
+        if (s.cap < TK_CAP || impatient) s.cap = TK_CAP;      // (impatient: as if there were no memory for more; tests)
     }
     s.row_select = s.nchunks <= TK_SEL_CHUNKS && cfg.comp.k <= TK_SEL_K ? 1u : 0u;
     s.hist_wgs = s.nchunks >= 64u * TK_HWG ? TK_HWG : (s.nchunks + 63u) / 64u;   // 64 chunks side by side in each

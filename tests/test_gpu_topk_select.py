@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 LAUNCHES = {"variant": 2}
 
 
-def run(w, gradients, steps, candidates):
-    ds = b.DeepSqueeze.from_workload(w, LAUNCHES)
+def run(w, gradients, steps, candidates, plan=LAUNCHES):
+    ds = b.DeepSqueeze.from_workload(w, plan)
     st = oracle_state(w)
     for t in range(steps):
         g = gradients(t)
@@ -47,3 +47,10 @@ def test_ties_by_the_thousand(k):
     rng = np.random.default_rng(3)
     gs = [rng.choice(np.array([0.5, -0.5, 1.0, -2.0], np.float32), (w.n, w.N)) for _ in range(4)]
     run(w, lambda t: gs[t], 4, candidates=False)
+
+
+def test_large_k_in_small_slots():
+    """What a state whose larger slots could not be allocated does: 1.3 k candidates aimed at, 512 places for 640 of them, rows that go the
+    exact way.  (300 x 8 chunks are too many for one launch.)"""
+    w = small(wl.KIND_TOPK, 300, 4096 * 7 + 5, k=3_584)
+    run(w, lambda t: wl.gradient(w, t), 4, candidates=False, plan={"variant": 3})
