@@ -25,7 +25,6 @@
 
 #include "dsq_internal.h"
 #include "dsq_philox.h"
-#include "dsq_resident.h"
 
 namespace dsq {
 namespace {
@@ -215,7 +214,7 @@ struct Tile {
                     const float* vrow = reinterpret_cast<const float*>(nrow);
 #pragma unroll
                     for (int c = 0; c < 4; ++c) {
-                        const float cv = (FULL || j + c < a.N) ? fetched<NOW>(vrow + j + c) : 0.f;
+                        const float cv = (FULL || j + c < a.N) ? vrow[j + c] : 0.f;
                         acc[s][c] = fmaf(w, cv, acc[s][c]);
                     }
                     continue;
@@ -605,8 +604,7 @@ struct Tile {
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
                         if (FULL || j + c < a.N) {           // as many bytes as x: nothing of it would stay
-                            if constexpr (MODE == 3) put<MODE>(mrow + j + c, comp(v[s], c));
-                            else __builtin_nontemporal_store(comp(v[s], c), mrow + j + c);
+                            __builtin_nontemporal_store(comp(v[s], c), mrow + j + c);
                         }
                 }
             }
