@@ -25,9 +25,12 @@ constexpr uint32_t kTeamParts = 64;                          // most parts a til
 // and, for each part, the number of the last launch that claimed it.
 constexpr uint32_t kTeamLine = 32;                           // 64-bit words: 256 bytes
 static_assert((kTeamParts + 1) / 2 + 1 <= 2 * kTeamLine && kTeamCellBytes == 2 * kTeamLine * sizeof(unsigned long long), "an arrival counter and the claims");
-// Waves per SIMD that the registers are rationed for: as many workgroups of eight waves on a compute unit as fit without spilling
-// in the path that every step takes.
-constexpr int team_waves(int sweeps, int rows) { return sweeps == 1 ? 7 : sweeps == 2 ? (rows <= 2 ? 7 : 6) : sweeps == 4 ? 4 : 2; }
+// Waves per SIMD that the registers are rationed for.  A workgroup of eight waves has two on each: three workgroups on a compute unit up to two
+// sweeps, two with four, one with eight.  (No scratch but 12 bytes a thread with four rows of two sweeps and 28 with two or four rows of
+// four.  Rationed for seven, which is three workgroups too, the kernels of one and two sweeps spilled half as many scalars again and took longer, us a
+// step at 4 bits: 100 x 100,000, blocks of 256, 53.8 and 50.8, 256 x 262,144 269 and 263; blocks of 512, 64 x 16,384 11.7 and 10.8, 100 x 2,621 9.9
+// and 10.0.)
+constexpr int team_waves(int sweeps) { return sweeps <= 2 ? 6 : sweeps == 4 ? 4 : 2; }
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 // Ticks of the 100 MHz clock: 50 us, many times what a part takes.
 constexpr uint64_t kTeamPatience = 5'000;
@@ -288,7 +291,7 @@ struct Team {
 };
 
 template <int KIND, int BITS, int B, int SW, int NW, int RPW>
-__global__ void __launch_bounds__(NW* kWave, team_waves(SW, RPW)) team_tile_kernel(TileArgs a) {
+__global__ void __launch_bounds__(NW* kWave, team_waves(SW)) team_tile_kernel(TileArgs a) {
     using M = Team<KIND, BITS, B, SW, NW, RPW>;
     extern __shared__ __align__(16) uint8_t lds[];
     a.msg += (a.t_ptr[0] & 1ull) * a.msg_half;                // a handle of the row-streaming plan has two message buffers
