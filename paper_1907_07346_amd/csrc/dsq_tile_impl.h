@@ -1135,11 +1135,25 @@ bool pick_for_block(int n, int nnz, std::vector<TilePlan>& plans, std::string& e
     return true;
 }
 
-// Up to two workgroups per compute unit the time is that of one wave's rows, one after the other: sixteen waves share them then.  (8
-// waves and 16, 4 bits, blocks of 512: 48 workers x 5,461 17.2 and 13.8 us, x 87,381 20.3 and 17.7; 64 x 65,536 25.5 and 22.5; with
-// more tiles the eight-wave workgroups overlap: 12 x 349,525 17.2 and 18.2.)
-inline void sixteen_waves_first(uint64_t N, std::vector<TilePlan>& plans) {
-    if (plans.empty() || (N + plans[0].tile_cols - 1) / plans[0].tile_cols > 512) return;
+// Up to one workgroup per compute unit the time is that of one wave's rows, one after the other: sixteen waves share them then.  Times of 16
+// waves in units of those of 8, state complete after every step, all compressors, 9 to 64 workers: 0.73 to 0.99 up to 256 tiles (1.03 to 1.07 at
+// 24 workers), from there to 512 0.75 to 1.03 but for
+//   the random sparsifier up to 32 workers: 0.97 to 1.10 (from 34 on 0.76 to 1.01);
+//   four sweeps with a row to a wave: 0.93 to 1.08 (9 workers 1.04 to 1.08);
+//   workers that sixteen waves do not halve the rows of a wave for (17 to 24, 33 to 40), beyond 400 tiles: 0.95 to 1.12 (with 300 tiles 0.76 to 1.03).
+// With more tiles the eight-wave workgroups overlap (0.92 to 1.11).
+inline bool sixteen_waves_faster(int kind, int n, uint64_t tiles, int sweeps) {
+    if (tiles <= 256) return true;
+    if (tiles > 512) return false;
+    if (kind == DS_COMP_RAND_SPARSE) return n > 32;
+    if (sweeps >= 4 && n <= 16) return false;
+    return tiles <= 400 || 2 * ((n + 15) / 16) <= (n + 7) / 8;
+}
+
+inline void sixteen_waves_first(const ds_config& cfg, std::vector<TilePlan>& plans) {
+    if (plans.empty()) return;
+    const uint64_t tiles = (cfg.N + plans[0].tile_cols - 1) / plans[0].tile_cols;
+    if (!sixteen_waves_faster(cfg.comp.kind, cfg.n, tiles, plans[0].sweeps)) return;
     for (size_t q = 1; q < plans.size(); ++q)
         if (plans[q].waves == 16 && plans[q].tile_cols == plans[0].tile_cols && plans[0].waves == 8 && plans[0].rows_per_wave > 1) {
             std::swap(plans[0], plans[q]);

@@ -108,7 +108,7 @@ static bool list_tile_plans(const ds_config& cfg, int nnz, std::vector<TilePlan>
 bool choose_tile_plans(const ds_config& cfg, int nnz, std::vector<TilePlan>& plan, std::string& err) {
     plan.reserve(16);                                         // ds_step_static comes here in every call
     if (!list_tile_plans(cfg, nnz, plan, err)) return false;
-    if (cfg.algo == DS_ALGO_DEEPSQUEEZE) sixteen_waves_first(cfg.N, plan);
+    if (cfg.algo == DS_ALGO_DEEPSQUEEZE) sixteen_waves_first(cfg, plan);
     return true;
 }
 
