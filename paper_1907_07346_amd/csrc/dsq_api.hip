@@ -3,7 +3,6 @@
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
-#include <cstring>
 #include <mutex>
 #include <new>
 
@@ -398,15 +397,17 @@ bool whole_steps_faster(const ds_config& cfg, const dsq::TilePlan& stream) {
 }
 
 // Is it faster than the fused kernel of shape `fused`?  Where that forms its rows twice: 100 x 671,088 357 us fused, 265 as teams; 256 x
-// 1,024 61 and 12; but 124 and 139 (64 x 400,000, 8 bits, blocks of 2048) and 76 and 78 (256 x 65,536, sign, blocks of 64) where
-// there is a workgroup for nearly every compute unit and the second forming reads the memory-side cache (100 x 500,000 does
-// not fit there: 240 and 213).  Where registers hold the rows, only if
-// there are few tiles of many rows: 64 x 16,384 (32 tiles) 19 and 11, 48 x 87,381 (171 tiles) 18 and 25; not for tiles of one
+// 1,024 61 and 12.  Not where there is a workgroup for nearly every compute unit, so that one round of them does all tiles, and the second
+// forming reads the memory-side cache (x and g of 112 MiB at most together).  Fused in units of the best shape of teams, 4 bits, 155 to 256 tiles:
+// tiles of one sweep, 120 to 220 workers 0.82 to 1.06, 256 workers 0.99 to 1.11; of eight sweeps, 36 to 48 workers 0.86 to 1.01 from 175 tiles on
+// (1.08 to 1.18 below), 56 to 72 workers 0.95 to 1.11.  Of two sweeps 80 workers 0.99 to 1.17, 140 to 256 1.08 to 1.32, and of four 48 workers 0.98 to
+// 1.14, 100 to 140 1.07 to 1.21: teams there.  1.02 to 1.45 at 280 to 400 tiles and 1.04 to 1.60 at 100 to 150, all of them.  Where registers hold
+// the rows, only if there are few tiles of many rows: 64 x 16,384 (32 tiles) 19 and 11, 48 x 87,381 (171 tiles) 18 and 25; not for tiles of one
 // sweep, whose sixteen-wave shape takes 7 to 8 us (9 as teams).
 bool teams_faster(const ds_config& cfg, const dsq::TilePlan& fused) {
     const uint64_t tiles = (cfg.N + fused.tile_cols - 1) / fused.tile_cols;
     const bool cached = (uint64_t)cfg.n * cfg.N <= (28u << 20);              // x and g fit in the memory-side cache
-    if (std::strstr(fused.name, "looped")) return !((fused.sweeps == 1 || fused.sweeps == 8) && tiles >= 160 && tiles <= 256 && cached);
+    if (fused.looped) return !((fused.sweeps == 1 || fused.sweeps == 8) && tiles >= 160 && tiles <= 256 && cached);
     return cfg.n > 32 && fused.sweeps >= 2 && tiles <= 64;
 }
 

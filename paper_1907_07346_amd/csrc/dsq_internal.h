@@ -126,6 +126,7 @@ struct TilePlan {
     int waves = 0;             // waves per workgroup
     int rows_per_wave = 0;     // rows each wave owns (held in registers when the variant says so)
     int sweeps = 0;            // 256-column sweeps per tile
+    bool looped = false;       // a wave owns more rows than its registers hold and forms them twice
     // Row-streaming variant (no LDS exchange, so no limit on n): a step leaves x = x - gamma g and its gossip sum
     // to the next step's pass, which decodes the neighbours' codes from the previous messages; `flush` adds a
     // pending sum now.

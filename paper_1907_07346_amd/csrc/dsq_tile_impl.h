@@ -1078,6 +1078,7 @@ TilePlan make_plan(const char* name) {
     p.waves = NW;
     p.rows_per_wave = RPW;
     p.sweeps = SW;
+    p.looped = RPW == 0;
     return p;
 }
 
