@@ -28,7 +28,7 @@ struct ds_handle {
                                          // step's kernels; the rest: the tile kernel's finished-workgroup counters
     dsq::TilePlan tile;
     std::vector<dsq::TilePlan> tile_candidates;
-    dsq::TilePlan team;                  // row-streaming plan: what takes a step whole (launch == nullptr: nothing does)
+    dsq::TilePlan team;                  // row-streaming plan: what takes a step whole (no team: nothing does)
     unsigned long long* d_team = nullptr;    // arrival counters of the team kernels
     bool impatient = false;              // ... whose workgroups then look for parts nobody works on at once (tests)
     // Steps since x and delta were last asked for, and how many there were between the last two times.
@@ -190,7 +190,7 @@ ds_status apply_deferred(ds_handle* h) {
     if (h->tile.streaming && h->stepped) {
         // (A graph that begins with this call: its steps go the way of the steps so far, whole only if nothing is pending before it either.)
         if (h->unseen && h->captured == ds_handle::kFree)
-            h->captured = h->team.launch && h->complete && h->period == 1 ? ds_handle::kWhole : ds_handle::kStreamed;
+            h->captured = h->team.team && h->complete && h->period == 1 ? ds_handle::kWhole : ds_handle::kStreamed;
         if (h->complete && h->captured != ds_handle::kStreamed) return DS_OK;
         dsq::TileArgs a = tile_args(h, nullptr, 0);
         a.known = h->unseen ? 0u : 1u;
@@ -249,9 +249,6 @@ dsq::TileArgs tile_args(const ds_handle* h, const float* g_dev, uint64_t g_ld) {
     a.msg_half = h->msg_half;
     a.stay = stay_share(h);
     a.pending = reinterpret_cast<uint32_t*>(h->d_t + 3);        // cell 3: the row-streaming variant's pending flag
-    a.team_cells = h->d_team;
-    a.team_patience = h->impatient ? 0 : dsq::kTeamPatienceTicks;
-    a.team_solo = h->impatient ? 1u : 0u;
     if (h->cfg.comp.kind == DS_COMP_RAND_SPARSE) {
         a.keep_off = h->d_keep;
         a.keep_group_off = h->d_keep + (size_t)h->cfg.n * h->nsweeps;
@@ -264,12 +261,18 @@ dsq::TileArgs tile_args(const ds_handle* h, const float* g_dev, uint64_t g_ld) {
     return a;
 }
 
-dsq::TileArgs plan_args(const ds_handle* h, const dsq::TilePlan& plan, const float* g_dev, uint64_t g_ld) {
-    dsq::TileArgs a = tile_args(h, g_dev, g_ld);
+void launch_plan(const ds_handle* h, const dsq::TilePlan& plan, const float* g_dev, uint64_t g_ld, hipStream_t stream) {
+    const dsq::TileArgs args = tile_args(h, g_dev, g_ld);
+    if (!plan.team) return plan.launch(args, plan.rows_per_wave, stream);
+    dsq::TeamArgs a{};
+    static_cast<dsq::TileArgs&>(a) = args;
+    a.team_cells = h->d_team;
+    a.team_patience = h->impatient ? 0 : dsq::kTeamPatienceTicks;
+    a.team_solo = h->impatient ? 1u : 0u;
     a.team_rows = plan.team_rows;
     a.team_slots = plan.team_slots;
     a.team_edges = plan.team_edges;
-    return a;
+    plan.launch_team(a, stream);
 }
 
 // Row pitch candidates (floats added to N rounded up to kPitchAlign).  A tile kernel has all n rows
@@ -295,13 +298,12 @@ size_t team_bytes(const ds_handle* h) {
 
 // Times `plan` at the current h->ld on the all-zero state (3 launches, twice, after a warm-up); < 0 on failure.
 float time_plan(ds_handle* h, const dsq::TilePlan& plan, const float* g, hipEvent_t e0, hipEvent_t e1) {
-    const dsq::TileArgs a = plan_args(h, plan, g, h->ld);
     if (plan.team && hipMemset(h->d_team, 0, team_bytes(h)) != hipSuccess) return -1.f;   // another plan's parts may be another number
-    plan.launch(a, plan.rows_per_wave, nullptr);
+    launch_plan(h, plan, g, h->ld, nullptr);
     float best = 1e30f;
     for (int rep = 0; rep < 2; ++rep) {                        // the better of two timings: less noise in the choice
         (void)hipEventRecord(e0, nullptr);
-        for (int r = 0; r < 3; ++r) plan.launch(a, plan.rows_per_wave, nullptr);
+        for (int r = 0; r < 3; ++r) launch_plan(h, plan, g, h->ld, nullptr);
         (void)hipEventRecord(e1, nullptr);
         float ms = 0.f;
         if (hipGetLastError() != hipSuccess) return -1.f;      // a launch that was refused would look fast
@@ -613,7 +615,7 @@ ds_status ds_step_static(const ds_config* cfg, float* x_dev, float* delta_dev, u
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     // One launch: the kernel takes the step number by value and works the graph out for itself.  (A kernel of its own that
     // put both into device memory took 2.4 us and a second launch of a 12.4 us call: 8 workers x 4,645 parameters.)
-    dsq::GivenTileArgs a{};
+    dsq::GivenStep a{};
     a.x = x_dev; a.delta = delta_dev; a.g = g_dev; a.msg = static_cast<uint8_t*>(msg_dev);
     a.ld = ld; a.g_ld = g_ld; a.N = cfg->N; a.msg_row_bytes = dsq::message_row_bytes(cfg);
     a.n = cfg->n; a.nnz = nnz;
@@ -848,15 +850,15 @@ ds_status ds_step(ds_handle* h, const float* g_dev, uint64_t g_ld, void* hip_str
             // sum to the next one's pass, which reads x anyway.  A step that is captured may be replayed between any others:
             // the way of the first one that is captured is the way of all that follow, and that of a graph of steps alone, whose
             // replays may follow one another, is to stream (256 x 272,474: 246 us a replay, whole 291).
-            const bool able = h->team.launch && h->complete;
+            const bool able = h->team.team && h->complete;
             bool whole = able && h->run == 1 && h->period == 1;
             if (h->captured == ds_handle::kFree && h->unseen) h->captured = able && h->completes ? ds_handle::kWhole : ds_handle::kStreamed;
             if (h->captured != ds_handle::kFree) whole = h->captured == ds_handle::kWhole;
             const dsq::TilePlan& plan = whole ? h->team : h->tile;
-            plan.launch(plan_args(h, plan, g_dev, g_ld), plan.rows_per_wave, stream);
+            launch_plan(h, plan, g_dev, g_ld, stream);
             h->complete = whole;
         } else {
-            h->tile.launch(plan_args(h, h->tile, g_dev, g_ld), h->tile.rows_per_wave, stream);
+            launch_plan(h, h->tile, g_dev, g_ld, stream);
         }
     }
     DSQ_HIP(h, hipGetLastError());
@@ -885,7 +887,7 @@ ds_status ds_set_mixing(ds_handle* h, const int32_t* W_rowptr, const int32_t* W_
         if (tile.team && !dsq::fit_team(g, tile)) tile = plans.front();
     }
     // (Where graphs may run whole steps all others have to be whole too: with the LDS of the old W, and rows that need more finished from memory.)
-    if (team.launch && !dsq::fit_team(g, team) && h->captured != ds_handle::kWhole) team = dsq::TilePlan();
+    if (team.team && !dsq::fit_team(g, team) && h->captured != ds_handle::kWhole) team = dsq::TilePlan();
     // a deferred tail belongs to the old W: apply it first
     if (flush_deferred(h) != DS_OK) return fail(h, DS_EHIP, "applying the deferred tail of the last step failed");
     DSQ_HIP(h, hipStreamSynchronize(h->last_stream));

@@ -64,7 +64,7 @@ ds_status validate_config(const ds_config* cfg, std::string& err, std::string* w
 ds_status build_graph(const ds_config* cfg, Graph& g, std::string& err);
 uint64_t message_row_bytes(const ds_config* cfg);
 
-constexpr uint64_t kTeamCellBytes = 512;  // see TileArgs::team_cells
+constexpr uint64_t kTeamCellBytes = 512;  // see TeamArgs::team_cells
 
 // Arguments of the fused tile kernels (block quantiser / sign / identity).
 struct TileArgs {
@@ -102,7 +102,11 @@ struct TileArgs {
                                        // to hand out, counted from the grid size); [32 (1+c)], c < 64: finished
                                        // workgroups with blockIdx % 64 == c.
                                        // Cells [1], [16] and [32 (1+c)] are zero between launches.
-    // teams of workgroups only (dsq_team_impl.h):
+};
+
+// Teams of workgroups (dsq_team_impl.h).  (Apart from the others: every launch copies what its kernel is given, and a caller of small steps
+// waits for that: 8 x 4,645 through ds_step_static, whose kernel was given all of this and TileArgs too, 8.05 us a call and 7.9 with GivenStep.)
+struct TeamArgs : TileArgs {
     unsigned long long* team_cells;    // kTeamCellBytes for the launch and for each tile: counters that are never set back
     uint64_t team_patience;            // ticks a workgroup waits before it looks for parts nobody has claimed
     uint32_t team_parts;               // workgroups that share a tile (set by the launch) ...
@@ -111,17 +115,31 @@ struct TileArgs {
     uint32_t team_solo;                // tests: one workgroup of each tile works, and finds the other parts unclaimed
 };
 
-// The fused tile kernel without anything in device memory beside the caller's arrays (t_ptr and rowptr are nullptr).
-struct GivenTileArgs : TileArgs {
+// The fused tile kernel without anything in device memory beside the caller's arrays (t_ptr and rowptr are nullptr): what the launch
+// copies ...
+struct GivenGraph {
     uint32_t t;                        // the step's number, low word
     int topo, torus_rows, torus_cols;  // DS_TOPO_RING or DS_TOPO_TORUS2D: each workgroup works W - I out for itself
 };
+struct GivenStep : GivenGraph {
+    float* x;
+    float* delta;
+    const float* g;
+    uint8_t* msg;
+    uint64_t ld, g_ld, N, msg_row_bytes;
+    int n, nnz;
+    float gamma, eta;
+    uint32_t seed_lo, seed_hi;
+};
+// ... and what the kernel makes of it.
+struct GivenTileArgs : TileArgs, GivenGraph {};
 
 // A compiled variant of the fused tile kernel, chosen once at init.
 struct TilePlan {
     const char* name = "";
     void (*launch)(const TileArgs&, int rows_per_wave, hipStream_t) = nullptr;
-    void (*launch_given)(const GivenTileArgs&, int rows_per_wave, hipStream_t) = nullptr;   // nullptr: not built for this shape
+    void (*launch_team)(const TeamArgs&, hipStream_t) = nullptr;                            // in its place where the rows of a tile are split
+    void (*launch_given)(const GivenStep&, int rows_per_wave, hipStream_t) = nullptr;   // nullptr: not built for this shape
     int tile_cols = 0;         // columns per workgroup
     int waves = 0;             // waves per workgroup
     int rows_per_wave = 0;     // rows each wave owns (held in registers when the variant says so)
@@ -132,7 +150,7 @@ struct TilePlan {
     // pending sum now.
     bool streaming = false;
     void (*flush)(const TileArgs&, hipStream_t) = nullptr;
-    // The rows of a tile are split over several workgroups: see TileArgs::team_*.
+    // The rows of a tile are split over several workgroups: see TeamArgs.
     bool team = false;
     int team_rows = 0, team_slots = 0, team_edges = 0;
     size_t (*lds)(int n, int rows, int slots, int edges) = nullptr;

@@ -54,7 +54,7 @@ struct Team {
         return sizeof(Shared) + (size_t)(rows + slots) * (T::ROW_CODE_BYTES + T::BPT * sizeof(float)) + ((size_t)rows + 1 + 2 * (size_t)edges + n + slots) * 4;
     }
 
-    const TileArgs& a;
+    const TeamArgs& a;
     Shared& sh;
     const int lane, wave;
     uint8_t* codes;
@@ -67,7 +67,7 @@ struct Team {
     uint64_t tile = 0, col0 = 0;
     uint32_t launch = 0;                                     // the number of this launch
 
-    __device__ __forceinline__ Team(const TileArgs& a_, uint8_t* lds)
+    __device__ __forceinline__ Team(const TeamArgs& a_, uint8_t* lds)
         : a(a_), sh(*reinterpret_cast<Shared*>(lds)), lane(threadIdx.x & (kWave - 1)), wave(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
         codes = lds + sizeof(Shared);
         units = reinterpret_cast<float*>(codes + (size_t)(a.team_rows + a.team_slots) * T::ROW_CODE_BYTES);
@@ -291,7 +291,7 @@ struct Team {
 };
 
 template <int KIND, int BITS, int B, int SW, int NW, int RPW>
-__global__ void __launch_bounds__(NW* kWave, team_waves(SW)) team_tile_kernel(TileArgs a) {
+__global__ void __launch_bounds__(NW* kWave, team_waves(SW)) team_tile_kernel(TeamArgs a) {
     using M = Team<KIND, BITS, B, SW, NW, RPW>;
     extern __shared__ __align__(16) uint8_t lds[];
     a.msg += (a.t_ptr[0] & 1ull) * a.msg_half;                // a handle of the row-streaming plan has two message buffers
@@ -313,9 +313,9 @@ __global__ void __launch_bounds__(NW* kWave, team_waves(SW)) team_tile_kernel(Ti
 }
 
 template <int KIND, int BITS, int B, int SW, int NW, int RPW>
-void launch_team(const TileArgs& args, int, hipStream_t stream) {
+void launch_team(const TeamArgs& args, hipStream_t stream) {
     using M = Team<KIND, BITS, B, SW, NW, RPW>;
-    TileArgs a = args;
+    TeamArgs a = args;
     a.team_parts = (uint32_t)((a.n + a.team_rows - 1) / a.team_rows);
     const uint64_t tiles = (a.N + M::T::TC - 1) / M::T::TC;
     const uint64_t want = tiles * a.team_parts, max_x = 0xFFFFFFFFull / (NW * kWave);
@@ -336,7 +336,7 @@ void add_team_plan(int n, const char* name, std::vector<TilePlan>& plans) {
         if (parts < 2 || parts > (int)kTeamParts) return;
         TilePlan p;
         p.name = name;
-        p.launch = &launch_team<KIND, BITS, B, SW, NW, RPW>;
+        p.launch_team = &launch_team<KIND, BITS, B, SW, NW, RPW>;
         p.tile_cols = SW * kSweep;
         p.waves = NW;
         p.rows_per_wave = RPW;

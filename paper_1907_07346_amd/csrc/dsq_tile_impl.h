@@ -157,7 +157,7 @@ template <> struct CodeTraits<DS_COMP_RAND_SPARSE, 32> { using lane_t = float4; 
 __device__ __forceinline__ float comp(const float4& v, int c) { return c == 0 ? v.x : c == 1 ? v.y : c == 2 ? v.z : v.w; }
 __device__ __forceinline__ void set_comp(float4& v, int c, float f) { if (c == 0) v.x = f; else if (c == 1) v.y = f; else if (c == 2) v.z = f; else v.w = f; }
 
-// GIVEN: a launch of GivenTileArgs, with the step's number and the graph by value.  A kernel of its own, and not a test of
+// GIVEN: a launch of GivenStep, with the step's number and the graph by value.  A kernel of its own, and not a test of
 // a pointer in the one that handles launch: there the test and the graph's integer divisions cost 14 scalar and 2 vector
 // registers of the sign kernel (60 -> 74, 26 -> 28).
 template <int KIND, int BITS, int B, int SW, int NW, bool GIVEN = false>
@@ -874,9 +874,21 @@ __global__ void __launch_bounds__(1024) keep_scan_kernel(TileArgs a, uint32_t* _
     }
 }
 
+__device__ __forceinline__ const TileArgs& arguments(const TileArgs& a) { return a; }
+__device__ __forceinline__ GivenTileArgs arguments(const GivenStep& s) {
+    GivenTileArgs a{};
+    a.x = s.x; a.delta = s.delta; a.g = s.g; a.msg = s.msg;
+    a.ld = s.ld; a.g_ld = s.g_ld; a.N = s.N; a.msg_row_bytes = s.msg_row_bytes;
+    a.n = s.n; a.nnz = s.nnz; a.gamma = s.gamma; a.eta = s.eta;
+    a.seed_lo = s.seed_lo; a.seed_hi = s.seed_hi;
+    static_cast<GivenGraph&>(a) = s;
+    return a;
+}
+
 template <int KIND, int BITS, int B, int SW, int NW, int RPW, bool GIVEN, bool STAY>
-__global__ void __launch_bounds__(NW* kWave) fused_tile_kernel(typename Tile<KIND, BITS, B, SW, NW, GIVEN>::Args a, int rpw_runtime) {
+__global__ void __launch_bounds__(NW* kWave) fused_tile_kernel(std::conditional_t<GIVEN, GivenStep, TileArgs> launched, int rpw_runtime) {
     using T = Tile<KIND, BITS, B, SW, NW, GIVEN>;
+    const auto& a = arguments(launched);
     extern __shared__ __align__(16) uint8_t lds[];
     // tiles are numbered along x first; the grid has a second row only when x alone would pass the
     // 2^32 work-items a launch dimension can hold, and its last row may then have spare workgroups
@@ -1047,7 +1059,7 @@ inline void raise_lds_limit(const void* kernel, size_t lds, unsigned long long& 
 }
 
 template <int KIND, int BITS, int B, int SW, int NW, int RPW, bool GIVEN>
-void launch_tile(const typename Tile<KIND, BITS, B, SW, NW, GIVEN>::Args& a, int rpw_runtime, hipStream_t stream) {
+void launch_tile(const std::conditional_t<GIVEN, GivenStep, TileArgs>& a, int rpw_runtime, hipStream_t stream) {
     using T = Tile<KIND, BITS, B, SW, NW, GIVEN>;
     const uint64_t tiles = (a.N + T::TC - 1) / T::TC;
     // a launch dimension holds fewer than 2^32 work-items: very long vectors get a second grid row
