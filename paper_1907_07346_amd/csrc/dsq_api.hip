@@ -608,7 +608,8 @@ ds_status ds_step_static(const ds_config* cfg, float* x_dev, float* delta_dev, u
     if (reinterpret_cast<uintptr_t>(msg_dev) & 3) return fail_with(DS_EINVAL, "msg_dev must be 4-byte aligned");
     const int deg = cfg->topo == DS_TOPO_RING ? 3 : 5;
     const int nnz = deg * cfg->n;
-    std::vector<dsq::TilePlan> plans;
+    static thread_local std::vector<dsq::TilePlan> plans;     // (kept for its memory only: a list per call)
+    plans.clear();
     if (!dsq::choose_tile_plans(*cfg, nnz, plans, err)) return fail_with(DS_EINVAL, err);
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return fail_with(DS_EHIP, "no current HIP device");
