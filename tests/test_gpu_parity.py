@@ -246,6 +246,21 @@ def test_which_sizes_stream(n, tiles, degree, streams):
     ds.ds_destroy()
 
 
+@pytest.mark.parametrize("kind,block,n,tiles,waves", [
+    (wl.KIND_RAND_SPARSE, 0, 32, 256, 16), (wl.KIND_RAND_SPARSE, 0, 32, 257, 8), (wl.KIND_RAND_SPARSE, 0, 33, 257, 16),
+    (wl.KIND_QUANT_MAXABS, 1024, 16, 256, 16), (wl.KIND_QUANT_MAXABS, 1024, 16, 257, 8), (wl.KIND_QUANT_MAXABS, 1024, 17, 257, 16),
+    (wl.KIND_QUANT_MAXABS, 512, 17, 400, 16), (wl.KIND_QUANT_MAXABS, 512, 17, 401, 8), (wl.KIND_QUANT_MAXABS, 512, 25, 512, 16),
+    (wl.KIND_QUANT_MAXABS, 512, 25, 513, 8)])
+def test_few_tiles_and_sixteen_waves(kind, block, n, tiles, waves):
+    """The lines between workgroups of eight and of sixteen waves, a column behind the last whole tile."""
+    N = (tiles - 1) * max(block, 512) + 1
+    w = small(kind, n, N, bits=4 if block else 0, block=block, k=0 if block else N // 50)
+    ds = b.DeepSqueeze.from_workload(w)
+    assert f"/{waves}w/" in ds.ds_plan_name(), ds.ds_plan_name()
+    ds.ds_destroy()
+    lock_step(w, steps=1)
+
+
 def test_streaming_of_many_tiles():
     """The large end of the streaming rule: 192 workers, 513 tiles, the last one ragged, nine neighbours; a free run of two steps
     with the state read at its end."""
@@ -875,7 +890,7 @@ def test_l2norm_codes_of_infinite_values(bits, variant):
 @pytest.mark.parametrize("n,N,bits", [(64, 4096 * 27 + 5, 4), (64, 4096 * 28 + 5, 4), (64, 4096 * 32 + 5, 4), (64, 4096 * 32 + 5, 8), (64, 4096 * 56 + 5, 8),
                                       (64, 4096 * 28 + 5, 2)])
 def test_l2norm_tails_by_number_of_workgroups(n, N, bits):
-    """The tail on its own, by how many of its workgroups the GPU holds at once: up to 1792, up to 2048, up to 3584 and more."""
+    """The tail on its own with 1,792 to 3,648 workgroups, which are one to three times as many as the GPU holds at once."""
     lock_step(small(wl.KIND_QUANT_L2NORM, n, N, bits=bits), steps=2, plan={"variant": 2})
 
 
