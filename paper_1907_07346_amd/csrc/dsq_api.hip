@@ -436,8 +436,8 @@ __device__ __forceinline__ void add_diagnostics(double cons, double dsq_, double
 // n rows of C columns at a time in LDS, so that x and delta are read once: the deviations from the mean and the mixed
 // errors, which need all rows of a column, come from there.  A quad of columns per lane; the C/4 lanes of a row side by
 // side, 1024/C rows in flight per load of the workgroup, the next tile's asked for while a tile is summed up.  Bound by HBM: the whole
-// call, 64 workers x 4 Mi columns on a torus (2.1 GB), 424 us, without the look-ahead 495; 8 x 8 Mi 195 and 259; 256 x 272,474 214 and
-// 239.  (The kernel below, which reads x twice and delta once more for every neighbour, mostly past the caches: 1595.)
+// call, 64 workers x 4 Mi columns on a torus (2.1 GB), 516 us (the kernel 490), without the look-ahead 575; 8 x 8 Mi 203 and 264; 256 x
+// 272,474 226 and 256.  (The kernel below, which reads x twice and delta once more for every neighbour, mostly past the caches: 1595.)
 // LDS: [x: n x C][delta: n x C][column sums: 1024/C x C, then the means: C][rowptr n+1][col nnz][coef nnz]
 constexpr int kDiagGraphWords = 4096;
 constexpr size_t diagnostics_lds(int n, int C, size_t nnz) {

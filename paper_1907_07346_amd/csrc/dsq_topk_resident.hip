@@ -765,8 +765,8 @@ __global__ void __launch_bounds__(kResThreads, 5) topk_resident(SparseLaunch lau
 //             order                                                                                -> scratch
 //   meeting
 //   finish    as for top-k; the message's header and the zeros behind it by the workgroups of chunk 0
-// 8 workers x 272,474 parameters, 10 % kept, the state complete after every step: 25.3 us (kernel 24.7); the ten launches it
-// takes otherwise: 52 us.
+// 8 workers x 272,474 parameters, 10 % kept, the state complete after every step: 25.2 us (kernel 25.2 under the profiler); the eight launches it
+// takes otherwise: 47 us.
 struct GsparResident : SparseResident {
     using SparseResident::SparseResident;
     uint32_t t_lo = 0;                                        // the step's counter, read before it is advanced
